@@ -149,8 +149,8 @@ hc_status hc_get_share_weights(const hc_ctx* ctx, float* weights16);
 hc_status hc_layer_tune(hc_ctx* ctx, hc_layer* layer, const void* kv_arena, const void* q, float* out, float* lse,
                         float* rep_logits, int32_t rounds, void* stream);
 
-/* Tuning knob: how many 1024-candidate chunks a workgroup of the monitor's selection passes takes
- * (1..64); 0 (default) lets every call choose: 1 for a single layer (many small workgroups, lowest
+/* Tuning knob: how many 1024-candidate chunks a workgroup of the monitor's first pass over a long candidate range
+ * takes (1..64); 0 (default) lets every call choose: 1 for a single layer (many small workgroups, lowest
  * latency), up to 8 for a batch of layers (histograms cleared and flushed once per workgroup). */
 hc_status hc_set_monitor_span(hc_ctx* ctx, int32_t span);
 
@@ -196,7 +196,7 @@ hc_status hc_layer_filter_view(const hc_layer* layer, const int32_t** kept_pos, 
 hc_status hc_set_gather_shape(hc_ctx* ctx, int32_t workgroups, int32_t threads);
 
 /* Tuning knob: how much LDS every workgroup that hc_decode_step launches on its side stream reserves (bytes: 80 KB + 1
- * .. 100 KB, default 81 KB; or 0: only what the kernels need).  More than half of a compute unit's LDS means that a
+ * .. 100 KB, default 81 KB; or 0: only what the kernels need; a kernel that needs more takes more).  More than half of a compute unit's LDS means that a
  * compute unit never holds two workgroups of the side stream at once, so that, whichever stream's kernel gets to an
  * idle compute unit first, the two workgroups of the attention pass still find their registers, wave slots and LDS
  * there: an attention workgroup that has to wait for a place delays its whole launch.  The price: a side-stream

@@ -674,13 +674,18 @@ template <> struct Tune<8> { static constexpr int WG = 1; };
 // its check of a filtered step fails (need[rep] != 0; evaluated on the device, so the launch is unconditional and
 // normally finds nothing to do).  Same plan, same lanes, same dot products in the same order as the split pass,
 // so the logits are bit for bit those an unfiltered pass would have stored.  Queries come from the copy the
-// split pass kept.  Rare: plain stores, no staging.
+// split pass kept.  The candidates' scores and the histogram of the scores' first digits, which the monitor's chain
+// over a long range begins with, are made on the way.  Rare: plain stores, no staging.
 struct RepLogitsItem {
     const uint16_t* arena;
     const uint16_t* q_keep;
     const BlkDev* blks;
     const SegDev* segs;
+    const RepDev* reps;
+    const float* lse;
     float* rep_logits;
+    float* scores;
+    uint32_t* hist;          // [n_reps][HC_RADIX_BINS]
     const int32_t* need;
     int n_blocks, n_reps;
 };
@@ -689,53 +694,72 @@ struct RepLogitsBatch {
 };
 
 template <int G>
-__global__ __launch_bounds__(256) void rep_logits_kernel(RepLogitsBatch batch, int max_ctx)
+__global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogitsBatch batch, int max_ctx)
 {
+    __shared__ uint32_t sm_hist[HC_RADIX_BINS];
     const RepLogitsItem& item = batch.it[blockIdx.y];
     bool any = false;                                      // (a few words, read by every workgroup: the usual case is "none")
     for (int i = 0; i < item.n_reps; ++i) any |= item.need[i] != 0;
     if (!any) return;
-    const uint16_t* __restrict__ arena = item.arena;
-    const uint16_t* __restrict__ q_keep = item.q_keep;
-    const BlkDev* __restrict__ blks = item.blks;
-    const SegDev* __restrict__ segs = item.segs;
-    float* __restrict__ rep_logits = item.rep_logits;
-    const int32_t* __restrict__ need = item.need;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane >> 3, c = lane & 7;
+    for (int i = tid; i < HC_RADIX_BINS; i += 256) sm_hist[i] = 0u;
+    __syncthreads();
     // few workgroups (the launch is there at every step and normally has nothing to do): each takes every
     // gridDim.x-th workgroup share of the split pass's plan
     for (int share = blockIdx.x; share < item.n_blocks; share += gridDim.x) {
-    const BlkDev blk = blks[share];
-    SegDev seg = blk.first;
-    int next_extra = blk.extra_begin;
-    for (;;) {
-        if (seg.rep_slot >= 0 && need[seg.rep_slot] != 0) {
-            const char* __restrict__ Kp = reinterpret_cast<const char*>(arena + seg.k_off);
-            float* rep_base = rep_logits + (size_t)seg.rep_slot * G * max_ctx;
-            uint32_t qreg[G][8];
+        const BlkDev blk = item.blks[share];
+        SegDev seg = blk.first;
+        int next_extra = blk.extra_begin;
+        for (;;) {
+            if (seg.rep_slot >= 0 && item.need[seg.rep_slot] != 0) {      // (the same for the whole workgroup)
+                const char* __restrict__ Kp = reinterpret_cast<const char*>(item.arena + seg.k_off);
+                float* rep_base = item.rep_logits + (size_t)seg.rep_slot * G * max_ctx;
+                float* score_base = item.scores + (size_t)seg.rep_slot * max_ctx;
+                const int cand_lo = item.reps[seg.rep_slot].lo, cand_hi = item.reps[seg.rep_slot].hi;
+                uint32_t qreg[G][8];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const uint4* qp = reinterpret_cast<const uint4*>(q_keep + ((size_t)seg.rep_slot * G + g) * HC_D);
-                const uint4 a = qp[c], b = qp[8 + c];
-                qreg[g][0] = a.x; qreg[g][1] = a.y; qreg[g][2] = a.z; qreg[g][3] = a.w;
-                qreg[g][4] = b.x; qreg[g][5] = b.y; qreg[g][6] = b.z; qreg[g][7] = b.w;
+                for (int g = 0; g < G; ++g) {
+                    const uint4* qp = reinterpret_cast<const uint4*>(item.q_keep + ((size_t)seg.rep_slot * G + g) * HC_D);
+                    const uint4 a = qp[c], b = qp[8 + c];
+                    qreg[g][0] = a.x; qreg[g][1] = a.y; qreg[g][2] = a.z; qreg[g][3] = a.w;
+                    qreg[g][4] = b.x; qreg[g][5] = b.y; qreg[g][6] = b.z; qreg[g][7] = b.w;
+                }
+                for (int row0 = seg.row_begin + 8 * w; row0 < seg.row_end; row0 += 32) {
+                    const int row = row0 + r;
+                    const bool valid = row < seg.row_end;
+                    const uint32_t off = (uint32_t)(valid ? row : seg.row_end - 1) * 256u + (uint32_t)c * 16u;
+                    Tile t;
+                    t.k0 = *reinterpret_cast<const uint4*>(Kp + off);
+                    t.k1 = *reinterpret_cast<const uint4*>(Kp + off + 128);
+                    t.v0 = t.v1 = make_uint4(0u, 0u, 0u, 0u);
+                    float sc[G];
+                    qk<G>(qreg, t, sc);
+                    stash_rep<G>(rep_base + (size_t)row * G, sc, c, valid);
+                }
+                __syncthreads();                             // the segment's logits are stored: score its candidates
+                for (int row = max(seg.row_begin, cand_lo) + tid; row < min(seg.row_end, cand_hi); row += 256) {
+                    float l[G], lse[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        l[g] = rep_base[(size_t)row * G + g];
+                        lse[g] = item.lse[(size_t)seg.bh * G + g];
+                    }
+                    const float sc = hc_group_score<G>(l, lse, HC_AGG_PROB);
+                    score_base[row] = sc;
+                    atomicAdd(&sm_hist[hc_score_key(sc) >> 21], 1u);
+                }
+                __syncthreads();
+                uint32_t* h = item.hist + (size_t)seg.rep_slot * HC_RADIX_BINS;
+                for (int i = tid; i < HC_RADIX_BINS; i += 256)
+                    if (sm_hist[i]) {
+                        atomicAdd(&h[i], sm_hist[i]);
+                        sm_hist[i] = 0u;
+                    }
+                __syncthreads();
             }
-            for (int row0 = seg.row_begin + 8 * w; row0 < seg.row_end; row0 += 32) {
-                const int row = row0 + r;
-                const bool valid = row < seg.row_end;
-                const uint32_t off = (uint32_t)(valid ? row : seg.row_end - 1) * 256u + (uint32_t)c * 16u;
-                Tile t;
-                t.k0 = *reinterpret_cast<const uint4*>(Kp + off);
-                t.k1 = *reinterpret_cast<const uint4*>(Kp + off + 128);
-                t.v0 = t.v1 = make_uint4(0u, 0u, 0u, 0u);
-                float sc[G];
-                qk<G>(qreg, t, sc);
-                stash_rep<G>(rep_base + (size_t)row * G, sc, c, valid);
-            }
+            if (next_extra >= blk.extra_end) break;
+            seg = item.segs[next_extra++];
         }
-        if (next_extra >= blk.extra_end) break;
-        seg = segs[next_extra++];
-    }
     }
 }
 
@@ -770,14 +794,15 @@ hc_status launch(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* 
 }
 
 template <int G>
-hc_status launch_rep_logits(hc_ctx* ctx, int n, const hc_layer* const* layers, const void* const* arenas, float* const* rep_logits,
-                            hipStream_t st)
+hc_status launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st)
 {
     RepLogitsBatch batch{};
     int max_blocks = 0;
     for (int i = 0; i < n; ++i) {
-        const hc_layer* L = layers[i];
-        batch.it[i] = RepLogitsItem{(const uint16_t*)arenas[i], L->q_keep, L->blks, L->segs, rep_logits[i], L->need, L->n_blocks, L->n_reps};
+        const hc_rep_logits_call& x = calls[i];
+        const hc_layer* L = x.L;
+        batch.it[i] = RepLogitsItem{(const uint16_t*)x.arena, L->q_keep, L->blks, L->segs, L->reps, x.lse, x.rep_logits, x.scores, x.hist,
+                                    L->need, L->n_blocks, L->n_reps};
         max_blocks = std::max(max_blocks, L->n_blocks);
     }
     rep_logits_kernel<G><<<dim3(std::min(max_blocks, 64), n), dim3(256), hc_side_lds(ctx, (const void*)rep_logits_kernel<G>, 0), st>>>(batch, ctx->cfg.max_ctx);
@@ -834,15 +859,14 @@ hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* aren
     return launch_any(ctx, L, arena, q, out, lse, rep_logits, st, ctx->static_scratch, ctx->static_scratch + STATIC_ACC_FLOATS);
 }
 
-hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_layer* const* layers, const void* const* arenas, float* const* rep_logits,
-                               hipStream_t st)
+hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st)
 {
     if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "batch of %d layers", n);
     switch (ctx->G) {
-    case 1: return launch_rep_logits<1>(ctx, n, layers, arenas, rep_logits, st);
-    case 2: return launch_rep_logits<2>(ctx, n, layers, arenas, rep_logits, st);
-    case 4: return launch_rep_logits<4>(ctx, n, layers, arenas, rep_logits, st);
-    case 8: return launch_rep_logits<8>(ctx, n, layers, arenas, rep_logits, st);
+    case 1: return launch_rep_logits<1>(ctx, n, calls, st);
+    case 2: return launch_rep_logits<2>(ctx, n, calls, st);
+    case 4: return launch_rep_logits<4>(ctx, n, calls, st);
+    case 8: return launch_rep_logits<8>(ctx, n, calls, st);
     }
     return hc_fail(ctx, HC_ESHAPE, "unsupported group size");
 }

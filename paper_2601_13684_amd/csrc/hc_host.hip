@@ -60,11 +60,6 @@ extern "C" const char* hc_last_error(const hc_ctx* ctx)
 static bool ctx_ok(const hc_ctx* c) { return c && c->magic == HC_CTX_MAGIC; }
 static bool layer_ok(const hc_layer* l) { return l && l->magic == HC_LAYER_MAGIC && ctx_ok(l->ctx); }
 
-// Words of selection workspace per pivot that a monitor call clears before use:
-// digit histograms (one shared first pass, then one per set size for passes two and three),
-// the selection state and the intersection accumulator / ticket.
-static size_t rep_hist_words() { return (size_t)(1 + 2 * HC_MAX_K_PER_REP) * HC_RADIX_BINS; }
-
 static hc_status check_config(const hc_config* cfg)
 {
     if (!cfg) return HC_EINVAL;
@@ -108,18 +103,17 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     }
     c->n_cu = prop.multiProcessorCount;
 
-    // pivots are at most half of the heads; the prefill-time selection runs over up to all of them
-    c->max_reps = std::max(1, cfg->B * cfg->Hkv);
+    // pivots are at most half of the heads; the prefill-time selection, which uses the first copy alone, runs over
+    // up to all of them
     c->max_chunks = (cfg->max_ctx + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-    const size_t hist_w = (size_t)c->max_reps * rep_hist_words();
-    const size_t sel_w = (size_t)c->max_reps * HC_MAX_K_PER_REP * 4;
-    const size_t misc_w = (size_t)c->max_reps * 4;
-    const size_t cnt_w = (size_t)c->max_reps * HC_MAX_K_PER_REP * c->max_chunks * 2;
-    const size_t bm_w = (size_t)c->max_reps * (cfg->max_ctx / 32);
-    const size_t hits_w = (size_t)c->max_reps * (c->max_chunks + 1);
-    const size_t lane_w = hist_w + sel_w + misc_w + cnt_w + bm_w + hits_w;
+    const size_t rep_w = HC_RADIX_BINS + c->max_chunks + cfg->max_ctx / 32 + (size_t)cfg->max_ctx * 2 + cfg->max_ctx / 2;
+    size_t ws_w = 0;
+    for (int i = 0; i < HC_MAX_GROUP; ++i) {
+        c->ws[i].reps = std::max(1, i == 0 ? cfg->B * cfg->Hkv : cfg->B * cfg->Hkv / 2);
+        ws_w += (((size_t)c->ws[i].reps * rep_w) + 3) & ~(size_t)3;
+    }
     uint32_t* base = nullptr;
-    e = hipMalloc((void**)&base, HC_MAX_GROUP * lane_w * sizeof(uint32_t));
+    e = hipMalloc((void**)&base, ws_w * sizeof(uint32_t));
     if (e != hipSuccess) {
         delete c;
         return e == hipErrorOutOfMemory ? HC_ENOMEM : HC_EHIP;
@@ -147,13 +141,14 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     }
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
         hc_monitor_ws& w = c->ws[i];
-        w.hist = base + (size_t)i * lane_w;
-        w.sel = w.hist + hist_w;
-        w.misc = w.sel + sel_w;
-        w.cnt = w.misc + misc_w;
-        w.bitmap = w.cnt + cnt_w;
-        w.hits = w.bitmap + bm_w;
+        w.hist = base;
+        w.sv_key = w.hist + (size_t)w.reps * HC_RADIX_BINS;
+        w.sv_pos = reinterpret_cast<int32_t*>(w.sv_key + (size_t)w.reps * cfg->max_ctx);
+        w.sv_off = reinterpret_cast<uint16_t*>(w.sv_pos + (size_t)w.reps * cfg->max_ctx);
+        w.bitmap = w.sv_key + (size_t)w.reps * (2 * (size_t)cfg->max_ctx + cfg->max_ctx / 2);
+        w.cnt = w.bitmap + (size_t)w.reps * (cfg->max_ctx / 32);
         w.dirty = true;
+        base += (((size_t)w.reps * rep_w) + 3) & ~(size_t)3;
     }
     *out = c;
     return HC_OK;
@@ -1298,11 +1293,12 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         hipStream_t run = ss ? ss : ms;
         if (ss) HC_HIP(ctx, hipStreamWaitEvent(ss, w.Lg->ev_attn, 0));
         hc_status st = HC_OK;
+        ctx->beside_now = ss != nullptr;
         if (w.n_test > 0) st = rescore_passes(ctx, w.n_test, w.test_job, run);       // test step of a re-scored window: the earlier queries first
         ctx->side_pad_now = ss != nullptr && w.all_filtered;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
         if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, run);
-        ctx->side_pad_now = false;
+        ctx->side_pad_now = ctx->beside_now = false;
         if (ss) {
             // recorded even after a failed launch, so that no later call waits on a stale event
             const hipError_t e = hipEventRecord(w.Lg->ev_side, ss);

@@ -83,12 +83,13 @@ struct SatDev {
 };
 
 struct hc_monitor_ws {
-    uint32_t* hist = nullptr;      // [max_reps][HC_MAX_K_PER_REP][3][HC_RADIX_BINS]
-    uint32_t* sel = nullptr;       // [max_reps][HC_MAX_K_PER_REP][4]: prefix, remaining k, (tau, need)
-    uint32_t* misc = nullptr;      // [max_reps][4]: spare
-    uint32_t* cnt = nullptr;       // [max_reps][HC_MAX_K_PER_REP][max_chunks][2]: greater, equal
-    uint32_t* bitmap = nullptr;    // [max_reps][max_ctx/32]
-    uint32_t* hits = nullptr;      // [max_reps][max_chunks+1]: per-chunk |T ∩ baseline|
+    int reps = 0;                  // pivots this copy has room for
+    uint32_t* hist = nullptr;      // [reps][HC_RADIX_BINS]: first-digit histogram of a long candidate range
+    uint32_t* cnt = nullptr;       // [reps][max_chunks]: survivors per chunk
+    uint32_t* bitmap = nullptr;    // [reps][max_ctx/32]: baseline set, where it does not fit in LDS
+    uint32_t* sv_key = nullptr;    // [reps][max_ctx]: survivors' keys
+    uint16_t* sv_off = nullptr;    // [reps][max_ctx]: survivors' positions inside their chunk
+    int32_t* sv_pos = nullptr;     // [reps][max_ctx]: survivors' positions, dense
     bool dirty = true;             // histograms / bitmap not known to be clear (first call, or a call that failed midway)
 };
 
@@ -104,6 +105,8 @@ struct hc_ctx {
     float filter_margin = 0.f;   // > 0: pivot logits are filtered (hc_set_logit_filter); layers created afterwards carry the buffers
     int filter_min_candidates = 0;   // ... if one of their pivots has at least this many candidate positions
     int side_lds_total = 81 * 1024;   // > 0: LDS bytes every side-stream workgroup of hc_decode_step reserves (hc_set_side_lds)
+    bool beside_now = false;     // set while hc_decode_step enqueues a group's side work on a stream of its own: the kernels
+                                 // have to fit beside the attention pass
     bool side_pad_now = false;   // set while hc_decode_step enqueues a group's side work on a stream of its own
     int device;
     char err[512];
@@ -114,9 +117,8 @@ struct hc_ctx {
     float* part_ml = nullptr;    // [slots][G][2]  (running max in log2 units, sum)
     size_t part_slots = 0;
     float* static_scratch = nullptr;   // this device's address of the fixed scratch array of hc_decode_attn_static
-    // selection workspace, sized for max_reps pivots; one copy per layer of a batched monitor call
-    int max_reps = 0;
-    uint32_t* ws_base = nullptr;   // the one allocation behind all lanes
+    // selection workspace; one copy per layer of a batched monitor call (the first has room for every head, the others for every pivot)
+    uint32_t* ws_base = nullptr;   // the one allocation behind all copies
     hc_monitor_ws ws[HC_MAX_GROUP];
     int max_chunks = 0;
     int monitor_span = 0;          // chunks per workgroup of the selection passes; 0: chosen per launch
@@ -183,6 +185,36 @@ struct hc_layer {
     hipEvent_t pending_ev = nullptr;   // side work of the previous hc_decode_step that this layer's attention must wait for
 };
 
+#if defined(__HIPCC__)
+// GQA-aggregated score of a position from the G scaled logits of its row (App. C.1): mean of the softmax weights, or
+// of the logits.  One place for it: the monitor's passes must score a row alike whichever of them does.
+template <int G>
+__device__ __forceinline__ float hc_group_score(const float (&l)[G], const float (&lse)[G], int agg)
+{
+    float a;
+    if (agg == HC_AGG_PROB) {
+        a = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) a += expf(l[g] - lse[g]);
+    } else if (G == 4) {
+        a = (l[0] + l[1]) + (l[2] + l[3]);
+    } else {
+        a = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) a += l[g];
+    }
+    return a * (1.0f / (float)G);
+}
+// Order-preserving 32-bit key of a score.
+__device__ __forceinline__ uint32_t hc_score_key(float s)
+{
+    uint32_t u = __float_as_uint(s);
+    if (s != s) return 0u;                    // NaN ranks below everything
+    if (u == 0x80000000u) u = 0u;             // -0 and +0 are the same score
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+#endif
+
 constexpr uint32_t HC_CTX_MAGIC = 0x48435458u;    // "HCTX"
 constexpr uint32_t HC_LAYER_MAGIC = 0x48434c59u;  // "HCLY"
 
@@ -231,8 +263,15 @@ hc_status hc_launch_attn(hc_ctx* ctx, const hc_layer* L, const void* arena, cons
 hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out,
                                 float* lse, float* rep_logits, hipStream_t st);
 hc_status hc_attn_static_scratch(hc_ctx* ctx, float** base);     // at context creation, with the context's device current
-hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_layer* const* layers, const void* const* arenas,
-                               float* const* rep_logits, hipStream_t st);
+struct hc_rep_logits_call {
+    const hc_layer* L;
+    const void* arena;
+    float* rep_logits;
+    const float* lse;
+    float* scores;
+    uint32_t* hist;        // the layer's workspace copy: first-digit histograms
+};
+hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st);
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st);
 hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipStream_t st);
 hc_status hc_gather_set_lds_limit();     // once per process, at context creation

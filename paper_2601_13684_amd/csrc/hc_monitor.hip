@@ -2,72 +2,68 @@
 // GQA-aggregated score (App. C.1), TopIndices_k for every needed set size, overlap with the
 // baseline set, windowed-median retrieval signal, baseline update.
 //
-// Selection is an exact 3-digit radix select (11 + 11 + 10 bits) on order-preserving 32-bit keys of
-// the fp32 scores, run by many workgroups per pivot because the score array (up to ~1 MB) is far
-// too long for one.  Ties at the threshold key are resolved by position: the equal-keyed candidates
-// with the lowest indices are taken, which makes the result the unique first-k set under
-// (score descending, index ascending).  The lists are emitted in ascending index order by an
-// ordered compaction (per-chunk counts, then prefix sums).
+// Selection is exact: the k-th largest order-preserving 32-bit key of the fp32 scores is found, and ties at that
+// threshold key are resolved by position (the equal-keyed candidates with the lowest indices are taken), which
+// makes the result the unique first-k set under (score descending, index ascending).  Lists are emitted in
+// ascending index order.
 //
-// The work is latency-bound, not bandwidth-bound (a few MB, L2-resident), so every kernel is shaped to
-// have few dependent memory round trips: four candidates per thread fetched with one 16-byte load, all set
-// sizes of a pivot handled in the same pass over the scores, no local arrays (no scratch memory) and no
-// device-wide fences (the decision has a kernel of its own instead).  Workgroups are 256 threads with few
-// registers so that they can share compute units with the attention pass of the next layer when the
-// caller runs the monitor on a side stream.
+// The work is a few MB at most and bound by latency: what costs is the number of dependent launches (5-8 us each
+// for one layer, several times that beside the attention pass) and of dependent memory round trips inside one.  So
+// everything after the scores is ONE kernel, mon_select, with one workgroup per pivot and set size that keeps the keys
+// of its items in LDS: threshold, ordered lists, |T ∩ baseline| through a bitmap in LDS, window, decision and
+// baseline update.  What reaches it:
+//   short candidate ranges   mon_select scores the candidates itself: one launch
+//   long ranges              mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact
+//                            (the candidates from the threshold digit of the longest list up, in position order),
+//                            mon_select over those (a few thousand): three launches
+//   rows a filtering split pass kept
+//                            mon_sparse_score (their scores, one dense run), mon_select: two launches, and behind
+//                            them the long-range chain, which normally finds nothing to do, for a pivot whose
+//                            check failed (its first kernel, in hc_attn.hip, makes all logits again)
+// (mon_prep clears the histograms and bitmaps, only after a call that failed midway; normally mon_select leaves
+// them clear.)
 //
-// Kernels, all on the caller's stream:
-//   (mon_prep       clear the digit histograms and the baseline bitmap: only after a failed call; normally
-//                   they are left clear by the previous call's last kernel)
-//   mon_score_hist  score + first-digit histogram; scatter the baseline list into the bitmap
-//   mon_hist<2>     find the first digit of every set size; histograms of the second digit
-//   mon_hist<3>     find the second digit; histograms of the third digit
-//   mon_count       find the threshold key; per-chunk counts of greater / equal keys
-//   mon_write       ordered compaction into topk_idx; |T ∩ baseline| through the bitmap
-//   mon_decide      window update and trigger decision (exact integer form of Eq. 10): writes inter, flag,
-//                   ring and, on a trigger, the new baseline; clears histograms and bitmap for the next call
+// Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
+// histograms, counts, ordered write, decision): one 32K layer 29.5 instead of 51.5 us per call, eight sequences of 9K to
+// 131K 42 instead of 80 us, the decode step of one 4K layer 29 instead of 49 us.
+//
+// Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
+// two attention workgroups, whose registers leave 80 per lane of a SIMD: 256 threads of at most 64 registers, or
+// (mon_select) 512 threads of at most 40.  No local arrays (a kernel that needs scratch memory costs tens of us to
+// launch), no device-wide fences.
+#include <algorithm>
+
 #include "hc_internal.h"
 
 namespace {
 
-constexpr int BLK = 256;     // small workgroups: they fit beside the attention pass's waves on a compute unit
-constexpr int PER_THREAD = HC_SEL_CHUNK / BLK;   // 4 consecutive candidates per thread
-static_assert(PER_THREAD == 4, "one 16-byte load per thread");
+constexpr int BLK = 256;
+constexpr int PER_THREAD = HC_SEL_CHUNK / BLK;   // candidates of a chunk per thread
 constexpr int NWAVE = BLK / 64;
-static_assert(NWAVE == 4, "reductions below add four wave sums");
 
-__device__ __forceinline__ uint32_t score_key(float s)
+__device__ __forceinline__ float key_score(uint32_t key)      // inverse of hc_score_key
 {
-    uint32_t u = __float_as_uint(s);
-    if (s != s) return 0u;                    // NaN ranks below everything
-    if (u == 0x80000000u) u = 0u;             // -0 and +0 are the same score
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-struct RepWs {
-    uint32_t* h1;     // [HC_RADIX_BINS]
-    uint32_t* h2;     // [HC_MAX_K_PER_REP][HC_RADIX_BINS]
-    uint32_t* h3;     // [HC_MAX_K_PER_REP][HC_RADIX_BINS]
-    uint32_t* sel;    // [HC_MAX_K_PER_REP][4]: digit-1 prefix / remaining, then 22-bit prefix / remaining, then tau / need
-    uint32_t* misc;   // [4]: intersection accumulator, ticket
-    uint32_t* cnt;    // [HC_MAX_K_PER_REP][max_chunks][2]
-    uint32_t* bitmap; // [max_ctx/32]
-};
-
+// Workspace of one layer of a batch (rep: pivot).
 struct Ws {
-    uint32_t *hist, *sel, *misc, *cnt, *bitmap, *hits;
+    uint32_t* hist;      // [HC_RADIX_BINS]: first-digit histogram of a long range
+    uint32_t* cnt;       // [max_chunks]: survivors of every chunk of a long range
+    uint32_t* bitmap;    // [max_ctx / 32]: baseline set, where it does not fit in LDS
+    uint32_t* sv_key;    // [max_ctx]: survivors' keys, chunk c's from c * HC_SEL_CHUNK
+    uint16_t* sv_off;    // [max_ctx]: their positions inside the chunk
+    int32_t* sv_pos;     // [max_ctx]: the survivors' positions, dense, where mon_select has all their keys in LDS
     int max_chunks, max_ctx;
-    __device__ RepWs rep(int r) const
+    __device__ Ws rep(int r) const
     {
-        RepWs w;
-        uint32_t* h = hist + (size_t)r * (1 + 2 * HC_MAX_K_PER_REP) * HC_RADIX_BINS;
-        w.h1 = h;
-        w.h2 = h + HC_RADIX_BINS;
-        w.h3 = h + (size_t)(1 + HC_MAX_K_PER_REP) * HC_RADIX_BINS;
-        w.sel = sel + (size_t)r * HC_MAX_K_PER_REP * 4;
-        w.misc = misc + (size_t)r * 4;
-        w.cnt = cnt + (size_t)r * HC_MAX_K_PER_REP * max_chunks * 2;
-        w.bitmap = bitmap + (size_t)r * (max_ctx / 32);
+        Ws w = *this;
+        w.hist += (size_t)r * HC_RADIX_BINS;
+        w.cnt += (size_t)r * max_chunks;
+        w.bitmap += (size_t)r * (max_ctx / 32);
+        w.sv_key += (size_t)r * max_ctx;
+        w.sv_off += (size_t)r * max_ctx;
+        w.sv_pos += (size_t)r * max_ctx;
         return w;
     }
 };
@@ -89,20 +85,19 @@ struct MonItem {
     int32_t* flag;
     int n_reps, n_outs;
     int store_slot;
-    // A layer whose split pass filters the pivot logits: the selection passes run over the kept rows only
-    // (reps = the pivots as seen over those rows, pos_map = their positions), and a second, dense chain of the
-    // same passes stands by for the pivots whose check failed (need[rep] != 0).
+    // A layer whose split pass filters the pivot logits: the selection runs over the kept rows only (reps = the
+    // pivots as seen over those rows, pos_map = their positions), and a second, dense chain stands by for the
+    // pivots whose check failed (need[rep] != 0).
     int need_sense;               // -1: unconditional; 0: run where need[rep] == 0; 1: run where need[rep] != 0
-    const int32_t* need_r;        // [n_reps], read by every pass
-    int32_t* need_w;              // the same table, written by the first pass and the check
+    int32_t* need;                // [n_reps]
     const RepDev* real_reps;      // the pivots by position (candidate range, table row); == reps unless filtered
-    const int32_t* pos_map;       // [n_reps][max_ctx] position of every kept row, or nullptr: a row is its position
-    int32_t* dense_pos;           // the same table, written by the first filtered pass
-    const HeadDev* heads;         // filtered first pass: where a pivot's segments are ...
+    int32_t* pos_map;             // [n_reps][max_ctx] position of every kept row (written by mon_sparse_score), or
+                                  // nullptr: a row is its position
+    const HeadDev* heads;         // mon_sparse_score: where a pivot's segments are ...
     const SegDev* segs;           // ... which rows of the pivot's block they begin at ...
     const int32_t* seg_cnt;       // ... and how many rows each of them kept
     const int32_t* surv_pos;      // [n_reps][max_ctx] positions of the kept rows, by segment
-    RepDev* vreps;                // written by the first filtered pass
+    RepDev* vreps;                // written by mon_sparse_score
     RepFilter* filt;              // checked (this step's) and set (the next step's) when not nullptr
     uint32_t* counts;             // [n_reps][4] or nullptr
     int cap_rows;                 // filtered: more kept rows than this (or fewer than the largest list) go to the dense chain
@@ -114,77 +109,91 @@ struct MonBatch {
 
 __device__ __forceinline__ bool mon_skip(const MonItem& it, int rep)
 {
-    return it.need_sense >= 0 && ((it.need_r[rep] != 0) != (it.need_sense != 0));
+    return it.need_sense >= 0 && ((it.need[rep] != 0) != (it.need_sense != 0));
 }
 
-__device__ __forceinline__ float key_score(uint32_t key)      // inverse of score_key
+// Cross-lane moves of the data-parallel primitives (no LDS traffic, unlike a shuffle).
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp(uint32_t other, uint32_t v)       // lanes without a source get `other`
 {
-    return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)other, (int)v, CTRL, ROWS, 0xF, false);
 }
+constexpr int DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118;      // inside rows of 16 lanes
+constexpr int DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;                                    // a row's last lane to the next row / half
+
+__device__ __forceinline__ uint32_t lane_get(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
 
 __device__ __forceinline__ uint32_t wave_exscan(uint32_t v, uint32_t& total)
 {
-    const int lane = threadIdx.x & 63;
     uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
-    total = __shfl(inc, 63);
+    inc += dpp<DPP_SHR1>(0u, inc);
+    inc += dpp<DPP_SHR2>(0u, inc);
+    inc += dpp<DPP_SHR4>(0u, inc);
+    inc += dpp<DPP_SHR8>(0u, inc);
+    inc += dpp<DPP_BCAST15, 0xA>(0u, inc);
+    inc += dpp<DPP_BCAST31, 0xC>(0u, inc);
+    total = lane_get(inc, 63);
     return inc - v;
 }
 
-// In a histogram of nbins (<= 2048) digit counts, walking from the highest digit down, find the digit
-// in which the k-th largest element falls and how many of that digit's elements are still needed.
-// Done by ONE wave (lane l owns 32 consecutive digits); result valid in all its lanes.
-template <int nbins>
-__device__ __forceinline__ void find_digit_wave(const uint32_t* __restrict__ hist, uint32_t k, uint32_t& digit,
-                                                uint32_t& remaining)
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
-    const int lane = threadIdx.x & 63;
-    constexpr int per = nbins / 64;               // 32 or 16
-    // lane l owns digits nbins-1-l*per ... nbins-(l+1)*per (descending)
-    uint32_t local = 0;
-    const uint4* h4 = reinterpret_cast<const uint4*>(hist + (nbins - (lane + 1) * per));
-    uint4 v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if (i < per / 4) {
-            v[i] = h4[i];
-            local += v[i].x + v[i].y + v[i].z + v[i].w;
-        }
-    uint32_t tot;
-    uint32_t above = wave_exscan(local, tot);      // elements in higher digits than this lane's
-    const bool mine = above < k && k <= above + local;
-    uint32_t d = 0, rem = 0;
-    if (mine) {
-        // walk this lane's digits from the highest (last word of its span) down
-#pragma unroll
-        for (int i = per - 1; i >= 0; --i) {
-            const uint4 q = v[i >> 2];
-            const uint32_t c = (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
-            if (above < k && k <= above + c) {
-                d = (uint32_t)(nbins - (lane + 1) * per + i);
-                rem = k - above;
-            }
-            above += c;
-        }
-    }
-    const uint64_t who = __builtin_amdgcn_ballot_w64(mine);
-    const int src = who ? __builtin_ctzll(who) : 0;
-    digit = __shfl(d, src);
-    remaining = __shfl(rem, src);
+    uint32_t total;
+    wave_exscan(v, total);
+    return total;
 }
 
-__global__ __launch_bounds__(256) void mon_prep(Ws ws, int max_ctx)
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
 {
-    const RepWs w = ws.rep(blockIdx.y);
-    const size_t hist_words = (size_t)(1 + 2 * HC_MAX_K_PER_REP) * HC_RADIX_BINS;
-    const size_t bm_words = (size_t)max_ctx / 32;
+    v = max(v, dpp<DPP_SHR1>(v, v));
+    v = max(v, dpp<DPP_SHR2>(v, v));
+    v = max(v, dpp<DPP_SHR4>(v, v));
+    v = max(v, dpp<DPP_SHR8>(v, v));
+    v = max(v, dpp<DPP_BCAST15, 0xA>(v, v));
+    v = max(v, dpp<DPP_BCAST31, 0xC>(v, v));
+    return lane_get(v, 63);
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)      // set bits of mask below this lane
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// In a histogram of HC_RADIX_BINS digit counts, walking from the highest digit down, find the digit in which the
+// k-th largest element falls, how many of that digit's elements are still needed and how many there are.  Done by
+// ONE wave (lane l owns 32 consecutive digits); result valid in all its lanes.  The lanes start their walks at
+// different digits of their spans, so that in LDS they do not all hit the same bank.
+__device__ __forceinline__ void find_digit(const uint32_t* hist, uint32_t k, uint32_t& digit, uint32_t& remaining, uint32_t& count)
+{
+    const int lane = threadIdx.x & 63;
+    constexpr int per = HC_RADIX_BINS / 64;
+    static_assert(per == 32, "a lane's span");
+    const uint32_t* h = hist + (HC_RADIX_BINS - (lane + 1) * per);      // lane 0 owns the highest digits
+    uint32_t local = 0;
+#pragma unroll 8
+    for (int i = 0; i < per; ++i) local += h[(i + lane) & (per - 1)];
+    uint32_t tot;
+    const uint32_t above = wave_exscan(local, tot);                     // elements in higher digits than this lane's
+    const uint64_t who = __builtin_amdgcn_ballot_w64(above < k && k <= above + local);
+    const int src = who ? __builtin_ctzll(who) : 0;
+    const uint32_t base = lane_get(above, src);
+    // the digits of that lane's span, one to a lane, from the highest down
+    const uint32_t* hs = hist + (HC_RADIX_BINS - (src + 1) * per);
+    const uint32_t c = lane < per ? hs[per - 1 - lane] : 0u;
+    const uint32_t ab = base + wave_exscan(c, tot);
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(ab < k && k <= ab + c);
+    const int at = hit ? __builtin_ctzll(hit) : 0;
+    digit = (uint32_t)(HC_RADIX_BINS - (src + 1) * per + per - 1 - at);
+    remaining = k - lane_get(ab, at);
+    count = lane_get(c, at);
+}
+
+__global__ __launch_bounds__(256) void mon_prep(Ws ws)
+{
+    const Ws w = ws.rep(blockIdx.y);
     const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < hist_words; i += stride) w.h1[i] = 0u;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < bm_words; i += stride) w.bitmap[i] = 0u;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < HC_RADIX_BINS; i += stride) w.hist[i] = 0u;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < (size_t)ws.max_ctx / 32; i += stride) w.bitmap[i] = 0u;
 }
 
 // Score of candidate j from the G scaled logits of its row (rep_logits is [ctx][G] per pivot).
@@ -204,58 +213,28 @@ __device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j,
             l[4 * q] = v.x; l[4 * q + 1] = v.y; l[4 * q + 2] = v.z; l[4 * q + 3] = v.w;
         }
     }
-    float a;
-    if (agg == HC_AGG_PROB) {
-        a = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g) a += expf(l[g] - lse[g]);
-    } else if (G == 4) {
-        a = (l[0] + l[1]) + (l[2] + l[3]);
-    } else {
-        a = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g) a += l[g];
-    }
-    return a * (1.0f / (float)G);
+    return hc_group_score<G>(l, lse, agg);
 }
 
-// A workgroup of the selection passes takes `span` consecutive chunks of HC_SEL_CHUNK candidates: 1 when a
-// single layer is handled (many small workgroups: latency), more when a batch of layers is (the histograms
-// in LDS are cleared and flushed once per workgroup, so fewer, longer workgroups do far less work in total
-// and a batch fits a small part of the GPU).
+// Scores and first-digit histogram of a long candidate range.  A workgroup takes `span` consecutive chunks of
+// HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
 template <int G>
-__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int max_k, int span)
+__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span)
 {
     __shared__ uint32_t sh[HC_RADIX_BINS];
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
-    const Ws ws = it.ws;
-    const RepDev* __restrict__ reps = it.reps;
-    const float* __restrict__ rep_logits = it.rep_logits;
-    const float* __restrict__ lse = it.lse;
-    float* __restrict__ scores = it.scores;
-    const int32_t* __restrict__ base_idx = it.base_idx;
-    const RepDev rd = reps[rep];
+    const RepDev rd = it.reps[rep];
     const int c0 = blockIdx.x * span, c1 = min(c0 + span, rd.nchunk);
     if (c0 >= rd.nchunk) return;
-    const RepWs w = ws.rep(rep);
-    for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
-
-    // baseline list -> bitmap (each workgroup takes a slice of the list)
-    const int32_t* base = base_idx + (size_t)rd.bh * max_k;
-    const int nblk = (rd.nchunk + span - 1) / span;
-    for (int i = blockIdx.x * BLK + threadIdx.x; i < rd.k[0]; i += nblk * BLK) {
-        const int j = base[i];
-        if (j >= rd.lo && j < rd.hi) atomicOr(&w.bitmap[j >> 5], 1u << (j & 31));
-    }
-    __syncthreads();
-
-    float* srow = scores + (size_t)rep * ws.max_ctx;
-    const float* lrow = rep_logits ? rep_logits + (size_t)rep * G * ws.max_ctx : nullptr;
+    float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
+    const float* lrow = it.rep_logits ? it.rep_logits + (size_t)rep * G * it.ws.max_ctx : nullptr;
     float l[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) l[g] = (!scores_given && agg == HC_AGG_PROB) ? lse[(size_t)rd.bh * G + g] : 0.f;
+    for (int g = 0; g < G; ++g) l[g] = (!scores_given && agg == HC_AGG_PROB) ? it.lse[(size_t)rd.bh * G + g] : 0.f;
+    for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
+    __syncthreads();
     for (int ch = c0; ch < c1; ++ch) {
         const int first = rd.lo + ch * HC_SEL_CHUNK;
         float s[PER_THREAD];
@@ -270,444 +249,668 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
             const int j = first + i * BLK + threadIdx.x;
             if (j < rd.hi) {
                 if (!scores_given) srow[j] = s[i];
-                atomicAdd(&sh[score_key(s[i]) >> 21], 1u);
+                atomicAdd(&sh[hc_score_key(s[i]) >> 21], 1u);
             }
         }
     }
     __syncthreads();
+    uint32_t* h1 = it.ws.rep(rep).hist;
     for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK)
-        if (sh[i]) atomicAdd(&w.h1[i], sh[i]);
+        if (sh[i]) atomicAdd(&h1[i], sh[i]);
 }
 
-// The four candidates of a thread: positions first4 .. first4+3 (first4 a multiple of 4, so one
-// 16-byte load), of which those inside [lo, hi) count.
-__device__ __forceinline__ void load_keys(const float* __restrict__ srow, int first4, int lo, int hi, uint32_t (&key)[4],
-                                          bool (&in)[4])
+// The survivors of a long range: every candidate whose first digit is at least that of the longest list's k-th
+// score, in position order, chunk by chunk (keys and positions inside the chunk, at the chunk's own place, and how
+// many).  At 229,376 candidates and a longest list of 7,872 about 11,000 survive.  A wave takes a chunk, 64
+// candidates to a round, and needs no workgroup barrier; its first loads do not wait for the threshold.
+__global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B)
 {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (first4 < hi) v = *reinterpret_cast<const float4*>(srow + first4);     // row stride is a multiple of 64: in bounds
-    const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        in[i] = first4 + i >= lo && first4 + i < hi;
-        key[i] = score_key(f[i]);
-    }
-}
-
-// The later passes work on chunks that start at a multiple of 4 positions (lo4), which can add one chunk.
-__device__ __forceinline__ int chunks_from_lo4(const RepDev& rd)
-{
-    return (rd.hi - (rd.lo & ~3) + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-}
-
-// PASS 2: digit two (bits 20..10) among keys whose first digit matches; PASS 3: digit three (bits 9..0)
-// among keys whose upper 22 bits match.  One workgroup handles every set size of its pivot: wave ks
-// finds the digit of set size ks, then all waves histogram their candidates for each set size.
-template <int PASS>
-__global__ __launch_bounds__(BLK, 8) void mon_hist(MonBatch B, int span)
-{
-    extern __shared__ uint32_t sh[];              // [nk][HC_RADIX_BINS]
-    __shared__ uint32_t sm_prefix[HC_MAX_K_PER_REP];
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
-    const Ws ws = it.ws;
-    const RepDev* __restrict__ reps = it.reps;
-    const float* __restrict__ scores = it.scores;
-    const RepDev rd = reps[rep];
-    const int lo4 = rd.lo & ~3;
-    const int nchunk = chunks_from_lo4(rd);
-    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
-    if (c0 >= nchunk) return;
-    const RepWs w = ws.rep(rep);
-    for (int i = threadIdx.x; i < rd.nk * HC_RADIX_BINS; i += BLK) sh[i] = 0u;
-
-    for (int ks = threadIdx.x >> 6; ks < rd.nk; ks += NWAVE) {     // one wave per set size
-        uint32_t prefix, remaining;
-        if (PASS == 2) {
-            find_digit_wave<HC_RADIX_BINS>(w.h1, (uint32_t)reps[rep].k[ks], prefix, remaining);   // (indexing the register copy would spill it)
-        } else {
-            uint32_t d2;
-            find_digit_wave<HC_RADIX_BINS>(w.h2 + (size_t)ks * HC_RADIX_BINS, w.sel[ks * 4 + 1], d2, remaining);
-            prefix = (w.sel[ks * 4 + 0] << 11) | d2;
-        }
-        if ((threadIdx.x & 63) == 0) {
-            sm_prefix[ks] = prefix;
-            if (blockIdx.x == 0) {   // state for the next pass (every workgroup computes the same value)
-                w.sel[ks * 4 + (PASS == 2 ? 0 : 2)] = prefix;
-                w.sel[ks * 4 + (PASS == 2 ? 1 : 3)] = remaining;
-            }
-        }
-    }
-    __syncthreads();
-    const float* srow = scores + (size_t)rep * ws.max_ctx;
-    for (int ch = c0; ch < c1; ch += 2) {         // two chunks' loads in flight
-        uint32_t key[2][4];
-        bool in[2][4];
-        load_keys(srow, lo4 + ch * HC_SEL_CHUNK + threadIdx.x * 4, rd.lo, rd.hi, key[0], in[0]);
-        load_keys(srow, lo4 + (ch + 1) * HC_SEL_CHUNK + threadIdx.x * 4, rd.lo, ch + 1 < c1 ? rd.hi : 0, key[1], in[1]);
-        for (int ks = 0; ks < rd.nk; ++ks) {
-            const uint32_t prefix = sm_prefix[ks];
+    const RepDev rd = it.reps[rep];
+    const int lane = threadIdx.x & 63, stride = gridDim.x * NWAVE;
+    int ch = blockIdx.x * NWAVE + (threadIdx.x >> 6);
+    if (ch >= rd.nchunk) return;
+    const Ws w = it.ws.rep(rep);
+    const float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
+    constexpr int HALF = HC_SEL_CHUNK / 64 / 2;
+    float s[HALF];
+    auto load = [&](int j0) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
+        for (int r = 0; r < HALF; ++r) {
+            const int j = j0 + r * 64 + lane;
+            s[r] = j < rd.hi ? srow[j] : 0.f;
+        }
+    };
+    load(rd.lo + ch * HC_SEL_CHUNK);
+    int kmax = 1;
+    for (int ks = 0; ks < rd.nk; ++ks) kmax = max(kmax, it.reps[rep].k[ks]);      // (indexing the register copy would spill it)
+    uint32_t digit, remaining, count;
+    find_digit(w.hist, (uint32_t)kmax, digit, remaining, count);
+    for (; ch < rd.nchunk; ch += stride) {
+        const int first = rd.lo + ch * HC_SEL_CHUNK;
+        uint32_t at = 0;
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            const int j0 = first + half * (HC_SEL_CHUNK / 2);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (!in[u][i]) continue;
-                    if (PASS == 2) {
-                        if ((key[u][i] >> 21) == prefix) atomicAdd(&sh[ks * HC_RADIX_BINS + ((key[u][i] >> 10) & 0x7ffu)], 1u);
-                    } else {
-                        if ((key[u][i] >> 10) == prefix) atomicAdd(&sh[ks * HC_RADIX_BINS + (key[u][i] & 0x3ffu)], 1u);
-                    }
+            for (int r = 0; r < HALF; ++r) {
+                const uint32_t key = hc_score_key(s[r]);
+                const bool keep = j0 + r * 64 + lane < rd.hi && (key >> 21) >= digit;
+                const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+                if (keep) {
+                    const size_t d = (size_t)ch * HC_SEL_CHUNK + at + lanes_below(m);
+                    w.sv_key[d] = key;
+                    w.sv_off[d] = (uint16_t)(half * (HC_SEL_CHUNK / 2) + r * 64 + lane);
                 }
+                at += (uint32_t)__builtin_popcountll(m);
             }
+            if (half == 0) load(j0 + HC_SEL_CHUNK / 2);
+            else if (ch + stride < rd.nchunk) load(rd.lo + (ch + stride) * HC_SEL_CHUNK);
         }
-    }
-    __syncthreads();
-    uint32_t* gh = PASS == 2 ? w.h2 : w.h3;
-    for (int i = threadIdx.x; i < rd.nk * HC_RADIX_BINS; i += BLK)
-        if (sh[i]) atomicAdd(&gh[i], sh[i]);
-}
-
-// Keys of the 16 consecutive candidates of a lane (positions first16 .. first16+15, first16 a multiple of 4:
-// four 16-byte loads) and the mask of those inside [lo, hi).  One wave covers a chunk this way, in position
-// order, so the ordered passes below need no workgroup barriers.
-__device__ __forceinline__ void load_keys16(const float* __restrict__ srow, int first16, int lo, int hi, uint32_t (&key)[16],
-                                            uint32_t& inmask)
-{
-    float4 v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (first16 + 4 * q < hi) v[q] = *reinterpret_cast<const float4*>(srow + first16 + 4 * q);   // row stride is a multiple of 64: in bounds
-    }
-    inmask = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float f[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = first16 + 4 * q + i;
-            if (j >= lo && j < hi) inmask |= 1u << (4 * q + i);
-            key[4 * q + i] = score_key(f[i]);
-        }
-    }
-}
-
-// Finds the threshold key of every set size, then per chunk the counts of greater and of equal keys.
-// Wave v of the workgroup takes the chunks c0 + v, c0 + v + 4, ... of the workgroup's span.
-__global__ __launch_bounds__(BLK) void mon_count(MonBatch B, int span, int G)
-{
-    __shared__ uint32_t sm_tau[HC_MAX_K_PER_REP];
-    const MonItem& it = B.it[blockIdx.z];
-    const int rep = blockIdx.y;
-    if (rep >= it.n_reps || mon_skip(it, rep)) return;
-    const Ws ws = it.ws;
-    const RepDev* __restrict__ reps = it.reps;
-    const float* __restrict__ scores = it.scores;
-    const RepDev rd = reps[rep];
-    const int lo4 = rd.lo & ~3;
-    const int nchunk = chunks_from_lo4(rd);
-    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
-    if (c0 >= nchunk) return;
-    const RepWs w = ws.rep(rep);
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int ks = wv; ks < rd.nk; ks += NWAVE) {
-        uint32_t d3, need;
-        find_digit_wave<1024>(w.h3 + (size_t)ks * HC_RADIX_BINS, w.sel[ks * 4 + 3], d3, need);
-        const uint32_t tau = (w.sel[ks * 4 + 2] << 10) | d3;
-        if (lane == 0) {
-            sm_tau[ks] = tau;
-            // The first workgroup leaves tau / need for mon_write in the first two words, which this
-            // kernel does not read (words 2 and 3 are still being read by the other workgroups).
-            if (blockIdx.x == 0) {
-                w.sel[ks * 4 + 0] = tau;
-                w.sel[ks * 4 + 1] = need;
-            }
-        }
-    }
-    __syncthreads();
-    if (it.need_sense == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
-        // The check of this step's filter.  The split pass dropped the rows whose statistic sum_g 2^(t_g - ref_g)
-        // stayed below cutsum; with this step's own log-sum-exp such a row's score is below
-        // (cutsum / G) max_g 2^(ref_g - lse_g).  If even the smallest list threshold found among the kept rows
-        // reaches that bound (with room for the rounding of the statistic), no dropped row belongs to any list and
-        // the lists are those of all rows.  Otherwise the dense passes redo this pivot from all of its logits.
-        const RepFilter f = it.filt[rep];
-        if (f.cutsum > 0.f) {
-            uint32_t tmin = sm_tau[0];
-            for (int ks = 1; ks < rd.nk; ++ks) tmin = min(tmin, sm_tau[ks]);
-            float delta = 0.f;
-            for (int g = 0; g < G; ++g) delta = fmaxf(delta, exp2f(f.ref[g] - it.lse[(size_t)rd.bh * G + g] * 1.4426950408889634f));
-            const float bound = f.cutsum / (float)G * delta * 1.0001f;
-            if (!(key_score(tmin) >= bound)) it.need_w[rep] = 5;
-        }
-    }
-    const float* srow = scores + (size_t)rep * ws.max_ctx;
-    for (int ch = c0 + wv; ch < c1; ch += NWAVE) {
-        uint32_t key[16], inmask;
-        load_keys16(srow, lo4 + ch * HC_SEL_CHUNK + lane * 16, rd.lo, rd.hi, key, inmask);
-        for (int ks = 0; ks < rd.nk; ++ks) {
-            const uint32_t tau = sm_tau[ks];
-            uint32_t gt = 0, eq = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const bool in = (inmask >> i) & 1u;
-                gt += in && key[i] > tau;
-                eq += in && key[i] == tau;
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                gt += __shfl_xor(gt, o);
-                eq += __shfl_xor(eq, o);
-            }
-            if (lane == 0) {
-                w.cnt[((size_t)ks * ws.max_chunks + ch) * 2 + 0] = gt;
-                w.cnt[((size_t)ks * ws.max_chunks + ch) * 2 + 1] = eq;
-            }
-        }
+        if (lane == 0) w.cnt[ch] = at;
     }
 }
 
 struct DriftCfg {
-    int window, metric, tau_num, tau_den, max_k, tumbling;
+    int window, metric, tau_num, tau_den, max_k, tumbling, agg;
 };
 
-// Keys of the 8 consecutive candidates of a lane (two 16-byte loads) and the mask of those inside [lo, hi).
-__device__ __forceinline__ void load_keys8(const float* __restrict__ srow, int first8, int lo, int hi, uint32_t (&key)[8],
-                                           uint32_t& inmask)
+// ---- the selection and the decision ----
+//
+// One workgroup per pivot and set size (blockIdx.y); the one of set size 0, the monitored list, also takes the
+// decision.  Items are the pivot's candidates in position order: SRC_LOGITS scores them from the stored logits,
+// SRC_SCORES finds their scores in place (given by the caller, or of the rows a filtering split pass kept, whose
+// positions pos_map names), SRC_SURVIVORS takes what mon_compact left.  Their keys are kept in LDS: `cap` of them;
+// items beyond that are read again from the scores in every pass, and survivors that do not all fit (a range full of
+// ties) are given up for the range itself, so that any number of items is handled.
+//
+// Threshold: the keys' range [smallest, largest] is cut into 2048 equal bins, so that the bins are evenly filled
+// whatever the scores' scale is (a fixed top digit of the key would put most items into a handful of bins, whose
+// LDS atomics then serialise).  The bin of the k-th key usually holds a few dozen items: they are collected and
+// ranked by counting.  A bin with more (ties, extreme outliers) is cut again.
+//
+// The kernel is a chain of latencies and, with one wave per SIMD (beside the attention pass) or four (alone), of
+// issue slots: every pass takes GROUP items a lane at a time, whose reads are issued together before the first is
+// used, and set sizes go to workgroups of their own because the passes behind the histogram cost the same for each
+// of them (one workgroup for all: 97 us for 16,700 rows and three set sizes with 256 threads; one each: 43; with 512
+// threads of half the registers, two waves per SIMD: 28).
+enum { SRC_LOGITS = 0, SRC_SCORES = 1, SRC_SURVIVORS = 2 };
+constexpr int SEL_LIST = 128;        // members of a threshold bin that are ranked by counting
+
+constexpr int SEL_KEYS(int words) { return words / 264 * 256; }           // keys, with their masks, that fit in so many words (whole 256s)
+constexpr int SEL_OUTS = 64;         // rows a list goes to that are kept at hand (in the lanes of a register)
+
+// From memory to LDS without passing through registers, so that any number can be in flight: 4 or 16 bytes per lane,
+// the lanes' pieces one behind the other in LDS.  dma_wait() before they are read.  (The wait is the builtin, which the
+// compiler's own counting of outstanding accesses understands: after an opaque one it would wait again, for every
+// store issued since, at each read of LDS.)
+__device__ __forceinline__ void dma4(const void* src_of_lane, void* lds_of_wave)
 {
-    float4 v[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (first8 + 4 * q < hi) v[q] = *reinterpret_cast<const float4*>(srow + first8 + 4 * q);   // row stride is a multiple of 64: in bounds
-    }
-    inmask = 0;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const float f[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = first8 + 4 * q + i;
-            if (j >= lo && j < hi) inmask |= 1u << (4 * q + i);
-            key[4 * q + i] = score_key(f[i]);
-        }
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src_of_lane,
+                                     (__attribute__((address_space(3))) void*)lds_of_wave, 4, 0, 0);
+}
+__device__ __forceinline__ void dma16(const void* src_of_lane, void* lds_of_wave)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src_of_lane,
+                                     (__attribute__((address_space(3))) void*)lds_of_wave, 16, 0, 0);
+}
+__device__ __forceinline__ void dma_wait()
+{
+    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+// words[0, n) to lds[0, n rounded up to 256) by the waves first, first + step, ... of 256 words each; what is past the
+// end repeats words before it.  (words + n rounded up to 4 must be readable where words is 16-byte aligned.)
+__device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n, int first, int step)
+{
+    const int lane = threadIdx.x & 63;
+    const char* src = reinterpret_cast<const char*>(words);
+    if (((uintptr_t)words & 15) == 0) {
+        for (int b = first; b * 256 < n; b += step) dma16(src + (uint32_t)min(b * 256 + lane * 4, (n - 1) & ~3) * 4u, lds + b * 256);
+    } else {
+        for (int b = first; b * 64 < n; b += step) dma4(src + (uint32_t)min(b * 64 + lane, n - 1) * 4u, lds + b * 64);
     }
 }
 
-// Ordered compaction of the index lists of one pivot (blockIdx.y) into topk_idx, and |T ∩ baseline| for the
-// monitored list.  Wave v takes the chunks c0 + v, c0 + v + 4, ... of the workgroup's span, each as two halves of
-// 512 candidates in position order (8 per lane), and reads a half's keys once for all set sizes; what a set size
-// carries from half to half (equal keys seen, entries emitted) lives in LDS: the kernel has to fit, in registers,
-// beside the attention pass's waves on a compute unit.  Lists of equal size (satellites with the same budget)
-// share the selection and differ only in the row they are written to.  No workgroup barriers.
-__global__ __launch_bounds__(BLK, 8) void mon_write(MonBatch B, DriftCfg cfg, int span)
-{
-    __shared__ uint32_t sm_carry[NWAVE][HC_MAX_K_PER_REP][2];      // per wave and set size: equal keys before, entries emitted
-    const MonItem& it = B.it[blockIdx.z];
-    const int rep = blockIdx.y;
-    if (rep >= it.n_reps || mon_skip(it, rep)) return;
-    const Ws ws = it.ws;
-    const RepDev* __restrict__ reps = it.reps;
-    const OutDev* __restrict__ outs = it.outs;
-    const int32_t* __restrict__ pmap = it.pos_map ? it.pos_map + (size_t)rep * ws.max_ctx : nullptr;
-    const float* __restrict__ scores = it.scores;
-    int32_t* __restrict__ topk_idx = it.topk_idx;
-    const RepDev rd = reps[rep];
-    const int lo4 = rd.lo & ~3;
-    const int nchunk = chunks_from_lo4(rd);
-    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
-    if (c0 >= nchunk) return;
-    const RepWs w = ws.rep(rep);
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const float* srow = scores + (size_t)rep * ws.max_ctx;
+__device__ __forceinline__ uint32_t count_true(bool x) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(x)); }
 
-    for (int chunk = c0 + wv; chunk < c1; chunk += NWAVE) {
-        for (int ks = 0; ks < rd.nk; ++ks) {
-            const uint32_t need = w.sel[ks * 4 + 1];
-            const uint32_t* cnt = w.cnt + (size_t)ks * ws.max_chunks * 2;
-            // Prefix over the chunks before this one: equal-keyed candidates seen, and list entries emitted.  A
-            // chunk emits all its greater keys plus as many equal keys as are still needed.
-            uint32_t eq_before = 0, emitted = 0;
-            for (int b0 = 0; b0 < chunk; b0 += 64) {
-                const int b = b0 + lane;
-                const uint32_t g = b < chunk ? cnt[b * 2] : 0u, e = b < chunk ? cnt[b * 2 + 1] : 0u;
-                uint32_t etot;
-                const uint32_t eprev = eq_before + wave_exscan(e, etot);
-                const uint32_t left = need > eprev ? need - eprev : 0u;
-                uint32_t mine = g + (e < left ? e : left);
-                for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-                emitted += mine;
-                eq_before += etot;
+template <int NT, int SRC, int G>
+__global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
+{
+    constexpr int SEL_CHUNKS = NT == 512 ? 1024 : 4096;      // chunks whose survivors' places are kept in LDS
+    constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    __shared__ uint32_t sm_hist[HC_RADIX_BINS];
+    __shared__ uint32_t sm_list[SEL_LIST];
+    __shared__ uint32_t sm_lo, sm_shift, sm_rem, sm_cnt, sm_tau, sm_need, sm_ties, sm_nlist;
+    __shared__ uint32_t sm_min[NW], sm_max[NW], sm_hits[NW], sm_gt[NW], sm_eq[NW];
+    __shared__ uint32_t sm_first[SRC == SRC_SURVIVORS ? SEL_CHUNKS + 1 : 1];   // where every chunk's survivors begin
+    __shared__ uint32_t sm_wsum[NW];
+    __shared__ int32_t sm_ring[HC_MAX_WINDOW + 1];
+    __shared__ int32_t sm_med, sm_trig;
+
+    const MonItem& it = B.it[blockIdx.z];
+    const int rep = blockIdx.x, ks = blockIdx.y;
+    if (rep >= it.n_reps || mon_skip(it, rep)) return;
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int max_ctx = it.ws.max_ctx;
+    const RepDev rd = it.reps[rep];
+    if (ks >= rd.nk) return;
+    const bool deciding = ks == 0;
+    const Ws w = it.ws.rep(rep);
+    const int32_t* pmap = it.pos_map ? it.pos_map + (size_t)rep * max_ctx : nullptr;
+    float* srow = it.scores + (size_t)rep * max_ctx;
+    const int k = it.reps[rep].k[ks];
+    int k_longest = 1;
+    for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
+    const int real_lo = it.real_reps[rep].lo, real_hi = it.real_reps[rep].hi;   // the bitmap is indexed by position
+    const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;               // words of the baseline bitmap
+    for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+    // what the decision needs from memory is asked for now
+    int32_t* rg = it.ring + (size_t)rd.bh * (cfg.window + 1);
+    const int ring_of = deciding && it.store_slot != -2 && tid <= cfg.window ? rg[tid] : 0;
+    const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
+    const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
+    float ref_minus_lse = -INFINITY;                 // lane g: of query head g of the group, in log2 units
+    if (checks && lane < n_group) ref_minus_lse = it.filt[rep].ref[lane] - it.lse[(size_t)rd.bh * n_group + lane] * 1.4426950408889634f;
+    // the rows this list goes to, one to a lane
+    uint32_t v_row = 0;
+    int n_rows = -1;                                 // -1: too many for the lanes, looked up when they are needed
+    if (rd.out_count <= SEL_OUTS) {
+        const OutDev od = it.outs[rd.out_begin + min(lane, rd.out_count - 1)];
+        const bool mine = lane < rd.out_count && od.kslot == ks;
+        uint64_t rows = __builtin_amdgcn_ballot_w64(mine);
+        n_rows = __builtin_popcountll(rows);
+        for (int i = 0; rows != 0; ++i, rows &= rows - 1) {
+            const uint32_t row = lane_get((uint32_t)od.row, __builtin_ctzll(rows));
+            v_row = lane == i ? row : v_row;
+        }
+    }
+
+    int n = rd.hi - rd.lo;
+    bool surv = false;                   // the items are survivors (all of whose keys fit in LDS)
+    if (SRC == SRC_SURVIVORS && rd.nchunk <= SEL_CHUNKS) {
+        uint32_t carry = 0;
+        for (int c0 = 0; c0 < rd.nchunk; c0 += NT) {
+            const int c = c0 + tid;
+            const uint32_t x = c < rd.nchunk ? w.cnt[c] : 0u;
+            uint32_t tot;
+            uint32_t before = carry + wave_exscan(x, tot);
+            if (lane == 0) sm_wsum[wv] = tot;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                before += i < wv ? sm_wsum[i] : 0u;
+                carry += sm_wsum[i];
             }
-            if (lane == 0) {
-                sm_carry[wv][ks][0] = eq_before;
-                sm_carry[wv][ks][1] = emitted;
+            if (c < rd.nchunk) sm_first[c] = before;
+            __syncthreads();
+        }
+        if (tid == 0) sm_first[rd.nchunk] = carry;
+        surv = (int)carry <= SEL_KEYS(lds_words);
+        if (surv) n = (int)carry;
+    }
+    // Dynamic LDS: the keys (a multiple of 256 of them), a mask per 64 keys saying which are in the list, and the
+    // baseline bitmap if it fits behind the items (otherwise the one in the workspace is used).
+    const bool bm_lds = (bw <= lds_words && SEL_KEYS(lds_words - bw) >= n) || (bw <= lds_words / 2 && SEL_KEYS(lds_words) < n);
+    const int cap = min(SEL_KEYS(lds_words - (bm_lds ? bw : 0)), (n + 255) & ~255);
+    uint32_t* sm_key = dyn;
+    uint64_t* sm_mask = reinterpret_cast<uint64_t*>(dyn + cap);
+    uint32_t* sm_bm = dyn + cap + cap / 32;
+    if (bm_lds)
+        for (int i = tid; i < bw; i += NT) sm_bm[i] = 0u;
+    __syncthreads();
+    const bool fits = n <= cap;
+    if (deciding) {                      // baseline list -> bitmap
+        const int32_t* base = it.base_idx + (size_t)rd.bh * cfg.max_k;
+        for (int i0 = tid; i0 < k; i0 += GROUP * NT) {
+            int j[GROUP];
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) j[u] = i0 + u * NT < k ? base[i0 + u * NT] : -1;
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u)
+                if (j[u] >= real_lo && j[u] < real_hi) {
+                    const int jj = j[u] - real_lo;
+                    if (bm_lds) atomicOr(&sm_bm[jj >> 5], 1u << (jj & 31));
+                    else atomicOr(&w.bitmap[jj >> 5], 1u << (jj & 31));
+                }
+        }
+    }
+
+    // ---- the items' keys, and their range ----
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    auto put = [&](int i, uint32_t key) {
+        if (i < cap) sm_key[i] = key;
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+    };
+    if (SRC == SRC_LOGITS) {
+        const float* lrow = it.rep_logits + (size_t)rep * G * max_ctx;
+        float l[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) l[g] = cfg.agg == HC_AGG_PROB ? it.lse[(size_t)rd.bh * G + g] : 0.f;
+        constexpr int U = (NT == 512 ? 2 : 4) / (G >= 8 ? 2 : 1);
+        for (int i0 = tid; i0 < n; i0 += U * NT) {
+            float s[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[u] = score_of<G>(lrow, rd.lo + min(i0 + u * NT, n - 1), l, cfg.agg);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * NT;
+                if (i < n) {
+                    if (deciding || !fits) srow[rd.lo + i] = s[u];
+                    put(i, hc_score_key(s[u]));
+                }
             }
         }
-        uint32_t hits = 0;
-        for (int half = 0; half < 2; ++half) {
-            uint32_t key[8], inmask;
-            const int first8 = lo4 + chunk * HC_SEL_CHUNK + half * (HC_SEL_CHUNK / 2) + lane * 8;
-            load_keys8(srow, first8, rd.lo, rd.hi, key, inmask);
-            // the positions of the lane's 8 rows: themselves, or (rows a filtering split pass kept) what the map says
-            int32_t jj[8];
-            if (pmap) {
-                int4 pa = make_int4(0, 0, 0, 0), pb = pa;
-                if (first8 < rd.hi) pa = *reinterpret_cast<const int4*>(pmap + first8);          // (row stride a multiple of 64: in bounds)
-                if (first8 + 4 < rd.hi) pb = *reinterpret_cast<const int4*>(pmap + first8 + 4);
-                jj[0] = pa.x; jj[1] = pa.y; jj[2] = pa.z; jj[3] = pa.w;
-                jj[4] = pb.x; jj[5] = pb.y; jj[6] = pb.z; jj[7] = pb.w;
+    } else if (SRC == SRC_SURVIVORS && surv) {
+        // item i is survivor i - sm_first[c] of the chunk c in whose run it falls; its position goes to a dense table
+        constexpr int U = NT == 512 ? 4 : 8;
+        for (int i0 = tid; i0 < n; i0 += U * NT) {
+            uint32_t key[U], off[U];
+            int c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = (uint32_t)min(i0 + u * NT, n - 1);
+                int lo = 0, hi = rd.nchunk;
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (sm_first[mid] <= i) lo = mid;
+                    else hi = mid;
+                }
+                c[u] = lo;
+                const uint32_t at = (uint32_t)lo * HC_SEL_CHUNK + (i - sm_first[lo]);
+                key[u] = w.sv_key[at];
+                off[u] = w.sv_off[at];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * NT;
+                if (i < n) {
+                    put(i, key[u]);
+                    const int row = rd.lo + c[u] * HC_SEL_CHUNK + (int)off[u];
+                    w.sv_pos[i] = pmap ? pmap[row] : row;
+                }
+            }
+        }
+    } else {
+        // the scores that fit, 64 to a round, straight to LDS; then each turned into its key in place
+        const int nd = min(n, cap);
+        dma_run(srow + rd.lo, sm_key, nd, wv, NW);
+        dma_wait();
+        __syncthreads();
+        constexpr int U = GROUP;
+        for (int i0 = tid; i0 < nd; i0 += U * NT) {
+            float s[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[u] = __uint_as_float(sm_key[min(i0 + u * NT, nd - 1)]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * NT < nd) put(i0 + u * NT, hc_score_key(s[u]));
+        }
+        for (int i = nd + tid; i < n; i += NT) put(i, hc_score_key(srow[rd.lo + i]));
+    }
+    kmin = ~wave_max(~kmin);
+    kmax = wave_max(kmax);
+    if (lane == 0) {
+        sm_min[wv] = kmin;
+        sm_max[wv] = kmax;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        kmin = min(kmin, sm_min[i]);
+        kmax = max(kmax, sm_max[i]);
+    }
+
+    // GROUP keys of a lane: items first, first + step, ... (those past the end read some item's key)
+    auto keys_of = [&](uint32_t (&key)[GROUP], int first, int step) {
+        if (fits) {
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) key[u] = sm_key[min(first + u * step, n - 1)];
+        } else {
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) key[u] = sm_key[min(first + u * step, cap - 1)];
+            if (first + (GROUP - 1) * step >= cap) {
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u)
+                    if (first + u * step >= cap)
+                        key[u] = hc_score_key(*reinterpret_cast<const float*>(reinterpret_cast<const char*>(srow) + (uint32_t)(rd.lo + min(first + u * step, n - 1)) * 4u));
+            }
+        }
+    };
+
+    // ---- threshold key, ties to take and ties there are, for a list of kt items; the answer in sm_tau / sm_need /
+    // sm_ties (the whole workgroup calls it; sm_hist holds the histogram of all items over [kmin, kmax]) ----
+    const uint32_t range = kmax - kmin;
+    const uint32_t shift = range < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(range);       // range >> shift < 2048
+    auto histogram = [&]() {
+        for (int i0 = tid; i0 < n; i0 += GROUP * NT) {
+            uint32_t key[GROUP];
+            keys_of(key, i0, NT);
+            if (i0 - tid + GROUP * NT <= n) {
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) atomicAdd(&sm_hist[(key[u] - kmin) >> shift], 1u);
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) jj[i] = first8 + i;
+                for (int u = 0; u < GROUP; ++u)
+                    if (i0 + u * NT < n) atomicAdd(&sm_hist[(key[u] - kmin) >> shift], 1u);
             }
-            for (int ks = 0; ks < rd.nk; ++ks) {
-                const uint32_t tau = w.sel[ks * 4 + 0], need = w.sel[ks * 4 + 1];
-                const int k = reps[rep].k[ks];               // (indexing the register copy would spill it)
-                const uint32_t eq_before = sm_carry[wv][ks][0], emitted = sm_carry[wv][ks][1];      // (written by this wave)
-                uint32_t my_eq = 0;
+        }
+        __syncthreads();
+    };
+    auto threshold = [&](int kt) {
+        if (wv == 0) {
+            uint32_t digit, rem, count;
+            find_digit(sm_hist, (uint32_t)kt, digit, rem, count);
+            if (lane == 0) {
+                sm_lo = kmin + (digit << shift);
+                sm_shift = shift;
+                sm_rem = rem;
+                sm_cnt = count;
+                sm_nlist = 0u;
+                sm_tau = 0xffffffffu;
+                sm_need = sm_ties = 0u;
+            }
+        }
+        __syncthreads();
+        while (sm_cnt > SEL_LIST && sm_shift > 0u) {                     // (the same for every thread)
+            const uint32_t lo = sm_lo, s = sm_shift, s2 = s > 11u ? s - 11u : 0u, k2 = sm_rem;
+            __syncthreads();
+            for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+            __syncthreads();
+            for (int i0 = tid; i0 < n; i0 += GROUP * NT) {
+                uint32_t key[GROUP];
+                keys_of(key, i0, NT);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) my_eq += ((inmask >> i) & 1u) && key[i] == tau;
-                uint32_t eq_tot;
-                uint32_t eq_rank = eq_before + wave_exscan(my_eq, eq_tot);
-                uint32_t selmask = 0, my_sel = 0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (!((inmask >> i) & 1u)) continue;
-                    bool sel = key[i] > tau;
-                    if (key[i] == tau) {
-                        sel = eq_rank < need;
-                        ++eq_rank;
-                    }
-                    if (sel) {
-                        selmask |= 1u << i;
-                        ++my_sel;
-                    }
-                }
-                uint32_t sel_tot;
-                const uint32_t pos0 = emitted + wave_exscan(my_sel, sel_tot);
+                for (int u = 0; u < GROUP; ++u)
+                    if (i0 + u * NT < n && key[u] >= lo && ((key[u] - lo) >> s) == 0u) atomicAdd(&sm_hist[(key[u] - lo) >> s2], 1u);
+            }
+            __syncthreads();
+            if (wv == 0) {
+                uint32_t digit, rem, count;
+                find_digit(sm_hist, k2, digit, rem, count);
                 if (lane == 0) {
-                    sm_carry[wv][ks][0] = eq_before + eq_tot;
-                    sm_carry[wv][ks][1] = emitted + sel_tot;
-                }
-                if (ks == 0) {
-                    // |T ∩ baseline| of the monitored list (set size 0): the bitmap words of the selected rows, all
-                    // loads issued together (a row that is not selected reads word 0 and does not count)
-                    uint32_t wd[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) wd[i] = w.bitmap[((selmask >> i) & 1u) ? (jj[i] >> 5) : 0];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) hits += ((selmask >> i) & 1u) & (wd[i] >> (jj[i] & 31));
-                }
-                for (int o = rd.out_begin; o < rd.out_begin + rd.out_count; ++o) {      // the rows this list goes to
-                    const OutDev od = outs[o];
-                    if (od.kslot != ks) continue;
-                    int32_t* dst = topk_idx + (size_t)od.row * cfg.max_k;
-                    uint32_t pos = pos0;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        if (selmask & (1u << i)) {
-                            if (pos < (uint32_t)k) dst[pos] = jj[i];     // pos < k always holds; the guard keeps a corrupt state in bounds
-                            ++pos;
-                        }
-                    }
+                    sm_lo = lo + (digit << s2);
+                    sm_shift = s2;
+                    sm_rem = rem;
+                    sm_cnt = count;
                 }
             }
+            __syncthreads();
         }
-        // Per-chunk hit counts of the monitored list, summed by mon_decide: hundreds of atomics on one word would serialise.
-        for (int o2 = 32; o2 > 0; o2 >>= 1) hits += __shfl_xor(hits, o2);
-        if (lane == 0) ws.hits[(size_t)rep * (ws.max_chunks + 1) + chunk] = hits;
-    }
-}
-
-// Leaves a pivot's histograms and baseline bitmap clear for the next call.
-__device__ __forceinline__ void clear_rep_ws(const RepWs& w, int hi)
-{
-    uint4* h4 = reinterpret_cast<uint4*>(w.h1);
-    for (int i = threadIdx.x; i < (1 + 2 * HC_MAX_K_PER_REP) * HC_RADIX_BINS / 4; i += BLK) h4[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = threadIdx.x; i < (hi + 31) / 32; i += BLK) w.bitmap[i] = 0u;
-}
-
-// One workgroup per pivot, after mon_write has completed (the kernel boundary makes its lists and the
-// intersection count visible): window update, decision, baseline update.
-__global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int G)
-{
-    const MonItem& it = B.it[blockIdx.y];
-    if ((int)blockIdx.x >= it.n_reps) return;
-    const Ws ws = it.ws;
-    const RepDev* __restrict__ reps = it.reps;
-    const int32_t* __restrict__ topk_idx = it.topk_idx;
-    int32_t* __restrict__ base_idx = it.base_idx;
-    int32_t* __restrict__ ring = it.ring;
-    int32_t* __restrict__ inter_out = it.inter;
-    int32_t* __restrict__ flag_out = it.flag;
-    // The lower median is found by ranking (no local arrays: they would live in scratch memory, and a
-    // kernel that needs scratch is far slower to launch).
-    __shared__ int32_t sm_ring[HC_MAX_WINDOW];
-    __shared__ int32_t sm_med;
-    __shared__ int32_t sm_trig;
-    const RepDev rd = reps[blockIdx.x];
-    const int real_hi = it.real_reps[blockIdx.x].hi;     // the bitmap is indexed by position
-    if (it.need_sense >= 0) {
-        const bool need = it.need_r[blockIdx.x] != 0;
-        if (it.need_sense == 1 && !need) return;          // the filtered chain decided: nothing to redo
-        if (it.need_sense == 0 && need) {                  // the dense chain decides; it starts from a clear workspace
-            clear_rep_ws(ws.rep(blockIdx.x), real_hi);
-            return;
+        const uint32_t lo = sm_lo, s = sm_shift, rem = sm_rem;
+        if (s == 0u) {                               // the bin is a single key
+            if (tid == 0) {
+                sm_tau = lo;
+                sm_need = rem;
+                sm_ties = sm_cnt;
+            }
+        } else {
+            for (int i0 = tid; i0 < n; i0 += GROUP * NT) {
+                uint32_t key[GROUP];
+                keys_of(key, i0, NT);
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u)
+                    if (key[u] - lo < 1u << s && i0 + u * NT < n) {         // (lo + 2^s does not pass the largest 32-bit value)
+                        const uint32_t at = atomicAdd(&sm_nlist, 1u);
+                        if (at < SEL_LIST) sm_list[at] = key[u];
+                    }
+            }
+            __syncthreads();
+            if (wv == 0) {                           // one member to a lane (or two), compared with all of them
+                const int m = (int)min(sm_nlist, (uint32_t)SEL_LIST);
+                const uint32_t a = lane < m ? sm_list[lane] : 0u;
+                uint32_t gt_a = 0, eq_a = 0;
+                auto settle = [&](bool one, uint32_t key, uint32_t gt, uint32_t eq) {
+                    if (one && gt < rem && rem <= gt + eq) {              // (equal keys write equal values)
+                        sm_tau = key;
+                        sm_need = rem - gt;
+                        sm_ties = eq;
+                    }
+                };
+                if (m <= 64) {
+#pragma unroll 4
+                    for (int i = 0; i < m; ++i) {
+                        const uint32_t o = lane_get(a, i);
+                        gt_a += o > a;
+                        eq_a += o == a;
+                    }
+                } else {
+                    const uint32_t b = lane + 64 < m ? sm_list[lane + 64] : 0u;
+                    uint32_t gt_b = 0, eq_b = 0;
+                    for (int i = 0; i < m; ++i) {
+                        const uint32_t o = i < 64 ? lane_get(a, i) : lane_get(b, i - 64);
+                        gt_a += o > a;
+                        eq_a += o == a;
+                        gt_b += o > b;
+                        eq_b += o == b;
+                    }
+                    settle(lane + 64 < m, b, gt_b, eq_b);
+                }
+                settle(lane < m, a, gt_a, eq_a);
+            }
         }
-    }
-    const int k = rd.k[0];
-    int32_t* rg = ring + (size_t)rd.bh * (cfg.window + 1);
-    int n = rg[0];
-    if (n < 0 || n > cfg.window) n = 0;
-    const int drop = n == cfg.window ? 1 : 0;        // sliding window: the oldest value leaves
-    __shared__ uint32_t sm_hits[NWAVE];
-    {
-        const int lo4 = rd.lo & ~3;
-        const int nchunk = (rd.hi - lo4 + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-        uint32_t h = 0;
-        for (int c = threadIdx.x; c < nchunk; c += BLK) h += ws.hits[(size_t)blockIdx.x * (ws.max_chunks + 1) + c];
-        for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o);
-        if ((threadIdx.x & 63) == 0) sm_hits[threadIdx.x >> 6] = h;
+        __syncthreads();
+    };
+    uint32_t tmin = 0;                               // deciding, with a filter: the smallest list threshold
+#pragma unroll 1
+    for (bool longest = deciding && it.filt && k_longest != k;; longest = false) {
+        histogram();
+        threshold(longest ? k_longest : k);
+        tmin = longest || k_longest == k ? sm_tau : tmin;
+        if (!longest) break;
+        __syncthreads();
+        for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;       // (a bin may have been cut again)
         __syncthreads();
     }
-    const int32_t inter = (int32_t)(sm_hits[0] + sm_hits[1] + sm_hits[2] + sm_hits[3]);
+    const uint32_t tau = sm_tau, need = sm_need;
+    const bool all_ties = need == sm_ties;           // every item at the threshold is taken: the usual case
+
+    bool decided_elsewhere = false;
+    if (checks && cutsum > 0.f) {
+        // The check of this step's filter.  The split pass dropped the rows whose statistic sum_g 2^(t_g - ref_g)
+        // stayed below cutsum; with this step's own log-sum-exp such a row's score is below
+        // (cutsum / G) max_g 2^(ref_g - lse_g).  If even the smallest list threshold found among the kept rows
+        // reaches that bound (with room for the rounding of the statistic), no dropped row belongs to any list and
+        // the lists are those of all rows.  Otherwise the dense chain redoes this pivot from all of its logits.
+        // (Only the deciding workgroup looks and sets the filter: the others' lists are then written again.)
+        const float d = exp2f(ref_minus_lse);
+        float delta = 0.f;
+        for (int g = 0; g < n_group; ++g) delta = fmaxf(delta, __uint_as_float(lane_get(__float_as_uint(d), g)));
+        const float bound = cutsum / (float)n_group * delta * 1.0001f;
+        if (!(key_score(tmin) >= bound)) {
+            decided_elsewhere = true;
+            if (tid == 0) it.need[rep] = 5;
+        }
+    }
+
+    uint32_t hits = 0, lane_hits = 0;                // of the wave; of a lane
+    if (!decided_elsewhere) {
+        // The usual case: every round's choice is known now and kept as a mask; the keys are done with, and where the
+        // positions come from a table, the run's part of it takes their place.
+        const bool masked = fits && all_ties;
+        const int32_t* table = SRC == SRC_SURVIVORS && surv ? w.sv_pos : pmap ? pmap + rd.lo : nullptr;
+        // A wave takes a run of the items, 64 to a round, GROUP rounds at a time.  First how many keys above (and at)
+        // the threshold its run holds; then, from the runs before it, where its own entries go, and the list in
+        // position order with |T ∩ baseline| of the monitored one.
+        const int rounds = (n + 63) / 64;
+        // (a table's run is copied 256 entries at a time)
+        const int per = table && masked ? ((rounds + NW - 1) / NW + 3) & ~3 : (rounds + NW - 1) / NW;
+        const int i_begin = min(wv * per * 64, n), i_end = min(i_begin + per * 64, n);
+        const uint32_t floor_key = all_ties ? tau : tau + 1u;            // taken whatever its rank (tau is at most the key of +inf)
+        uint32_t gt = 0, eq = 0;
+        for (int i0 = i_begin; i0 < i_end; i0 += GROUP * 64) {
+            uint32_t key[GROUP], mask_lo = 0, mask_hi = 0;
+            keys_of(key, i0 + lane, 64);
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) {
+                uint64_t m = __builtin_amdgcn_ballot_w64(key[u] >= floor_key);
+                const int left = i_end - (i0 + u * 64);          // of this round's items
+                if (left < 64) m = left > 0 ? m & ((1ull << left) - 1ull) : 0ull;
+                gt += (uint32_t)__builtin_popcountll(m);
+                mask_lo = lane == u ? (uint32_t)m : mask_lo;
+                mask_hi = lane == u ? (uint32_t)(m >> 32) : mask_hi;
+            }
+            if (masked && lane < GROUP && i0 + lane * 64 < i_end) sm_mask[(i0 >> 6) + lane] = ((uint64_t)mask_hi << 32) | mask_lo;
+            if (!all_ties) {
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) eq += count_true(i0 + u * 64 + lane < i_end && key[u] == tau);
+            }
+        }
+        if (masked && table) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // (the run's keys are in no other wave's way)
+            dma_run(table + i_begin, sm_key + i_begin, i_end - i_begin, 0, 1);
+        }
+        if (lane == 0) {
+            sm_gt[wv] = gt;
+            sm_eq[wv] = eq;
+        }
+        __syncthreads();
+        uint32_t out = 0, eqb = 0;                   // entries before this run; ties before it, of which `need` are entries
+        for (int i = 0; i < wv; ++i) {
+            out += sm_gt[i] + min(sm_eq[i], need > eqb ? need - eqb : 0u);
+            eqb += sm_eq[i];
+        }
+        out = (uint32_t)__builtin_amdgcn_readfirstlane((int)out);
+        eqb = (uint32_t)__builtin_amdgcn_readfirstlane((int)eqb);
+        dma_wait();
+        if (masked && bm_lds && n_rows >= 0) {
+            // (nothing but LDS is read here: a read of memory would wait for the stores before it)
+            const uint32_t* bm = sm_bm;
+            for (int i0 = i_begin; i0 < i_end; i0 += GROUP * 64) {
+                const uint64_t masks = lane < GROUP && i0 + lane * 64 < i_end ? sm_mask[(i0 >> 6) + lane] : 0ull;       // lane u: round u
+                int pos[GROUP];
+                if (table) {
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) pos[u] = (int)sm_key[min(i0 + u * 64, cap - 64) + lane];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) pos[u] = rd.lo + i0 + u * 64 + lane;
+                }
+                uint64_t sel[GROUP];
+                uint32_t dst[GROUP];                 // byte offset of the entry in its list
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) {
+                    sel[u] = ((uint64_t)lane_get((uint32_t)(masks >> 32), u) << 32) | lane_get((uint32_t)masks, u);
+                    dst[u] = min(out + lanes_below(sel[u]), (uint32_t)k - 1u) * 4u;      // (always below k; the limit keeps a corrupt state in bounds)
+                    out += (uint32_t)__builtin_popcountll(sel[u]);
+                }
+                for (int o = 0; o < n_rows; ++o) {
+                    char* list = reinterpret_cast<char*>(it.topk_idx + (size_t)lane_get(v_row, o) * cfg.max_k);
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u)
+                        if (__builtin_amdgcn_inverse_ballot_w64(sel[u])) *reinterpret_cast<int32_t*>(list + dst[u]) = pos[u];
+                }
+                if (deciding) {
+                    uint32_t word[GROUP];
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) {
+                        pos[u] = __builtin_amdgcn_inverse_ballot_w64(sel[u]) ? pos[u] - real_lo : 0;
+                        word[u] = bm[pos[u] >> 5];
+                    }
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) hits += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64((word[u] >> (pos[u] & 31)) & 1u) & sel[u]);
+                }
+            }
+        } else {
+#pragma unroll 1
+            for (int i0 = i_begin; i0 < i_end; i0 += 64) {
+                const int i = i0 + lane;
+                const bool in = i < i_end;
+                bool sel = false;
+                int pos = 0;
+                if (masked) {
+                    sel = in && ((sm_mask[i0 >> 6] >> lane) & 1u);
+                    pos = table ? (int)sm_key[min(i, cap - 1)] : rd.lo + i;
+                } else {
+                    const uint32_t key = !in ? 0u : i < cap ? sm_key[i] : hc_score_key(srow[rd.lo + i]);
+                    pos = !in ? 0 : table ? table[i] : rd.lo + i;
+                    const bool is_eq = in && key == tau;
+                    const uint64_t eqm = __builtin_amdgcn_ballot_w64(is_eq);
+                    sel = in && (key > tau || (is_eq && eqb + lanes_below(eqm) < need));
+                    eqb += (uint32_t)__builtin_popcountll(eqm);
+                }
+                const uint64_t selm = __builtin_amdgcn_ballot_w64(sel);
+                const uint32_t dst = min(out + lanes_below(selm), (uint32_t)k - 1u);
+                out += (uint32_t)__builtin_popcountll(selm);
+                if (!sel) continue;
+                if (deciding) {
+                    const int jj = pos - real_lo;
+                    const uint32_t word = bm_lds ? sm_bm[jj >> 5] : __hip_atomic_load(&w.bitmap[jj >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    lane_hits += (word >> (jj & 31)) & 1u;
+                }
+                if (n_rows >= 0) {
+                    for (int o = 0; o < n_rows; ++o) it.topk_idx[(size_t)lane_get(v_row, o) * cfg.max_k + dst] = pos;
+                } else {
+                    for (int o = 0; o < rd.out_count; ++o)
+                        if (it.outs[rd.out_begin + o].kslot == ks) it.topk_idx[(size_t)it.outs[rd.out_begin + o].row * cfg.max_k + dst] = pos;
+                }
+            }
+        }
+    }
+    if (!deciding) return;
+    hits += wave_sum(lane_hits);
+    if (lane == 0) sm_hits[wv] = hits;
+    __syncthreads();
+
+    // ---- the next call finds histogram and bitmap clear ----
+    if (SRC == SRC_SURVIVORS)
+        for (int i = tid; i < HC_RADIX_BINS; i += NT) w.hist[i] = 0u;
+    if (!bm_lds)
+        for (int i = tid; i < bw; i += NT) w.bitmap[i] = 0u;
+    if (decided_elsewhere) return;
+
+    // ---- window, decision, baseline ----
+    int32_t inter = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) inter += (int32_t)sm_hits[i];
+    if (it.store_slot == -2) return;                 // the lists were all that was wanted
+    if (tid <= cfg.window) sm_ring[tid] = ring_of;
+    __syncthreads();
+    int cnt = sm_ring[0];
+    if (cnt < 0 || cnt > cfg.window) cnt = 0;
     if (it.store_slot != -1) {
-        // >= 0: a buffered query of the window scored again at the test step (Algorithm 1): its overlap replaces
+        // A buffered query of the window scored again at the test step (Algorithm 1): its overlap replaces
         // the one stored when the query was current.  Only while the ring is one short of full, i.e. the
-        // monitor call that follows is the one that tests.  -2: the lists were all that was wanted.
-        if (threadIdx.x == 0 && it.store_slot >= 0 && n == cfg.window - 1 && it.store_slot < n) rg[1 + it.store_slot] = inter;
-        clear_rep_ws(ws.rep(blockIdx.x), real_hi);
+        // monitor call that follows is the one that tests.
+        if (tid == 0 && cnt == cfg.window - 1 && it.store_slot < cnt) rg[1 + it.store_slot] = inter;
         return;
     }
-    const int m = n - drop + 1;                      // values in the window after the push
-    if ((int)threadIdx.x < m) sm_ring[threadIdx.x] = (int)threadIdx.x == m - 1 ? inter : rg[1 + drop + threadIdx.x];
+    const int drop = cnt == cfg.window ? 1 : 0;      // sliding window: the oldest value leaves
+    const int m = cnt - drop + 1;                    // values in the window after the push
+    // The lower median is found by ranking (no local arrays: they would live in scratch memory).
+    const int32_t value = tid < m ? (tid == m - 1 ? inter : sm_ring[1 + drop + tid]) : 0;
     __syncthreads();
-    if ((int)threadIdx.x < m) {
-        const int32_t v = sm_ring[threadIdx.x];
+    if (tid < m) sm_ring[tid] = value;
+    __syncthreads();
+    if (tid < m) {
+        const int32_t v = sm_ring[tid];
         int rank = 0;
-        for (int j = 0; j < m; ++j) rank += sm_ring[j] < v || (sm_ring[j] == v && j < (int)threadIdx.x);
+        for (int j = 0; j < m; ++j) rank += sm_ring[j] < v || (sm_ring[j] == v && j < tid);
         if (rank == (m - 1) / 2) sm_med = v;         // lower median
     }
     __syncthreads();
-    if ((int)threadIdx.x < m) rg[1 + threadIdx.x] = sm_ring[threadIdx.x];
-    if (threadIdx.x == 0) {
+    if (tid < m) rg[1 + tid] = sm_ring[tid];
+    if (tid == 0) {
         int trig = 0;
         if (m == cfg.window) {
-            const long long med = sm_med;
-            const long long kk = k;
+            const long long med = sm_med, kl = k;
             if (cfg.metric == HC_METRIC_OVERLAP)
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * kk;                     // med/k < tau
+                trig = med * cfg.tau_den < (long long)cfg.tau_num * kl;                     // med/k < tau
             else
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * (2 * kk - med);         // med/(2k-med) < tau
+                trig = med * cfg.tau_den < (long long)cfg.tau_num * (2 * kl - med);         // med/(2k-med) < tau
         }
         // the window restarts after a retrieval; a tumbling window after every test
         rg[0] = (trig || (cfg.tumbling && m == cfg.window)) ? 0 : m;
-        inter_out[rd.bh] = inter;
-        flag_out[rd.bh] = trig;
+        it.inter[rd.bh] = inter;
+        it.flag[rd.bh] = trig;
         sm_trig = trig;
         if (it.counts) {
-            uint32_t* cn = it.counts + (size_t)blockIdx.x * 4;
+            uint32_t* cn = it.counts + (size_t)rep * 4;
             cn[0] += m == cfg.window;
             cn[1] += (uint32_t)trig;
             cn[2] += it.need_sense == 1;
@@ -716,39 +919,32 @@ __global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int 
         if (it.filt) {
             // The filter of the next step's split pass: rows whose statistic, taken against this step's
             // log-sum-exp, stays below the smallest list threshold of this step divided by the margin are dropped.
-            const RepWs w = ws.rep(blockIdx.x);
-            uint32_t tmin = w.sel[0];                  // (mon_count left every set size's threshold key in word 0)
-            for (int ks = 1; ks < rd.nk; ++ks) tmin = min(tmin, w.sel[ks * 4]);
-            const float tau = key_score(tmin);
+            const float t = key_score(tmin);
             RepFilter f;
-            f.cutsum = (tau > 0.f && tau < 1.0e30f && it.margin >= 1.f) ? (float)G * tau / it.margin : 0.f;
-            for (int g = 0; g < 8; ++g) f.ref[g] = g < G ? it.lse[(size_t)rd.bh * G + g] * 1.4426950408889634f : 0.f;
+            f.cutsum = (t > 0.f && t < 1.0e30f && it.margin >= 1.f) ? (float)n_group * t / it.margin : 0.f;
+            for (int g = 0; g < 8; ++g) f.ref[g] = g < n_group ? it.lse[(size_t)rd.bh * n_group + g] * 1.4426950408889634f : 0.f;
             f.armed = 1;
             for (int i = 0; i < 6; ++i) f.pad[i] = 0;
-            it.filt[blockIdx.x] = f;
+            it.filt[rep] = f;
         }
     }
     __syncthreads();
     if (sm_trig) {                                   // K_base <- K_t
-        const int32_t* src = topk_idx + (size_t)rd.bh * cfg.max_k;
-        int32_t* base = base_idx + (size_t)rd.bh * cfg.max_k;
-        for (int i = threadIdx.x; i < k; i += BLK) base[i] = src[i];
+        const int32_t* src = it.topk_idx + (size_t)rd.bh * cfg.max_k;
+        int32_t* base = it.base_idx + (size_t)rd.bh * cfg.max_k;
+        for (int i = tid; i < k; i += NT) base[i] = src[i];
     }
-    // every other kernel of this call is done with the histograms and the bitmap: leave them clear
-    clear_rep_ws(ws.rep(blockIdx.x), real_hi);
 }
 
-// First pass of the selection over a pivot whose logits the split pass filtered: the rows it kept lie segment by
-// segment in the pivot's block of rep_logits (positions in surv_pos, counts in seg_cnt).  They are scored with this
-// step's log-sum-exp and laid out as one dense run in position order (scores[rep][0, n), dense_pos[rep][0, n)),
-// over which the later passes then work as over a short context; the first-digit histogram and the baseline
-// bitmap are made on the way, as in mon_score_hist.  Every workgroup makes the prefix sums of the pivot's
-// segment counts itself (a few hundred numbers).
+// Scores of the rows a filtering split pass kept.  They lie segment by segment in the pivot's block of rep_logits
+// (positions in surv_pos, counts in seg_cnt); here they are scored with this step's log-sum-exp and laid out as one
+// dense run in position order (scores[rep][0, n), pos_map[rep][0, n)), over which mon_select then works as over a
+// short context.  Every workgroup makes the prefix sums of the pivot's segment counts itself (a few hundred numbers);
+// then a wave takes a segment, whose rows are contiguous on both sides.
 constexpr int MAX_FILTER_SEGS = 2048;
 template <int G>
-__global__ __launch_bounds__(BLK) void mon_sparse_score(MonBatch B, int max_k, int span)
+__global__ __launch_bounds__(BLK, 8) void mon_sparse_score(MonBatch B)
 {
-    __shared__ uint32_t sh[HC_RADIX_BINS];
     __shared__ int sm_pref[MAX_FILTER_SEGS + 1];
     __shared__ int sm_row0[MAX_FILTER_SEGS];
     __shared__ int sm_wsum[NWAVE];
@@ -756,11 +952,14 @@ __global__ __launch_bounds__(BLK) void mon_sparse_score(MonBatch B, int max_k, i
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps) return;
-    const Ws ws = it.ws;
+    const int max_ctx = it.ws.max_ctx;
     const RepDev rd = it.real_reps[rep];
-    const HeadDev hd = it.heads[rd.bh];
-    const int nseg = min(hd.part_count, MAX_FILTER_SEGS);
+    const int part_begin = it.heads[rd.bh].part_begin, part_count = it.heads[rd.bh].part_count;
+    const int nseg = min(part_count, MAX_FILTER_SEGS);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float l[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) l[g] = it.lse[(size_t)rd.bh * G + g];
     if (threadIdx.x == 0) sm_unknown = 0;
     __syncthreads();
     int carry = 0;
@@ -768,13 +967,13 @@ __global__ __launch_bounds__(BLK) void mon_sparse_score(MonBatch B, int max_k, i
         const int sidx = base + threadIdx.x;
         int c = 0;
         if (sidx < nseg) {
-            const SegDev sg = it.segs[hd.part_begin + sidx];
-            c = it.seg_cnt[hd.part_begin + sidx];
-            if (c < 0 || c > sg.row_end - sg.row_begin) {      // not a count the split pass can have written
+            const int row0 = it.segs[part_begin + sidx].row_begin, row1 = it.segs[part_begin + sidx].row_end;
+            c = it.seg_cnt[part_begin + sidx];
+            if (c < 0 || c > row1 - row0) {                    // not a count the split pass can have written
                 sm_unknown = 1;
                 c = 0;
             }
-            sm_row0[sidx] = sg.row_begin;
+            sm_row0[sidx] = row0;
         }
         int inc = c;
 #pragma unroll
@@ -791,86 +990,98 @@ __global__ __launch_bounds__(BLK) void mon_sparse_score(MonBatch B, int max_k, i
         __syncthreads();
     }
     if (threadIdx.x == 0) sm_pref[nseg] = carry;
+    __syncthreads();
     const int n = carry;                                    // rows kept, all of them candidates
     int kmax = 0;
     for (int ks = 0; ks < rd.nk; ++ks) kmax = max(kmax, it.real_reps[rep].k[ks]);       // (indexing the register copy would spill it)
-    // why a pivot goes to the dense passes: 1 more rows kept than the launch was sized for, 2 fewer than the longest
-    // list needs, 3 a segment's count is out of range, 4 too many segments, (5: the check failed, below)
-    const int why = sm_unknown != 0 ? 3 : hd.part_count > MAX_FILTER_SEGS ? 4 : n > it.cap_rows ? 1 : n < kmax ? 2 : 0;
-    const bool bad = why != 0;
+    // why a pivot goes to the dense chain: 1 more rows kept than the launch was sized for, 2 fewer than the longest
+    // list needs, 3 a segment's count is out of range, 4 too many segments, (5: the check of mon_select failed)
+    const int why = sm_unknown != 0 ? 3 : part_count > MAX_FILTER_SEGS ? 4 : n > it.cap_rows ? 1 : n < kmax ? 2 : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // the pivot as the later passes see it: a context of n rows, all of them candidates
+        // the pivot as mon_select sees it: a context of n rows, all of them candidates
         RepDev* v = it.vreps + rep;
         v->bh = rd.bh;
         v->lo = 0;
-        v->hi = bad ? 0 : n;
+        v->hi = why ? 0 : n;
         v->nk = rd.nk;
         for (int ks = 0; ks < rd.nk; ++ks) v->k[ks] = it.real_reps[rep].k[ks];
-        v->nchunk = bad ? 0 : (n + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
+        v->nchunk = why ? 0 : (n + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
         v->out_begin = rd.out_begin;
         v->out_count = rd.out_count;
-        it.need_w[rep] = why;
+        it.need[rep] = why;
     }
-    if (bad) return;
-    const int nchunk = (n + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
-    if (c0 >= nchunk) return;
-    const RepWs w = ws.rep(rep);
-    for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
-    // baseline list -> bitmap (each active workgroup takes a slice of the list)
-    const int32_t* basel = it.base_idx + (size_t)rd.bh * max_k;
-    const int nblk = (nchunk + span - 1) / span;
-    for (int i = blockIdx.x * BLK + threadIdx.x; i < rd.k[0]; i += nblk * BLK) {
-        const int j = basel[i];
-        if (j >= rd.lo && j < rd.hi) atomicOr(&w.bitmap[j >> 5], 1u << (j & 31));
-    }
-    __syncthreads();
-    float l[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) l[g] = it.lse[(size_t)rd.bh * G + g];
-    const float* lrow = it.rep_logits + (size_t)rep * G * ws.max_ctx;
-    const int32_t* prow = it.surv_pos + (size_t)rep * ws.max_ctx;
-    float* srow = it.scores + (size_t)rep * ws.max_ctx;
-    int32_t* drow = it.dense_pos + (size_t)rep * ws.max_ctx;
-    for (int ch = c0; ch < c1; ++ch) {
-#pragma unroll
-        for (int i = 0; i < PER_THREAD; ++i) {
-            const int d = ch * HC_SEL_CHUNK + i * BLK + threadIdx.x;
-            if (d >= n) continue;
-            int lo = 0, hi = nseg;                             // the segment whose run holds kept row d
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (sm_pref[mid] <= d) lo = mid;
-                else hi = mid;
-            }
-            const int src = sm_row0[lo] + (d - sm_pref[lo]);
-            const float sc = score_of<G>(lrow, src, l, HC_AGG_PROB);
-            srow[d] = sc;
-            drow[d] = prow[src];
-            atomicAdd(&sh[score_key(sc) >> 21], 1u);
+    if (why) return;
+    const float* lrow = it.rep_logits + (size_t)rep * G * max_ctx;
+    const int32_t* prow = it.surv_pos + (size_t)rep * max_ctx;
+    float* srow = it.scores + (size_t)rep * max_ctx;
+    int32_t* drow = it.pos_map + (size_t)rep * max_ctx;
+    for (int s = blockIdx.x * NWAVE + wv; s < nseg; s += gridDim.x * NWAVE) {
+        const int row0 = sm_row0[s], d0 = sm_pref[s], cnt = sm_pref[s + 1] - d0;
+        for (int i = lane; i < cnt; i += 64) {
+            const float sc = score_of<G>(lrow, row0 + i, l, HC_AGG_PROB);
+            const int32_t p = prow[row0 + i];
+            srow[d0 + i] = sc;
+            drow[d0 + i] = p;
         }
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK)
-        if (sh[i]) atomicAdd(&w.h1[i], sh[i]);
 }
 
 }   // namespace
 
-// The launches of one chain of selection passes over a batch of layers.  mode 0: the plain chain (every pivot, all
-// candidate positions).  mode 1: the chain over the rows a filtering split pass kept.  mode 2: the dense chain that
-// stands by behind mode 1, for the pivots whose check failed.  ws_first: which workspace copy the first layer uses.
+// Launches mon_select over the batch, with LDS for want_keys items and a baseline bitmap of bm_words as far as it goes.
+template <int NT, int SRC>
+static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
+{
+    // Alone a workgroup may take a whole compute unit's LDS.  Beside the attention pass it has to leave room for two
+    // of its workgroups: 26 KB each with the pivot-logit filter, 41 KB without.
+    constexpr int STATIC = (SRC != SRC_SURVIVORS ? 10 : NT == 512 ? 15 : 27) * 1024;          // (what the kernel itself declares, rounded up)
+    const int room = (!ctx->beside_now ? 152 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - STATIC;
+    const unsigned lds = (unsigned)std::min((long long)room, ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
+#define HC_SELECT(GG)                                                                                                        \
+    mon_select<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4))
+    if constexpr (SRC != SRC_LOGITS) {
+        HC_SELECT(1);                                                // (the group size only matters where logits are read)
+    } else {
+        switch (ctx->G) {
+        case 1: HC_SELECT(1); break;
+        case 2: HC_SELECT(2); break;
+        case 4: HC_SELECT(4); break;
+        default: HC_SELECT(8); break;
+        }
+    }
+#undef HC_SELECT
+    HC_HIP(ctx, hipGetLastError());
+    return HC_OK;
+}
+
+template <int SRC>
+static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
+{
+    return ctx->beside_now ? launch_select_nt<512, SRC>(ctx, B, dc, grid, want_keys, bm_words, st)
+                           : launch_select_nt<1024, SRC>(ctx, B, dc, grid, want_keys, bm_words, st);
+}
+
+// Candidates up to which one workgroup per pivot does everything, from the scores on.  What lies against more is that
+// the exponentials of the scores are then made by one compute unit: at 32K candidates and a group of four this takes 18
+// of 44 us, where the three launches take 29 in all; at 4K it takes 3.5 us of 13, where two more launches cost 8.
+constexpr int SELECT_DIRECT_ALONE = 8192, SELECT_DIRECT_BESIDE = 8192;
+
+// The launches of one chain over a batch of layers.  mode 0: the plain chain (every pivot, all candidate positions).
+// mode 1: the chain over the rows a filtering split pass kept.  mode 2: the dense chain that stands by behind
+// mode 1, for the pivots whose check failed (their logits, scores and histogram are there already: see
+// hc_launch_rep_logits).  ws_first: which workspace copy the first layer uses.
 static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* calls, int ws_first, int scores_given, int mode,
                            hipStream_t st)
 {
     const hc_config& c = ctx->cfg;
     MonBatch B{};
-    int max_reps = 0, max_nchunk = 0, max_nk = 0;
+    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0;
+    bool armed = true;
     for (int i = 0; i < n; ++i) {
         const hc_monitor_call& x = *calls[i];
         hc_monitor_ws& m = ctx->ws[ws_first + i];
         MonItem& it = B.it[i];
-        it.ws = Ws{m.hist, m.sel, m.misc, m.cnt, m.bitmap, m.hits, ctx->max_chunks, c.max_ctx};
+        it.ws = Ws{m.hist, m.cnt, m.bitmap, m.sv_key, m.sv_off, m.sv_pos, ctx->max_chunks, c.max_ctx};
         it.reps = x.reps ? x.reps : x.L->reps;
         it.real_reps = it.reps;
         it.outs = x.reps ? x.outs : x.L->outs;
@@ -888,26 +1099,27 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         it.need_sense = -1;
         if (!x.reps && x.store_slot == -1) it.counts = x.L->mon_counts;
         int nchunk = x.reps ? x.max_nchunk : x.L->max_nchunk;
+        max_real_chunk = std::max(max_real_chunk, nchunk);
         if (mode != 0) {
             const hc_layer* L = x.L;
             it.need_sense = mode == 1 ? 0 : 1;
-            it.need_r = it.need_w = L->need;
+            it.need = L->need;
             it.filt = L->filt;
             it.counts = L->mon_counts;
             it.margin = ctx->filter_margin;
             if (mode == 1) {
                 it.reps = L->vreps;
-                it.pos_map = it.dense_pos = L->dense_pos;
+                it.pos_map = L->dense_pos;
                 it.heads = L->heads;
                 it.segs = L->segs;
                 it.seg_cnt = L->seg_cnt;
                 it.surv_pos = L->surv_pos;
                 it.vreps = L->vreps;
                 // Once the filter is set few rows are kept (about 1.6 times the longest list at the usual margin of
-                // 1.25); a step that keeps more is handed to the dense chain, so the launches need not be sized for
-                // it, and every workgroup a launch does not have is one that does not queue for a compute unit.
+                // 1.25); a step that keeps more is handed to the dense chain.
                 const int armed_cap = std::min(c.max_ctx, (ctx->filter_margin <= 1.5f ? 2 : 4) * L->max_k_any + 4096);
                 it.cap_rows = L->filter_armed ? armed_cap : c.max_ctx;
+                armed = armed && L->filter_armed;
                 nchunk = std::min(nchunk, (it.cap_rows + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK);
             }
         }
@@ -915,50 +1127,49 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         max_nchunk = std::max(max_nchunk, nchunk);
         max_nk = std::max(max_nk, x.reps ? x.max_nk : x.L->max_nk);
         if (m.dirty && mode != 2) {     // a previous call that used this workspace copy did not run to its last kernel
-            mon_prep<<<dim3(16, ctx->max_reps), dim3(256), 0, st>>>(it.ws, c.max_ctx);
+            mon_prep<<<dim3(16, m.reps), dim3(256), 0, st>>>(it.ws);
             HC_HIP(ctx, hipGetLastError());
         }
         m.dirty = true;
     }
     if (max_reps == 0) return HC_OK;
-    // chunks per workgroup: aim at about 512 workgroups per launch, at most 8 chunks each
-    // (the stand-by chain is there at every step and normally has nothing to do: few, long workgroups)
-    const int span = mode == 2 ? 32
-                               : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (n * max_reps * (max_nchunk + 1)) / 512));
-    const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
+    const DriftCfg dc{c.window, c.metric, c.tau_num, c.tau_den, c.max_k, c.window_mode != HC_WINDOW_SLIDING, c.agg};
+    const dim3 gsel(max_reps, max_nk, n);
+    const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
+    const int pivots = max_reps * n;
     if (mode == 1) {
+        // enough waves for a segment each of a long context's few hundred, no more workgroups than compute units
+        const dim3 g(std::max(4, std::min(armed ? 32 : 128, (armed ? 256 : 1024) / pivots)), max_reps, n);
         switch (ctx->G) {
-        case 1: mon_sparse_score<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<1>, 0), st>>>(B, c.max_k, span); break;
-        case 2: mon_sparse_score<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<2>, 0), st>>>(B, c.max_k, span); break;
-        case 4: mon_sparse_score<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<4>, 0), st>>>(B, c.max_k, span); break;
-        default: mon_sparse_score<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<8>, 0), st>>>(B, c.max_k, span); break;
+        case 1: mon_sparse_score<1><<<g, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<1>, 0), st>>>(B); break;
+        case 2: mon_sparse_score<2><<<g, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<2>, 0), st>>>(B); break;
+        case 4: mon_sparse_score<4><<<g, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<4>, 0), st>>>(B); break;
+        default: mon_sparse_score<8><<<g, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<8>, 0), st>>>(B); break;
         }
-    } else {
-        switch (ctx->G) {
-        case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, c.max_k, span); break;
-        case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, c.max_k, span); break;
-        case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, c.max_k, span); break;
-        default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, c.max_k, span); break;
-        }
+        HC_HIP(ctx, hipGetLastError());
+        scores_given = 1;                     // from here on the scores are there
+        if (armed) return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
     }
+    if (mode != 2 && max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
+        return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st)
+                            : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
+    if (mode != 2) {
+        // chunks per workgroup: aim at about 512 workgroups per launch, at most 8 chunks each
+        const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / 512));
+        const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
+        switch (ctx->G) {
+        case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span); break;
+        case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span); break;
+        case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span); break;
+        default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span); break;
+        }
+        HC_HIP(ctx, hipGetLastError());
+    }
+    // (the stand-by chain is there at every step and normally has nothing to do: few workgroups, several chunks a wave)
+    const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, mode == 2 ? 8 : std::max(4, 1024 / pivots)));
+    mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B);
     HC_HIP(ctx, hipGetLastError());
-    // the later passes start at a multiple of 4 positions, which can add one chunk
-    const dim3 gk((max_nchunk + 1 + span - 1) / span, max_reps, n);
-    const size_t hist_lds = (size_t)max_nk * HC_RADIX_BINS * sizeof(uint32_t);
-    mon_hist<2><<<gk, dim3(BLK), hc_side_lds(ctx, (const void*)mon_hist<2>, (unsigned)hist_lds), st>>>(B, span);
-    HC_HIP(ctx, hipGetLastError());
-    mon_hist<3><<<gk, dim3(BLK), hc_side_lds(ctx, (const void*)mon_hist<3>, (unsigned)hist_lds), st>>>(B, span);
-    HC_HIP(ctx, hipGetLastError());
-    mon_count<<<gk, dim3(BLK), hc_side_lds(ctx, (const void*)mon_count, 0), st>>>(B, span, ctx->G);
-    HC_HIP(ctx, hipGetLastError());
-    DriftCfg dc{c.window, c.metric, c.tau_num, c.tau_den, c.max_k, c.window_mode != HC_WINDOW_SLIDING};
-    // the write pass has no per-workgroup set-up to amortise: one chunk per wave
-    const int span_w = mode == 2 ? 4 * NWAVE : NWAVE;
-    mon_write<<<dim3((max_nchunk + 1 + span_w - 1) / span_w, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_write, 0), st>>>(B, dc, span_w);
-    HC_HIP(ctx, hipGetLastError());
-    mon_decide<<<dim3(max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_decide, 0), st>>>(B, dc, ctx->G);
-    HC_HIP(ctx, hipGetLastError());
-    return HC_OK;
+    return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
 }
 
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st)
@@ -982,17 +1193,15 @@ hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, in
     if (s == HC_OK && n_filt > 0) {
         s = run_chain(ctx, n_filt, filt, n_plain, 0, 1, st);
         // behind it, for the pivots whose check failed (decided on the device; normally none): all logits over
-        // again, then the plain passes over them
+        // again with their scores and histogram, then the plain chain from there
         if (s == HC_OK) {
-            const hc_layer* layers[HC_MAX_GROUP];
-            const void* arenas[HC_MAX_GROUP];
-            float* logits[HC_MAX_GROUP];
+            hc_rep_logits_call rl[HC_MAX_GROUP];
             for (int i = 0; i < n_filt; ++i) {
-                layers[i] = filt[i]->L;
-                arenas[i] = filt[i]->arena ? filt[i]->arena : filt[i]->L->last_arena;
-                logits[i] = const_cast<float*>(filt[i]->rep_logits);
+                const hc_monitor_call& x = *filt[i];
+                rl[i] = hc_rep_logits_call{x.L, x.arena ? x.arena : x.L->last_arena, const_cast<float*>(x.rep_logits), x.lse, x.scores,
+                                           ctx->ws[n_plain + i].hist};
             }
-            s = hc_launch_rep_logits(ctx, n_filt, layers, arenas, logits, st);
+            s = hc_launch_rep_logits(ctx, n_filt, rl, st);
         }
         if (s == HC_OK) s = run_chain(ctx, n_filt, filt, n_plain, 0, 2, st);
         if (s == HC_OK)
@@ -1010,13 +1219,17 @@ hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, in
 
 hc_status hc_monitor_set_lds_limit()
 {
-    // a pivot with HC_MAX_K_PER_REP distinct set sizes needs 64 KB of dynamic LDS for its histograms, on top of
-    // the kernels' static LDS: above the default limit of 64 KB per workgroup; and beside the attention pass every
-    // kernel here reserves more than half of a compute unit's LDS (hc_side_lds)
-    const void* fns[] = {(const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write,
-                         (const void*)mon_decide, (const void*)mon_sparse_score<1>, (const void*)mon_sparse_score<2>,
+    // mon_select takes most of a compute unit's LDS, and beside the attention pass every kernel here reserves more
+    // than half of it (hc_side_lds)
+    const void* fns[] = {(const void*)mon_compact, (const void*)mon_sparse_score<1>, (const void*)mon_sparse_score<2>,
                          (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>, (const void*)mon_score_hist<1>,
-                         (const void*)mon_score_hist<2>, (const void*)mon_score_hist<4>, (const void*)mon_score_hist<8>};
+                         (const void*)mon_score_hist<2>, (const void*)mon_score_hist<4>, (const void*)mon_score_hist<8>,
+                         (const void*)mon_select<512, SRC_LOGITS, 1>, (const void*)mon_select<512, SRC_LOGITS, 2>,
+                         (const void*)mon_select<512, SRC_LOGITS, 4>, (const void*)mon_select<512, SRC_LOGITS, 8>,
+                         (const void*)mon_select<512, SRC_SCORES, 1>, (const void*)mon_select<512, SRC_SURVIVORS, 1>,
+                         (const void*)mon_select<1024, SRC_LOGITS, 1>, (const void*)mon_select<1024, SRC_LOGITS, 2>,
+                         (const void*)mon_select<1024, SRC_LOGITS, 4>, (const void*)mon_select<1024, SRC_LOGITS, 8>,
+                         (const void*)mon_select<1024, SRC_SCORES, 1>, (const void*)mon_select<1024, SRC_SURVIVORS, 1>};
     for (const void* fn : fns)
         if (hc_allow_lds(fn) != hipSuccess) return HC_EHIP;
     return HC_OK;
