@@ -203,8 +203,8 @@ hc_status hc_set_gather_shape(hc_ctx* ctx, int32_t workgroups, int32_t threads);
  * kernel with more workgroups than compute units runs in several rounds (the filtered monitor's launches are sized
  * for about twice the longest list, not for the context, to stay below that).  Measured: -1.1 % of the step at the
  * 224K workload, -1.5 % with 16 ragged sequences, no change at 128K with refills at most steps.  Applies to groups of
- * layers whose attention passes all filter the pivot logits (hc_set_logit_filter): only that form of the split pass
- * is small enough (25 KB of LDS per workgroup) to fit twice beside such a reservation. */
+ * layers whose attention passes all filter the pivot logits (hc_set_logit_filter), with up to four query heads per KV
+ * head: only that form of the split pass is small enough (25 KB of LDS per workgroup) to fit twice beside it. */
 hc_status hc_set_side_lds(hc_ctx* ctx, int32_t bytes);
 
 /* Measurement hook: hands the library n pairs of hipEvent_t (host arrays of handles, copied).  The

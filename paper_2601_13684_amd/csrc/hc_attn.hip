@@ -430,8 +430,11 @@ struct FilterArgs {
     uint16_t* q_keep;          // [n_reps][G][D] copy of the pivots' queries (the monitor may have to score again)
 };
 
-template <int G, int WG_PER_CU, bool FILT>
-__global__ __launch_bounds__(256, WG_PER_CU) void attn_split_kernel(const uint16_t* __restrict__ arena,
+// (Two workgroups per compute unit.  A wave keeps two tiles of 8 rows, 4 KB each, in flight; the group-of-4 case holds
+// 32 query + 64 accumulator registers, and two workgroups keep 64 KB in flight, which measurement shows is enough.
+// Groups of eight have a kernel of their own below.)
+template <int G, bool FILT>
+__global__ __launch_bounds__(256, 2) void attn_split_kernel(const uint16_t* __restrict__ arena,
                                                                     const uint16_t* __restrict__ q,
                                                                     const BlkDev* __restrict__ blks,
                                                                     const SegDev* __restrict__ segs,
@@ -584,6 +587,336 @@ __global__ __launch_bounds__(256, WG_PER_CU) void attn_split_kernel(const uint16
     }
 }
 
+// ---- the split pass for groups of eight query heads: matrix cores ----
+//
+// With eight heads to a K/V row the vector ALUs are the bound, not memory: dot products, cross-lane sums and p.V
+// FMAs come to about 260 instructions per 8 rows and wave, and 64 query + 128 accumulator registers leave room for one
+// wave per SIMD (measured: 84 us for 250 MB, 37 % of the HBM peak).  Here a wave takes 32 rows at a time:
+//   logits   S^T[row][head] = K Q^T by v_mfma_f32_16x16x32_bf16, the K rows straight from memory as the A operand (lane:
+//            row lane % 16, 8 dimensions), the queries as the B operand, held in 16 registers.  The 16 columns are the
+//            eight heads twice.
+//   softmax  lane (n, g) then holds the logits of head n % 8 and of rows 4 g .. 4 g + 3 and 16 + 4 g .. 16 + 4 g + 3,
+//            which is exactly the B operand of the next product (its 8 contraction slots may stand for any 8 rows, as
+//            long as the A operand agrees).  The reference maximum is per head, moved lazily as in the plain pass.
+//   p.V      O^T[dim][head] += V^T P^T.  V goes through a padded LDS tile of the wave's own and comes back transposed
+//            (ds_read_b64_tr_b16).  The weights are not rounded to bf16: a weight is the sum of three bf16 numbers
+//            (8 + 8 + 8 bits of its 24), the products with V are exact and the sums are fp32.  Columns n < 8 take the
+//            high parts and columns n >= 8 the middle ones in one instruction, the low parts follow in a second one.
+// Relative error of the outputs against 64 bits: 1.8e-7 at 20K-90K (1.85e-7 with vector FMAs), 1.8e-7 at 229K (1.9e-7).
+// About 200 vector instructions per 32 rows, 16 query + 32 accumulator registers, two workgroups per compute unit:
+// 250 MB (four sequences of 20K to 90K) in 42 us where the vector form took 83.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int G8 = 8;
+constexpr int T8_ROWS = 32;                       // rows of a wave's tile
+constexpr int V8_ROW = 256 + 16;                  // bytes of a V row in LDS: padded, the transposed reads of 16 rows spread over all banks
+constexpr int V8_WAVE = T8_ROWS * V8_ROW;
+
+// Rows row0 .. row0 + 31 of a block of K: two groups of 16 rows, four pieces of 32 dimensions.  Rows past `last` are
+// clamped to it (their weights are masked).
+__device__ __forceinline__ void load_k8(u32x4 (&k)[2][4], const char* __restrict__ Kb, int row0, int last, int lane)
+{
+    const int r = row0 + (lane & 15);
+    const uint32_t piece = (uint32_t)(lane >> 4) * 16u;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t off = (uint32_t)min(r + 16 * h, last) * 256u + piece;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) k[h][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Kb + off + 64 * s));
+    }
+}
+// The same rows of V, whole rows to an instruction: instruction i, lane l holds piece l % 16 of row 4 i + l / 16.
+__device__ __forceinline__ void load_v8(u32x4 (&v)[8], const char* __restrict__ Vb, int row0, int last, int lane)
+{
+    const int r = row0 + (lane >> 4);
+    const uint32_t piece = (uint32_t)(lane & 15) * 16u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Vb + (uint32_t)min(r + 4 * i, last) * 256u + piece));
+}
+// The queries of a group as the B operand: lane (n, g) holds dimensions 32 s + 8 g .. + 7 of head n % 8.
+__device__ __forceinline__ void load_q8(u32x4 (&qa)[4], const uint16_t* __restrict__ q_group, int lane)
+{
+    const u32x4* qp = reinterpret_cast<const u32x4*>(q_group + (size_t)(lane & 7) * HC_D);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qa[s] = qp[4 * s + (lane >> 4)];
+}
+// Unscaled logits of the lane's head: s[r] of row 4 g + r, s[4 + r] of row 16 + 4 g + r.
+__device__ __forceinline__ void qk8(const u32x4 (&k)[2][4], const u32x4 (&qa)[4], float (&s)[8])
+{
+    // (four sums of 32 dimensions each, added as a tree: one chain through the accumulator rounds more often)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        f32x4 c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[h][i]), __builtin_bit_cast(bf16x8, qa[i]),
+                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[4 * h + r] = (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
+    }
+}
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b)      // (a >> 16) | (b & 0xffff0000)
+{
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
+template <bool FILT>
+__global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __restrict__ arena, const uint16_t* __restrict__ q,
+                                                             const BlkDev* __restrict__ blks, const SegDev* __restrict__ segs,
+                                                             float* __restrict__ part_acc, float* __restrict__ part_ml,
+                                                             float* __restrict__ rep_logits, int max_ctx,
+                                                             unsigned long long* __restrict__ stamps, FilterArgs fa)
+{
+    __shared__ float sm_m[4][G8];
+    __shared__ float sm_Z[16][G8];
+    __shared__ __attribute__((aligned(16))) float sm_stash[REP_STASH_FLOATS];
+    __shared__ __attribute__((aligned(16))) char sm_v[4][V8_WAVE];      // a wave's V tile; at the end of a segment its sums [G8][128]
+    __shared__ int sm_kept[4];
+    static_assert(V8_WAVE >= G8 * HC_D * 4, "a wave's sums fit in its V tile");
+    constexpr int CAP = REP_STASH_FLOATS / G8;       // positions per chunk of staged logits
+    constexpr int CHUNK_TILES = CAP / T8_ROWS;
+    static_assert(CHUNK_TILES % 4 == 0, "a chunk holds as many tiles of every wave");
+
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const bool first_half = n < G8;
+    char* vt = sm_v[w];
+    const char* vt_read = vt + (4 * g + (n >> 2)) * V8_ROW + (n & 3) * 8;    // transposed read: four lanes to a row of 16 dimensions
+    char* vt_write = vt + (lane >> 4) * V8_ROW + (lane & 15) * 16;
+
+    if (stamps && tid == 0) stamps[2 * blockIdx.x] = __builtin_amdgcn_s_memrealtime();
+    const BlkDev blk = blks[blockIdx.x];
+    SegDev seg = blk.first;
+    int next_extra = blk.extra_begin;
+    for (;;) {
+        const char* __restrict__ Kp = reinterpret_cast<const char*>(arena + seg.k_off);
+        const char* __restrict__ Vp = reinterpret_cast<const char*>(arena + seg.v_off);
+        const int rows = seg.row_end - seg.row_begin, tiles = (rows + T8_ROWS - 1) / T8_ROWS, last = seg.row_end - 1;
+        u32x4 k[2][4], v[8], qa[4];
+        if (w < tiles) {
+            load_k8(k, Kp, seg.row_begin + T8_ROWS * w, last, lane);
+            load_v8(v, Vp, seg.row_begin + T8_ROWS * w, last, lane);
+        }
+        load_q8(qa, q + (size_t)seg.bh * G8 * HC_D, lane);
+        float* rep_base = nullptr;
+        int32_t* kept_pos = nullptr;
+        int32_t* kept_count = nullptr;
+        FilterCtx<G8> fc;
+        fc.cutsum = 0.f;
+        fc.lo = fc.hi = 0;
+#pragma unroll
+        for (int i = 0; i < G8; ++i) fc.ref[i] = 0.f;
+        if (rep_logits && seg.rep_slot >= 0) {
+            rep_base = rep_logits + (size_t)seg.rep_slot * G8 * max_ctx;
+            if (FILT) {
+                kept_pos = fa.surv_pos + (size_t)seg.rep_slot * max_ctx;
+                kept_count = fa.seg_cnt + seg.slot;
+                const RepFilter f = fa.filt[seg.rep_slot];
+                fc.cutsum = f.cutsum;
+#pragma unroll
+                for (int i = 0; i < G8; ++i) fc.ref[i] = f.ref[i];
+                fc.lo = fa.reps[seg.rep_slot].lo;
+                fc.hi = fa.reps[seg.rep_slot].hi;
+                if (seg.row_begin == 0 && tid < G8 * 16)      // the pivot's queries, kept for the monitor
+                    reinterpret_cast<uint4*>(fa.q_keep + (size_t)seg.rep_slot * G8 * HC_D)[tid] =
+                        reinterpret_cast<const uint4*>(q + (size_t)seg.bh * G8 * HC_D)[tid];
+            }
+        }
+
+        float m = M_INIT, Z = 0.f;               // of the lane's head; Z of the lane's rows
+        f32x4 acc[8];                            // acc[b][r]: dimension 16 b + 4 g + r, column n
+#pragma unroll
+        for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int seg_kept = 0;
+        const bool dense = rep_base != nullptr;
+        const int nchunk = dense ? (rows + CAP - 1) / CAP : 1;
+        int t = w;
+#pragma unroll 1
+        for (int ch = 0; ch < nchunk; ++ch) {
+            const bool last_chunk = ch == nchunk - 1;
+            const int t_hi = last_chunk ? tiles : (ch + 1) * CHUNK_TILES;
+#pragma unroll 1
+            for (; t < t_hi; t += 4) {
+                float s[8], x[8];
+                qk8(k, qa, s);
+                // V's tile to LDS; the next tile's loads take the registers over
+#pragma unroll
+                for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(vt_write + 4 * i * V8_ROW) = v[i];
+                if (t + 4 < tiles) {
+                    load_k8(k, Kp, seg.row_begin + T8_ROWS * (t + 4), last, lane);
+                    load_v8(v, Vp, seg.row_begin + T8_ROWS * (t + 4), last, lane);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int left = rows - T8_ROWS * t - 4 * g;          // rows of this tile from the lane's first on
+                if (dense && first_half) {
+                    float* to = sm_stash + (T8_ROWS * t - CAP * ch + 4 * g) * G8 + n;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int row = (j & 3) + 16 * (j >> 2);
+                        if (row < left) to[row * G8] = s[j] * INV_SQRT_D;
+                    }
+                }
+                float mx = -INFINITY;
+                if (T8_ROWS * (t + 1) <= rows) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[j] = fmaf(s[j], LOG2E * INV_SQRT_D, -m);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const bool valid = (j & 3) + 16 * (j >> 2) < left;
+                        s[j] = valid ? s[j] : -INFINITY;
+                        x[j] = valid ? fmaf(s[j], LOG2E * INV_SQRT_D, -m) : -INFINITY;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mx = fmaxf(mx, x[j]);
+                if (__builtin_amdgcn_ballot_w64(mx > LAZY_SLACK)) {   // rare: raise the reference to the tile's largest logit
+                    float hi = -INFINITY;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) hi = fmaxf(hi, s[j] * (LOG2E * INV_SQRT_D));
+                    hi = fmaxf(hi, __shfl_xor(hi, 16));
+                    hi = fmaxf(hi, __shfl_xor(hi, 32));
+                    const float mn = fmaxf(m, hi);
+                    const float alpha = __builtin_amdgcn_exp2f(m - mn);
+                    m = mn;
+                    Z *= alpha;
+#pragma unroll
+                    for (int b = 0; b < 8; ++b) acc[b] *= alpha;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[j] = s[j] * (LOG2E * INV_SQRT_D) - mn;
+                }
+                // weights, and their three parts
+                uint32_t b1[8], b2[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float p = __builtin_amdgcn_exp2f(x[j]);
+                    Z += p;
+                    const float r1 = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+                    const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+                    b1[j] = first_half ? __float_as_uint(p) : __float_as_uint(r1);
+                    b2[j] = first_half ? __float_as_uint(r2) : 0u;
+                }
+                u32x4 p1, p2;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    p1[j] = high_halves(b1[2 * j], b1[2 * j + 1]);
+                    p2[j] = high_halves(b2[2 * j], b2[2 * j + 1]);
+                }
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    typedef __attribute__((address_space(3))) s16x4* lds4;
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(vt_read + 32 * b));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(vt_read + 16 * V8_ROW + 32 * b));
+                    const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                    // (The tile's sums start from zero and are added here: carried through the matrix cores' accumulator from
+                    // tile to tile they end up 1.2 times as far from a 64-bit sum as the plain pass's, so they are closer.)
+                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                    const f32x4 c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, p1), zero, 0, 0, 0);
+                    const f32x4 c2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, p2), zero, 0, 0, 0);
+                    acc[b] += c1 + c2;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();                      // the tile is consumed: the next one may overwrite it
+            }
+            if (dense && FILT) {
+                if (last_chunk) break;           // the segment's last chunk is written out below, behind the barrier of the merge
+                __syncthreads();
+                seg_kept += write_kept<G8>(sm_stash, seg.row_begin + ch * CAP, CAP, rep_base, kept_pos, seg.row_begin + seg_kept, fc, sm_kept, w, lane);
+                __syncthreads();
+            } else if (dense) {
+                __syncthreads();
+                const int first = seg.row_begin + ch * CAP;
+                const int nf = min(seg.row_end - first, CAP) * G8;     // floats of this chunk: a multiple of 8
+                float* dst = rep_base + (size_t)first * G8;
+                for (int f = tid * 4; f < nf; f += 1024) __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(sm_stash + f), reinterpret_cast<f32x4*>(dst + f));
+                if (!last_chunk) __syncthreads();                      // one staging buffer: its next rows wait until it has been written
+            }
+        }
+        if (stamps && tid == 0 && next_extra >= blk.extra_end && Z >= 0.f)
+            stamps[2 * blockIdx.x + 1] = __builtin_amdgcn_s_memrealtime();
+
+        // ---- merge: high + middle columns, then the four waves in LDS, each relative to its own reference ----
+        float* red = reinterpret_cast<float*>(vt);
+        bool bad = false;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[b][r] += dpp<DPP_ROR8>(acc[b][r]);
+                bad |= acc[b][r] != acc[b][r];
+            }
+            if (first_half) *reinterpret_cast<f32x4*>(red + n * HC_D + 16 * b + 4 * g) = acc[b];
+        }
+        if (__builtin_amdgcn_ballot_w64(bad)) {
+            // Something was not finite.  If that is V, a zero part of a weight has made a NaN of an infinity that the
+            // weight itself would have kept: these rows again with whole weights, one at a time, two dimensions to a lane.
+            float a0[G8], a1[G8];
+#pragma unroll
+            for (int h = 0; h < G8; ++h) a0[h] = a1[h] = 0.f;
+#pragma unroll 1
+            for (int tt = w; tt < tiles; tt += 4) {
+                const int row0 = seg.row_begin + T8_ROWS * tt;
+                load_k8(k, Kp, row0, last, lane);
+                float s[8];
+                qk8(k, qa, s);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[j], LOG2E * INV_SQRT_D, -m));
+#pragma unroll 1
+                    for (int gg = 0; gg < 4; ++gg) {
+                        const int row = row0 + 4 * gg + (j & 3) + 16 * (j >> 2);
+                        if (row > last) continue;
+                        const uint32_t vw = *reinterpret_cast<const uint32_t*>(Vp + (uint32_t)row * 256u + lane * 4u);
+#pragma unroll
+                        for (int h = 0; h < G8; ++h) {
+                            const float ph = __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_int(p), 16 * gg + h));
+                            a0[h] = fmaf(ph, bf_lo(vw), a0[h]);
+                            a1[h] = fmaf(ph, bf_hi(vw), a1[h]);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < G8; ++h) *reinterpret_cast<float2*>(red + h * HC_D + 2 * lane) = make_float2(a0[h], a1[h]);
+        }
+        if (first_half) {
+            sm_Z[w * 4 + g][n] = Z;
+            if (g == 0) sm_m[w][n] = m;
+        }
+        __syncthreads();
+        for (int o = tid; o < G8 * HC_D; o += 256) {
+            const int h = o / HC_D;
+            const float M = fmaxf(fmaxf(sm_m[0][h], sm_m[1][h]), fmaxf(sm_m[2][h], sm_m[3][h]));
+            float a = 0.f;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) a += reinterpret_cast<const float*>(sm_v[p])[o] * __builtin_amdgcn_exp2f(sm_m[p][h] - M);
+            part_acc[(size_t)seg.slot * G8 * HC_D + o] = a;
+        }
+        if (tid < G8) {
+            const float M = fmaxf(fmaxf(sm_m[0][tid], sm_m[1][tid]), fmaxf(sm_m[2][tid], sm_m[3][tid]));
+            float z = 0.f;
+#pragma unroll
+            for (int p = 0; p < 16; ++p) z += sm_Z[p][tid] * __builtin_amdgcn_exp2f(sm_m[p / 4][tid] - M);
+            part_ml[((size_t)seg.slot * G8 + tid) * 2 + 0] = M;
+            part_ml[((size_t)seg.slot * G8 + tid) * 2 + 1] = z;
+        }
+        if (FILT && rep_base) {          // the last chunk's kept rows (the barrier above followed its last staged row)
+            const int lastc = (rows - 1) / CAP;
+            const int first = seg.row_begin + lastc * CAP;
+            seg_kept += write_kept<G8>(sm_stash, first, seg.row_end - first, rep_base, kept_pos, seg.row_begin + seg_kept, fc, sm_kept, w, lane);
+            if (tid == 0) *kept_count = seg_kept;
+        }
+        if (next_extra >= blk.extra_end) break;
+        __syncthreads();
+        seg = segs[next_extra++];
+    }
+}
+
 // Second pass: out = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) Z_s over the partials of one head.
 // One workgroup per (b, query head, quarter of the columns): 32 partial lanes x CQ column quads; every thread's
 // loads are independent and issued together.  (Four small workgroups per query head instead of one of 1024
@@ -664,12 +997,6 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(const HeadDev
     }
 }
 
-// Workgroups per compute unit the kernel is compiled for.  A wave keeps two tiles of 8 rows (4 KB each) in
-// flight; the group-of-4 case holds 32 query + 64 accumulator registers, and two workgroups (8 waves)
-// per compute unit keep 64 KB in flight there, which measurement shows is enough.
-template <int G> struct Tune { static constexpr int WG = 2; };
-template <> struct Tune<8> { static constexpr int WG = 1; };
-
 // The pivots' logits over again, every row, into the dense [ctx][G] layout: what the monitor falls back on when
 // its check of a filtered step fails (need[rep] != 0; evaluated on the device, so the launch is unconditional and
 // normally finds nothing to do).  Same plan, same lanes, same dot products in the same order as the split pass,
@@ -716,25 +1043,40 @@ __global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogi
                 float* rep_base = item.rep_logits + (size_t)seg.rep_slot * G * max_ctx;
                 float* score_base = item.scores + (size_t)seg.rep_slot * max_ctx;
                 const int cand_lo = item.reps[seg.rep_slot].lo, cand_hi = item.reps[seg.rep_slot].hi;
-                uint32_t qreg[G][8];
+                if constexpr (G == 8) {
+                    u32x4 qa[4], k[2][4];
+                    load_q8(qa, item.q_keep + (size_t)seg.rep_slot * G * HC_D, lane);
+                    for (int row0 = seg.row_begin + T8_ROWS * w; row0 < seg.row_end; row0 += 4 * T8_ROWS) {
+                        load_k8(k, Kp, row0, seg.row_end - 1, lane);
+                        float sc[8];
+                        qk8(k, qa, sc);
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const uint4* qp = reinterpret_cast<const uint4*>(item.q_keep + ((size_t)seg.rep_slot * G + g) * HC_D);
-                    const uint4 a = qp[c], b = qp[8 + c];
-                    qreg[g][0] = a.x; qreg[g][1] = a.y; qreg[g][2] = a.z; qreg[g][3] = a.w;
-                    qreg[g][4] = b.x; qreg[g][5] = b.y; qreg[g][6] = b.z; qreg[g][7] = b.w;
-                }
-                for (int row0 = seg.row_begin + 8 * w; row0 < seg.row_end; row0 += 32) {
-                    const int row = row0 + r;
-                    const bool valid = row < seg.row_end;
-                    const uint32_t off = (uint32_t)(valid ? row : seg.row_end - 1) * 256u + (uint32_t)c * 16u;
-                    Tile t;
-                    t.k0 = *reinterpret_cast<const uint4*>(Kp + off);
-                    t.k1 = *reinterpret_cast<const uint4*>(Kp + off + 128);
-                    t.v0 = t.v1 = make_uint4(0u, 0u, 0u, 0u);
-                    float sc[G];
-                    qk<G>(qreg, t, sc);
-                    stash_rep<G>(rep_base + (size_t)row * G, sc, c, valid);
+                        for (int j = 0; j < 8; ++j) {
+                            const int row = row0 + 4 * (lane >> 4) + (j & 3) + 16 * (j >> 2);
+                            if ((lane & 15) < G && row < seg.row_end) rep_base[(size_t)row * G + (lane & 15)] = sc[j] * INV_SQRT_D;
+                        }
+                    }
+                } else {
+                    uint32_t qreg[G][8];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint4* qp = reinterpret_cast<const uint4*>(item.q_keep + ((size_t)seg.rep_slot * G + g) * HC_D);
+                        const uint4 a = qp[c], b = qp[8 + c];
+                        qreg[g][0] = a.x; qreg[g][1] = a.y; qreg[g][2] = a.z; qreg[g][3] = a.w;
+                        qreg[g][4] = b.x; qreg[g][5] = b.y; qreg[g][6] = b.z; qreg[g][7] = b.w;
+                    }
+                    for (int row0 = seg.row_begin + 8 * w; row0 < seg.row_end; row0 += 32) {
+                        const int row = row0 + r;
+                        const bool valid = row < seg.row_end;
+                        const uint32_t off = (uint32_t)(valid ? row : seg.row_end - 1) * 256u + (uint32_t)c * 16u;
+                        Tile t;
+                        t.k0 = *reinterpret_cast<const uint4*>(Kp + off);
+                        t.k1 = *reinterpret_cast<const uint4*>(Kp + off + 128);
+                        t.v0 = t.v1 = make_uint4(0u, 0u, 0u, 0u);
+                        float sc[G];
+                        qk<G>(qreg, t, sc);
+                        stash_rep<G>(rep_base + (size_t)row * G, sc, c, valid);
+                    }
                 }
                 __syncthreads();                             // the segment's logits are stored: score its candidates
                 for (int row = max(seg.row_begin, cand_lo) + tid; row < min(seg.row_end, cand_hi); row += 256) {
@@ -782,10 +1124,17 @@ hc_status launch(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* 
                           (const uint16_t*)arena, (const uint16_t*)q, (const BlkDev*)L->blks,                    \
                           (const SegDev*)L->segs, part_acc, part_ml, rep_logits, ctx->cfg.max_ctx,                 \
                           ctx->tune_stamps, fa)
-    if (filtered)
-        HC_LAUNCH((attn_split_kernel<G, Tune<G>::WG, true>));
-    else
-        HC_LAUNCH((attn_split_kernel<G, Tune<G>::WG, false>));
+    if constexpr (G == 8) {
+        if (filtered)
+            HC_LAUNCH((attn_split8_kernel<true>));
+        else
+            HC_LAUNCH((attn_split8_kernel<false>));
+    } else {
+        if (filtered)
+            HC_LAUNCH((attn_split_kernel<G, true>));
+        else
+            HC_LAUNCH((attn_split_kernel<G, false>));
+    }
 #undef HC_LAUNCH
     HC_HIP(ctx, hipGetLastError());
     attn_combine_kernel<G><<<dim3(L->n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(L->heads, part_acc, part_ml, out, lse);

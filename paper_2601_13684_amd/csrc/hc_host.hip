@@ -1295,7 +1295,8 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         hc_status st = HC_OK;
         ctx->beside_now = ss != nullptr;
         if (w.n_test > 0) st = rescore_passes(ctx, w.n_test, w.test_job, run);       // test step of a re-scored window: the earlier queries first
-        ctx->side_pad_now = ss != nullptr && w.all_filtered;
+        // (groups of eight heads: the split pass takes 52 KB of LDS per workgroup, two do not fit beside the reservation)
+        ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
         if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, run);
         ctx->side_pad_now = ctx->beside_now = false;

@@ -1033,9 +1033,9 @@ template <int NT, int SRC>
 static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
 {
     // Alone a workgroup may take a whole compute unit's LDS.  Beside the attention pass it has to leave room for two
-    // of its workgroups: 26 KB each with the pivot-logit filter, 41 KB without.
+    // of its workgroups: 26 KB each with the pivot-logit filter, 41 KB without, 52 KB in groups of eight heads.
     constexpr int STATIC = (SRC != SRC_SURVIVORS ? 10 : NT == 512 ? 15 : 27) * 1024;          // (what the kernel itself declares, rounded up)
-    const int room = (!ctx->beside_now ? 152 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - STATIC;
+    const int room = (!ctx->beside_now ? 152 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - STATIC;
     const unsigned lds = (unsigned)std::min((long long)room, ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
 #define HC_SELECT(GG)                                                                                                        \
     mon_select<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4))
