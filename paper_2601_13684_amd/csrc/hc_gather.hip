@@ -20,10 +20,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GATHER_PASSES = 4;     // host reads a lane has in flight; a workgroup of T threads has T / 32 * 4 positions in flight
-constexpr int GATHER_WORKGROUPS = 96; // workgroups of a gather launch, whatever the batch (measured at the 224K shape, batches
-                                      // of 8 layers: 48 and fewer make the refill itself the bottleneck of the step, 128 and
-                                      // more slow the attention pass that runs beside it; an untriggered call costs ~2 us)
-constexpr int PLAN_THREADS = 256;      // (a larger workgroup does not find room on a compute unit beside the attention pass)
+constexpr int PLAN_THREADS = 256;
 
 // One layer of a batched call (blockIdx.z picks the layer).
 struct GatherItem {
@@ -89,8 +86,114 @@ __device__ __forceinline__ void block_exscan2(uint32_t a, uint32_t b, uint32_t* 
 }
 
 // One workgroup per satellite: which slots hold positions that left the list (free), which positions of
-// the list are not resident (fresh); the k-th free slot takes the k-th fresh position.  Dynamic LDS: the
-// list (4 r bytes), found[r], keep[r].
+// the list are not resident (fresh); the k-th free slot takes the k-th fresh position.
+//
+// The usual form: two bitmaps over the context in LDS, of the listed positions and of those found in a slot, so that
+// every slot and every list entry costs one LDS access; choices are kept as one mask per 64 entries, and a wave's run of
+// them is compacted with ballots.  Bound by latency (a few tens of KB in all).  A list of 7,872 takes 11 us; the form
+// below, a binary search of the list for every slot, took 43.
+template <int NT>
+__global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void gather_plan_bitmap_kernel(GatherBatch B, int max_k)
+{
+    constexpr int NW = NT / 64, U = 8;
+    extern __shared__ __attribute__((aligned(16))) uint32_t sm_words[];
+    __shared__ uint32_t sm_cnt[2][NW];
+    const GatherItem& it = B.it[blockIdx.z];
+    if ((int)blockIdx.y >= it.n_sats) return;
+    const SatDev sd = it.sats[blockIdx.y];
+    if (it.flag[sd.rep_bh] == 0) return;
+    const int r = sd.r, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const uint32_t ctx = (uint32_t)it.heads[sd.bh].ctx;
+    const int words = (int)(ctx + 31) / 32, rounds = (r + 63) / 64;
+    uint32_t* listed = sm_words;
+    uint32_t* found = sm_words + words;
+    uint64_t* free_mask = reinterpret_cast<uint64_t*>(sm_words + ((2 * words + 3) & ~3));       // [rounds]: slots whose position left the list
+    uint64_t* fresh_mask = free_mask + rounds;                                                   // [rounds]: list entries no slot holds
+    const int32_t* list = it.topk_idx + (size_t)sd.bh * max_k;
+    int32_t* sp = it.slot_pos + (size_t)sd.bh * max_k;
+    int32_t* pslot = it.pair_slot + (size_t)sd.bh * max_k;
+    int32_t* ppos = it.pair_pos + (size_t)sd.bh * max_k;
+    for (int i = tid; i < 2 * words; i += NT) sm_words[i] = 0u;
+    __syncthreads();
+    for (int i0 = tid; i0 < r; i0 += U * NT) {
+        uint32_t p[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) p[u] = i0 + u * NT < r ? (uint32_t)list[i0 + u * NT] : ctx;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p[u] < ctx) atomicOr(&listed[p[u] >> 5], 1u << (p[u] & 31));
+    }
+    __syncthreads();
+    // a wave takes a run of rounds of 64
+    const int per = (rounds + NW - 1) / NW, r0 = min(rounds, wv * per), r1 = min(rounds, r0 + per);
+    uint32_t n_free = 0, n_fresh = 0;
+    for (int q0 = r0; q0 < r1; q0 += U) {
+        uint32_t p[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) p[u] = q0 + u < r1 && (q0 + u) * 64 + lane < r ? (uint32_t)sp[(q0 + u) * 64 + lane] : ctx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q0 + u >= r1) break;
+            const bool in = (q0 + u) * 64 + lane < r;
+            const bool keep = p[u] < ctx && ((listed[min(p[u], ctx - 1) >> 5] >> (p[u] & 31)) & 1u);
+            if (keep) atomicOr(&found[p[u] >> 5], 1u << (p[u] & 31));      // (a position held twice, a corrupt map, is caught by the count check below)
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in && !keep);
+            if (lane == 0) free_mask[q0 + u] = m;
+            n_free += (uint32_t)__builtin_popcountll(m);
+        }
+    }
+    __syncthreads();
+    for (int q0 = r0; q0 < r1; q0 += U) {
+        uint32_t p[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) p[u] = q0 + u < r1 && (q0 + u) * 64 + lane < r ? (uint32_t)list[(q0 + u) * 64 + lane] : ctx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q0 + u >= r1) break;
+            const bool in = (q0 + u) * 64 + lane < r;
+            const bool have = p[u] < ctx && ((found[min(p[u], ctx - 1) >> 5] >> (p[u] & 31)) & 1u);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in && !have);
+            if (lane == 0) fresh_mask[q0 + u] = m;
+            n_fresh += (uint32_t)__builtin_popcountll(m);
+        }
+    }
+    if (lane == 0) {
+        sm_cnt[0][wv] = n_free;
+        sm_cnt[1][wv] = n_fresh;
+    }
+    __syncthreads();
+    uint32_t at_free = 0, at_fresh = 0, tot_free = 0, tot_fresh = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        at_free += i < wv ? sm_cnt[0][i] : 0u;
+        at_fresh += i < wv ? sm_cnt[1][i] : 0u;
+        tot_free += sm_cnt[0][i];
+        tot_fresh += sm_cnt[1][i];
+    }
+    if (tot_free != tot_fresh) {
+        // the slot map does not describe a set of r distinct positions: start over from the list
+        for (int i = tid; i < r; i += NT) {
+            pslot[i] = i;
+            ppos[i] = list[i];
+            sp[i] = list[i];
+        }
+        if (tid == 0) it.npairs[sd.bh] = r;
+        return;
+    }
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (int q = r0; q < r1; ++q) {
+        const uint64_t mf = free_mask[q], mn = fresh_mask[q];
+        if ((mf >> lane) & 1u) pslot[at_free + __builtin_popcountll(mf & below)] = q * 64 + lane;
+        if ((mn >> lane) & 1u) ppos[at_fresh + __builtin_popcountll(mn & below)] = list[q * 64 + lane];
+        at_free += (uint32_t)__builtin_popcountll(mf);
+        at_fresh += (uint32_t)__builtin_popcountll(mn);
+    }
+    __syncthreads();                        // the pairs are complete (and visible to the whole workgroup)
+    for (int k = tid; k < (int)tot_free; k += NT) sp[pslot[k]] = ppos[k];
+    if (tid == 0) it.npairs[sd.bh] = (int32_t)tot_free;
+}
+
+// The same for contexts whose bitmaps do not fit.  Dynamic LDS: the list (4 r bytes), found[r], keep[r].
 __global__ __launch_bounds__(PLAN_THREADS) void gather_plan_kernel(GatherBatch B, int max_k)
 {
     extern __shared__ int32_t sm_list[];
@@ -260,7 +363,17 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
             if (!calls[i].slot_pos) return hc_fail(ctx, HC_EINVAL, "hc_gather: in one batch either every layer has a slot map or none");
         const size_t lds = (size_t)max_k * (sizeof(int32_t) + 2);
         if (lds > 144 * 1024) return hc_fail(ctx, HC_ESHAPE, "hc_gather: max_k %d is too large for the slot-map path", max_k);
-        gather_plan_kernel<<<dim3(1, max_sats, n), dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
+        // Bitmaps of the longest context and a mask per 64 entries; beside the attention pass within what its workgroups
+        // leave of a compute unit's LDS.
+        const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16;
+        const unsigned room = !ctx->beside_now ? 150 * 1024 : ctx->G == 8 ? 55 * 1024 : ctx->side_pad_now ? 108 * 1024 : 75 * 1024;
+        const dim3 grid(1, max_sats, n);
+        if (maps > room)
+            gather_plan_kernel<<<grid, dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
+        else if (ctx->beside_now)
+            gather_plan_bitmap_kernel<512><<<grid, dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, max_k);
+        else
+            gather_plan_bitmap_kernel<1024><<<grid, dim3(1024), maps, st>>>(B, max_k);
         HC_HIP(ctx, hipGetLastError());
     }
     // A few dozen workgroups keep the host link busy.  More do not make the refill faster, and every compute unit
@@ -281,6 +394,8 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
 // reserve more than half of a compute unit's LDS (hc_side_lds)
 hc_status hc_gather_set_lds_limit()
 {
+    if (hc_allow_lds((const void*)gather_plan_bitmap_kernel<512>) != hipSuccess ||
+        hc_allow_lds((const void*)gather_plan_bitmap_kernel<1024>) != hipSuccess) return HC_EHIP;
     if (hc_allow_lds((const void*)gather_plan_kernel) != hipSuccess || hc_allow_lds((const void*)gather_kernel) != hipSuccess) return HC_EHIP;
     return HC_OK;
 }

@@ -1,0 +1,67 @@
+"""The difference-only refill's plan: which slots are free, which listed positions are not resident, paired in order.  The
+bitmap form and the search form (contexts whose bitmaps do not fit) against the definition written out.  Run with `-m gpu`
+on an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_13684_amd import inputs as I
+from paper_2601_13684_amd import runtime as R
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def expected(slots, lst):
+    """Definition: the k-th slot whose position is not listed takes the k-th listed position that no slot holds; a map
+    that does not hold as many distinct listed positions as it has listed slots starts over from the list."""
+    listed, held = set(lst.tolist()), set(slots.tolist())
+    free = [i for i, p in enumerate(slots.tolist()) if p not in listed]
+    fresh = [p for p in lst.tolist() if p not in held]
+    if len(free) != len(fresh):
+        return lst.copy()
+    out = slots.copy()
+    out[free] = fresh
+    return out
+
+
+# r around one and several rounds of 64 and beyond one round of the workgroup; 650,001 positions: the search form
+@pytest.mark.parametrize("N,r", [(700, 1), (700, 63), (700, 64), (701, 65), (5000, 1025), (40001, 9001), (229376, 7872), (650001, 3000)])
+def test_plan_and_moved_rows(N, r):
+    print("gather plan", N, r, flush=True)
+    heads = [I.HeadSpec(I.ROLE_FULL), I.HeadSpec(I.ROLE_SATELLITE, rep=0, sink=3, recent=2, budget=5 + r)]
+    spec = I.LayerSpec(B=1, Hq=2, Hkv=2, D=128, ctx=[N], heads=[heads])
+    g = torch.Generator().manual_seed(N)
+    kv = torch.randn((N, 128), generator=g).to(torch.bfloat16)
+    data = I.LayerData({(0, 0): kv, (0, 1): kv}, {(0, 0): kv, (0, 1): -kv}, {})
+    retrieved, base = I.initial_lists(spec)
+    ctx = R.Context(R.make_config(spec), DEV)
+    gpu = R.LayerRuntime(ctx, spec, data, retrieved, base)
+    gpu.flag.fill_(1)
+    rng = np.random.default_rng(r)
+    cand = np.arange(3, N - 2, dtype=np.int32)
+    d = gpu.descs[1]
+    slots = gpu.slot_pos[1, :r].cpu().numpy()
+    for share in (0.0, 0.25, 1.0, "corrupt", 0.5):
+        lst = np.sort(rng.choice(cand, r, replace=False))
+        if share == "corrupt":                       # a position held twice, and one that no context has
+            slots = slots.copy()
+            slots[0] = slots[-1]
+            slots[r // 2] = -7
+            gpu.slot_pos[1, :r] = torch.from_numpy(slots).to(DEV)
+        elif share < 1.0:                            # this share of the list is new
+            keep = rng.choice(slots, r - int(r * share), replace=False)
+            lst = np.sort(np.concatenate([keep, rng.choice(np.setdiff1d(cand, slots), r - keep.size, replace=False)])).astype(np.int32) \
+                if cand.size >= 2 * r else np.sort(slots)
+        gpu.topk_idx[1, :r] = torch.from_numpy(lst).to(DEV)
+        want = expected(slots, lst)
+        gpu.gather()
+        torch.cuda.synchronize()
+        slots = gpu.slot_pos[1, :r].cpu().numpy()
+        np.testing.assert_array_equal(slots, want)
+        rows = gpu.arena[d.k_off + 5 * 128:d.k_off + (5 + r) * 128].view(r, 128).cpu()
+        assert torch.equal(rows, kv[torch.from_numpy(slots).long()])
+        rows = gpu.arena[d.v_off + 5 * 128:d.v_off + (5 + r) * 128].view(r, 128).cpu()
+        assert torch.equal(rows, -kv[torch.from_numpy(slots).long()])
+    gpu.close()
+    ctx.close()
