@@ -921,14 +921,29 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
 // One workgroup per (b, query head, quarter of the columns): 32 partial lanes x CQ column quads; every thread's
 // loads are independent and issued together.  (Four small workgroups per query head instead of one of 1024
 // threads: they find room beside the monitor's kernels sooner.)
+// The layers of a hc_decode_step group are combined with one launch (blockIdx.z picks the layer): a launch of its own
+// behind every layer's split pass is mostly latency, 4.5 us and a gap in which the compute units stand empty.
 constexpr int CQ = 8;                       // column quads (of 32) per workgroup
 constexpr int COMBINE_BLK = 32 * CQ;
+struct CombineItem {
+    const HeadDev* heads;
+    const float* part_acc;
+    const float* part_ml;
+    float* out;
+    float* lse;
+};
+struct CombineBatch {
+    CombineItem it[HC_MAX_GROUP];
+};
 template <int G>
-__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(const HeadDev* __restrict__ heads,
-                                                                   const float* __restrict__ part_acc,
-                                                                   const float* __restrict__ part_ml,
-                                                                   float* __restrict__ out, float* __restrict__ lse)
+__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(CombineBatch batch)
 {
+    const CombineItem& item = batch.it[blockIdx.z];
+    const HeadDev* __restrict__ heads = item.heads;
+    const float* __restrict__ part_acc = item.part_acc;
+    const float* __restrict__ part_ml = item.part_ml;
+    float* __restrict__ out = item.out;
+    float* __restrict__ lse = item.lse;
     __shared__ float sm_max[COMBINE_BLK / 64];
     __shared__ float4 sm_acc[32][CQ];
     __shared__ float sm_z[32];
@@ -1001,8 +1016,8 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(const HeadDev
 // its check of a filtered step fails (need[rep] != 0; evaluated on the device, so the launch is unconditional and
 // normally finds nothing to do).  Same plan, same lanes, same dot products in the same order as the split pass,
 // so the logits are bit for bit those an unfiltered pass would have stored.  Queries come from the copy the
-// split pass kept.  The candidates' scores and the histogram of the scores' first digits, which the monitor's chain
-// over a long range begins with, are made on the way.  Rare: plain stores, no staging.
+// split pass kept.  The candidates' scores, which the monitor then selects from, are made on the way.  Rare: plain
+// stores, no staging.
 struct RepLogitsItem {
     const uint16_t* arena;
     const uint16_t* q_keep;
@@ -1012,7 +1027,6 @@ struct RepLogitsItem {
     const float* lse;
     float* rep_logits;
     float* scores;
-    uint32_t* hist;          // [n_reps][HC_RADIX_BINS]
     const int32_t* need;
     int n_blocks, n_reps;
 };
@@ -1023,14 +1037,11 @@ struct RepLogitsBatch {
 template <int G>
 __global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogitsBatch batch, int max_ctx)
 {
-    __shared__ uint32_t sm_hist[HC_RADIX_BINS];
     const RepLogitsItem& item = batch.it[blockIdx.y];
     bool any = false;                                      // (a few words, read by every workgroup: the usual case is "none")
     for (int i = 0; i < item.n_reps; ++i) any |= item.need[i] != 0;
     if (!any) return;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane >> 3, c = lane & 7;
-    for (int i = tid; i < HC_RADIX_BINS; i += 256) sm_hist[i] = 0u;
-    __syncthreads();
     // few workgroups (the launch is there at every step and normally has nothing to do): each takes every
     // gridDim.x-th workgroup share of the split pass's plan
     for (int share = blockIdx.x; share < item.n_blocks; share += gridDim.x) {
@@ -1086,18 +1097,8 @@ __global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogi
                         l[g] = rep_base[(size_t)row * G + g];
                         lse[g] = item.lse[(size_t)seg.bh * G + g];
                     }
-                    const float sc = hc_group_score<G>(l, lse, HC_AGG_PROB);
-                    score_base[row] = sc;
-                    atomicAdd(&sm_hist[hc_score_key(sc) >> 21], 1u);
+                    score_base[row] = hc_group_score<G>(l, lse, HC_AGG_PROB);
                 }
-                __syncthreads();
-                uint32_t* h = item.hist + (size_t)seg.rep_slot * HC_RADIX_BINS;
-                for (int i = tid; i < HC_RADIX_BINS; i += 256)
-                    if (sm_hist[i]) {
-                        atomicAdd(&h[i], sm_hist[i]);
-                        sm_hist[i] = 0u;
-                    }
-                __syncthreads();
             }
             if (next_extra >= blk.extra_end) break;
             seg = item.segs[next_extra++];
@@ -1106,8 +1107,8 @@ __global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogi
 }
 
 template <int G>
-hc_status launch(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,
-                 float* rep_logits, hipStream_t st, float* part_acc, float* part_ml)
+hc_status launch_split(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* rep_logits, hipStream_t st, float* part_acc,
+                       float* part_ml)
 {
     // The optional timing events are attached to the kernel's own dispatch, so that their distance is the
     // kernel's execution time (what a profiler's kernel trace reports), not launch latency plus execution.
@@ -1137,7 +1138,13 @@ hc_status launch(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* 
     }
 #undef HC_LAUNCH
     HC_HIP(ctx, hipGetLastError());
-    attn_combine_kernel<G><<<dim3(L->n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(L->heads, part_acc, part_ml, out, lse);
+    return HC_OK;
+}
+
+template <int G>
+hc_status launch_combine(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
+{
+    attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ, n), dim3(COMBINE_BLK), 0, st>>>(batch);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
@@ -1150,7 +1157,7 @@ hc_status launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls,
     for (int i = 0; i < n; ++i) {
         const hc_rep_logits_call& x = calls[i];
         const hc_layer* L = x.L;
-        batch.it[i] = RepLogitsItem{(const uint16_t*)x.arena, L->q_keep, L->blks, L->segs, L->reps, x.lse, x.rep_logits, x.scores, x.hist,
+        batch.it[i] = RepLogitsItem{(const uint16_t*)x.arena, L->q_keep, L->blks, L->segs, L->reps, x.lse, x.rep_logits, x.scores,
                                     L->need, L->n_blocks, L->n_reps};
         max_blocks = std::max(max_blocks, L->n_blocks);
     }
@@ -1179,23 +1186,72 @@ hc_status hc_attn_static_scratch(hc_ctx* ctx, float** base)
     return HC_OK;
 }
 
-static hc_status launch_any(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,
-                            float* rep_logits, hipStream_t st, float* part_acc, float* part_ml)
+static hc_status split_any(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* rep_logits, hipStream_t st,
+                           float* part_acc, float* part_ml)
 {
     switch (ctx->G) {
-    case 1: return launch<1>(ctx, L, arena, q, out, lse, rep_logits, st, part_acc, part_ml);
-    case 2: return launch<2>(ctx, L, arena, q, out, lse, rep_logits, st, part_acc, part_ml);
-    case 4: return launch<4>(ctx, L, arena, q, out, lse, rep_logits, st, part_acc, part_ml);
-    case 8: return launch<8>(ctx, L, arena, q, out, lse, rep_logits, st, part_acc, part_ml);
+    case 1: return launch_split<1>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    case 2: return launch_split<2>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    case 4: return launch_split<4>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    case 8: return launch_split<8>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
     }
     return hc_fail(ctx, HC_ESHAPE, "unsupported group size");
 }
 
-hc_status hc_launch_attn(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,
-                         float* rep_logits, hipStream_t st)
+static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
 {
-    if ((size_t)L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
-    return launch_any(ctx, L, arena, q, out, lse, rep_logits, st, ctx->part_acc, ctx->part_ml);
+    switch (ctx->G) {
+    case 1: return launch_combine<1>(ctx, batch, n, n_heads, st);
+    case 2: return launch_combine<2>(ctx, batch, n, n_heads, st);
+    case 4: return launch_combine<4>(ctx, batch, n, n_heads, st);
+    case 8: return launch_combine<8>(ctx, batch, n, n_heads, st);
+    }
+    return hc_fail(ctx, HC_ESHAPE, "unsupported group size");
+}
+
+static hc_status launch_any(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,
+                            float* rep_logits, hipStream_t st, float* part_acc, float* part_ml)
+{
+    const hc_status s = split_any(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    if (s != HC_OK) return s;
+    CombineBatch batch{};
+    batch.it[0] = CombineItem{L->heads, part_acc, part_ml, out, lse};
+    return combine_any(ctx, batch, 1, L->n_heads, st);
+}
+
+hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st)
+{
+    if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "attention batch of %d layers", n);
+    // Every layer of the batch leaves its partial results in a copy of the workspace of its own, as far as there are
+    // copies.  Layers that share an output buffer (the last one's results stay, as if each were combined by itself) are
+    // not combined together.
+    const size_t acc_floats = ctx->part_slots * ctx->G * HC_D, ml_floats = ctx->part_slots * ctx->G * 2;
+    CombineBatch batch{};
+    int m = 0, n_heads = 0;
+    auto flush = [&]() -> hc_status {
+        const hc_status s = m > 0 ? combine_any(ctx, batch, m, n_heads, st) : HC_OK;
+        m = 0;
+        return s;
+    };
+    for (int i = 0; i < n; ++i) {
+        const hc_attn_call& x = calls[i];
+        if ((size_t)x.L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
+        n_heads = x.L->n_heads;                       // (of the context: the same for every layer)
+        const size_t lse_floats = (size_t)n_heads * ctx->G, out_floats = lse_floats * HC_D;
+        bool shared = false;
+        auto overlap = [](const float* p, const float* q, size_t len) { return p < q + len && q < p + len; };
+        for (int j = 0; j < m; ++j) shared = shared || overlap(batch.it[j].out, x.out, out_floats) || overlap(batch.it[j].lse, x.lse, lse_floats);
+        if (m == ctx->part_copies || shared) {
+            const hc_status s = flush();
+            if (s != HC_OK) return s;
+        }
+        float* acc = ctx->part_acc + m * acc_floats;
+        float* ml = ctx->part_ml + m * ml_floats;
+        const hc_status s = split_any(ctx, x.L, x.arena, x.q, x.rep_logits, st, acc, ml);
+        if (s != HC_OK) return s;
+        batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse};
+    }
+    return flush();
 }
 
 hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,

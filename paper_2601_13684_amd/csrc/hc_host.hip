@@ -253,8 +253,11 @@ static hc_status ensure_partials(hc_ctx* ctx, size_t slots)
     (void)hipFree(ctx->part_ml);
     ctx->part_acc = ctx->part_ml = nullptr;
     ctx->part_slots = 0;
-    HC_HIP(ctx, hipMalloc((void**)&ctx->part_acc, slots * ctx->G * HC_D * sizeof(float)));
-    HC_HIP(ctx, hipMalloc((void**)&ctx->part_ml, slots * ctx->G * 2 * sizeof(float)));
+    // one copy per layer of a group while that is small (a 224K layer's is 1 MB), never less than one
+    const size_t acc_bytes = slots * ctx->G * HC_D * sizeof(float), ml_bytes = slots * ctx->G * 2 * sizeof(float);
+    ctx->part_copies = (int)std::max<size_t>(1, std::min<size_t>(HC_MAX_GROUP, ((size_t)256 << 20) / acc_bytes));
+    HC_HIP(ctx, hipMalloc((void**)&ctx->part_acc, acc_bytes * ctx->part_copies));
+    HC_HIP(ctx, hipMalloc((void**)&ctx->part_ml, ml_bytes * ctx->part_copies));
     ctx->part_slots = slots;
     return HC_OK;
 }
@@ -759,7 +762,8 @@ extern "C" hc_status hc_decode_attn(hc_ctx* ctx, const hc_layer* layer, const vo
     const hc_status chk = attn_check(ctx, layer, kv_arena, q, out, lse, rep_logits);
     if (chk != HC_OK) return chk;
     if (rep_logits) const_cast<hc_layer*>(layer)->last_arena = kv_arena;
-    return hc_launch_attn(ctx, layer, kv_arena, q, out, lse, rep_logits, (hipStream_t)stream);
+    const hc_attn_call call{layer, kv_arena, q, out, lse, rep_logits};
+    return hc_launch_attn(ctx, 1, &call, (hipStream_t)stream);
 }
 
 extern "C" hc_status hc_decode_attn_static(hc_ctx* ctx, const hc_layer* layer, const void* kv_arena, const void* q,
@@ -1342,6 +1346,7 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
             result = hc_launch_append(ctx, n_app, app, ms);
             for (int i = 0; i < n_app && result == HC_OK; ++i) result = append_done(ctx, const_cast<hc_layer*>(app[i].L), ms);
         }
+        hc_attn_call att[HC_MAX_GROUP];
         for (int l = g0; l < g1 && result == HC_OK; ++l) {
             const hc_layer_io& x = io[l];
             hc_layer* L = x.layer;
@@ -1361,8 +1366,9 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
                 if (x.host_tier && L->n_sats > 0)
                     w.gat[w.n_gat++] = hc_gather_call{L, x.host_tier, x.topk_idx, x.flag, const_cast<void*>(x.kv_arena), x.slot_pos};
             }
-            result = hc_launch_attn(ctx, L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr, ms);
+            att[l - g0] = hc_attn_call{L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr};
         }
+        if (result == HC_OK) result = hc_launch_attn(ctx, g1 - g0, att, ms);
         // The queries go into the window buffers on the main stream: the caller may overwrite q as soon
         // as this call returns, in main-stream order, while the side stream may still be behind.  A layer's
         // count of steps inside its window moves on once its query is in the buffer.

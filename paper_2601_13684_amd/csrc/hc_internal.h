@@ -113,9 +113,10 @@ struct hc_ctx {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timing;   // optional timing hook: one pair per split-pass launch
     size_t timing_next = 0;
     // split-K partial workspace
-    float* part_acc = nullptr;   // [slots][G][D]
-    float* part_ml = nullptr;    // [slots][G][2]  (running max in log2 units, sum)
+    float* part_acc = nullptr;   // [copies][slots][G][D]
+    float* part_ml = nullptr;    // [copies][slots][G][2]  (running max in log2 units, sum)
     size_t part_slots = 0;
+    int part_copies = 1;         // copies of both: the layers of a hc_decode_step group are combined with one launch
     float* static_scratch = nullptr;   // this device's address of the fixed scratch array of hc_decode_attn_static
     // selection workspace; one copy per layer of a batched monitor call (the first has room for every head, the others for every pivot)
     uint32_t* ws_base = nullptr;   // the one allocation behind all copies
@@ -258,8 +259,15 @@ struct hc_gather_call {
     void* arena;
     int32_t* slot_pos;     // or nullptr
 };
-hc_status hc_launch_attn(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out,
-                         float* lse, float* rep_logits, hipStream_t st);
+struct hc_attn_call {
+    const hc_layer* L;
+    const void* arena;
+    const void* q;
+    float* out;
+    float* lse;
+    float* rep_logits;     // or nullptr
+};
+hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st);
 hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out,
                                 float* lse, float* rep_logits, hipStream_t st);
 hc_status hc_attn_static_scratch(hc_ctx* ctx, float** base);     // at context creation, with the context's device current
@@ -269,7 +277,6 @@ struct hc_rep_logits_call {
     float* rep_logits;
     const float* lse;
     float* scores;
-    uint32_t* hist;        // the layer's workspace copy: first-digit histograms
 };
 hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st);
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st);

@@ -18,8 +18,10 @@
 //                            mon_select over those (a few thousand): three launches
 //   rows a filtering split pass kept
 //                            mon_sparse_score (their scores, one dense run), mon_select: two launches, and behind
-//                            them the long-range chain, which normally finds nothing to do, for a pivot whose
-//                            check failed (its first kernel, in hc_attn.hip, makes all logits again)
+//                            them two that normally find nothing to do, for a pivot whose check failed:
+//                            rep_logits_kernel (hc_attn.hip; all logits again, with their scores) and mon_select over
+//                            the whole range (slow, 0.1 ms at 224K, and rare; the short way around it, a launch more
+//                            to cut the range down first, would cost every step 6 us)
 // (mon_prep clears the histograms and bitmaps, only after a call that failed midway; normally mon_select leaves
 // them clear.)
 //
@@ -1067,8 +1069,8 @@ static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& d
 constexpr int SELECT_DIRECT_ALONE = 8192, SELECT_DIRECT_BESIDE = 8192;
 
 // The launches of one chain over a batch of layers.  mode 0: the plain chain (every pivot, all candidate positions).
-// mode 1: the chain over the rows a filtering split pass kept.  mode 2: the dense chain that stands by behind
-// mode 1, for the pivots whose check failed (their logits, scores and histogram are there already: see
+// mode 1: the chain over the rows a filtering split pass kept.  mode 2: the selection that stands by behind
+// mode 1, for the pivots whose check failed (their logits and scores are there already: see
 // hc_launch_rep_logits).  ws_first: which workspace copy the first layer uses.
 static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* calls, int ws_first, int scores_given, int mode,
                            hipStream_t st)
@@ -1150,23 +1152,21 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         scores_given = 1;                     // from here on the scores are there
         if (armed) return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
     }
-    if (mode != 2 && max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
+    if (mode == 2) return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
+    if (max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
         return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st)
                             : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
-    if (mode != 2) {
-        // chunks per workgroup: aim at about 512 workgroups per launch, at most 8 chunks each
-        const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / 512));
-        const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
-        switch (ctx->G) {
-        case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span); break;
-        case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span); break;
-        case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span); break;
-        default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span); break;
-        }
-        HC_HIP(ctx, hipGetLastError());
+    // chunks per workgroup: aim at about 512 workgroups per launch, at most 8 chunks each
+    const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / 512));
+    const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
+    switch (ctx->G) {
+    case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span); break;
+    case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span); break;
+    case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span); break;
+    default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span); break;
     }
-    // (the stand-by chain is there at every step and normally has nothing to do: few workgroups, several chunks a wave)
-    const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, mode == 2 ? 8 : std::max(4, 1024 / pivots)));
+    HC_HIP(ctx, hipGetLastError());
+    const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, std::max(4, 1024 / pivots)));
     mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B);
     HC_HIP(ctx, hipGetLastError());
     return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
@@ -1193,13 +1193,12 @@ hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, in
     if (s == HC_OK && n_filt > 0) {
         s = run_chain(ctx, n_filt, filt, n_plain, 0, 1, st);
         // behind it, for the pivots whose check failed (decided on the device; normally none): all logits over
-        // again with their scores and histogram, then the plain chain from there
+        // again with their scores, then the selection over those
         if (s == HC_OK) {
             hc_rep_logits_call rl[HC_MAX_GROUP];
             for (int i = 0; i < n_filt; ++i) {
                 const hc_monitor_call& x = *filt[i];
-                rl[i] = hc_rep_logits_call{x.L, x.arena ? x.arena : x.L->last_arena, const_cast<float*>(x.rep_logits), x.lse, x.scores,
-                                           ctx->ws[n_plain + i].hist};
+                rl[i] = hc_rep_logits_call{x.L, x.arena ? x.arena : x.L->last_arena, const_cast<float*>(x.rep_logits), x.lse, x.scores};
             }
             s = hc_launch_rep_logits(ctx, n_filt, rl, st);
         }
