@@ -264,16 +264,17 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
 // The survivors of a long range: every candidate whose first digit is at least that of the longest list's k-th
 // score, in position order, chunk by chunk (keys and positions inside the chunk, at the chunk's own place, and how
 // many).  At 229,376 candidates and a longest list of 7,872 about 11,000 survive.  A wave takes a chunk, 64
-// candidates to a round, and needs no workgroup barrier; its first loads do not wait for the threshold.
+// candidates to a round; its first loads do not wait for the threshold.
 __global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B)
 {
+    __shared__ __attribute__((aligned(16))) uint32_t sm_hist[HC_RADIX_BINS];
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
     const RepDev rd = it.reps[rep];
     const int lane = threadIdx.x & 63, stride = gridDim.x * NWAVE;
     int ch = blockIdx.x * NWAVE + (threadIdx.x >> 6);
-    if (ch >= rd.nchunk) return;
+    if ((int)blockIdx.x * NWAVE >= rd.nchunk) return;
     const Ws w = it.ws.rep(rep);
     const float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
     constexpr int HALF = HC_SEL_CHUNK / 64 / 2;
@@ -285,11 +286,17 @@ __global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B)
             s[r] = j < rd.hi ? srow[j] : 0.f;
         }
     };
+    uint4 h[HC_RADIX_BINS / 4 / BLK];
+#pragma unroll
+    for (int i = 0; i < HC_RADIX_BINS / 4 / BLK; ++i) h[i] = reinterpret_cast<const uint4*>(w.hist)[i * BLK + threadIdx.x];
     load(rd.lo + ch * HC_SEL_CHUNK);
+#pragma unroll
+    for (int i = 0; i < HC_RADIX_BINS / 4 / BLK; ++i) reinterpret_cast<uint4*>(sm_hist)[i * BLK + threadIdx.x] = h[i];
     int kmax = 1;
     for (int ks = 0; ks < rd.nk; ++ks) kmax = max(kmax, it.reps[rep].k[ks]);      // (indexing the register copy would spill it)
+    __syncthreads();
     uint32_t digit, remaining, count;
-    find_digit(w.hist, (uint32_t)kmax, digit, remaining, count);
+    find_digit(sm_hist, (uint32_t)kmax, digit, remaining, count);
     for (; ch < rd.nchunk; ch += stride) {
         const int first = rd.lo + ch * HC_SEL_CHUNK;
         uint32_t at = 0;
@@ -515,15 +522,15 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
             int c[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t i = (uint32_t)min(i0 + u * NT, n - 1);
-                int lo = 0, hi = rd.nchunk;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (sm_first[mid] <= i) lo = mid;
-                    else hi = mid;
-                }
-                c[u] = lo;
-                const uint32_t at = (uint32_t)lo * HC_SEL_CHUNK + (i - sm_first[lo]);
+                // a wave's 64 items are consecutive: the chunk of the first by counting the chunks that begin before it,
+                // the others' a few chunks on
+                const uint32_t i = (uint32_t)min(i0 + u * NT, n - 1), i_wave = (uint32_t)min(i0 - lane + u * NT, n - 1);
+                int at_chunk = -1;
+                for (int cb = 0; cb < rd.nchunk; cb += 64)
+                    at_chunk += (int)count_true(cb + lane < rd.nchunk && sm_first[min(cb + lane, rd.nchunk)] <= i_wave);
+                while (sm_first[at_chunk + 1] <= i) ++at_chunk;       // (ends: an item lies before the last entry, the total)
+                c[u] = at_chunk;
+                const uint32_t at = (uint32_t)at_chunk * HC_SEL_CHUNK + (i - sm_first[at_chunk]);
                 key[u] = w.sv_key[at];
                 off[u] = w.sv_off[at];
             }
@@ -1156,8 +1163,9 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     if (max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
         return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st)
                             : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
-    // chunks per workgroup: aim at about 512 workgroups per launch, at most 8 chunks each
-    const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / 512));
+    // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K: 40 us per call
+    // with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.
+    const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
     const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
     switch (ctx->G) {
     case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span); break;
