@@ -1245,8 +1245,8 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
             const hc_status s = flush();
             if (s != HC_OK) return s;
         }
-        float* acc = ctx->part_acc + m * acc_floats;
-        float* ml = ctx->part_ml + m * ml_floats;
+        float* acc = m == 0 ? ctx->part_acc : ctx->part_more + (m - 1) * acc_floats;
+        float* ml = m == 0 ? ctx->part_ml : ctx->part_more + (ctx->part_copies - 1) * acc_floats + (m - 1) * ml_floats;
         const hc_status s = split_any(ctx, x.L, x.arena, x.q, x.rep_logits, st, acc, ml);
         if (s != HC_OK) return s;
         batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse};

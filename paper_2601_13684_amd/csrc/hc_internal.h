@@ -113,9 +113,10 @@ struct hc_ctx {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timing;   // optional timing hook: one pair per split-pass launch
     size_t timing_next = 0;
     // split-K partial workspace
-    float* part_acc = nullptr;   // [copies][slots][G][D]
-    float* part_ml = nullptr;    // [copies][slots][G][2]  (running max in log2 units, sum)
+    float* part_acc = nullptr;   // [slots][G][D]
+    float* part_ml = nullptr;    // [slots][G][2]  (running max in log2 units, sum)
     size_t part_slots = 0;
+    float* part_more = nullptr;  // [copies - 1] of the accumulators, then [copies - 1] of (max, sum)
     int part_copies = 1;         // copies of both: the layers of a hc_decode_step group are combined with one launch
     float* static_scratch = nullptr;   // this device's address of the fixed scratch array of hc_decode_attn_static
     // selection workspace; one copy per layer of a batched monitor call (the first has room for every head, the others for every pivot)

@@ -26,8 +26,8 @@
 // them clear.)
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
-// histograms, counts, ordered write, decision): one 32K layer 29.5 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 42 instead of 80 us, the decode step of one 4K layer 29 instead of 49 us.
+// histograms, counts, ordered write, decision): one 32K layer 27.4 instead of 51.5 us per call, eight sequences of 9K to
+// 131K 33 instead of 81 us, the decode step of one 4K layer 29 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers leave 80 per lane of a SIMD: 256 threads of at most 64 registers, or
@@ -1163,8 +1163,8 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     if (max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
         return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st)
                             : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
-    // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K: 40 us per call
-    // with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.
+    // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K took
+    // 40 us per call with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.
     const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
     const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
     switch (ctx->G) {
