@@ -13,7 +13,6 @@
 // does not care about.  gather_plan_kernel finds the difference, gather_kernel moves the rows.
 #include <algorithm>
 
-#include <hip/hip_ext.h>
 #include "hc_internal.h"
 
 namespace {
@@ -340,9 +339,7 @@ __global__ __launch_bounds__(256, 8) void gather_kernel(GatherBatch B, int n_ite
 
 }   // namespace
 
-// A pending event (done && *done) is recorded by the last launch itself, as its completion signal, and taken off the
-// caller (*done = nullptr); where nothing is launched it stays pending.
-hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipStream_t st, hipEvent_t* done)
+hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipStream_t st)
 {
     if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "gather batch of %d layers", n);
     GatherBatch B{};
@@ -388,13 +385,7 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
     for (int i = 0; i < n; ++i) rows_max += (long long)calls[i].L->n_sats * calls[i].L->max_r;
     const int thr = ctx->gather_threads, in_flight = thr / 32 * GATHER_PASSES;
     const int nwg = (int)std::max<long long>(1, std::min<long long>(ctx->gather_workgroups, (rows_max + in_flight - 1) / in_flight));
-    const unsigned gather_lds = hc_side_lds(ctx, (const void*)gather_kernel, 0);
-    if (done && *done) {
-        hipExtLaunchKernelGGL(gather_kernel, dim3(nwg), dim3(thr), gather_lds, st, nullptr, *done, 0, B, n, max_sats, max_k);
-        *done = nullptr;
-    } else {
-        gather_kernel<<<dim3(nwg), dim3(thr), gather_lds, st>>>(B, n, max_sats, max_k);
-    }
+    gather_kernel<<<dim3(nwg), dim3(thr), hc_side_lds(ctx, (const void*)gather_kernel, 0), st>>>(B, n, max_sats, max_k);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }

@@ -1303,18 +1303,6 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         hc_layer* Lg = nullptr;                 // the group's events live in its last layer
     };
     SideWork work[2];
-    // The event that the main stream waits for rides on the side chain's last kernel instead of a record of its own behind
-    // it: a record is one more barrier packet between the gather and the attention that waits for it.  Steps of four
-    // layers in two groups, back to back: 197 instead of 220 us at 224K, 221 instead of 252 us for six sequences of 12K to
-    // 81K, 131 instead of 149 us at 32K with a re-scored window.  The event the side stream waits for is better recorded:
-    // riding on the combine kernel as well, which holds up the main stream's next kernel, the same steps take 216 and
-    // 247 us (on the push of the window's queries: 146 us).  A stream capture has no form for it: there both are recorded.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-    if (ss && hipStreamIsCapturing(ms, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusActive;
-    }
-    const bool ride = cap == hipStreamCaptureStatusNone;
     auto launch_side = [&](SideWork& w) -> hc_status {
         if (w.n_mon == 0) return HC_OK;
         hipStream_t run = ss ? ss : ms;
@@ -1325,12 +1313,11 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         // (groups of eight heads: the split pass takes 52 KB of LDS per workgroup, two do not fit beside the reservation)
         ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
-        hipEvent_t ev = ride ? w.Lg->ev_side : nullptr;
-        if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, run, &ev);
+        if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, run);
         ctx->side_pad_now = ctx->beside_now = false;
         if (ss) {
-            // recorded also where no gather was launched or a launch failed, so that no later call waits on a stale event
-            const hipError_t e = st != HC_OK || !ride || ev ? hipEventRecord(w.Lg->ev_side, ss) : hipSuccess;
+            // recorded even after a failed launch, so that no later call waits on a stale event
+            const hipError_t e = hipEventRecord(w.Lg->ev_side, ss);
             for (int i = 0; i < w.n_mon; ++i) const_cast<hc_layer*>(w.mon[i].L)->pending_ev = w.Lg->ev_side;
             if (st == HC_OK) HC_HIP(ctx, e);
         }
