@@ -106,7 +106,10 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     // pivots are at most half of the heads; the prefill-time selection, which uses the first copy alone, runs over
     // up to all of them
     c->max_chunks = (cfg->max_ctx + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-    const size_t rep_w = HC_RADIX_BINS + c->max_chunks + cfg->max_ctx / 32 + (size_t)cfg->max_ctx * 2 + cfg->max_ctx / 2;
+    c->sv_cap = std::min(cfg->max_ctx, HC_MAX_SURVIVORS);
+    c->area_words = std::max(2 * (size_t)cfg->max_ctx + cfg->max_ctx / 2, HC_MAX_SURVIVORS + 2 * HC_MAX_K_PER_REP * (size_t)HC_RADIX_BINS) + 64 * (size_t)c->max_chunks;
+    c->area_words &= ~(size_t)3;
+    const size_t rep_w = HC_RADIX_BINS + cfg->max_ctx / 32 + c->area_words;
     size_t ws_w = 0;
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
         c->ws[i].reps = std::max(1, i == 0 ? cfg->B * cfg->Hkv : cfg->B * cfg->Hkv / 2);
@@ -142,11 +145,8 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
         hc_monitor_ws& w = c->ws[i];
         w.hist = base;
-        w.sv_key = w.hist + (size_t)w.reps * HC_RADIX_BINS;
-        w.sv_pos = reinterpret_cast<int32_t*>(w.sv_key + (size_t)w.reps * cfg->max_ctx);
-        w.sv_off = reinterpret_cast<uint16_t*>(w.sv_pos + (size_t)w.reps * cfg->max_ctx);
-        w.bitmap = w.sv_key + (size_t)w.reps * (2 * (size_t)cfg->max_ctx + cfg->max_ctx / 2);
-        w.cnt = w.bitmap + (size_t)w.reps * (cfg->max_ctx / 32);
+        w.area = w.hist + (size_t)w.reps * HC_RADIX_BINS;
+        w.bitmap = w.area + (size_t)w.reps * c->area_words;
         w.dirty = true;
         base += (((size_t)w.reps * rep_w) + 3) & ~(size_t)3;
     }

@@ -12,8 +12,10 @@
 
 constexpr int HC_D = 128;            // head dimension the kernels are written for
 constexpr int HC_UNIT_ROWS = 32;     // split-K granule: 4 waves x 8 rows
-constexpr int HC_SEL_CHUNK = 1024;   // candidates per workgroup in the selection passes
-constexpr int HC_RADIX_BINS = 2048;  // 11-bit digits (11 + 11 + 10 bits of the 32-bit key)
+constexpr int HC_SEL_CHUNK = 1024;   // candidates a workgroup or wave of the monitor's first passes takes at a time
+constexpr int HC_RADIX_BINS = 2048;  // bins of the monitor's histograms: 11 bits of a key, or of its distance from the smallest
+constexpr int HC_SAMPLES = 4096;     // items of a long candidate range from which the monitor estimates its threshold
+constexpr int HC_MAX_SURVIVORS = 20480;   // survivors that a pivot's workspace holds
 
 // One KV head as the kernels see it.
 struct HeadDev {
@@ -85,11 +87,8 @@ struct SatDev {
 struct hc_monitor_ws {
     int reps = 0;                  // pivots this copy has room for
     uint32_t* hist = nullptr;      // [reps][HC_RADIX_BINS]: first-digit histogram of a long candidate range
-    uint32_t* cnt = nullptr;       // [reps][max_chunks]: survivors per chunk
     uint32_t* bitmap = nullptr;    // [reps][max_ctx/32]: baseline set, where it does not fit in LDS
-    uint32_t* sv_key = nullptr;    // [reps][max_ctx]: survivors' keys
-    uint16_t* sv_off = nullptr;    // [reps][max_ctx]: survivors' positions inside their chunk
-    int32_t* sv_pos = nullptr;     // [reps][max_ctx]: survivors' positions, dense
+    uint32_t* area = nullptr;      // [reps][area_words]: survivors of a long range, or histograms and counts of long lists
     bool dirty = true;             // histograms / bitmap not known to be clear (first call, or a call that failed midway)
 };
 
@@ -122,7 +121,9 @@ struct hc_ctx {
     // selection workspace; one copy per layer of a batched monitor call (the first has room for every head, the others for every pivot)
     uint32_t* ws_base = nullptr;   // the one allocation behind all copies
     hc_monitor_ws ws[HC_MAX_GROUP];
-    int max_chunks = 0;
+    int max_chunks = 0;            // chunks of HC_SEL_CHUNK candidates a range can have
+    int sv_cap = 0;                // survivors a pivot's workspace holds
+    size_t area_words = 0;         // words per pivot for them, or for the histograms and counts of long lists
     int monitor_span = 0;          // chunks per workgroup of the selection passes; 0: chosen per launch
     // gather workspace, one copy per layer of a batched call: the (slot, position) pairs of a refill
     int32_t* pair_slot = nullptr;  // [HC_MAX_GROUP][B*Hkv][max_k]

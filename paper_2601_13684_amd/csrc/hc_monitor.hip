@@ -13,16 +13,17 @@
 // of its items in LDS: threshold, ordered lists, |T ∩ baseline| through a bitmap in LDS, window, decision and
 // baseline update.  What reaches it:
 //   short candidate ranges   mon_select scores the candidates itself: one launch
-//   long ranges              mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact
-//                            (the candidates from the threshold digit of the longest list up, in position order),
-//                            mon_select over those (a few thousand): three launches
+//   long ranges              mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact (the
+//                            candidates that can be in the longest list, and few more), mon_select over those (a few
+//                            thousand): three launches
+//   long lists               mon_score_hist, mon_hist twice, mon_count, mon_write, mon_decide: six launches of many workgroups
 //   rows a filtering split pass kept
-//                            mon_sparse_score (their scores, one dense run), mon_select: two launches, and behind
-//                            them two that normally find nothing to do, for a pivot whose check failed:
-//                            rep_logits_kernel (hc_attn.hip; all logits again, with their scores) and mon_select over
-//                            the whole range (slow, 0.1 ms at 224K, and rare; the short way around it, a launch more
-//                            to cut the range down first, would cost every step 6 us)
-// (mon_prep clears the histograms and bitmaps, only after a call that failed midway; normally mon_select leaves
+//                            mon_sparse_score (their scores, one dense run), mon_select (with the long ranges' first two in
+//                            front of it where more rows are kept than it has room for): two launches, and behind them
+//                            two that normally find nothing to do, for a pivot whose check failed: rep_logits_kernel
+//                            (hc_attn.hip; all logits again, with their scores) and mon_select, which cuts the whole range
+//                            down by itself (a launch more for that would cost every step 3 us)
+// (mon_prep clears the histograms, counters and bitmaps, only after a call that failed midway; normally mon_select leaves
 // them clear.)
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
@@ -34,6 +35,7 @@
 // (mon_select) 512 threads of at most 40.  No local arrays (a kernel that needs scratch memory costs tens of us to
 // launch), no device-wide fences.
 #include <algorithm>
+#include <cmath>
 
 #include "hc_internal.h"
 
@@ -51,21 +53,30 @@ __device__ __forceinline__ float key_score(uint32_t key)      // inverse of hc_s
 // Workspace of one layer of a batch (rep: pivot).
 struct Ws {
     uint32_t* hist;      // [HC_RADIX_BINS]: first-digit histogram of a long range
-    uint32_t* cnt;       // [max_chunks]: survivors of every chunk of a long range
     uint32_t* bitmap;    // [max_ctx / 32]: baseline set, where it does not fit in LDS
-    uint32_t* sv_key;    // [max_ctx]: survivors' keys, chunk c's from c * HC_SEL_CHUNK
-    uint16_t* sv_off;    // [max_ctx]: their positions inside the chunk
-    int32_t* sv_pos;     // [max_ctx]: the survivors' positions, dense, where mon_select has all their keys in LDS
-    int max_chunks, max_ctx;
+    // one piece of memory, `area` words per pivot, that a call uses either for survivors ...
+    uint64_t* mask;      // [max_chunks][HC_SEL_CHUNK / 64]: which candidates survive
+    int32_t* sv_pos;     // [sv_cap]: the survivors' positions
+    // ... or for long lists
+    uint32_t* h2;        // [HC_MAX_K_PER_REP][HC_RADIX_BINS]: second digits
+    uint32_t* h3;        // [HC_MAX_K_PER_REP][HC_RADIX_BINS]: third digits
+    uint32_t* sel;       // [HC_MAX_K_PER_REP][4]: first digits found / still needed, then two digits found / still needed
+    uint32_t* cnt;       // [HC_MAX_K_PER_REP][max_chunks][2]: greater, equal
+    uint32_t* hits;      // [max_chunks]: |T ∩ baseline| of every chunk
+    int max_chunks, max_ctx, sv_cap;
+    size_t area;
     __device__ Ws rep(int r) const
     {
         Ws w = *this;
         w.hist += (size_t)r * HC_RADIX_BINS;
-        w.cnt += (size_t)r * max_chunks;
         w.bitmap += (size_t)r * (max_ctx / 32);
-        w.sv_key += (size_t)r * max_ctx;
-        w.sv_off += (size_t)r * max_ctx;
-        w.sv_pos += (size_t)r * max_ctx;
+        w.h2 += (size_t)r * area;
+        w.h3 = w.h2 + HC_MAX_K_PER_REP * HC_RADIX_BINS;
+        w.sel = w.h3 + HC_MAX_K_PER_REP * HC_RADIX_BINS;
+        w.cnt = w.sel + HC_MAX_K_PER_REP * 4;
+        w.hits = w.cnt + (size_t)HC_MAX_K_PER_REP * max_chunks * 2;
+        w.mask = reinterpret_cast<uint64_t*>(w.h2);
+        w.sv_pos = reinterpret_cast<int32_t*>(w.mask + (size_t)max_chunks * (HC_SEL_CHUNK / 64));
         return w;
     }
 };
@@ -85,7 +96,7 @@ struct MonItem {
     int32_t* ring;
     int32_t* inter;
     int32_t* flag;
-    int n_reps, n_outs;
+    int n_reps;
     int store_slot;
     // A layer whose split pass filters the pivot logits: the selection runs over the kept rows only (reps = the
     // pivots as seen over those rows, pos_map = their positions), and a second, dense chain stands by for the
@@ -161,6 +172,8 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)      // set bits 
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+__device__ __forceinline__ uint32_t count_true(bool x) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(x)); }
+
 // In a histogram of HC_RADIX_BINS digit counts, walking from the highest digit down, find the digit in which the
 // k-th largest element falls, how many of that digit's elements are still needed and how many there are.  Done by
 // ONE wave (lane l owns 32 consecutive digits); result valid in all its lanes.  The lanes start their walks at
@@ -218,10 +231,91 @@ __device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j,
     return hc_group_score<G>(l, lse, agg);
 }
 
+// ---- the survivors of a long range ----
+//
+// mon_select is one workgroup with room for some tens of thousands of items, so a long range is cut down first, by many.
+// The histogram of the keys' first digits (11 bits) shows the digit in which the longest list ends: everything from that digit
+// up survives.  At 229,376 candidates and a longest list of 7,872 these are 8,000 to 11,000 if the scores are spread out.  But a
+// digit holds every score within 25 % of each other: where it would let more through than `limit`, the cut is estimated
+// instead.  What comes before some item in the order (score descending, index ascending) survives then, and that item is
+// taken from a sample of the range: one position out of each of HC_SAMPLES equal pieces, at a scattered place inside it.  Of k
+// list entries t = k HC_SAMPLES / n are expected in the sample, with a spread of at most sqrt(t); the sample's item number
+// t + 5 sqrt(t) + 8 lies beyond the k-th item of the range but for about one sample in a million, and then (mon_select counts)
+// the whole range is selected from.  The order has no ties, so how the scores are distributed does not matter: about 11,700
+// of the 229,376 survive, be they all within a per cent or all equal.  One call, three set sizes, lists of 7,872 and shorter:
+// 34 us with spread-out scores, 52 with scores within 2 % of each other, 64 with equal ones (a cut at the digit alone, and
+// one workgroup for what it lets through: 34, 352, 424; six launches over the whole range: 56, 60, 69).
+__device__ __forceinline__ int sample_row(int i, int lo, int n)
+{
+    const uint32_t a = (uint32_t)(((uint64_t)i * (uint32_t)n) / HC_SAMPLES), b = (uint32_t)(((uint64_t)(i + 1) * (uint32_t)n) / HC_SAMPLES);
+    return lo + (int)(a + (uint32_t)(((uint64_t)((uint32_t)i * 2654435761u) * (b - a)) >> 32));
+}
+
+// The last item that survives, for lists of up to k of the n items from lo on (the whole workgroup of NT threads calls it, with
+// LDS for HC_RADIX_BINS and HC_SAMPLES / 32 words).
+template <int NT, class ScoreAt>
+__device__ __forceinline__ void sample_threshold(uint32_t* sm_hist, uint32_t* sm_tied, int lo, int n, int k, const ScoreAt& score_at, uint32_t& key_out, int& row_out)
+{
+    constexpr int PER = HC_SAMPLES / NT;
+    const float t = (float)k * ((float)HC_SAMPLES / (float)n);
+    const float place = t + 5.0f * sqrtf(t) + 8.0f;
+    key_out = 0u;
+    row_out = 0x7fffffff;
+    if (place >= (float)HC_SAMPLES) return;          // everything survives (the same for every thread)
+    uint32_t key[PER], rem = (uint32_t)place, prefix = 0, count;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        key[u] = hc_score_key(score_at(sample_row(u * NT + (int)threadIdx.x, lo, n)));
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);       // (four loads in flight: more only cost registers)
+    }
+#pragma unroll 1
+    for (int shift = 21; shift >= 0; shift = shift == 21 ? 10 : shift - 10) {      // digits of 11, 11 and 10 bits
+        const uint32_t known = shift == 21 ? 0u : shift == 10 ? 0xffe00000u : 0xfffffc00u, width = shift == 0 ? 1023u : 2047u;
+        __syncthreads();
+        for (int i = threadIdx.x; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const bool in = ((key[u] ^ prefix) & known) == 0u;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+            const uint32_t digit = (key[u] >> shift) & width, one = m ? lane_get(digit, __builtin_ctzll(m)) : 0u;
+            if (m == __builtin_amdgcn_ballot_w64(in && digit == one)) {      // (near-equal scores: one sum instead of 64 in turn)
+                if (m && (threadIdx.x & 63) == 0) atomicAdd(&sm_hist[one], (uint32_t)__builtin_popcountll(m));
+            } else if (in) {
+                atomicAdd(&sm_hist[digit], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t digit;
+        find_digit(sm_hist, rem, digit, rem, count);
+        prefix |= digit << shift;
+    }
+    key_out = prefix;
+    // of the sample's items with that key, the rem-th in position order
+    for (int i = threadIdx.x; i < HC_SAMPLES / 32; i += NT) sm_tied[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (key[u] == prefix) atomicOr(&sm_tied[(u * NT + (int)threadIdx.x) >> 5], 1u << (threadIdx.x & 31));
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    static_assert(HC_SAMPLES / 32 == 128, "two words to a lane");
+    const uint32_t w0 = sm_tied[2 * lane], w1 = sm_tied[2 * lane + 1], c0 = (uint32_t)__builtin_popcount(w0), c1 = (uint32_t)__builtin_popcount(w1);
+    uint32_t tot;
+    const uint32_t before = wave_exscan(c0 + c1, tot);
+    const uint64_t who = __builtin_amdgcn_ballot_w64(before < rem && rem <= before + c0 + c1);
+    const int src = who ? __builtin_ctzll(who) : 0;
+    const uint32_t a0 = lane_get(w0, src), a1 = lane_get(w1, src);
+    uint32_t left = rem - lane_get(before, src);     // 1 .. set bits of the two words
+    uint64_t bits = ((uint64_t)a1 << 32) | a0;
+    for (; left > 1u; --left) bits &= bits - 1;
+    row_out = sample_row(src * 64 + (bits ? __builtin_ctzll(bits) : 0), lo, n);
+}
+
 // Scores and first-digit histogram of a long candidate range.  A workgroup takes `span` consecutive chunks of
 // HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
 template <int G>
-__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span)
+__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k)
 {
     __shared__ uint32_t sh[HC_RADIX_BINS];
     const MonItem& it = B.it[blockIdx.z];
@@ -236,6 +330,17 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
 #pragma unroll
     for (int g = 0; g < G; ++g) l[g] = (!scores_given && agg == HC_AGG_PROB) ? it.lse[(size_t)rd.bh * G + g] : 0.f;
     for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
+    if (long_lists) {                                // a slice each: the later histograms cleared, the baseline list to its bitmap
+        const Ws w = it.ws.rep(rep);
+        const int first = blockIdx.x * BLK + threadIdx.x, step = (rd.nchunk + span - 1) / span * BLK;
+        const int lo = it.real_reps[rep].lo, hi = it.real_reps[rep].hi;
+        const int32_t* base = it.base_idx + (size_t)rd.bh * max_k;
+        for (int i = first; i < 2 * HC_MAX_K_PER_REP * HC_RADIX_BINS; i += step) w.h2[i] = 0u;
+        for (int i = first; i < rd.k[0]; i += step) {
+            const int j = base[i] - lo;
+            if (j >= 0 && j < hi - lo) atomicOr(&w.bitmap[j >> 5], 1u << (j & 31));
+        }
+    }
     __syncthreads();
     for (int ch = c0; ch < c1; ++ch) {
         const int first = rd.lo + ch * HC_SEL_CHUNK;
@@ -261,13 +366,21 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
         if (sh[i]) atomicAdd(&h1[i], sh[i]);
 }
 
-// The survivors of a long range: every candidate whose first digit is at least that of the longest list's k-th
-// score, in position order, chunk by chunk (keys and positions inside the chunk, at the chunk's own place, and how
-// many).  At 229,376 candidates and a longest list of 7,872 about 11,000 survive.  A wave takes a chunk, 64
-// candidates to a round; its first loads do not wait for the threshold.
-__global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B)
+// The survivors are kept as one bit per candidate: nothing to reserve, little to write, few bits for mon_select to read.  A wave
+// takes a chunk at a time, 64 candidates to a round.
+constexpr int ROUNDS = HC_SEL_CHUNK / 64;
+__device__ __forceinline__ void load_chunk(float (&s)[ROUNDS], const float* __restrict__ srow, int lo, int hi, int ch)
+{
+    const int first = lo + ch * HC_SEL_CHUNK + (int)(threadIdx.x & 63);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) s[r] = srow[min(first + r * 64, hi - 1)];
+}
+
+// (Its first loads do not wait for the cut.)
+__global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B, int limit)
 {
     __shared__ __attribute__((aligned(16))) uint32_t sm_hist[HC_RADIX_BINS];
+    __shared__ uint32_t sm_tied[HC_SAMPLES / 32];
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
@@ -277,48 +390,36 @@ __global__ __launch_bounds__(BLK, 8) void mon_compact(MonBatch B)
     if ((int)blockIdx.x * NWAVE >= rd.nchunk) return;
     const Ws w = it.ws.rep(rep);
     const float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
-    constexpr int HALF = HC_SEL_CHUNK / 64 / 2;
-    float s[HALF];
-    auto load = [&](int j0) {
-#pragma unroll
-        for (int r = 0; r < HALF; ++r) {
-            const int j = j0 + r * 64 + lane;
-            s[r] = j < rd.hi ? srow[j] : 0.f;
-        }
-    };
+    float s[ROUNDS];
     uint4 h[HC_RADIX_BINS / 4 / BLK];
 #pragma unroll
     for (int i = 0; i < HC_RADIX_BINS / 4 / BLK; ++i) h[i] = reinterpret_cast<const uint4*>(w.hist)[i * BLK + threadIdx.x];
-    load(rd.lo + ch * HC_SEL_CHUNK);
+    load_chunk(s, srow, rd.lo, rd.hi, ch);
 #pragma unroll
     for (int i = 0; i < HC_RADIX_BINS / 4 / BLK; ++i) reinterpret_cast<uint4*>(sm_hist)[i * BLK + threadIdx.x] = h[i];
-    int kmax = 1;
+    int row_max = 0x7fffffff, kmax = 1;
     for (int ks = 0; ks < rd.nk; ++ks) kmax = max(kmax, it.reps[rep].k[ks]);      // (indexing the register copy would spill it)
     __syncthreads();
     uint32_t digit, remaining, count;
     find_digit(sm_hist, (uint32_t)kmax, digit, remaining, count);
+    uint32_t key_min = digit << 21;
+    if ((uint32_t)kmax - remaining + count > (uint32_t)limit) {       // (the same for every thread)
+        sample_threshold<BLK>(sm_hist, sm_tied, rd.lo, rd.hi - rd.lo, kmax, [&](int j) { return srow[j]; }, key_min, row_max);
+        load_chunk(s, srow, rd.lo, rd.hi, ch);
+    }
     for (; ch < rd.nchunk; ch += stride) {
-        const int first = rd.lo + ch * HC_SEL_CHUNK;
-        uint32_t at = 0;
-#pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            const int j0 = first + half * (HC_SEL_CHUNK / 2);
+        const int first = rd.lo + ch * HC_SEL_CHUNK + lane;
+        uint32_t lo = 0, hi = 0;                     // lane r: round r's mask
 #pragma unroll
-            for (int r = 0; r < HALF; ++r) {
-                const uint32_t key = hc_score_key(s[r]);
-                const bool keep = j0 + r * 64 + lane < rd.hi && (key >> 21) >= digit;
-                const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
-                if (keep) {
-                    const size_t d = (size_t)ch * HC_SEL_CHUNK + at + lanes_below(m);
-                    w.sv_key[d] = key;
-                    w.sv_off[d] = (uint16_t)(half * (HC_SEL_CHUNK / 2) + r * 64 + lane);
-                }
-                at += (uint32_t)__builtin_popcountll(m);
-            }
-            if (half == 0) load(j0 + HC_SEL_CHUNK / 2);
-            else if (ch + stride < rd.nchunk) load(rd.lo + (ch + stride) * HC_SEL_CHUNK);
+        for (int r = 0; r < ROUNDS; ++r) {
+            const uint32_t key = hc_score_key(s[r]);
+            const int j = first + r * 64;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(j < rd.hi && (key > key_min || (key == key_min && j <= row_max)));
+            lo = lane == r ? (uint32_t)m : lo;
+            hi = lane == r ? (uint32_t)(m >> 32) : hi;
         }
-        if (lane == 0) w.cnt[ch] = at;
+        if (lane < ROUNDS) w.mask[(size_t)ch * ROUNDS + lane] = ((uint64_t)hi << 32) | lo;
+        if (ch + stride < rd.nchunk) load_chunk(s, srow, rd.lo, rd.hi, ch + stride);
     }
 }
 
@@ -326,14 +427,93 @@ struct DriftCfg {
     int window, metric, tau_num, tau_den, max_k, tumbling, agg;
 };
 
-// ---- the selection and the decision ----
+// ---- the decision ----
+
+// Window update, decision, baseline update of a pivot, and the filter of the next step: by the whole workgroup (NT threads),
+// after the lists are written.  ring_of: thread i's word of the pivot's ring row; inter: |T ∩ baseline|; tmin: the
+// smallest list threshold, rows: how many rows the lists were taken from (both only for a filtering layer).
+template <int NT>
+__device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int rows, int k, const DriftCfg& cfg, int n_group, int32_t ring_of,
+                                       int32_t inter, uint32_t tmin, int32_t* sm_ring, int32_t& sm_med, int32_t& sm_trig)
+{
+    const int tid = threadIdx.x;
+    int32_t* rg = it.ring + (size_t)bh * (cfg.window + 1);
+    if (it.store_slot == -2) return;                 // the lists were all that was wanted
+    if (tid <= cfg.window) sm_ring[tid] = ring_of;
+    __syncthreads();
+    int cnt = sm_ring[0];
+    if (cnt < 0 || cnt > cfg.window) cnt = 0;
+    if (it.store_slot != -1) {
+        // A buffered query of the window scored again at the test step (Algorithm 1): its overlap replaces
+        // the one stored when the query was current.  Only while the ring is one short of full, i.e. the
+        // monitor call that follows is the one that tests.
+        if (tid == 0 && cnt == cfg.window - 1 && it.store_slot < cnt) rg[1 + it.store_slot] = inter;
+        return;
+    }
+    const int drop = cnt == cfg.window ? 1 : 0;      // sliding window: the oldest value leaves
+    const int m = cnt - drop + 1;                    // values in the window after the push
+    // The lower median is found by ranking (no local arrays: they would live in scratch memory).
+    const int32_t value = tid < m ? (tid == m - 1 ? inter : sm_ring[1 + drop + tid]) : 0;
+    __syncthreads();
+    if (tid < m) sm_ring[tid] = value;
+    __syncthreads();
+    if (tid < m) {
+        const int32_t v = sm_ring[tid];
+        int rank = 0;
+        for (int j = 0; j < m; ++j) rank += sm_ring[j] < v || (sm_ring[j] == v && j < tid);
+        if (rank == (m - 1) / 2) sm_med = v;         // lower median
+    }
+    __syncthreads();
+    if (tid < m) rg[1 + tid] = sm_ring[tid];
+    if (tid == 0) {
+        int trig = 0;
+        if (m == cfg.window) {
+            const long long med = sm_med, kl = k;
+            if (cfg.metric == HC_METRIC_OVERLAP)
+                trig = med * cfg.tau_den < (long long)cfg.tau_num * kl;                     // med/k < tau
+            else
+                trig = med * cfg.tau_den < (long long)cfg.tau_num * (2 * kl - med);         // med/(2k-med) < tau
+        }
+        // the window restarts after a retrieval; a tumbling window after every test
+        rg[0] = (trig || (cfg.tumbling && m == cfg.window)) ? 0 : m;
+        it.inter[bh] = inter;
+        it.flag[bh] = trig;
+        sm_trig = trig;
+        if (it.counts) {
+            uint32_t* cn = it.counts + (size_t)rep * 4;
+            cn[0] += m == cfg.window;
+            cn[1] += (uint32_t)trig;
+            cn[2] += it.need_sense == 1;
+            cn[3] = it.need_sense == 0 ? (uint32_t)rows : 0xffffffffu;
+        }
+        if (it.filt) {
+            // The filter of the next step's split pass: rows whose statistic, taken against this step's
+            // log-sum-exp, stays below the smallest list threshold of this step divided by the margin are dropped.
+            const float t = key_score(tmin);
+            RepFilter f;
+            f.cutsum = (t > 0.f && t < 1.0e30f && it.margin >= 1.f) ? (float)n_group * t / it.margin : 0.f;
+            for (int g = 0; g < 8; ++g) f.ref[g] = g < n_group ? it.lse[(size_t)bh * n_group + g] * 1.4426950408889634f : 0.f;
+            f.armed = 1;
+            for (int i = 0; i < 6; ++i) f.pad[i] = 0;
+            it.filt[rep] = f;
+        }
+    }
+    __syncthreads();
+    if (sm_trig) {                                   // K_base <- K_t
+        const int32_t* src = it.topk_idx + (size_t)bh * cfg.max_k;
+        int32_t* base = it.base_idx + (size_t)bh * cfg.max_k;
+        for (int i = tid; i < k; i += NT) base[i] = src[i];
+    }
+}
+
+// ---- the selection ----
 //
 // One workgroup per pivot and set size (blockIdx.y); the one of set size 0, the monitored list, also takes the
 // decision.  Items are the pivot's candidates in position order: SRC_LOGITS scores them from the stored logits,
 // SRC_SCORES finds their scores in place (given by the caller, or of the rows a filtering split pass kept, whose
-// positions pos_map names), SRC_SURVIVORS takes what mon_compact left.  Their keys are kept in LDS: `cap` of them;
-// items beyond that are read again from the scores in every pass, and survivors that do not all fit (a range full of
-// ties) are given up for the range itself, so that any number of items is handled.
+// positions pos_map names), SRC_SURVIVORS takes what mon_compact left, SRC_RANGE cuts the range down itself.  Their keys are kept in LDS: `cap` of them;
+// items beyond that are read again from the scores in every pass, so that any number of items is handled.  (Survivors
+// that are fewer than the longest list or do not all fit, about one sample in a million, are given up for the range.)
 //
 // Threshold: the keys' range [smallest, largest] is cut into 2048 equal bins, so that the bins are evenly filled
 // whatever the scores' scale is (a fixed top digit of the key would put most items into a handful of bins, whose
@@ -345,7 +525,7 @@ struct DriftCfg {
 // used, and set sizes go to workgroups of their own because the passes behind the histogram cost the same for each
 // of them (one workgroup for all: 97 us for 16,700 rows and three set sizes with 256 threads; one each: 43; with 512
 // threads of half the registers, two waves per SIMD: 28).
-enum { SRC_LOGITS = 0, SRC_SCORES = 1, SRC_SURVIVORS = 2 };
+enum { SRC_LOGITS = 0, SRC_SCORES = 1, SRC_SURVIVORS = 2, SRC_RANGE = 3 };
 constexpr int SEL_LIST = 128;        // members of a threshold bin that are ranked by counting
 
 constexpr int SEL_KEYS(int words) { return words / 264 * 256; }           // keys, with their masks, that fit in so many words (whole 256s)
@@ -383,19 +563,15 @@ __device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n,
     }
 }
 
-__device__ __forceinline__ uint32_t count_true(bool x) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(x)); }
-
 template <int NT, int SRC, int G>
 __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
 {
-    constexpr int SEL_CHUNKS = NT == 512 ? 1024 : 4096;      // chunks whose survivors' places are kept in LDS
     constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t sm_hist[HC_RADIX_BINS];
     __shared__ uint32_t sm_list[SEL_LIST];
     __shared__ uint32_t sm_lo, sm_shift, sm_rem, sm_cnt, sm_tau, sm_need, sm_ties, sm_nlist;
     __shared__ uint32_t sm_min[NW], sm_max[NW], sm_hits[NW], sm_gt[NW], sm_eq[NW];
-    __shared__ uint32_t sm_first[SRC == SRC_SURVIVORS ? SEL_CHUNKS + 1 : 1];   // where every chunk's survivors begin
     __shared__ uint32_t sm_wsum[NW];
     __shared__ int32_t sm_ring[HC_MAX_WINDOW + 1];
     __shared__ int32_t sm_med, sm_trig;
@@ -418,8 +594,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;               // words of the baseline bitmap
     for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
     // what the decision needs from memory is asked for now
-    int32_t* rg = it.ring + (size_t)rd.bh * (cfg.window + 1);
-    const int ring_of = deciding && it.store_slot != -2 && tid <= cfg.window ? rg[tid] : 0;
+    const int ring_of = deciding && it.store_slot != -2 && tid <= cfg.window ? it.ring[(size_t)rd.bh * (cfg.window + 1) + tid] : 0;
     const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
     float ref_minus_lse = -INFINITY;                 // lane g: of query head g of the group, in log2 units
@@ -439,27 +614,49 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
     }
 
     int n = rd.hi - rd.lo;
-    bool surv = false;                   // the items are survivors (all of whose keys fit in LDS)
-    if (SRC == SRC_SURVIVORS && rd.nchunk <= SEL_CHUNKS) {
-        uint32_t carry = 0;
-        for (int c0 = 0; c0 < rd.nchunk; c0 += NT) {
-            const int c = c0 + tid;
-            const uint32_t x = c < rd.nchunk ? w.cnt[c] : 0u;
-            uint32_t tot;
-            uint32_t before = carry + wave_exscan(x, tot);
-            if (lane == 0) sm_wsum[wv] = tot;
+    bool surv = false;                   // the items are survivors
+    // survivors: a thread takes a run of the masks of 64 candidates, whose survivors are items first_item on
+    const int rounds_all = rd.nchunk * (HC_SEL_CHUNK / 64), per_thread = (rounds_all + NT - 1) / NT;
+    const int m_begin = min(tid * per_thread, rounds_all), m_end = min(m_begin + per_thread, rounds_all);
+    uint32_t first_item = 0;
+    if (SRC == SRC_RANGE) {
+        static_assert(SEL_LIST >= HC_SAMPLES / 32, "the sample's ties");
+        uint32_t key_min;
+        int row_max;
+        sample_threshold<NT>(sm_hist, sm_list, rd.lo, n, k_longest, [&](int j) { return srow[j]; }, key_min, row_max);
+        // through LDS, as much of the range as there is room for at a time: all of its loads are in flight at once
+        const int part = lds_words / HC_SEL_CHUNK * HC_SEL_CHUNK;
+        for (int b = 0; b < n; b += part) {
+            const int here = min(part, n - b);
             __syncthreads();
-#pragma unroll
-            for (int i = 0; i < NW; ++i) {
-                before += i < wv ? sm_wsum[i] : 0u;
-                carry += sm_wsum[i];
+            dma_run(srow + rd.lo + b, dyn, here, wv, NW);
+            dma_wait();
+            __syncthreads();
+            for (int r = wv; r * 64 < here; r += NW) {
+                const uint32_t key = hc_score_key(__uint_as_float(dyn[r * 64 + lane]));
+                const int i = r * 64 + lane;
+                const uint64_t m = __builtin_amdgcn_ballot_w64(i < here && (key > key_min || (key == key_min && rd.lo + b + i <= row_max)));
+                if (lane == 0) w.mask[b / 64 + r] = m;                 // (the same in every set size's workgroup)
             }
-            if (c < rd.nchunk) sm_first[c] = before;
-            __syncthreads();
         }
-        if (tid == 0) sm_first[rd.nchunk] = carry;
-        surv = (int)carry <= SEL_KEYS(lds_words);
-        if (surv) n = (int)carry;
+        for (int r = (n + 63) / 64 + tid; r < rd.nchunk * ROUNDS; r += NT) w.mask[r] = 0u;
+        __syncthreads();
+        for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+    }
+    if (SRC >= SRC_SURVIVORS) {
+        uint32_t mine = 0, tot, all = 0;
+#pragma unroll 4
+        for (int m = m_begin; m < m_end; ++m) mine += (uint32_t)__builtin_popcountll(w.mask[m]);
+        first_item = wave_exscan(mine, tot);
+        if (lane == 0) sm_wsum[wv] = tot;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            first_item += i < wv ? sm_wsum[i] : 0u;
+            all += sm_wsum[i];
+        }
+        surv = all >= (uint32_t)k_longest && all <= (uint32_t)min(w.sv_cap, SEL_KEYS(lds_words));
+        if (surv) n = (int)all;
     }
     // Dynamic LDS: the keys (a multiple of 256 of them), a mask per 64 keys saying which are in the list, and the
     // baseline bitmap if it fits behind the items (otherwise the one in the workspace is used).
@@ -514,33 +711,30 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
                 }
             }
         }
-    } else if (SRC == SRC_SURVIVORS && surv) {
-        // item i is survivor i - sm_first[c] of the chunk c in whose run it falls; its position goes to a dense table
+    } else if (SRC >= SRC_SURVIVORS && surv) {
+        // the survivors' rows of the range, then in their places their keys; the positions go to a table
+        for (int m = m_begin; m < m_end; ++m)
+            for (uint64_t bits = w.mask[m]; bits != 0; bits &= bits - 1) sm_key[first_item++] = (uint32_t)(m * 64 + __builtin_ctzll(bits));
+        __syncthreads();
         constexpr int U = NT == 512 ? 4 : 8;
         for (int i0 = tid; i0 < n; i0 += U * NT) {
-            uint32_t key[U], off[U];
-            int c[U];
+            float s[U];
+            int row[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // a wave's 64 items are consecutive: the chunk of the first by counting the chunks that begin before it,
-                // the others' a few chunks on
-                const uint32_t i = (uint32_t)min(i0 + u * NT, n - 1), i_wave = (uint32_t)min(i0 - lane + u * NT, n - 1);
-                int at_chunk = -1;
-                for (int cb = 0; cb < rd.nchunk; cb += 64)
-                    at_chunk += (int)count_true(cb + lane < rd.nchunk && sm_first[min(cb + lane, rd.nchunk)] <= i_wave);
-                while (sm_first[at_chunk + 1] <= i) ++at_chunk;       // (ends: an item lies before the last entry, the total)
-                c[u] = at_chunk;
-                const uint32_t at = (uint32_t)at_chunk * HC_SEL_CHUNK + (i - sm_first[at_chunk]);
-                key[u] = w.sv_key[at];
-                off[u] = w.sv_off[at];
+            for (int u = 0; u < U; ++u) row[u] = i0 + u * NT < n ? rd.lo + (int)sm_key[i0 + u * NT] : rd.lo;      // (its own items only: another's may be a key by now)
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[u] = srow[row[u]];
+            if (pmap) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) row[u] = pmap[row[u]];
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = i0 + u * NT;
                 if (i < n) {
-                    put(i, key[u]);
-                    const int row = rd.lo + c[u] * HC_SEL_CHUNK + (int)off[u];
-                    w.sv_pos[i] = pmap ? pmap[row] : row;
+                    put(i, hc_score_key(s[u]));
+                    w.sv_pos[i] = row[u];
                 }
             }
         }
@@ -597,6 +791,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
     const uint32_t range = kmax - kmin;
     const uint32_t shift = range < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(range);       // range >> shift < 2048
     auto histogram = [&]() {
+        if (range == 0u) return;                     // all equal
         for (int i0 = tid; i0 < n; i0 += GROUP * NT) {
             uint32_t key[GROUP];
             keys_of(key, i0, NT);
@@ -613,8 +808,8 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
     };
     auto threshold = [&](int kt) {
         if (wv == 0) {
-            uint32_t digit, rem, count;
-            find_digit(sm_hist, (uint32_t)kt, digit, rem, count);
+            uint32_t digit = 0u, rem = (uint32_t)kt, count = (uint32_t)n;
+            if (range != 0u) find_digit(sm_hist, (uint32_t)kt, digit, rem, count);
             if (lane == 0) {
                 sm_lo = kmin + (digit << shift);
                 sm_shift = shift;
@@ -742,7 +937,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
         // The usual case: every round's choice is known now and kept as a mask; the keys are done with, and where the
         // positions come from a table, the run's part of it takes their place.
         const bool masked = fits && all_ties;
-        const int32_t* table = SRC == SRC_SURVIVORS && surv ? w.sv_pos : pmap ? pmap + rd.lo : nullptr;
+        const int32_t* table = SRC >= SRC_SURVIVORS && surv ? w.sv_pos : pmap ? pmap + rd.lo : nullptr;
         // A wave takes a run of the items, 64 to a round, GROUP rounds at a time.  First how many keys above (and at)
         // the threshold its run holds; then, from the runs before it, where its own entries go, and the list in
         // position order with |T ∩ baseline| of the monitored one.
@@ -877,72 +1072,312 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
     int32_t inter = 0;
 #pragma unroll
     for (int i = 0; i < NW; ++i) inter += (int32_t)sm_hits[i];
-    if (it.store_slot == -2) return;                 // the lists were all that was wanted
-    if (tid <= cfg.window) sm_ring[tid] = ring_of;
-    __syncthreads();
-    int cnt = sm_ring[0];
-    if (cnt < 0 || cnt > cfg.window) cnt = 0;
-    if (it.store_slot != -1) {
-        // A buffered query of the window scored again at the test step (Algorithm 1): its overlap replaces
-        // the one stored when the query was current.  Only while the ring is one short of full, i.e. the
-        // monitor call that follows is the one that tests.
-        if (tid == 0 && cnt == cfg.window - 1 && it.store_slot < cnt) rg[1 + it.store_slot] = inter;
-        return;
+    decide<NT>(it, rep, rd.bh, rd.hi, k, cfg, n_group, ring_of, inter, tmin, sm_ring, sm_med, sm_trig);
+}
+
+// ---- long lists ----
+//
+// A workgroup per list is only as good as the lists are short (its time grows with them).  Lists of more than about 9,500
+// entries are selected by many workgroups in six launches: mon_score_hist, two more digits of the keys (11 + 10 bits), counts per
+// chunk, ordered write, decision.  229,376 candidates, a longest list of 40,000: 52 us with spread-out scores, 56 within 2 % of
+// each other, 68 equal (by mon_select over the range: 408, 365, 472).
+
+// The keys of four consecutive candidates, positions first4 .. first4 + 3 (first4 a multiple of 4: one 16-byte load), of which
+// those inside [lo, hi) count.
+__device__ __forceinline__ void load_keys(const float* __restrict__ srow, int first4, int lo, int hi, uint32_t (&key)[4], bool (&in)[4])
+{
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (first4 < hi) v = *reinterpret_cast<const float4*>(srow + first4);     // (row stride a multiple of 64: in bounds)
+    const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        in[i] = first4 + i >= lo && first4 + i < hi;
+        key[i] = hc_score_key(f[i]);
     }
-    const int drop = cnt == cfg.window ? 1 : 0;      // sliding window: the oldest value leaves
-    const int m = cnt - drop + 1;                    // values in the window after the push
-    // The lower median is found by ranking (no local arrays: they would live in scratch memory).
-    const int32_t value = tid < m ? (tid == m - 1 ? inter : sm_ring[1 + drop + tid]) : 0;
+}
+
+// dst[0, n) = src[0, n) by a workgroup of BLK threads (n a multiple of 4 BLK, both 16-byte aligned).
+__device__ __forceinline__ void copy_words(uint32_t* dst, const uint32_t* __restrict__ src, int n)
+{
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n / 4; i += BLK) reinterpret_cast<uint4*>(dst)[i] = reinterpret_cast<const uint4*>(src)[i];
+}
+
+// These passes work on chunks that start at a multiple of 4 positions, which can add one.
+__device__ __forceinline__ int chunks_from_lo4(const RepDev& rd) { return (rd.hi - (rd.lo & ~3) + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK; }
+
+// PASS 2: second digits (bits 20..10) of the keys whose first digit matches; PASS 3: third digits (bits 9..0) of those whose
+// upper 22 bits match.  A workgroup handles every set size of its pivot over `span` chunks.
+template <int PASS>
+__global__ __launch_bounds__(BLK, 8) void mon_hist(MonBatch B, int span)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];      // [nk][HC_RADIX_BINS]
+    __shared__ uint32_t sm_prefix[HC_MAX_K_PER_REP];
+    const MonItem& it = B.it[blockIdx.z];
+    const int rep = blockIdx.y;
+    if (rep >= it.n_reps || mon_skip(it, rep)) return;
+    const RepDev rd = it.reps[rep];
+    const int lo4 = rd.lo & ~3, nchunk = chunks_from_lo4(rd);
+    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
+    if (c0 >= nchunk) return;
+    const Ws w = it.ws.rep(rep);
+    const uint32_t* before = PASS == 2 ? w.hist : w.h2;
+    copy_words(dyn, before, (PASS == 2 ? 1 : rd.nk) * HC_RADIX_BINS);
     __syncthreads();
-    if (tid < m) sm_ring[tid] = value;
-    __syncthreads();
-    if (tid < m) {
-        const int32_t v = sm_ring[tid];
-        int rank = 0;
-        for (int j = 0; j < m; ++j) rank += sm_ring[j] < v || (sm_ring[j] == v && j < tid);
-        if (rank == (m - 1) / 2) sm_med = v;         // lower median
-    }
-    __syncthreads();
-    if (tid < m) rg[1 + tid] = sm_ring[tid];
-    if (tid == 0) {
-        int trig = 0;
-        if (m == cfg.window) {
-            const long long med = sm_med, kl = k;
-            if (cfg.metric == HC_METRIC_OVERLAP)
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * kl;                     // med/k < tau
-            else
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * (2 * kl - med);         // med/(2k-med) < tau
+    for (int ks = threadIdx.x >> 6; ks < rd.nk; ks += NWAVE) {          // a wave per set size
+        uint32_t digit, remaining, count;
+        if (PASS == 2) {
+            find_digit(dyn, (uint32_t)it.reps[rep].k[ks], digit, remaining, count);      // (indexing the register copy would spill it)
+        } else {
+            find_digit(dyn + ks * HC_RADIX_BINS, w.sel[ks * 4 + 1], digit, remaining, count);
+            digit |= w.sel[ks * 4] << 11;
         }
-        // the window restarts after a retrieval; a tumbling window after every test
-        rg[0] = (trig || (cfg.tumbling && m == cfg.window)) ? 0 : m;
-        it.inter[rd.bh] = inter;
-        it.flag[rd.bh] = trig;
-        sm_trig = trig;
-        if (it.counts) {
-            uint32_t* cn = it.counts + (size_t)rep * 4;
-            cn[0] += m == cfg.window;
-            cn[1] += (uint32_t)trig;
-            cn[2] += it.need_sense == 1;
-            cn[3] = it.need_sense == 0 ? (uint32_t)rd.hi : 0xffffffffu;
-        }
-        if (it.filt) {
-            // The filter of the next step's split pass: rows whose statistic, taken against this step's
-            // log-sum-exp, stays below the smallest list threshold of this step divided by the margin are dropped.
-            const float t = key_score(tmin);
-            RepFilter f;
-            f.cutsum = (t > 0.f && t < 1.0e30f && it.margin >= 1.f) ? (float)n_group * t / it.margin : 0.f;
-            for (int g = 0; g < 8; ++g) f.ref[g] = g < n_group ? it.lse[(size_t)rd.bh * n_group + g] * 1.4426950408889634f : 0.f;
-            f.armed = 1;
-            for (int i = 0; i < 6; ++i) f.pad[i] = 0;
-            it.filt[rep] = f;
+        if ((threadIdx.x & 63) == 0) {
+            sm_prefix[ks] = digit;
+            if (blockIdx.x == 0) {       // for the next pass (every workgroup finds the same)
+                w.sel[ks * 4 + (PASS == 2 ? 0 : 2)] = digit;
+                w.sel[ks * 4 + (PASS == 2 ? 1 : 3)] = remaining;
+            }
         }
     }
     __syncthreads();
-    if (sm_trig) {                                   // K_base <- K_t
-        const int32_t* src = it.topk_idx + (size_t)rd.bh * cfg.max_k;
-        int32_t* base = it.base_idx + (size_t)rd.bh * cfg.max_k;
-        for (int i = tid; i < k; i += NT) base[i] = src[i];
+    for (int i = threadIdx.x; i < rd.nk * HC_RADIX_BINS; i += BLK) dyn[i] = 0u;
+    __syncthreads();
+    const float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
+    for (int ch = c0; ch < c1; ch += 2) {            // two chunks' loads in flight
+        uint32_t key[2][4];
+        bool in[2][4];
+        load_keys(srow, lo4 + ch * HC_SEL_CHUNK + threadIdx.x * 4, rd.lo, rd.hi, key[0], in[0]);
+        load_keys(srow, lo4 + (ch + 1) * HC_SEL_CHUNK + threadIdx.x * 4, rd.lo, ch + 1 < c1 ? rd.hi : 0, key[1], in[1]);
+        for (int ks = 0; ks < rd.nk; ++ks) {
+            const uint32_t prefix = sm_prefix[ks];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (!in[u][i]) continue;
+                    if (PASS == 2) {
+                        if ((key[u][i] >> 21) == prefix) atomicAdd(&dyn[ks * HC_RADIX_BINS + ((key[u][i] >> 10) & 0x7ffu)], 1u);
+                    } else {
+                        if ((key[u][i] >> 10) == prefix) atomicAdd(&dyn[ks * HC_RADIX_BINS + (key[u][i] & 0x3ffu)], 1u);
+                    }
+                }
+            }
+        }
     }
+    __syncthreads();
+    uint32_t* out = PASS == 2 ? w.h2 : w.h3;
+    for (int i = threadIdx.x; i < rd.nk * HC_RADIX_BINS; i += BLK)
+        if (dyn[i]) atomicAdd(&out[i], dyn[i]);
+}
+
+// The threshold key of every set size, then per chunk the counts of greater and of equal keys: a wave takes a chunk, every
+// fourth of the workgroup's span.  The check of a filtering layer (see mon_select) is made here.
+__global__ __launch_bounds__(BLK) void mon_count(MonBatch B, int span, int n_group)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];      // [nk][HC_RADIX_BINS]
+    __shared__ uint32_t sm_tau[HC_MAX_K_PER_REP];
+    const MonItem& it = B.it[blockIdx.z];
+    const int rep = blockIdx.y;
+    if (rep >= it.n_reps || mon_skip(it, rep)) return;
+    const RepDev rd = it.reps[rep];
+    const int lo4 = rd.lo & ~3, nchunk = chunks_from_lo4(rd);
+    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
+    if (c0 >= nchunk) return;
+    const Ws w = it.ws.rep(rep);
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    copy_words(dyn, w.h3, rd.nk * HC_RADIX_BINS);
+    __syncthreads();
+    for (int ks = wv; ks < rd.nk; ks += NWAVE) {
+        uint32_t digit, need, count;
+        find_digit(dyn + ks * HC_RADIX_BINS, w.sel[ks * 4 + 3], digit, need, count);
+        const uint32_t tau = (w.sel[ks * 4 + 2] << 10) | digit;
+        if (lane == 0) {
+            sm_tau[ks] = tau;
+            if (blockIdx.x == 0) {       // for mon_write (the other two words are still being read)
+                w.sel[ks * 4] = tau;
+                w.sel[ks * 4 + 1] = need;
+            }
+        }
+    }
+    __syncthreads();
+    if (it.need_sense == 0 && it.filt && blockIdx.x == 0 && threadIdx.x == 0) {
+        const RepFilter* f = it.filt + rep;
+        if (f->cutsum > 0.f) {
+            uint32_t tmin = sm_tau[0];
+            for (int ks = 1; ks < rd.nk; ++ks) tmin = min(tmin, sm_tau[ks]);
+            float delta = 0.f;
+            for (int g = 0; g < n_group; ++g) delta = fmaxf(delta, exp2f(f->ref[g] - it.lse[(size_t)rd.bh * n_group + g] * 1.4426950408889634f));
+            const float bound = f->cutsum / (float)n_group * delta * 1.0001f;
+            if (!(key_score(tmin) >= bound)) it.need[rep] = 5;
+        }
+    }
+    const float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
+    for (int ch = c0 + wv; ch < c1; ch += NWAVE) {
+        uint32_t key[4][4];
+        bool in[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_keys(srow, lo4 + ch * HC_SEL_CHUNK + q * 256 + lane * 4, rd.lo, rd.hi, key[q], in[q]);
+        for (int ks = 0; ks < rd.nk; ++ks) {
+            const uint32_t tau = sm_tau[ks];
+            uint32_t gt = 0, eq = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    gt += count_true(in[q][i] && key[q][i] > tau);
+                    eq += count_true(in[q][i] && key[q][i] == tau);
+                }
+            }
+            if (lane == 0) {
+                uint32_t* cnt = w.cnt + ((size_t)ks * w.max_chunks + ch) * 2;
+                cnt[0] = gt;
+                cnt[1] = eq;
+            }
+        }
+    }
+}
+
+// The lists of a pivot in ascending order, and |T ∩ baseline| of the monitored one.  A wave takes a chunk, in two halves
+// of 512 candidates in position order (8 to a lane), and reads a half's keys once for all set sizes; what a set size
+// carries from half to half (equal keys seen, entries emitted) lives in LDS: the kernel has to fit, in registers, beside
+// the attention pass.
+__global__ __launch_bounds__(BLK, 8) void mon_write(MonBatch B, DriftCfg cfg, int span)
+{
+    __shared__ uint32_t sm_carry[NWAVE][HC_MAX_K_PER_REP][2];
+    const MonItem& it = B.it[blockIdx.z];
+    const int rep = blockIdx.y;
+    if (rep >= it.n_reps || mon_skip(it, rep)) return;
+    const int max_ctx = it.ws.max_ctx;
+    const int32_t* __restrict__ pmap = it.pos_map ? it.pos_map + (size_t)rep * max_ctx : nullptr;
+    const RepDev rd = it.reps[rep];
+    const int real_lo = it.real_reps[rep].lo, real_hi = it.real_reps[rep].hi;
+    const int lo4 = rd.lo & ~3, nchunk = chunks_from_lo4(rd);
+    const int c0 = blockIdx.x * span, c1 = min(c0 + span, nchunk);
+    if (c0 >= nchunk) return;
+    const Ws w = it.ws.rep(rep);
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const float* srow = it.scores + (size_t)rep * max_ctx;
+    for (int chunk = c0 + wv; chunk < c1; chunk += NWAVE) {
+        for (int ks = 0; ks < rd.nk; ++ks) {
+            const uint32_t need = w.sel[ks * 4 + 1];
+            const uint32_t* cnt = w.cnt + (size_t)ks * w.max_chunks * 2;
+            // over the chunks before this one: equal keys seen, and entries emitted (a chunk's greater keys plus as many
+            // equal ones as are still needed)
+            uint32_t eq_before = 0, emitted = 0;
+            for (int b0 = 0; b0 < chunk; b0 += 64) {
+                const int b = b0 + lane;
+                const uint32_t g = b < chunk ? cnt[b * 2] : 0u, e = b < chunk ? cnt[b * 2 + 1] : 0u;
+                uint32_t etot;
+                const uint32_t eprev = eq_before + wave_exscan(e, etot);
+                const uint32_t left = need > eprev ? need - eprev : 0u;
+                emitted += wave_sum(g + min(e, left));
+                eq_before += etot;
+            }
+            if (lane == 0) {
+                sm_carry[wv][ks][0] = eq_before;
+                sm_carry[wv][ks][1] = emitted;
+            }
+        }
+        uint32_t hits = 0;
+        for (int half = 0; half < 2; ++half) {
+            uint32_t key[2][4];
+            bool in[2][4];
+            const int first8 = lo4 + chunk * HC_SEL_CHUNK + half * (HC_SEL_CHUNK / 2) + lane * 8;
+            load_keys(srow, first8, rd.lo, rd.hi, key[0], in[0]);
+            load_keys(srow, first8 + 4, rd.lo, rd.hi, key[1], in[1]);
+            // the positions of the lane's 8 rows: themselves, or (rows a filtering split pass kept) what the map says
+            int32_t jj[8];
+            if (pmap) {
+                int4 pa = make_int4(0, 0, 0, 0), pb = pa;
+                if (first8 < rd.hi) pa = *reinterpret_cast<const int4*>(pmap + first8);          // (row stride a multiple of 64: in bounds)
+                if (first8 + 4 < rd.hi) pb = *reinterpret_cast<const int4*>(pmap + first8 + 4);
+                jj[0] = pa.x; jj[1] = pa.y; jj[2] = pa.z; jj[3] = pa.w;
+                jj[4] = pb.x; jj[5] = pb.y; jj[6] = pb.z; jj[7] = pb.w;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) jj[i] = first8 + i;
+            }
+            for (int ks = 0; ks < rd.nk; ++ks) {
+                const uint32_t tau = w.sel[ks * 4], need = w.sel[ks * 4 + 1], k = (uint32_t)it.reps[rep].k[ks];
+                const uint32_t eq_before = sm_carry[wv][ks][0], emitted = sm_carry[wv][ks][1];      // (written by this wave)
+                uint32_t my_eq = 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) my_eq += in[i / 4][i % 4] && key[i / 4][i % 4] == tau;
+                uint32_t eq_tot, sel_tot, selmask = 0;
+                uint32_t eq_rank = eq_before + wave_exscan(my_eq, eq_tot);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const bool at = in[i / 4][i % 4] && key[i / 4][i % 4] == tau;
+                    const bool sel = at ? eq_rank < need : in[i / 4][i % 4] && key[i / 4][i % 4] > tau;
+                    eq_rank += at;
+                    selmask |= (uint32_t)sel << i;
+                }
+                const uint32_t pos0 = emitted + wave_exscan((uint32_t)__builtin_popcount(selmask), sel_tot);
+                if (lane == 0) {
+                    sm_carry[wv][ks][0] = eq_before + eq_tot;
+                    sm_carry[wv][ks][1] = emitted + sel_tot;
+                }
+                if (ks == 0) {
+                    // (all loads issued together; a row that is not selected reads word 0 and does not count)
+                    uint32_t wd[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int j = (selmask >> i) & 1u ? min(max(jj[i], real_lo), real_hi - 1) - real_lo : 0;
+                        wd[i] = (w.bitmap[j >> 5] >> (j & 31)) & (selmask >> i) & 1u;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) hits += wd[i];
+                }
+                for (int o = rd.out_begin; o < rd.out_begin + rd.out_count; ++o) {      // the rows this list goes to
+                    if (it.outs[o].kslot != ks) continue;
+                    int32_t* dst = it.topk_idx + (size_t)it.outs[o].row * cfg.max_k;
+                    uint32_t pos = pos0;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if (selmask & (1u << i)) {
+                            if (pos < k) dst[pos] = jj[i];      // (always; the guard keeps a corrupt state in bounds)
+                            ++pos;
+                        }
+                    }
+                }
+            }
+        }
+        hits = wave_sum(hits);
+        if (lane == 0) w.hits[chunk] = hits;
+    }
+}
+
+// A workgroup per pivot, behind mon_write.
+__global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int n_group)
+{
+    __shared__ int32_t sm_ring[HC_MAX_WINDOW + 1];
+    __shared__ int32_t sm_med, sm_trig;
+    __shared__ uint32_t sm_hits[NWAVE];
+    const MonItem& it = B.it[blockIdx.y];
+    const int rep = blockIdx.x, tid = threadIdx.x;
+    if (rep >= it.n_reps) return;
+    if (it.need_sense == 1 && it.need[rep] == 0) return;         // decided over the kept rows
+    const bool elsewhere = it.need_sense == 0 && it.need[rep] != 0;
+    const RepDev rd = it.reps[rep];
+    const Ws w = it.ws.rep(rep);
+    const int32_t ring_of = it.store_slot != -2 && tid <= cfg.window ? it.ring[(size_t)rd.bh * (cfg.window + 1) + tid] : 0;
+    uint32_t h = 0;
+    if (!elsewhere)
+        for (int c = tid; c < chunks_from_lo4(rd); c += BLK) h += w.hits[c];
+    h = wave_sum(h);
+    if ((tid & 63) == 0) sm_hits[tid >> 6] = h;
+    __syncthreads();
+    // every other kernel of this call is done with histogram and bitmap: the next call finds them clear
+    const int words = (it.real_reps[rep].hi - it.real_reps[rep].lo + 31) / 32;
+    for (int i = tid; i < HC_RADIX_BINS; i += BLK) w.hist[i] = 0u;
+    for (int i = tid; i < words; i += BLK) w.bitmap[i] = 0u;
+    if (elsewhere) return;
+    uint32_t tmin = 0xffffffffu;
+    if (it.filt)
+        for (int ks = 0; ks < rd.nk; ++ks) tmin = min(tmin, w.sel[ks * 4]);
+    decide<BLK>(it, rep, rd.bh, rd.hi, rd.k[0], cfg, n_group, ring_of, (int32_t)(sm_hits[0] + sm_hits[1] + sm_hits[2] + sm_hits[3]), tmin, sm_ring, sm_med,
+                sm_trig);
 }
 
 // Scores of the rows a filtering split pass kept.  They lie segment by segment in the pivot's block of rep_logits
@@ -1037,15 +1472,25 @@ __global__ __launch_bounds__(BLK, 8) void mon_sparse_score(MonBatch B)
 
 }   // namespace
 
+// mon_select's two forms.  Beside the attention pass the small one (512 threads of at most 40 registers) leaves room for two
+// attention workgroups on its compute unit: 26 KB of LDS each with the pivot-logit filter, 41 KB without.  The large one
+// (1024 threads) may take a whole compute unit, also beside the attention pass where the small one has no room for the
+// items, and in groups of eight heads, two of whose attention workgroups leave no room for either.
+constexpr int SELECT_STATIC = 10 * 1024;            // (what the kernel itself declares, rounded up)
+template <int NT> static int select_room(const hc_ctx* ctx)
+{
+    return (NT == 1024 ? 152 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - SELECT_STATIC;
+}
+static bool select_small(const hc_ctx* ctx, int items)
+{
+    return ctx->beside_now && ctx->G < 8 && items <= SEL_KEYS(select_room<512>(ctx) / 4);
+}
+
 // Launches mon_select over the batch, with LDS for want_keys items and a baseline bitmap of bm_words as far as it goes.
 template <int NT, int SRC>
 static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
 {
-    // Alone a workgroup may take a whole compute unit's LDS.  Beside the attention pass it has to leave room for two
-    // of its workgroups: 26 KB each with the pivot-logit filter, 41 KB without, 52 KB in groups of eight heads.
-    constexpr int STATIC = (SRC != SRC_SURVIVORS ? 10 : NT == 512 ? 15 : 27) * 1024;          // (what the kernel itself declares, rounded up)
-    const int room = (!ctx->beside_now ? 152 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - STATIC;
-    const unsigned lds = (unsigned)std::min((long long)room, ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
+    const unsigned lds = (unsigned)std::min((long long)select_room<NT>(ctx), ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
 #define HC_SELECT(GG)                                                                                                        \
     mon_select<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4))
     if constexpr (SRC != SRC_LOGITS) {
@@ -1055,7 +1500,7 @@ static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg
         case 1: HC_SELECT(1); break;
         case 2: HC_SELECT(2); break;
         case 4: HC_SELECT(4); break;
-        default: HC_SELECT(8); break;
+        default: if constexpr (NT == 1024) HC_SELECT(8); break;
         }
     }
 #undef HC_SELECT
@@ -1064,19 +1509,51 @@ static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg
 }
 
 template <int SRC>
-static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
+static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, bool small,
+                               hipStream_t st)
 {
-    return ctx->beside_now ? launch_select_nt<512, SRC>(ctx, B, dc, grid, want_keys, bm_words, st)
-                           : launch_select_nt<1024, SRC>(ctx, B, dc, grid, want_keys, bm_words, st);
+    return small ? launch_select_nt<512, SRC>(ctx, B, dc, grid, want_keys, bm_words, st)
+                 : launch_select_nt<1024, SRC>(ctx, B, dc, grid, want_keys, bm_words, st);
+}
+
+// Items that the sample lets through for a longest list of k out of n candidates: expected, and with room for its spread.
+static void expected_survivors(long long k, long long n, int* mean, int* most)
+{
+    const double t = (double)k * HC_SAMPLES / (double)n, place = std::min((double)HC_SAMPLES, t + 5.0 * std::sqrt(t) + 8.0);
+    *mean = (int)(place * (double)n / HC_SAMPLES);
+    *most = (int)std::min((double)n, (place + 4.0 * std::sqrt(place)) * (double)n / HC_SAMPLES);
+}
+
+// The launches of long lists: see mon_hist.
+static hc_status launch_long(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, int n, int max_reps, int max_nk, int max_nchunk, int span, hipStream_t st)
+{
+    const dim3 grid((max_nchunk + 1 + span - 1) / span, max_reps, n);      // (chunks that start at a multiple of 4 can be one more)
+    const unsigned lds = (unsigned)max_nk * HC_RADIX_BINS * 4;
+    mon_hist<2><<<grid, dim3(BLK), hc_side_lds(ctx, (const void*)mon_hist<2>, lds), st>>>(B, span);
+    HC_HIP(ctx, hipGetLastError());
+    mon_hist<3><<<grid, dim3(BLK), hc_side_lds(ctx, (const void*)mon_hist<3>, lds), st>>>(B, span);
+    HC_HIP(ctx, hipGetLastError());
+    mon_count<<<grid, dim3(BLK), hc_side_lds(ctx, (const void*)mon_count, lds), st>>>(B, span, ctx->G);
+    HC_HIP(ctx, hipGetLastError());
+    // (the write pass has nothing to set up per workgroup: a chunk per wave)
+    mon_write<<<dim3((max_nchunk + 1 + NWAVE - 1) / NWAVE, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_write, 0), st>>>(B, dc, NWAVE);
+    HC_HIP(ctx, hipGetLastError());
+    mon_decide<<<dim3(max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_decide, 0), st>>>(B, dc, ctx->G);
+    HC_HIP(ctx, hipGetLastError());
+    return HC_OK;
 }
 
 // Candidates up to which one workgroup per pivot does everything, from the scores on.  What lies against more is that
 // the exponentials of the scores are then made by one compute unit: at 32K candidates and a group of four this takes 18
 // of 44 us, where the three launches take 29 in all; at 4K it takes 3.5 us of 13, where two more launches cost 8.
-constexpr int SELECT_DIRECT_ALONE = 8192, SELECT_DIRECT_BESIDE = 8192;
+constexpr int SELECT_DIRECT = 8192;
+// Survivors (as the sample would let through) up to which one workgroup per list beats the six launches of long lists, with
+// the sample in front of it where it is needed.  131,072 candidates, scores spread out / within 2 % / equal: a longest list of 8,192
+// (11,000 expected) 37 / 48 / 58 us against 47 / 49 / 62; of 10,000 (13,100) 41 / 50 / 63 against 47 / 49 / 62.
+constexpr int SELECT_SURVIVORS = 13000;
 
 // The launches of one chain over a batch of layers.  mode 0: the plain chain (every pivot, all candidate positions).
-// mode 1: the chain over the rows a filtering split pass kept.  mode 2: the selection that stands by behind
+// mode 1: the chain over the rows a filtering split pass kept.  mode 2: the chain that stands by behind
 // mode 1, for the pivots whose check failed (their logits and scores are there already: see
 // hc_launch_rep_logits).  ws_first: which workspace copy the first layer uses.
 static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* calls, int ws_first, int scores_given, int mode,
@@ -1084,13 +1561,13 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
 {
     const hc_config& c = ctx->cfg;
     MonBatch B{};
-    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0;
+    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0, max_k = 1;
     bool armed = true;
     for (int i = 0; i < n; ++i) {
         const hc_monitor_call& x = *calls[i];
         hc_monitor_ws& m = ctx->ws[ws_first + i];
         MonItem& it = B.it[i];
-        it.ws = Ws{m.hist, m.cnt, m.bitmap, m.sv_key, m.sv_off, m.sv_pos, ctx->max_chunks, c.max_ctx};
+        it.ws = Ws{m.hist, m.bitmap, nullptr, nullptr, m.area, nullptr, nullptr, nullptr, nullptr, ctx->max_chunks, c.max_ctx, ctx->sv_cap, ctx->area_words};
         it.reps = x.reps ? x.reps : x.L->reps;
         it.real_reps = it.reps;
         it.outs = x.reps ? x.outs : x.L->outs;
@@ -1103,7 +1580,6 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         it.inter = x.inter;
         it.flag = x.flag;
         it.n_reps = x.reps ? x.n_reps : x.L->n_reps;
-        it.n_outs = x.reps ? x.n_outs : x.L->n_outs;
         it.store_slot = x.store_slot;
         it.need_sense = -1;
         if (!x.reps && x.store_slot == -1) it.counts = x.L->mon_counts;
@@ -1135,6 +1611,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         max_reps = std::max(max_reps, it.n_reps);
         max_nchunk = std::max(max_nchunk, nchunk);
         max_nk = std::max(max_nk, x.reps ? x.max_nk : x.L->max_nk);
+        max_k = std::max(max_k, x.reps ? c.max_k : x.L->max_k_any);
         if (m.dirty && mode != 2) {     // a previous call that used this workspace copy did not run to its last kernel
             mon_prep<<<dim3(16, m.reps), dim3(256), 0, st>>>(it.ws);
             HC_HIP(ctx, hipGetLastError());
@@ -1156,28 +1633,46 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         default: mon_sparse_score<8><<<g, dim3(BLK), hc_side_lds(ctx, (const void*)mon_sparse_score<8>, 0), st>>>(B); break;
         }
         HC_HIP(ctx, hipGetLastError());
-        scores_given = 1;                     // from here on the scores are there
-        if (armed) return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
     }
-    if (mode == 2) return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
-    if (max_nchunk * HC_SEL_CHUNK <= (ctx->beside_now ? SELECT_DIRECT_BESIDE : SELECT_DIRECT_ALONE))
-        return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st)
-                            : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
-    // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K took
-    // 40 us per call with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.
-    const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
-    const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
-    switch (ctx->G) {
-    case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span); break;
-    case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span); break;
-    case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span); break;
-    default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span); break;
+    if (mode != 0) scores_given = 1;                     // they are there from here on
+    const int candidates = max_nchunk * HC_SEL_CHUNK;
+    // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
+    // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
+    const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
+    const bool few = mode == 1 && armed && (select_small(ctx, kept) || (!(ctx->beside_now && ctx->G < 8) && kept <= SEL_KEYS(select_room<1024>(ctx) / 4)));
+    if (few || candidates <= SELECT_DIRECT) {
+        const bool small = few ? select_small(ctx, kept) : select_small(ctx, candidates);
+        return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, candidates, bm_words, small, st)
+                            : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, candidates, bm_words, small, st);
     }
-    HC_HIP(ctx, hipGetLastError());
+    int survivors, most;
+    expected_survivors(max_k, candidates, &survivors, &most);
+    const bool long_lists = survivors > SELECT_SURVIVORS || most > ctx->sv_cap;
+    if (mode != 2 || long_lists) {
+        // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K took
+        // 40 us per call with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.  (The launches
+        // that stand by: few, long workgroups.)
+        const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
+        const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
+        switch (ctx->G) {
+        case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
+        case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
+        case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
+        default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
+        }
+        HC_HIP(ctx, hipGetLastError());
+        if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
+    }
+    const bool small = select_small(ctx, most);
+    const int room = (small ? select_room<512>(ctx) : select_room<1024>(ctx)) / 4;
+    const int fit = std::min(ctx->sv_cap, SEL_KEYS(bm_words <= room / 2 ? room - bm_words : room));
+    // How many may survive by the first digit alone: the sample takes 11 us, as long as mon_select takes over 4,000 more items.
+    const int limit = std::max(survivors, std::min(survivors + 4096, fit));
+    if (mode == 2) return launch_select<SRC_RANGE>(ctx, B, dc, gsel, std::max(most, 8192), bm_words, small, st);
     const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, std::max(4, 1024 / pivots)));
-    mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B);
+    mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B, limit);
     HC_HIP(ctx, hipGetLastError());
-    return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, max_nchunk * HC_SEL_CHUNK, bm_words, st);
+    return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, std::max(most, limit), bm_words, small, st);
 }
 
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st)
@@ -1201,7 +1696,7 @@ hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, in
     if (s == HC_OK && n_filt > 0) {
         s = run_chain(ctx, n_filt, filt, n_plain, 0, 1, st);
         // behind it, for the pivots whose check failed (decided on the device; normally none): all logits over
-        // again with their scores, then the selection over those
+        // again with their scores, then the plain chain's rest over those
         if (s == HC_OK) {
             hc_rep_logits_call rl[HC_MAX_GROUP];
             for (int i = 0; i < n_filt; ++i) {
@@ -1228,15 +1723,16 @@ hc_status hc_monitor_set_lds_limit()
 {
     // mon_select takes most of a compute unit's LDS, and beside the attention pass every kernel here reserves more
     // than half of it (hc_side_lds)
-    const void* fns[] = {(const void*)mon_compact, (const void*)mon_sparse_score<1>, (const void*)mon_sparse_score<2>,
-                         (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>, (const void*)mon_score_hist<1>,
-                         (const void*)mon_score_hist<2>, (const void*)mon_score_hist<4>, (const void*)mon_score_hist<8>,
+    const void* fns[] = {(const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
+                         (const void*)mon_compact, (const void*)mon_sparse_score<1>,
+                         (const void*)mon_sparse_score<2>, (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>,
+                         (const void*)mon_score_hist<1>, (const void*)mon_score_hist<2>, (const void*)mon_score_hist<4>, (const void*)mon_score_hist<8>,
                          (const void*)mon_select<512, SRC_LOGITS, 1>, (const void*)mon_select<512, SRC_LOGITS, 2>,
-                         (const void*)mon_select<512, SRC_LOGITS, 4>, (const void*)mon_select<512, SRC_LOGITS, 8>,
-                         (const void*)mon_select<512, SRC_SCORES, 1>, (const void*)mon_select<512, SRC_SURVIVORS, 1>,
+                         (const void*)mon_select<512, SRC_LOGITS, 4>,
+                         (const void*)mon_select<512, SRC_SCORES, 1>, (const void*)mon_select<512, SRC_SURVIVORS, 1>, (const void*)mon_select<512, SRC_RANGE, 1>,
                          (const void*)mon_select<1024, SRC_LOGITS, 1>, (const void*)mon_select<1024, SRC_LOGITS, 2>,
                          (const void*)mon_select<1024, SRC_LOGITS, 4>, (const void*)mon_select<1024, SRC_LOGITS, 8>,
-                         (const void*)mon_select<1024, SRC_SCORES, 1>, (const void*)mon_select<1024, SRC_SURVIVORS, 1>};
+                         (const void*)mon_select<1024, SRC_SCORES, 1>, (const void*)mon_select<1024, SRC_SURVIVORS, 1>, (const void*)mon_select<1024, SRC_RANGE, 1>};
     for (const void* fn : fns)
         if (hc_allow_lds(fn) != hipSuccess) return HC_EHIP;
     return HC_OK;
