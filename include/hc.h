@@ -110,6 +110,9 @@ typedef struct {
 } hc_head_desc;
 
 /* ---- life cycle (these may allocate and synchronise; not for capture) -------------------- */
+/* Device memory that hc_create takes: the monitor's workspaces, for 4.5 B Hkv pivots (a copy per layer of a group) about 140 KB
+ * and max_ctx / 4 bytes each (94 MB at 16 sequences of 131,072 with 8 KV heads, 6 MB at one of 229,376), and the refill's tables,
+ * 64 B Hkv max_k bytes. */
 hc_status hc_create(const hc_config* cfg, hc_ctx** out);
 hc_status hc_destroy(hc_ctx* ctx);
 const char* hc_strerror(hc_status st);

@@ -107,8 +107,9 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     // up to all of them
     c->max_chunks = (cfg->max_ctx + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
     c->sv_cap = std::min(cfg->max_ctx, HC_MAX_SURVIVORS);
-    c->area_words = std::max(2 * (size_t)cfg->max_ctx + cfg->max_ctx / 2, HC_MAX_SURVIVORS + 2 * HC_MAX_K_PER_REP * (size_t)HC_RADIX_BINS) + 64 * (size_t)c->max_chunks;
-    c->area_words &= ~(size_t)3;
+    // (more survivors than that are never asked for: see SELECT_SURVIVORS in hc_monitor.hip)
+    c->area_words = (std::max((size_t)c->sv_cap + HC_SEL_CHUNK / 32 * (size_t)c->max_chunks,
+                              2 * HC_MAX_K_PER_REP * (size_t)HC_RADIX_BINS + HC_MAX_K_PER_REP * 4 + (2 * HC_MAX_K_PER_REP + 1) * (size_t)c->max_chunks) + 3) & ~(size_t)3;
     const size_t rep_w = HC_RADIX_BINS + cfg->max_ctx / 32 + c->area_words;
     size_t ws_w = 0;
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
