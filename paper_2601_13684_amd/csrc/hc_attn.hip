@@ -300,7 +300,7 @@ __device__ __forceinline__ int write_kept(const float* src, int first, int n, fl
     constexpr int CAP = REP_STASH_FLOATS / G, Q = CAP / 4, ROUNDS = Q / 64;
     static_assert(Q % 64 == 0, "a wave's quarter of a chunk is whole rounds of 64 positions");
     static_assert(ROUNDS <= 32, "a lane remembers its decisions of a chunk in one word");
-    constexpr int UNR = ROUNDS < 4 ? ROUNDS : 4;
+    constexpr int UNR = G >= 8 ? 1 : ROUNDS < 4 ? ROUNDS : 4;      // (groups of eight: registers for the kernel beside this one)
     int mine = 0;
     uint32_t kept_bits = 0;              // bit rd: this lane's row of round rd is kept
     // (unrolled: the rounds' LDS reads and exponentials overlap; rows past the chunk's end read staged data of an
@@ -676,6 +676,7 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
     __shared__ __attribute__((aligned(16))) float sm_stash[REP_STASH_FLOATS];
     __shared__ __attribute__((aligned(16))) char sm_v[4][V8_WAVE];      // a wave's V tile; at the end of a segment its sums [G8][128]
     __shared__ int sm_kept[4];
+    __shared__ FilterCtx<G8> fc;                     // (in registers all through the loop it leaves too few for a kernel beside this one)
     static_assert(V8_WAVE >= G8 * HC_D * 4, "a wave's sums fit in its V tile");
     constexpr int CAP = REP_STASH_FLOATS / G8;       // positions per chunk of staged logits
     constexpr int CHUNK_TILES = CAP / T8_ROWS;
@@ -705,22 +706,18 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
         float* rep_base = nullptr;
         int32_t* kept_pos = nullptr;
         int32_t* kept_count = nullptr;
-        FilterCtx<G8> fc;
-        fc.cutsum = 0.f;
-        fc.lo = fc.hi = 0;
-#pragma unroll
-        for (int i = 0; i < G8; ++i) fc.ref[i] = 0.f;
         if (rep_logits && seg.rep_slot >= 0) {
             rep_base = rep_logits + (size_t)seg.rep_slot * G8 * max_ctx;
             if (FILT) {
                 kept_pos = fa.surv_pos + (size_t)seg.rep_slot * max_ctx;
                 kept_count = fa.seg_cnt + seg.slot;
-                const RepFilter f = fa.filt[seg.rep_slot];
-                fc.cutsum = f.cutsum;
-#pragma unroll
-                for (int i = 0; i < G8; ++i) fc.ref[i] = f.ref[i];
-                fc.lo = fa.reps[seg.rep_slot].lo;
-                fc.hi = fa.reps[seg.rep_slot].hi;
+                // (read behind a barrier, and the segment before is done with it)
+                if (tid < G8) fc.ref[tid] = fa.filt[seg.rep_slot].ref[tid];
+                if (tid == 0) {
+                    fc.cutsum = fa.filt[seg.rep_slot].cutsum;
+                    fc.lo = fa.reps[seg.rep_slot].lo;
+                    fc.hi = fa.reps[seg.rep_slot].hi;
+                }
                 if (seg.row_begin == 0 && tid < G8 * 16)      // the pivot's queries, kept for the monitor
                     reinterpret_cast<uint4*>(fa.q_keep + (size_t)seg.rep_slot * G8 * HC_D)[tid] =
                         reinterpret_cast<const uint4*>(q + (size_t)seg.bh * G8 * HC_D)[tid];

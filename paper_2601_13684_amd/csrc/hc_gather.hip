@@ -93,7 +93,7 @@ __device__ __forceinline__ void block_exscan2(uint32_t a, uint32_t b, uint32_t* 
 // them is compacted with ballots.  Bound by latency (a few tens of KB in all).  A list of 7,872 takes 11 us; the form
 // below, a binary search of the list for every slot, took 43.
 template <int NT>
-__global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void gather_plan_bitmap_kernel(GatherBatch B, int max_k)
+__global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int max_k)
 {
     constexpr int NW = NT / 64, U = 8;
     extern __shared__ __attribute__((aligned(16))) uint32_t sm_words[];

@@ -31,9 +31,12 @@
 // 131K 33 instead of 81 us, the decode step of one 4K layer 29 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
-// two attention workgroups, whose registers leave 80 per lane of a SIMD: 256 threads of at most 64 registers, or
-// (mon_select) 512 threads of at most 40.  No local arrays (a kernel that needs scratch memory costs tens of us to
-// launch), no device-wide fences.
+// two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
+// registers, or 512 threads of at most 40 (mon_select's small form; no bound on waves per SIMD asks for so few, a
+// test of the built kernels holds them to it).  In groups of eight heads the attention workgroups leave too little LDS for
+// mon_select's keys: its large form runs there, on a compute unit of its own (measured with four layers of 229,376 and lists
+// of 3,840: 266 us a step, 282 with the small form for as many as fit).  No local arrays (a kernel that needs scratch memory
+// costs tens of us to launch), no device-wide fences.
 #include <algorithm>
 #include <cmath>
 
@@ -564,7 +567,7 @@ __device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n,
 }
 
 template <int NT, int SRC, int G>
-__global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
+__global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
 {
     constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -877,7 +880,6 @@ __global__ __launch_bounds__(NT, NT == 512 ? 12 : 4) void mon_select(MonBatch B,
                     }
                 };
                 if (m <= 64) {
-#pragma unroll 4
                     for (int i = 0; i < m; ++i) {
                         const uint32_t o = lane_get(a, i);
                         gt_a += o > a;
