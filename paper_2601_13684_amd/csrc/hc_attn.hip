@@ -1221,7 +1221,9 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
     if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "attention batch of %d layers", n);
     // Every layer of the batch leaves its partial results in a copy of the workspace of its own, as far as there are
     // copies.  Layers that share an output buffer (the last one's results stay, as if each were combined by itself) are
-    // not combined together.
+    // not combined together.  Where a launch fails, the layers before it are still combined.
+    for (int i = 0; i < n; ++i)
+        if ((size_t)calls[i].L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
     const size_t acc_floats = ctx->part_slots * ctx->G * HC_D, ml_floats = ctx->part_slots * ctx->G * 2;
     CombineBatch batch{};
     int m = 0, n_heads = 0;
@@ -1232,7 +1234,6 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
     };
     for (int i = 0; i < n; ++i) {
         const hc_attn_call& x = calls[i];
-        if ((size_t)x.L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
         n_heads = x.L->n_heads;                       // (of the context: the same for every layer)
         const size_t lse_floats = (size_t)n_heads * ctx->G, out_floats = lse_floats * HC_D;
         bool shared = false;
@@ -1245,7 +1246,10 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
         float* acc = m == 0 ? ctx->part_acc : ctx->part_more + (m - 1) * acc_floats;
         float* ml = m == 0 ? ctx->part_ml : ctx->part_more + (ctx->part_copies - 1) * acc_floats + (m - 1) * ml_floats;
         const hc_status s = split_any(ctx, x.L, x.arena, x.q, x.rep_logits, st, acc, ml);
-        if (s != HC_OK) return s;
+        if (s != HC_OK) {
+            (void)flush();
+            return s;
+        }
         batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse};
     }
     return flush();

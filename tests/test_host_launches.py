@@ -1,0 +1,83 @@
+"""The launches that the host side makes, and what it does when one fails, on a stand-in for the HIP runtime (fake_hip.cpp) in a
+process of its own.  No GPU needed."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake_hip") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-Wno-deprecated-declarations",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", so], check=True)
+    return so
+
+
+PROLOGUE = '''
+import ctypes as C, sys, types
+torch = types.ModuleType("torch")            # the binding only needs the name: its pointers are plain addresses here
+torch.Tensor = type("Tensor", (), {})
+torch.cuda = types.SimpleNamespace(Stream=type("Stream", (), {}), Event=type("Event", (), {}))
+sys.modules["torch"] = torch
+sys.path.insert(0, ROOT)
+fake = C.CDLL(FAKE, mode=C.RTLD_GLOBAL)
+fake.fake_log.restype = C.c_char_p
+from paper_2601_13684_amd import binding as hc
+L = hc.lib()
+def log():
+    return [l.split() for l in fake.fake_log().decode().splitlines()]
+def layer(ctx, N, r, n=4):
+    """One pivot and n - 1 satellites of r retrieved slots."""
+    descs = (hc.hc_head_desc * n)()
+    for h in range(n):
+        ln = N if h == 0 else 12 + r
+        descs[h] = hc.hc_head_desc(k_off=h * (1 << 26), v_off=h * (1 << 26) + (1 << 25), tier_off=h * (1 << 27), ctx=N, len=ln, role=0 if h == 0 else 1,
+                                   rep=-1 if h == 0 else 0, sink=0 if h == 0 else 5, recent=0 if h == 0 else 7, k_mon=0, cap=0)
+    out = C.c_void_p()
+    assert L.hc_layer_create(ctx, descs, C.byref(out)) == 0, L.hc_last_error(ctx)
+    return out.value
+def context(N, r, G=4, n=4):
+    cfg = hc.hc_config(B=1, Hq=G * n, Hkv=n, D=128, max_ctx=(N + 63) // 64 * 64, max_k=r, window=1, metric=0, tau_num=1, tau_den=2, agg=0, window_mode=0)
+    out = C.c_void_p()
+    assert L.hc_create(C.byref(cfg), C.byref(out)) == 0
+    return out.value
+def io_of(layers):
+    """Addresses that nothing reads: a launch is only written down."""
+    arr = (hc.hc_layer_io * len(layers))()
+    for i, l in enumerate(layers):
+        a = lambda k: (1 << 40) + (i << 34) + (k << 28)
+        arr[i] = hc.hc_layer_io(layer=l, kv_arena=a(0), host_tier=a(1), q=a(2), out=a(3), lse=a(4), rep_logits=a(5), scores=a(6), topk_idx=a(7), base_idx=a(8),
+                                ring=a(9), inter=a(10), flag=a(11), slot_pos=a(12))
+    return arr
+'''
+
+
+def run(fake, body):
+    code = f"ROOT, FAKE = {ROOT!r}, {fake!r}\n" + PROLOGUE + textwrap.dedent(body)
+    r = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
+    return r.stdout
+
+
+def test_a_failed_launch_leaves_the_layers_before_it_combined(fake):
+    """Four layers in one group, the third one's split pass fails: the first two are combined, in one launch, and nothing of the
+    group follows."""
+    run(fake, """
+        ctx = context(5000, 300)
+        layers = [layer(ctx, 5000, 300) for _ in range(4)]
+        fake.fake_reset(3)
+        assert L.hc_decode_step(ctx, io_of(layers), 4, 4, None, None) == hc.HC_EHIP
+        names = [(l[0], int(l[3])) for l in log()]
+        assert [n for n, z in names if "attn_split" in n] == [names[0][0]] * 2, names
+        assert len(names) == 3 and "attn_combine" in names[2][0] and names[2][1] == 2, names
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io_of(layers), 4, 4, None, None) == 0
+        names = [(l[0], int(l[3])) for l in log()]
+        assert sum("attn_split" in n for n, z in names) == 4 and [z for n, z in names if "attn_combine" in n] == [4], names
+    """)
