@@ -49,6 +49,9 @@ def test_plan_and_moved_rows(N, r):
             slots[0] = slots[-1]
             slots[r // 2] = -7
             gpu.slot_pos[1, :r] = torch.from_numpy(slots).to(DEV)
+            if r > 1:                                # the position held twice is listed: one slot fewer is free than positions are fresh
+                lst = np.sort(np.concatenate([slots[-1:], rng.choice(np.setdiff1d(cand, slots[-1:]), r - 1, replace=False)]))
+                assert np.isin(slots, lst, invert=True).sum() + 1 == np.setdiff1d(lst, slots).size
         elif share < 1.0:                            # this share of the list is new
             keep = rng.choice(slots, r - int(r * share), replace=False)
             lst = np.sort(np.concatenate([keep, rng.choice(np.setdiff1d(cand, slots), r - keep.size, replace=False)])).astype(np.int32) \
