@@ -632,7 +632,6 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
         for (int t = 0; t < r.nk; ++t) L->max_k_any = std::max(L->max_k_any, r.k[t]);
     }
     L->n_reps = (int)P.reps.size();
-    L->n_outs = (int)P.outs.size();
     L->n_sats = (int)P.sats.size();
     L->n_blocks = P.n_blocks;
     L->n_segs = L->n_partials = (int)P.segs.size();
@@ -1109,7 +1108,7 @@ extern "C" hc_status hc_prefill_init(hc_ctx* ctx, hc_layer* layer, const void* k
         hc_monitor_call call{L, nullptr, lse, scores, topk_idx, base_idx, ring, scratch, scratch + (size_t)ctx->cfg.B * ctx->cfg.Hkv, -2};
         call.reps = L->sel_reps;
         call.outs = L->sel_outs;
-        call.n_reps = call.n_outs = L->n_sel;
+        call.n_reps = L->n_sel;
         call.max_nchunk = L->sel_max_nchunk;
         call.max_nk = 1;
         s = hc_launch_monitor(ctx, 1, &call, 1, st);

@@ -136,7 +136,7 @@ struct hc_layer {
     hc_ctx* ctx;
     int n_heads;
     int n_blocks, n_partials, n_segs;
-    int n_reps, n_outs, n_sats;
+    int n_reps, n_sats;
     int max_r;                     // largest r among satellites
     int max_nchunk;
     int max_nk;                    // largest number of distinct set sizes of a pivot
@@ -249,7 +249,7 @@ struct hc_monitor_call {
     // prefill-time selection runs over its own list of heads instead of the layer's pivots
     const RepDev* reps = nullptr;
     const OutDev* outs = nullptr;
-    int n_reps = 0, n_outs = 0, max_nchunk = 0, max_nk = 0;
+    int n_reps = 0, max_nchunk = 0, max_nk = 0;
     const void* arena = nullptr;   // the layer's K/V arena, for a layer that filters its pivot logits (nullptr: the one
                                    // its last attention call was given)
 };

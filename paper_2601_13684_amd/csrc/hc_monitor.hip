@@ -1552,7 +1552,10 @@ constexpr int SELECT_DIRECT = 8192;
 // Survivors (as the sample would let through) up to which one workgroup per list beats the six launches of long lists, with
 // the sample in front of it where it is needed.  131,072 candidates, scores spread out / within 2 % / equal: a longest list of 8,192
 // (11,000 expected) 37 / 48 / 58 us against 47 / 49 / 62; of 10,000 (13,100) 41 / 50 / 63 against 47 / 49 / 62.
-constexpr int SELECT_SURVIVORS = 13000;
+// The prefill-time selection has one list per head and smoothed scores, so that it always needs the sample: at 131,072 positions
+// and lists of 7,872 its line is lower (a whole hc_prefill_init without the offload 239 us with survivors, 224 with the six
+// launches; at 32K, lists of 3,776, 129 and 141).
+constexpr int SELECT_SURVIVORS = 13000, SELECT_SURVIVORS_PREFILL = 8000;
 
 // The launches of one chain over a batch of layers.  mode 0: the plain chain (every pivot, all candidate positions).
 // mode 1: the chain over the rows a filtering split pass kept.  mode 2: the chain that stands by behind
@@ -1649,7 +1652,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     }
     int survivors, most;
     expected_survivors(max_k, candidates, &survivors, &most);
-    const bool long_lists = survivors > SELECT_SURVIVORS || most > ctx->sv_cap;
+    const bool long_lists = survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap;
     if (mode != 2 || long_lists) {
         // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K took
         // 40 us per call with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.  (The launches
@@ -1665,7 +1668,9 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         HC_HIP(ctx, hipGetLastError());
         if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
     }
-    const bool small = select_small(ctx, most);
+    // The small form where all that may survive fits, and what is expected fits with the baseline bitmap (without the bitmap in LDS
+    // the lists are written a round at a time: 229,376 candidates, no filter, 53.2 us per layer-step with it, 51.9 with the large one).
+    const bool small = select_small(ctx, std::max(most, survivors + (bm_words + 263) / 264 * 256));
     const int room = (small ? select_room<512>(ctx) : select_room<1024>(ctx)) / 4;
     const int fit = std::min(ctx->sv_cap, SEL_KEYS(bm_words <= room / 2 ? room - bm_words : room));
     // How many may survive by the first digit alone: the sample takes 11 us, as long as mon_select takes over 4,000 more items.
