@@ -1243,8 +1243,8 @@ extern "C" hc_status hc_rescore_window(hc_ctx* ctx, hc_layer* layer, const void*
 
 // One decode step over a stack of layers, launched from native code so that the host keeps ahead of the
 // GPU.  Layers are taken in groups: the attention of a group's layers on the main stream; then, on the
-// side stream, ONE batched monitor and ONE batched gather for the whole group (four to six launches per group
-// instead of per layer: these kernels are latency-bound, so a batch costs little more GPU time than
+// side stream, ONE batched monitor and ONE batched gather for the whole group (five or six launches per group, more
+// for long lists, instead of per layer: these kernels are latency-bound, so a batch costs little more GPU time than
 // one layer, and the host stays ahead).  They overlap the attention of the following groups.  One event
 // pair per group keeps the host cost of the cross-stream ordering small.  The attention of a layer
 // waits for that layer's side work of the previous step (a refill decided at step t is used from step

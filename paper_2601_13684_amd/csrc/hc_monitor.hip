@@ -22,13 +22,13 @@
 //                            front of it where more rows are kept than it has room for): two launches, and behind them
 //                            two that normally find nothing to do, for a pivot whose check failed: rep_logits_kernel
 //                            (hc_attn.hip; all logits again, with their scores) and mon_select, which cuts the whole range
-//                            down by itself (a launch more for that would cost every step 3 us)
-// (mon_prep clears the histograms, counters and bitmaps, only after a call that failed midway; normally mon_select leaves
+//                            down by itself (a launch more for that would cost every step 3 us), or the six of long lists
+// (mon_prep clears the histograms and bitmaps, only after a call that failed midway; normally mon_select leaves
 // them clear.)
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
 // histograms, counts, ordered write, decision): one 32K layer 27.4 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 33 instead of 81 us, the decode step of one 4K layer 29 instead of 49 us.
+// 131K 33-36 instead of 81 us, the decode step of one 4K layer 29 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
@@ -1654,9 +1654,9 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     expected_survivors(max_k, candidates, &survivors, &most);
     const bool long_lists = survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap;
     if (mode != 2 || long_lists) {
-        // Chunks per workgroup, at most 8: about 2048 workgroups per launch (eight sequences of 9K to 131K took
-        // 40 us per call with one chunk each, 41, 45, 54 with two, four, eight), beside the attention pass 512.  (The launches
-        // that stand by: few, long workgroups.)
+        // Chunks per workgroup, at most 8: about 2048 workgroups per launch (a call over eight sequences of 9K to 131K takes
+        // 36 us with one chunk each, 37, 41, 50 with two, four, eight; one of 32K 28, 29, 32, 39), beside the attention pass
+        // 512.  (The launches that stand by: few, long workgroups.)
         const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
         switch (ctx->G) {

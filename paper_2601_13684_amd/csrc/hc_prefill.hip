@@ -8,7 +8,7 @@
 // Steps, all on the caller's stream:
 //   logits + lse of the last token against every selecting head's full K   (the contraction of hc_rescore.hip)
 //   prefill_score_kernel   group mean of the softmax weights, then the pooling window           (below)
-//   selection              the monitor's radix select + ordered compaction, lists only          (hc_monitor.hip)
+//   selection              the monitor's, lists only                                            (hc_monitor.hip)
 //   prefill_place_kernel   rows of the resident positions -> the heads' blocks in the arena; baseline sets,
 //                          slot maps and rings                                                  (below)
 //   prefill_offload_kernel satellites' rows -> the pinned host tier, K row then V row per position (below)
