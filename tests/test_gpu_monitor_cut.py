@@ -89,6 +89,38 @@ def test_short_and_long_lists_in_turn():
     ctx.close()
 
 
+@pytest.mark.parametrize("rs", [(3000, 77), (11600, 77)])
+def test_captured_call_replays_like_eager(rs):
+    """One captured call, replayed over scores of every kind with eager work and an eager call between the replays."""
+    N, rng = 40003, np.random.default_rng(8)
+    T.say("monitor cut captured", rs)
+    spec = one_pivot(N, rs)
+    lo, hi = spec.cand_range(0, 0)
+    base = {(0, 0): torch.from_numpy(np.sort(rng.choice(np.arange(lo, hi), spec.k_mon(0, 0), replace=False)).astype(np.int32))}
+    ctx, gpu, base_all = T.monitor_case(spec, {(0, 0): draw("spread", N, rng)}, base)
+    cap = torch.cuda.Stream()
+    cap.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(cap):
+        with torch.cuda.graph(graph, stream=cap):
+            gpu.monitor(scores_given=True)
+    torch.cuda.synchronize()
+    junk = torch.zeros((1 << 20,), device=DEV)
+    for kind in ("spread", "flat", "equal", "tied", "spread"):
+        s = draw(kind, N, rng)
+        for call in (graph.replay, graph.replay, lambda: gpu.monitor(scores_given=True)):
+            gpu.scores[0, :N] = torch.from_numpy(s).to(DEV)
+            gpu.base_idx[0, :len(base_all[(0, 0)])] = base_all[(0, 0)].to(DEV)
+            gpu.ring.zero_()
+            junk.add_(1.0)
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
+    gpu.close()
+    ctx.close()
+
+
 def stack_spec(N, budgets, G):
     heads = [I.HeadSpec(I.ROLE_FULL), I.HeadSpec(I.ROLE_FULL)] + [I.HeadSpec(I.ROLE_SATELLITE, rep=j % 2, sink=5, recent=7, budget=12 + r) for j, r in enumerate(budgets)]
     return I.LayerSpec(B=1, Hq=G * len(heads), Hkv=len(heads), D=128, ctx=[N], heads=[heads])
