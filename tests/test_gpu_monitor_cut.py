@@ -89,6 +89,28 @@ def test_short_and_long_lists_in_turn():
     ctx.close()
 
 
+@pytest.mark.parametrize("N,rs", [(20011, (3000, 77)), (40003, (3000, 77)), (229376, (7872, 704))])
+def test_a_sample_that_misleads(N, rs):
+    """The sampled candidates (one of each of 4,096 equal pieces, at a scattered place) are the best ones of a range of near-equal
+    scores: the estimated cut then lets fewer through than the longest list needs, and the whole range is selected from."""
+    T.say("monitor cut misled", N, rs)
+    spec = one_pivot(N, rs)
+    lo, hi = spec.cand_range(0, 0)
+    n, i = hi - lo, np.arange(4096, dtype=np.uint64)
+    a, b = i * np.uint64(n) // np.uint64(4096), (i + np.uint64(1)) * np.uint64(n) // np.uint64(4096)
+    sampled = (a + (((i * np.uint64(2654435761)) & np.uint64(0xffffffff)) * (b - a) >> np.uint64(32))).astype(np.int64)
+    rng = np.random.default_rng(N)
+    s = (1.0 + 0.01 * rng.random(N)).astype(np.float32)
+    s[lo + sampled] += np.float32(0.02)
+    t = rs[0] * 4096 / n
+    assert t + 5 * np.sqrt(t) + 8 < rs[0]
+    base = {(0, 0): torch.from_numpy(np.sort(rng.choice(np.arange(lo, hi), spec.k_mon(0, 0), replace=False)).astype(np.int32))}
+    ctx, gpu, base_all = T.monitor_case(spec, {(0, 0): s}, base)
+    T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
+    gpu.close()
+    ctx.close()
+
+
 @pytest.mark.parametrize("rs", [(3000, 77), (11600, 77)])
 def test_captured_call_replays_like_eager(rs):
     """One captured call, replayed over scores of every kind with eager work and an eager call between the replays."""

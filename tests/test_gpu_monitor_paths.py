@@ -20,8 +20,8 @@ def one_pivot(N, rs, sink=5, recent=7):
     return I.LayerSpec(B=1, Hq=4 * len(heads), Hkv=len(heads), D=128, ctx=[N], heads=[heads])
 
 
-# candidates: one workgroup up to 8192, three launches above; 30,000 list entries of 40,000 candidates, a range of ties
-# and one of two values overflow the keys a workgroup holds; 700,000 candidates need the baseline bitmap in memory
+# candidates: one workgroup up to 8192, three launches above; 30,000 list entries of 40,000 candidates take six; a range of
+# ties and one of two values need the sampled cut; 700,000 candidates need the baseline bitmap in memory
 @pytest.mark.parametrize("N,rs,kind", [(8192 + 12, (700, 3), "normal"), (8193 + 12, (700, 3), "normal"), (8193 + 12, (8193, 1), "ties"),
                                        (40000, (30000, 77), "normal"), (90001, (4097, 256), "all_equal"), (90001, (300, 299), "two_values"),
                                        (700000, (2048,), "normal")])
@@ -49,7 +49,7 @@ def test_given_scores_across_the_choices(N, rs, kind):
 def test_beside_the_attention_pass_like_alone(N, margin, flat):
     """The same steps through hc_decode_step with a side stream (the monitor's small workgroups) and through the three
     calls on one stream (its large ones): the tables must be equal bit for bit.  flat: all keys equal, every score a
-    tie, more items than a workgroup holds."""
+    tie."""
     T.say("monitor beside attention", N, margin, "flat" if flat else "")
     tables = []
     for beside in (True, False):
