@@ -15,7 +15,7 @@ constexpr int HC_UNIT_ROWS = 32;     // split-K granule: 4 waves x 8 rows
 constexpr int HC_SEL_CHUNK = 1024;   // candidates a workgroup or wave of the monitor's first passes takes at a time
 constexpr int HC_RADIX_BINS = 2048;  // bins of the monitor's histograms: 11 bits of a key, or of its distance from the smallest
 constexpr int HC_SAMPLES = 4096;     // items of a long candidate range from which the monitor estimates its threshold
-constexpr int HC_MAX_SURVIVORS = 20480;   // survivors that a pivot's workspace holds
+constexpr int HC_MAX_SURVIVORS = 24576;   // survivors that a pivot's workspace holds
 
 // One KV head as the kernels see it.
 struct HeadDev {

@@ -1673,8 +1673,9 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     const bool small = select_small(ctx, std::max(most, survivors + (bm_words + 263) / 264 * 256));
     const int room = (small ? select_room<512>(ctx) : select_room<1024>(ctx)) / 4;
     const int fit = std::min(ctx->sv_cap, SEL_KEYS(bm_words <= room / 2 ? room - bm_words : room));
-    // How many may survive by the first digit alone: the sample takes 11 us, as long as mon_select takes over 4,000 more items.
-    const int limit = std::max(survivors, std::min(survivors + 4096, fit));
+    // How many may survive by the first digit alone: the sample takes 11 us, mon_select as long for 10,000 more items (131,072
+    // candidates, a longest list of 8,192: 34, 35, 35, 39, 41, 46 us with 0, 2,000, ... 10,000 more, 46 with the sample).
+    const int limit = std::max(survivors, std::min(survivors + 10000, fit));
     if (mode == 2) return launch_select<SRC_RANGE>(ctx, B, dc, gsel, std::max(most, 8192), bm_words, small, st);
     const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, std::max(4, 1024 / pivots)));
     mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B, limit);
