@@ -190,7 +190,7 @@ def test_beside_the_attention_pass_like_alone(N, budgets, G, margin, scale):
 
 def test_time_does_not_depend_on_the_distribution():
     """229,376 candidates, lists of 7,872 and shorter: near-equal and equal scores take at most three times what spread-out ones
-    take (measured: 1.5 and 1.7 times; 10 and 12 times when the range was not cut down)."""
+    take (measured: 1.5 and 1.9 times; 10 and 12 times when the range was not cut down)."""
     N = 229376
     spec = one_pivot(N, (7872, 3776, 1728))
     us = {}
