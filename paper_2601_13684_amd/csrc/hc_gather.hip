@@ -10,8 +10,10 @@
 // (slot_pos: which position every retrieved slot holds) only the difference moves: positions of the new
 // list that are not resident go into the slots of resident positions that left the list.  The resident
 // set afterwards is exactly the list; the order of the slots is not ascending any more, which attention
-// does not care about.  gather_plan_kernel finds the difference, gather_kernel moves the rows.
+// does not care about.  gather_plan_bitmap_kernel finds the difference and moves its rows (for contexts whose bitmaps do
+// not fit in LDS gather_plan_kernel finds it and gather_kernel moves the rows).
 #include <algorithm>
+#include <type_traits>
 
 #include "hc_internal.h"
 
@@ -19,7 +21,7 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GATHER_PASSES = 4;     // host reads a lane has in flight; a workgroup of T threads has T / 32 * 4 positions in flight
+constexpr int GATHER_PASSES = 4;     // host reads a lane of gather_kernel has in flight
 constexpr int PLAN_THREADS = 256;
 
 // One layer of a batched call (blockIdx.z picks the layer).
@@ -34,11 +36,18 @@ struct GatherItem {
     int32_t* pair_slot;     // [B*Hkv][max_k] workspace: the slots to overwrite ...
     int32_t* pair_pos;      // [B*Hkv][max_k]            ... and the positions that go there
     int32_t* npairs;        // [B*Hkv]
+    int32_t* done;          // [B*Hkv] workgroups that are through with a satellite's slot map; zero between launches
     int n_sats, pad;
 };
 struct GatherBatch {
     GatherItem it[HC_MAX_GROUP];
 };
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }       // (kept in a scalar register)
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
+}
 
 // Index of v in the ascending list a[0, n), or -1.
 __device__ __forceinline__ int find_sorted(const int32_t* a, int n, int32_t v)
@@ -85,112 +94,247 @@ __device__ __forceinline__ void block_exscan2(uint32_t a, uint32_t b, uint32_t* 
     ex_b = base_b + ib - b;
 }
 
-// One workgroup per satellite: which slots hold positions that left the list (free), which positions of
-// the list are not resident (fresh); the k-th free slot takes the k-th fresh position.
-//
-// The usual form: two bitmaps over the context in LDS, of the listed positions and of those found in a slot, so that
-// every slot and every list entry costs one LDS access; choices are kept as one mask per 64 entries, and a wave's run of
-// them is compacted with ballots.  Bound by latency (a few tens of KB in all).  A list of 7,872 takes 11 us; the form
-// below, a binary search of the list for every slot, took 43.
-template <int NT>
-__global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int max_k)
+// The rows to move, over all satellites of all layers of a batch, are numbered consecutively (satellite after satellite) and
+// dealt to the workgroups in equal contiguous runs, so that the time does not depend on how unequal the satellites' lists are
+// and a launch has as many workgroups as the host link needs, no more.  Every workgroup makes the prefix sums of the
+// satellites' row counts itself (a few hundred numbers): entry e is satellite e % max_sats of item e / max_sats, count(item,
+// satellite) its rows.  sm_start[0 .. n_ent] and the total, the same in every thread.
+constexpr int MAX_GATHER_SATS = 1024;     // satellites of a batch (layers x satellites per layer)
+// (Every wave does it for itself and wave 0 writes it down: a launch that finds nothing to move, the usual case in a decode
+// step, ends without a barrier.)
+template <class Count>
+__device__ __forceinline__ int row_starts(const GatherBatch& B, int n_ent, int max_sats, int* sm_start, const Count& count)
 {
-    constexpr int NW = NT / 64, U = 8;
-    extern __shared__ __attribute__((aligned(16))) uint32_t sm_words[];
+    const int lane = threadIdx.x & 63;
+    int carry = 0;
+    auto chunks = [&](auto per, int base) {          // `per` times 64 entries, whose reads are in flight together
+        constexpr int U = decltype(per)::value;
+        const GatherItem* it[U];
+        SatDev sd[U];
+        int c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = base + u * 64 + lane, sidx = e % max_sats;
+            it[u] = &B.it[min(e / max_sats, HC_MAX_GROUP - 1)];
+            sd[u].rep_bh = -1;
+            if (e < n_ent && sidx < it[u]->n_sats) sd[u] = it[u]->sats[sidx];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c[u] = 0;
+            if (sd[u].rep_bh >= 0) c[u] = it[u]->flag[sd[u].rep_bh];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = base + u * 64 + lane;
+            if (c[u] != 0) c[u] = count(*it[u], sd[u]);
+            int inc = c[u];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(inc, o);
+                if (lane >= o) inc += t;
+            }
+            if (threadIdx.x < 64 && e < n_ent) sm_start[e] = carry + inc - c[u];
+            carry += __builtin_amdgcn_readlane(inc, 63);
+        }
+    };
+    if (n_ent <= 64) {
+        chunks(std::integral_constant<int, 1>{}, 0);
+    } else {
+#pragma unroll 1
+        for (int base = 0; base < n_ent; base += 256) chunks(std::integral_constant<int, 4>{}, base);
+    }
+    if (carry == 0) return 0;
+    if (threadIdx.x == 0) sm_start[n_ent] = carry;
+    __syncthreads();
+    return carry;
+}
+constexpr int start_words(int n_ent) { return (n_ent + 4) & ~3; }      // LDS for them, a multiple of 16 bytes
+__device__ __forceinline__ int rows_per_workgroup(int total) { return ((total + (int)gridDim.x - 1) / (int)gridDim.x + 7) & ~7; }
+
+// Moves pairs [begin, end) of a satellite: the row of position pos[k] from the tier into slot[k].  32 lanes move one position
+// (lanes 0-15 its K row, 16-31 its V row, 16 bytes each), the first `movers` threads take part, PASSES positions each in flight:
+// every host read of a pass is issued before the first store.
+template <int PASSES>
+__device__ __forceinline__ void move_rows(const GatherItem& it, const HeadDev& hd, int first_slot, int r, const int32_t* slot, const int32_t* pos, int begin,
+                                          int end, int movers)
+{
+    int tid = threadIdx.x;
+    asm("" : "+v"(tid));                 // (what follows from it is not kept in registers across the caller's loop)
+    const int nsub = movers >> 5, sub = tid >> 5, is_v = (tid >> 4) & 1, chunk = tid & 15;
+    if (tid >= movers) return;
+    const u32x4* tier = reinterpret_cast<const u32x4*>(it.tier + uniform64(hd.tier_off));
+    const long long to = (is_v ? uniform64(hd.v_off) : uniform64(hd.k_off)) / 8 + (long long)first_slot * 16 + chunk;
+    u32x4* arena = reinterpret_cast<u32x4*>(it.arena);
+    const int ctx = uniform(hd.ctx), piece = is_v * 16 + chunk;
+#pragma unroll 1
+    for (int k0 = begin + sub; k0 < end; k0 += nsub * PASSES) {
+        u32x4 buf[PASSES];
+        bool ok[PASSES];
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int j = pos[min(k0 + p * nsub, end - 1)];
+            ok[p] = k0 + p * nsub < end && j >= 0 && j < ctx;        // a corrupt entry must not leave the tier block ...
+            if (ok[p]) buf[p] = __builtin_nontemporal_load(tier + (size_t)j * 32 + piece);
+        }
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int s = slot[min(k0 + p * nsub, end - 1)];
+            if (ok[p] && s >= 0 && s < r) arena[to + (long long)s * 16] = buf[p];       // ... or the head's slots
+        }
+    }
+}
+
+// Which slots of a satellite hold positions that left the list (free), which positions of the list are not resident (fresh);
+// the k-th free slot takes the k-th fresh position.  And the move of those rows, in the same launch: the list rows of
+// all satellites that are to be refilled are dealt to the workgroups, a workgroup plans every satellite that its run touches
+// and moves the share of that satellite's pairs that its run is of the list.  Several workgroups then make the same plan,
+// which costs no time (they would wait for it otherwise); the last of them to be through with the slot map brings it up to date.
+//
+// Two bitmaps over the context in LDS, of the listed positions and of those held by a slot, so that every slot and every
+// list entry costs one LDS access; choices are kept as one mask per 64 entries, and a wave's run of them is compacted with
+// ballots.  The plan is a chain of latencies: list and slot map are asked for together, at the start.
+// Six lists of 704 to 7,872 entries, a quarter new, 2.6 MB over the link (45 us at its rate): 57 us, 66 in two launches (a plan
+// by a workgroup per satellite, 11 us, then the rows, 54).  A launch that finds nothing to do takes 4 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int n_items, int max_sats, int max_k, int movers)
+{
+    constexpr int NW = NT / 64, U = NT == 512 ? 4 : 8;
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t sm_cnt[2][NW];
-    const GatherItem& it = B.it[blockIdx.z];
-    if ((int)blockIdx.y >= it.n_sats) return;
-    const SatDev sd = it.sats[blockIdx.y];
-    if (it.flag[sd.rep_bh] == 0) return;
-    const int r = sd.r, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-    const uint32_t ctx = (uint32_t)it.heads[sd.bh].ctx;
-    const int words = (int)(ctx + 31) / 32, rounds = (r + 63) / 64;
-    uint32_t* listed = sm_words;
-    uint32_t* found = sm_words + words;
-    uint64_t* free_mask = reinterpret_cast<uint64_t*>(sm_words + ((2 * words + 3) & ~3));       // [rounds]: slots whose position left the list
-    uint64_t* fresh_mask = free_mask + rounds;                                                   // [rounds]: list entries no slot holds
-    const int32_t* list = it.topk_idx + (size_t)sd.bh * max_k;
-    int32_t* sp = it.slot_pos + (size_t)sd.bh * max_k;
-    int32_t* pslot = it.pair_slot + (size_t)sd.bh * max_k;
-    int32_t* ppos = it.pair_pos + (size_t)sd.bh * max_k;
-    for (int i = tid; i < 2 * words; i += NT) sm_words[i] = 0u;
-    __syncthreads();
-    for (int i0 = tid; i0 < r; i0 += U * NT) {
-        uint32_t p[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) p[u] = i0 + u * NT < r ? (uint32_t)list[i0 + u * NT] : ctx;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (p[u] < ctx) atomicOr(&listed[p[u] >> 5], 1u << (p[u] & 31));
+    __shared__ int sm_last;
+    const int n_ent = n_items * max_sats;
+    int* sm_start = reinterpret_cast<int*>(dyn);
+    uint32_t* sm_words = dyn + start_words(n_ent);
+    const int total = row_starts(B, n_ent, max_sats, sm_start, [](const GatherItem&, const SatDev& sd) { return sd.r; });
+    const int share = rows_per_workgroup(total), g_begin = blockIdx.x * share, g_end = min(total, g_begin + share);
+    if (g_begin >= g_end) return;
+    const int tid = threadIdx.x, wv = uniform(tid >> 6), lane = tid & 63;
+    int e = 0;
+    for (int hi = n_ent; hi - e > 1;) {              // the entry whose run holds row g_begin
+        const int mid = (e + hi) >> 1;
+        if (sm_start[mid] <= g_begin) e = mid;
+        else hi = mid;
     }
-    __syncthreads();
-    // a wave takes a run of rounds of 64
-    const int per = (rounds + NW - 1) / NW, r0 = min(rounds, wv * per), r1 = min(rounds, r0 + per);
-    uint32_t n_free = 0, n_fresh = 0;
-    for (int q0 = r0; q0 < r1; q0 += U) {
-        uint32_t p[U];
+    for (e = uniform(e); e < n_ent; ++e) {      // (the same for the whole workgroup)
+        const int start = uniform(sm_start[e]), r = uniform(sm_start[e + 1]) - start;
+        if (start >= g_end) break;
+        if (r == 0) continue;
+        const GatherItem& it = B.it[e / max_sats];
+        const int bh = uniform(it.sats[e % max_sats].bh), first_slot = uniform(it.sats[e % max_sats].first_slot);
+        const HeadDev& hd = it.heads[bh];
+        const uint32_t ctx = (uint32_t)uniform(hd.ctx);
+        const int words = (int)(ctx + 31) / 32, rounds = (r + 63) / 64;
+        uint32_t* listed = sm_words;
+        uint32_t* held = sm_words + words;
+        uint64_t* free_mask = reinterpret_cast<uint64_t*>(sm_words + ((2 * words + 3) & ~3));       // [rounds]: slots whose position left the list
+        uint64_t* fresh_mask = free_mask + rounds;                                                   // [rounds]: list entries no slot holds
+        const int32_t* list = it.topk_idx + (size_t)bh * max_k;
+        int32_t* sp = it.slot_pos + (size_t)bh * max_k;
+        int32_t* pslot = it.pair_slot + (size_t)bh * max_k;
+        int32_t* ppos = it.pair_pos + (size_t)bh * max_k;
+        // a wave takes a run of rounds of 64, U of them at a time; the first U stay in registers
+        const int per = (rounds + NW - 1) / NW, r0 = min(rounds, wv * per), r1 = min(rounds, r0 + per);
+        auto load = [&](uint32_t (&p)[U], const int32_t* src, int q0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) p[u] = q0 + u < r1 && (q0 + u) * 64 + lane < r ? (uint32_t)sp[(q0 + u) * 64 + lane] : ctx;
+            for (int u = 0; u < U; ++u) p[u] = q0 + u < r1 && (q0 + u) * 64 + lane < r ? (uint32_t)src[(q0 + u) * 64 + lane] : ctx;
+        };
+        uint32_t want[U], have[U];
+        load(want, list, r0);
+        load(have, sp, r0);
+#pragma unroll 1
+        for (int i = tid; i < 2 * words; i += NT) sm_words[i] = 0u;
+        __syncthreads();
+#pragma unroll 1
+        for (int q0 = r0; q0 < r1; q0 += U) {
+            if (q0 != r0) {
+                load(want, list, q0);
+                load(have, sp, q0);
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (q0 + u >= r1) break;
-            const bool in = (q0 + u) * 64 + lane < r;
-            const bool keep = p[u] < ctx && ((listed[min(p[u], ctx - 1) >> 5] >> (p[u] & 31)) & 1u);
-            if (keep) atomicOr(&found[p[u] >> 5], 1u << (p[u] & 31));      // (a position held twice, a corrupt map, is caught by the count check below)
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in && !keep);
-            if (lane == 0) free_mask[q0 + u] = m;
-            n_free += (uint32_t)__builtin_popcountll(m);
+            for (int u = 0; u < U; ++u) {
+                if (want[u] < ctx) atomicOr(&listed[want[u] >> 5], 1u << (want[u] & 31));
+                if (have[u] < ctx) atomicOr(&held[have[u] >> 5], 1u << (have[u] & 31));
+            }
         }
-    }
-    __syncthreads();
-    for (int q0 = r0; q0 < r1; q0 += U) {
-        uint32_t p[U];
+        __syncthreads();
+        uint32_t n_free = 0, n_fresh = 0;
+#pragma unroll 1
+        for (int q0 = r0; q0 < r1; q0 += U) {
+            if (per > U) {                           // (registers hold the last rounds)
+                load(want, list, q0);
+                load(have, sp, q0);
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) p[u] = q0 + u < r1 && (q0 + u) * 64 + lane < r ? (uint32_t)list[(q0 + u) * 64 + lane] : ctx;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (q0 + u >= r1) break;
-            const bool in = (q0 + u) * 64 + lane < r;
-            const bool have = p[u] < ctx && ((found[min(p[u], ctx - 1) >> 5] >> (p[u] & 31)) & 1u);
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in && !have);
-            if (lane == 0) fresh_mask[q0 + u] = m;
-            n_fresh += (uint32_t)__builtin_popcountll(m);
+            for (int u = 0; u < U; ++u) {
+                if (q0 + u >= r1) break;
+                const bool in = (q0 + u) * 64 + lane < r;
+                const bool keep = have[u] < ctx && ((listed[min(have[u], ctx - 1) >> 5] >> (have[u] & 31)) & 1u);      // (a position held twice, a corrupt map, is caught by the count check below)
+                const bool there = want[u] < ctx && ((held[min(want[u], ctx - 1) >> 5] >> (want[u] & 31)) & 1u);
+                const uint64_t mf = __builtin_amdgcn_ballot_w64(in && !keep), mn = __builtin_amdgcn_ballot_w64(in && !there);
+                if (lane == 0) {
+                    free_mask[q0 + u] = mf;
+                    fresh_mask[q0 + u] = mn;
+                }
+                n_free += (uint32_t)__builtin_popcountll(mf);
+                n_fresh += (uint32_t)__builtin_popcountll(mn);
+            }
         }
-    }
-    if (lane == 0) {
-        sm_cnt[0][wv] = n_free;
-        sm_cnt[1][wv] = n_fresh;
-    }
-    __syncthreads();
-    uint32_t at_free = 0, at_fresh = 0, tot_free = 0, tot_fresh = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        at_free += i < wv ? sm_cnt[0][i] : 0u;
-        at_fresh += i < wv ? sm_cnt[1][i] : 0u;
-        tot_free += sm_cnt[0][i];
-        tot_fresh += sm_cnt[1][i];
-    }
-    if (tot_free != tot_fresh) {
-        // the slot map does not describe a set of r distinct positions: start over from the list
-        for (int i = tid; i < r; i += NT) {
-            pslot[i] = i;
-            ppos[i] = list[i];
-            sp[i] = list[i];
+        if (lane == 0) {
+            sm_cnt[0][wv] = n_free;
+            sm_cnt[1][wv] = n_fresh;
         }
-        if (tid == 0) it.npairs[sd.bh] = r;
-        return;
+        __syncthreads();                             // (this workgroup has read the slot map)
+        if (tid == 0) {
+            const int n_wg = (start + r - 1) / share - start / share + 1;      // the workgroups whose runs touch this satellite
+            int32_t* done = it.done + bh;
+            sm_last = n_wg == 1 || atomicAdd(done, 1) == n_wg - 1;
+            if (sm_last && n_wg > 1) *done = 0;
+        }
+        uint32_t at_free = 0, at_fresh = 0, tot_free = 0, tot_fresh = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            at_free += i < wv ? sm_cnt[0][i] : 0u;
+            at_fresh += i < wv ? sm_cnt[1][i] : 0u;
+            tot_free += sm_cnt[0][i];
+            tot_fresh += sm_cnt[1][i];
+        }
+        at_free = (uint32_t)uniform((int)at_free);
+        at_fresh = (uint32_t)uniform((int)at_fresh);
+        tot_free = (uint32_t)uniform((int)tot_free);
+        tot_fresh = (uint32_t)uniform((int)tot_fresh);
+        // the pairs (the same from every workgroup of this satellite)
+        const bool over = tot_free != tot_fresh;     // the slot map does not describe a set of r distinct positions: start over from the list
+        const int pairs = over ? r : (int)tot_free;
+        if (over) {
+#pragma unroll 1
+            for (int i = tid; i < r; i += NT) {
+                pslot[i] = i;
+                ppos[i] = list[i];
+            }
+        } else {
+#pragma unroll 1
+            for (int q0 = r0; q0 < r1; q0 += U) {
+                if (per > U) load(want, list, q0);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (q0 + u >= r1) break;
+                    const uint64_t mf = free_mask[q0 + u], mn = fresh_mask[q0 + u], below = (1ull << lane) - 1ull;
+                    if ((mf >> lane) & 1u) pslot[at_free + __builtin_popcountll(mf & below)] = (q0 + u) * 64 + lane;
+                    if ((mn >> lane) & 1u) ppos[at_fresh + __builtin_popcountll(mn & below)] = (int32_t)want[u];
+                    at_free += (uint32_t)__builtin_popcountll(mf);
+                    at_fresh += (uint32_t)__builtin_popcountll(mn);
+                }
+            }
+        }
+        __syncthreads();                             // the pairs are complete (and visible to the whole workgroup)
+        if (sm_last)
+#pragma unroll 1
+            for (int k = tid; k < pairs; k += NT) sp[pslot[k]] = ppos[k];
+        const int k_begin = (int)((long long)pairs * (max(g_begin, start) - start) / r), k_end = (int)((long long)pairs * (min(g_end, start + r) - start) / r);
+        move_rows<2>(it, hd, first_slot, r, pslot, ppos, k_begin, k_end, movers);
+        __syncthreads();                             // (the next satellite takes over the LDS and the workspace's pairs)
     }
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int q = r0; q < r1; ++q) {
-        const uint64_t mf = free_mask[q], mn = fresh_mask[q];
-        if ((mf >> lane) & 1u) pslot[at_free + __builtin_popcountll(mf & below)] = q * 64 + lane;
-        if ((mn >> lane) & 1u) ppos[at_fresh + __builtin_popcountll(mn & below)] = list[q * 64 + lane];
-        at_free += (uint32_t)__builtin_popcountll(mf);
-        at_fresh += (uint32_t)__builtin_popcountll(mn);
-    }
-    __syncthreads();                        // the pairs are complete (and visible to the whole workgroup)
-    for (int k = tid; k < (int)tot_free; k += NT) sp[pslot[k]] = ppos[k];
-    if (tid == 0) it.npairs[sd.bh] = (int32_t)tot_free;
 }
 
 // The same for contexts whose bitmaps do not fit.  Dynamic LDS: the list (4 r bytes), found[r], keep[r].
@@ -249,54 +393,17 @@ __global__ __launch_bounds__(PLAN_THREADS) void gather_plan_kernel(GatherBatch B
     if (tid == 0) it.npairs[sd.bh] = (int32_t)tot_free;
 }
 
-// The rows to move, over all satellites of all layers of the batch, are numbered consecutively (satellite
-// after satellite) and dealt to the workgroups in equal contiguous runs, so that the time does not depend on
-// how unequal the satellites' lists are and a launch has as many workgroups as the host link needs, no more.
-// Every workgroup makes the prefix sums of the satellites' row counts itself (a few hundred numbers).
-// 32 lanes move one position (lanes 0-15 its K row, 16-31 its V row, 16 bytes each); a workgroup has
-// ROWS_PER_PASS positions in flight.
-constexpr int MAX_GATHER_SATS = 1024;     // satellites of a batch (layers x satellites per layer)
+// The refill where no bitmap plan moves the rows as well: whole lists (no slot map), and the pairs of gather_plan_kernel.  A
+// workgroup of T threads (64, 128 or 256) has T / 8 positions in flight.
 __global__ __launch_bounds__(256, 8) void gather_kernel(GatherBatch B, int n_items, int max_sats, int max_k)
 {
     __shared__ int sm_start[MAX_GATHER_SATS + 1];
-    __shared__ int sm_wsum[4];
     const int n_ent = n_items * max_sats;
     const int nthr = blockDim.x;            // 64, 128 or 256
-    if (threadIdx.x < 4) sm_wsum[threadIdx.x] = 0;
-    __syncthreads();
-    // counts -> exclusive prefix sums (entry e = item e / max_sats, satellite e % max_sats)
-    int carry = 0;
-    for (int base = 0; base < n_ent; base += nthr) {
-        const int e = base + threadIdx.x;
-        int c = 0;
-        if (e < n_ent) {
-            const GatherItem& it = B.it[e / max_sats];
-            const int sidx = e % max_sats;
-            if (sidx < it.n_sats) {
-                const SatDev sd = it.sats[sidx];
-                if (it.flag[sd.rep_bh] != 0) c = it.slot_pos ? min(max(it.npairs[sd.bh], 0), sd.r) : sd.r;
-            }
-        }
-        int inc = c;
-        const int lane = threadIdx.x & 63;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(inc, o);
-            if (lane >= o) inc += t;
-        }
-        if (lane == 63) sm_wsum[threadIdx.x >> 6] = inc;
-        __syncthreads();
-        int before = carry;
-        for (int k = 0; k < (int)(threadIdx.x >> 6); ++k) before += sm_wsum[k];
-        if (e < n_ent) sm_start[e] = before + inc - c;
-        carry += sm_wsum[0] + sm_wsum[1] + sm_wsum[2] + sm_wsum[3];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) sm_start[n_ent] = carry;
-    __syncthreads();
-    const int total = carry;
+    const int total = row_starts(B, n_ent, max_sats, sm_start,
+                                 [](const GatherItem& it, const SatDev& sd) { return it.slot_pos ? min(max(it.npairs[sd.bh], 0), sd.r) : sd.r; });
     if (total == 0) return;
-    const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + 7) & ~7;
+    const int per = rows_per_workgroup(total);
     const int g_begin = blockIdx.x * per, g_end = min(total, g_begin + per);
     const int nsub = nthr >> 5;                // positions of a sub-pass
     const int sub = threadIdx.x >> 5;          // which of them this half-wave moves
@@ -352,39 +459,45 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
         GatherItem& it = B.it[i];
         it = GatherItem{x.L->sats, x.L->heads, (const uint16_t*)x.tier, x.topk_idx, x.flag, (uint16_t*)x.arena, x.slot_pos,
                         ctx->pair_slot + i * rows * max_k, ctx->pair_pos + i * rows * max_k, ctx->npairs + i * rows,
-                        x.L->n_sats, 0};
+                        ctx->gather_done + i * rows, x.L->n_sats, 0};
         any_delta |= x.slot_pos != nullptr;
         max_r = std::max(max_r, x.L->max_r);
         max_sats = std::max(max_sats, x.L->n_sats);
     }
     if (max_sats == 0 || max_r == 0) return HC_OK;
+    if (n * max_sats > MAX_GATHER_SATS) return hc_fail(ctx, HC_ESHAPE, "hc_gather: more than %d satellites in a batch", MAX_GATHER_SATS);
+    // A few dozen workgroups keep the host link busy.  More do not make the refill much faster, and every compute unit
+    // that hosts gather waves has its memory pipeline filled with reads that take microseconds, behind which the
+    // attention waves on the same unit queue (measured at the 224K shape with 16 workgroups per satellite in a
+    // batch of 8 layers: the attention launch that ran beside a refill took 400 us instead of 45).  One refill of 2.6 MB by
+    // itself with 32, 48, 64, 96, 160 workgroups: 60, 57, 57, 57, 54 us; steps of four layers, six sequences, with it on the side
+    // stream: 279, 279, 280, 282, 284 us.
+    long long rows_max = 0;
+    for (int i = 0; i < n; ++i) rows_max += (long long)calls[i].L->n_sats * calls[i].L->max_r;
+    const int thr = ctx->gather_threads, in_flight = thr / 32 * GATHER_PASSES;
+    const int most = ctx->gather_workgroups > 0 ? ctx->gather_workgroups : ctx->beside_now ? 48 : 96;
+    const int nwg = (int)std::max<long long>(1, std::min<long long>(most, (rows_max + in_flight - 1) / in_flight));
     if (any_delta) {
         for (int i = 0; i < n; ++i)
             if (!calls[i].slot_pos) return hc_fail(ctx, HC_EINVAL, "hc_gather: in one batch either every layer has a slot map or none");
         const size_t lds = (size_t)max_k * (sizeof(int32_t) + 2);
         if (lds > 144 * 1024) return hc_fail(ctx, HC_ESHAPE, "hc_gather: max_k %d is too large for the slot-map path", max_k);
-        // Bitmaps of the longest context and a mask per 64 entries; beside the attention pass within what its workgroups
-        // leave of a compute unit's LDS.
-        const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16;
+        // Where the bitmaps of the longest context, a mask per 64 entries and the satellites' first rows fit in LDS (beside the
+        // attention pass: within what its workgroups leave of a compute unit's), one launch plans and moves; otherwise
+        // a plan by binary search, a workgroup per satellite, and gather_kernel behind it (a list of 7,872: 43 us + 55).
+        const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16 + start_words(n * max_sats) * 4;
         const unsigned room = !ctx->beside_now ? 150 * 1024 : ctx->G == 8 ? 55 * 1024 : ctx->side_pad_now ? 108 * 1024 : 75 * 1024;
-        const dim3 grid(1, max_sats, n);
-        if (maps > room)
-            gather_plan_kernel<<<grid, dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
-        else if (ctx->beside_now)
-            gather_plan_bitmap_kernel<512><<<grid, dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, max_k);
-        else
-            gather_plan_bitmap_kernel<1024><<<grid, dim3(1024), maps, st>>>(B, max_k);
+        if (maps <= room) {
+            if (ctx->beside_now)
+                gather_plan_bitmap_kernel<512><<<dim3(nwg), dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, n, max_sats, max_k, thr);
+            else
+                gather_plan_bitmap_kernel<1024><<<dim3(nwg), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 2 * thr);
+            HC_HIP(ctx, hipGetLastError());
+            return HC_OK;
+        }
+        gather_plan_kernel<<<dim3(1, max_sats, n), dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
         HC_HIP(ctx, hipGetLastError());
     }
-    // A few dozen workgroups keep the host link busy.  More do not make the refill faster, and every compute unit
-    // that hosts gather waves has its memory pipeline filled with reads that take microseconds, behind which the
-    // attention waves on the same unit queue (measured at the 224K shape with 16 workgroups per satellite in a
-    // batch of 8 layers: the attention launch that ran beside a refill took 400 us instead of 45).
-    if (n * max_sats > MAX_GATHER_SATS) return hc_fail(ctx, HC_ESHAPE, "hc_gather: more than %d satellites in a batch", MAX_GATHER_SATS);
-    long long rows_max = 0;
-    for (int i = 0; i < n; ++i) rows_max += (long long)calls[i].L->n_sats * calls[i].L->max_r;
-    const int thr = ctx->gather_threads, in_flight = thr / 32 * GATHER_PASSES;
-    const int nwg = (int)std::max<long long>(1, std::min<long long>(ctx->gather_workgroups, (rows_max + in_flight - 1) / in_flight));
     gather_kernel<<<dim3(nwg), dim3(thr), hc_side_lds(ctx, (const void*)gather_kernel, 0), st>>>(B, n, max_sats, max_k);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;

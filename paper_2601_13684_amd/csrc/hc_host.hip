@@ -127,7 +127,11 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
         const size_t rows = (size_t)cfg->B * cfg->Hkv;
         const size_t pair_w = (size_t)HC_MAX_GROUP * rows * cfg->max_k;
         int32_t* g = nullptr;
-        e = hipMalloc((void**)&g, (2 * pair_w + (size_t)HC_MAX_GROUP * rows) * sizeof(int32_t));
+        e = hipMalloc((void**)&g, (2 * pair_w + 2 * (size_t)HC_MAX_GROUP * rows) * sizeof(int32_t));
+        if (e == hipSuccess) {
+            e = hipMemset(g + 2 * pair_w + (size_t)HC_MAX_GROUP * rows, 0, (size_t)HC_MAX_GROUP * rows * sizeof(int32_t));
+            if (e != hipSuccess) (void)hipFree(g);
+        }
         if (e != hipSuccess) {
             (void)hipFree(base);
             delete c;
@@ -136,6 +140,7 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
         c->pair_slot = g;
         c->pair_pos = g + pair_w;
         c->npairs = g + 2 * pair_w;
+        c->gather_done = c->npairs + (size_t)HC_MAX_GROUP * rows;
         (void)hc_gather_set_lds_limit();
         (void)hc_monitor_set_lds_limit();
         (void)hc_attn_set_lds_limit();

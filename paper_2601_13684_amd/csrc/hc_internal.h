@@ -100,7 +100,7 @@ struct hc_ctx {
     int wg_per_cu;
     unsigned long long* tune_stamps = nullptr;   // non-null only inside hc_layer_tune: per-workgroup start / rows-done times
     float share_weights[16];     // by die and dispatch slot, see hc_set_share_weights
-    int gather_workgroups = 96, gather_threads = 256;   // launch shape of the gather (hc_set_gather_shape)
+    int gather_workgroups = 0, gather_threads = 256;   // launch shape of the gather (hc_set_gather_shape); 0: chosen per launch
     float filter_margin = 0.f;   // > 0: pivot logits are filtered (hc_set_logit_filter); layers created afterwards carry the buffers
     int filter_min_candidates = 0;   // ... if one of their pivots has at least this many candidate positions
     int side_lds_total = 81 * 1024;   // > 0: LDS bytes every side-stream workgroup of hc_decode_step reserves (hc_set_side_lds)
@@ -129,6 +129,7 @@ struct hc_ctx {
     int32_t* pair_slot = nullptr;  // [HC_MAX_GROUP][B*Hkv][max_k]
     int32_t* pair_pos = nullptr;   // [HC_MAX_GROUP][B*Hkv][max_k]
     int32_t* npairs = nullptr;     // [HC_MAX_GROUP][B*Hkv]
+    int32_t* gather_done = nullptr;// [HC_MAX_GROUP][B*Hkv] zero between launches
 };
 
 struct hc_layer {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2601_13684_amd import binding as hc
 from paper_2601_13684_amd import inputs as I
 from paper_2601_13684_amd import runtime as R
 
@@ -66,5 +67,47 @@ def test_plan_and_moved_rows(N, r):
         assert torch.equal(rows, kv[torch.from_numpy(slots).long()])
         rows = gpu.arena[d.v_off + 5 * 128:d.v_off + (5 + r) * 128].view(r, 128).cpu()
         assert torch.equal(rows, -kv[torch.from_numpy(slots).long()])
+    gpu.close()
+    ctx.close()
+
+
+# one workgroup for all satellites, workgroups whose runs cross satellites, more workgroups than a short list has rows
+@pytest.mark.parametrize("workgroups,threads", [(1, 64), (3, 128), (7, 256), (96, 256), (4096, 64)])
+def test_unequal_satellites_share_the_workgroups(workgroups, threads):
+    """Satellites of very different lengths and shares of new rows, one pivot that has not fired, call after call: the workgroups
+    that plan one satellite agree, and its slot map is brought up to date once."""
+    print("gather shares", workgroups, threads, flush=True)
+    N, lens = 9001, [1, 63, 700, 1025, 3000, 64, 400]
+    heads = [I.HeadSpec(I.ROLE_FULL), I.HeadSpec(I.ROLE_FULL)] + \
+            [I.HeadSpec(I.ROLE_SATELLITE, rep=j % 2, sink=3, recent=2, budget=5 + r) for j, r in enumerate(lens)]
+    spec = I.LayerSpec(B=1, Hq=len(heads), Hkv=len(heads), D=128, ctx=[N], heads=[heads])
+    g = torch.Generator().manual_seed(5)
+    kv = torch.randn((N, 128), generator=g).to(torch.bfloat16)
+    data = I.LayerData({(0, h): kv for h in range(len(heads))}, {(0, h): -kv for h in range(len(heads))}, {})
+    retrieved, base = I.initial_lists(spec)
+    ctx = R.Context(R.make_config(spec), DEV)
+    hc.hc_set_gather_shape(ctx.handle, workgroups, threads)
+    gpu = R.LayerRuntime(ctx, spec, data, retrieved, base)
+    rng = np.random.default_rng(workgroups)
+    cand = np.arange(3, N - 2, dtype=np.int32)
+    held = {h: gpu.slot_pos[h, :r].cpu().numpy() for h, r in enumerate(lens, 2)}
+    for call in range(4):
+        fired = [True, call % 2 == 0]
+        gpu.flag[:2] = torch.tensor(fired, dtype=torch.int32, device=DEV)
+        want = {}
+        for h, r in enumerate(lens, 2):
+            keep = rng.choice(held[h], r - rng.integers(0, r + 1), replace=False)
+            lst = np.sort(np.concatenate([keep, rng.choice(np.setdiff1d(cand, held[h]), r - keep.size, replace=False)])).astype(np.int32)
+            gpu.topk_idx[h, :r] = torch.from_numpy(lst).to(DEV)
+            want[h] = expected(held[h], lst) if fired[(h - 2) % 2] else held[h]
+        gpu.gather()
+        torch.cuda.synchronize()
+        for h, r in enumerate(lens, 2):
+            held[h] = gpu.slot_pos[h, :r].cpu().numpy()
+            np.testing.assert_array_equal(held[h], want[h])
+            d = gpu.descs[h]
+            for off, sign in ((d.k_off, 1), (d.v_off, -1)):
+                rows = gpu.arena[off + 5 * 128:off + (5 + r) * 128].view(r, 128).cpu()
+                assert torch.equal(rows, sign * kv[torch.from_numpy(held[h]).long()])
     gpu.close()
     ctx.close()
