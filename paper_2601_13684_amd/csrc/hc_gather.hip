@@ -94,19 +94,14 @@ __device__ __forceinline__ void block_exscan2(uint32_t a, uint32_t b, uint32_t* 
     ex_b = base_b + ib - b;
 }
 
-// The rows to move, over all satellites of all layers of a batch, are numbered consecutively (satellite after satellite) and
-// dealt to the workgroups in equal contiguous runs, so that the time does not depend on how unequal the satellites' lists are
-// and a launch has as many workgroups as the host link needs, no more.  Every workgroup makes the prefix sums of the
-// satellites' row counts itself (a few hundred numbers): entry e is satellite e % max_sats of item e / max_sats, count(item,
-// satellite) its rows.  sm_start[0 .. n_ent] and the total, the same in every thread.
+// Rows to move of every satellite of a batch: entry e is satellite e % max_sats of item e / max_sats, count(item, satellite) its
+// rows if its pivot fired.  Every wave goes through the entries for itself (each(e, rows), 64 to a call, lanes past the end
+// with none), so that a launch that finds nothing to move, the usual case in a decode step, ends without a barrier.
 constexpr int MAX_GATHER_SATS = 1024;     // satellites of a batch (layers x satellites per layer)
-// (Every wave does it for itself and wave 0 writes it down: a launch that finds nothing to move, the usual case in a decode
-// step, ends without a barrier.)
-template <class Count>
-__device__ __forceinline__ int row_starts(const GatherBatch& B, int n_ent, int max_sats, int* sm_start, const Count& count)
+template <class Count, class Each>
+__device__ __forceinline__ void entry_rows(const GatherBatch& B, int n_ent, int max_sats, const Count& count, const Each& each)
 {
     const int lane = threadIdx.x & 63;
-    int carry = 0;
     auto chunks = [&](auto per, int base) {          // `per` times 64 entries, whose reads are in flight together
         constexpr int U = decltype(per)::value;
         const GatherItem* it[U];
@@ -126,16 +121,8 @@ __device__ __forceinline__ int row_starts(const GatherBatch& B, int n_ent, int m
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = base + u * 64 + lane;
             if (c[u] != 0) c[u] = count(*it[u], sd[u]);
-            int inc = c[u];
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
-            }
-            if (threadIdx.x < 64 && e < n_ent) sm_start[e] = carry + inc - c[u];
-            carry += __builtin_amdgcn_readlane(inc, 63);
+            each(base + u * 64 + lane, c[u]);
         }
     };
     if (n_ent <= 64) {
@@ -144,13 +131,17 @@ __device__ __forceinline__ int row_starts(const GatherBatch& B, int n_ent, int m
 #pragma unroll 1
         for (int base = 0; base < n_ent; base += 256) chunks(std::integral_constant<int, 4>{}, base);
     }
-    if (carry == 0) return 0;
-    if (threadIdx.x == 0) sm_start[n_ent] = carry;
-    __syncthreads();
-    return carry;
 }
-constexpr int start_words(int n_ent) { return (n_ent + 4) & ~3; }      // LDS for them, a multiple of 16 bytes
-__device__ __forceinline__ int rows_per_workgroup(int total) { return ((total + (int)gridDim.x - 1) / (int)gridDim.x + 7) & ~7; }
+__device__ __forceinline__ int wave_incl(int v)      // inclusive prefix sum over the wave
+{
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(v, o);
+        if ((int)(threadIdx.x & 63) >= o) v += t;
+    }
+    return v;
+}
+constexpr int entry_words(int n_ent) { return (n_ent + 4) & ~3; }      // LDS for a count each and one more, a multiple of 16 bytes
 
 // Moves pairs [begin, end) of a satellite: the row of position pos[k] from the tier into slot[k].  32 lanes move one position
 // (lanes 0-15 its K row, 16-31 its V row, 16 bytes each), the first `movers` threads take part, PASSES positions each in flight:
@@ -186,15 +177,18 @@ __device__ __forceinline__ void move_rows(const GatherItem& it, const HeadDev& h
 }
 
 // Which slots of a satellite hold positions that left the list (free), which positions of the list are not resident (fresh);
-// the k-th free slot takes the k-th fresh position.  And the move of those rows, in the same launch: the list rows of
-// all satellites that are to be refilled are dealt to the workgroups, a workgroup plans every satellite that its run touches
-// and moves the share of that satellite's pairs that its run is of the list.  Several workgroups then make the same plan,
-// which costs no time (they would wait for it otherwise); the last of them to be through with the slot map brings it up to date.
+// the k-th free slot takes the k-th fresh position.  And the move of those rows, in the same launch: the satellites that are to be
+// refilled get workgroups in proportion to their lists (so that the time does not depend on how unequal these are, and a launch
+// has as many workgroups as the host link needs, no more); each makes the plan and moves its share of the pairs.  Several
+// workgroups then make the same plan, which costs no time (they would wait for it otherwise); the last of them to be
+// through with the slot map brings it up to date.  (With the lists' rows dealt out in equal runs, some workgroups planned two
+// satellites one after the other: six lists of 420 to 800 entries 19.5 us, this way 15.0; in two
+// launches 16.3.)
 //
 // Two bitmaps over the context in LDS, of the listed positions and of those held by a slot, so that every slot and every
 // list entry costs one LDS access; choices are kept as one mask per 64 entries, and a wave's run of them is compacted with
 // ballots.  The plan is a chain of latencies: list and slot map are asked for together, at the start.
-// Six lists of 704 to 7,872 entries, a quarter new, 2.6 MB over the link (45 us at its rate): 57 us, 66 in two launches (a plan
+// Six lists of 704 to 7,872 entries, a quarter new, 2.6 MB over the link (45 us at its rate): 54 us, 66 in two launches (a plan
 // by a workgroup per satellite, 11 us, then the rows, 54).  A launch that finds nothing to do takes 4 us.
 template <int NT>
 __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int n_items, int max_sats, int max_k, int movers)
@@ -203,25 +197,43 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t sm_cnt[2][NW];
     __shared__ int sm_last;
-    const int n_ent = n_items * max_sats;
-    int* sm_start = reinterpret_cast<int*>(dyn);
-    uint32_t* sm_words = dyn + start_words(n_ent);
-    const int total = row_starts(B, n_ent, max_sats, sm_start, [](const GatherItem&, const SatDev& sd) { return sd.r; });
-    const int share = rows_per_workgroup(total), g_begin = blockIdx.x * share, g_end = min(total, g_begin + share);
-    if (g_begin >= g_end) return;
+    const int n_ent = n_items * max_sats, n_wgs = (int)gridDim.x;
+    int* sm_first = reinterpret_cast<int*>(dyn);     // [n_ent + 1]
+    uint32_t* sm_words = dyn + entry_words(n_ent);
+    int total = 0, fired = 0;
+    entry_rows(B, n_ent, max_sats, [](const GatherItem&, const SatDev& sd) { return sd.r; }, [&](int e, int rows) {
+        if (threadIdx.x < 64 && e < n_ent) sm_first[e] = rows;
+        total += uniform(__builtin_amdgcn_readlane(wave_incl(rows), 63));
+        fired += __builtin_popcountll(__builtin_amdgcn_ballot_w64(rows > 0));
+    });
+    if (total == 0) return;
     const int tid = threadIdx.x, wv = uniform(tid >> 6), lane = tid & 63;
-    int e = 0;
-    for (int hi = n_ent; hi - e > 1;) {              // the entry whose run holds row g_begin
-        const int mid = (e + hi) >> 1;
-        if (sm_start[mid] <= g_begin) e = mid;
-        else hi = mid;
+    // list rows to a workgroup, such that there are workgroups for all (half a workgroup's share is lost per satellite) while
+    // there are more of them than satellites
+    const int by = max(n_wgs - fired, (n_wgs + 1) / 2), share = (total + by - 1) / by;
+    if (wv == 0) {                                   // rows -> first task (one for each of a satellite's workgroups)
+        int before = 0;
+#pragma unroll 1
+        for (int base = 0; base < n_ent; base += 64) {
+            const int mine = base + lane < n_ent ? (sm_first[base + lane] + share - 1) / share : 0, incl = before + wave_incl(mine);
+            if (base + lane < n_ent) sm_first[base + lane] = incl - mine;
+            before = __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) sm_first[n_ent] = before;
     }
-    for (e = uniform(e); e < n_ent; ++e) {      // (the same for the whole workgroup)
-        const int start = uniform(sm_start[e]), r = uniform(sm_start[e + 1]) - start;
-        if (start >= g_end) break;
-        if (r == 0) continue;
+    __syncthreads();
+    const int tasks = uniform(sm_first[n_ent]);
+#pragma unroll 1
+    for (int task = blockIdx.x; task < tasks; task += n_wgs) {           // (the same for the whole workgroup)
+        int e = 0;
+        for (int hi = n_ent; hi - e > 1;) {          // the last entry whose tasks begin at or before this one
+            const int mid = (e + hi) >> 1;
+            if (uniform(sm_first[mid]) <= task) e = mid;
+            else hi = mid;
+        }
+        const int part = task - uniform(sm_first[e]), parts = uniform(sm_first[e + 1]) - uniform(sm_first[e]);
         const GatherItem& it = B.it[e / max_sats];
-        const int bh = uniform(it.sats[e % max_sats].bh), first_slot = uniform(it.sats[e % max_sats].first_slot);
+        const int bh = uniform(it.sats[e % max_sats].bh), r = uniform(it.sats[e % max_sats].r), first_slot = uniform(it.sats[e % max_sats].first_slot);
         const HeadDev& hd = it.heads[bh];
         const uint32_t ctx = (uint32_t)uniform(hd.ctx);
         const int words = (int)(ctx + 31) / 32, rounds = (r + 63) / 64;
@@ -286,10 +298,9 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         }
         __syncthreads();                             // (this workgroup has read the slot map)
         if (tid == 0) {
-            const int n_wg = (start + r - 1) / share - start / share + 1;      // the workgroups whose runs touch this satellite
             int32_t* done = it.done + bh;
-            sm_last = n_wg == 1 || atomicAdd(done, 1) == n_wg - 1;
-            if (sm_last && n_wg > 1) *done = 0;
+            sm_last = parts == 1 || atomicAdd(done, 1) == parts - 1;
+            if (sm_last && parts > 1) *done = 0;
         }
         uint32_t at_free = 0, at_fresh = 0, tot_free = 0, tot_fresh = 0;
 #pragma unroll
@@ -331,7 +342,7 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         if (sm_last)
 #pragma unroll 1
             for (int k = tid; k < pairs; k += NT) sp[pslot[k]] = ppos[k];
-        const int k_begin = (int)((long long)pairs * (max(g_begin, start) - start) / r), k_end = (int)((long long)pairs * (min(g_end, start + r) - start) / r);
+        const int k_begin = (int)((long long)pairs * part / parts), k_end = (int)((long long)pairs * (part + 1) / parts);
         move_rows<2>(it, hd, first_slot, r, pslot, ppos, k_begin, k_end, movers);
         __syncthreads();                             // (the next satellite takes over the LDS and the workspace's pairs)
     }
@@ -393,17 +404,25 @@ __global__ __launch_bounds__(PLAN_THREADS) void gather_plan_kernel(GatherBatch B
     if (tid == 0) it.npairs[sd.bh] = (int32_t)tot_free;
 }
 
-// The refill where no bitmap plan moves the rows as well: whole lists (no slot map), and the pairs of gather_plan_kernel.  A
+// The refill where no bitmap plan moves the rows as well: whole lists (no slot map), and the pairs of gather_plan_kernel.  The rows
+// of all satellites are numbered consecutively and dealt to the workgroups in equal runs.  A
 // workgroup of T threads (64, 128 or 256) has T / 8 positions in flight.
 __global__ __launch_bounds__(256, 8) void gather_kernel(GatherBatch B, int n_items, int max_sats, int max_k)
 {
     __shared__ int sm_start[MAX_GATHER_SATS + 1];
     const int n_ent = n_items * max_sats;
     const int nthr = blockDim.x;            // 64, 128 or 256
-    const int total = row_starts(B, n_ent, max_sats, sm_start,
-                                 [](const GatherItem& it, const SatDev& sd) { return it.slot_pos ? min(max(it.npairs[sd.bh], 0), sd.r) : sd.r; });
+    int total = 0;
+    entry_rows(B, n_ent, max_sats, [](const GatherItem& it, const SatDev& sd) { return it.slot_pos ? min(max(it.npairs[sd.bh], 0), sd.r) : sd.r; },
+               [&](int e, int rows) {
+                   const int incl = total + wave_incl(rows);
+                   if (threadIdx.x < 64 && e < n_ent) sm_start[e] = incl - rows;
+                   total = __builtin_amdgcn_readlane(incl, 63);
+               });
     if (total == 0) return;
-    const int per = rows_per_workgroup(total);
+    if (threadIdx.x == 0) sm_start[n_ent] = total;
+    __syncthreads();
+    const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + 7) & ~7;
     const int g_begin = blockIdx.x * per, g_end = min(total, g_begin + per);
     const int nsub = nthr >> 5;                // positions of a sub-pass
     const int sub = threadIdx.x >> 5;          // which of them this half-wave moves
@@ -485,7 +504,7 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
         // Where the bitmaps of the longest context, a mask per 64 entries and the satellites' first rows fit in LDS (beside the
         // attention pass: within what its workgroups leave of a compute unit's), one launch plans and moves; otherwise
         // a plan by binary search, a workgroup per satellite, and gather_kernel behind it (a list of 7,872: 43 us + 55).
-        const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16 + start_words(n * max_sats) * 4;
+        const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16 + entry_words(n * max_sats) * 4;
         const unsigned room = !ctx->beside_now ? 150 * 1024 : ctx->G == 8 ? 55 * 1024 : ctx->side_pad_now ? 108 * 1024 : 75 * 1024;
         if (maps <= room) {
             if (ctx->beside_now)
