@@ -110,7 +110,7 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     // (more survivors than that are never asked for: see SELECT_SURVIVORS in hc_monitor.hip)
     c->area_words = (std::max((size_t)c->sv_cap + HC_SEL_CHUNK / 32 * (size_t)c->max_chunks,
                               2 * HC_MAX_K_PER_REP * (size_t)HC_RADIX_BINS + HC_MAX_K_PER_REP * 4 + (2 * HC_MAX_K_PER_REP + 1) * (size_t)c->max_chunks) + 3) & ~(size_t)3;
-    const size_t rep_w = HC_RADIX_BINS + cfg->max_ctx / 32 + c->area_words;
+    const size_t rep_w = HC_HIST_WORDS + cfg->max_ctx / 32 + c->area_words;
     size_t ws_w = 0;
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
         c->ws[i].reps = std::max(1, i == 0 ? cfg->B * cfg->Hkv : cfg->B * cfg->Hkv / 2);
@@ -151,7 +151,7 @@ extern "C" hc_status hc_create(const hc_config* cfg, hc_ctx** out)
     for (int i = 0; i < HC_MAX_GROUP; ++i) {
         hc_monitor_ws& w = c->ws[i];
         w.hist = base;
-        w.area = w.hist + (size_t)w.reps * HC_RADIX_BINS;
+        w.area = w.hist + (size_t)w.reps * HC_HIST_WORDS;
         w.bitmap = w.area + (size_t)w.reps * c->area_words;
         w.dirty = true;
         base += (((size_t)w.reps * rep_w) + 3) & ~(size_t)3;
@@ -329,7 +329,7 @@ struct Plan {
     std::vector<OutDev> outs;
     std::vector<SatDev> sats;
     std::vector<int32_t> rep_slot_of;
-    int n_blocks = 0, max_r = 0, max_nchunk = 1;
+    int n_blocks = 0, max_r = 0, max_nchunk = 1, max_cand = 1;
     int64_t total_rows = 0;
 };
 
@@ -448,6 +448,7 @@ static hc_status make_plan(const hc_config& cfg, const hc_head_desc* hd, int n_c
             r.out_count = (int32_t)P.outs.size() - r.out_begin;
             r.nchunk = (r.hi - r.lo + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
             P.max_nchunk = std::max(P.max_nchunk, r.nchunk);
+            P.max_cand = std::max(P.max_cand, r.hi - r.lo);
             P.rep_slot_of[pi] = slot;
             P.reps.push_back(r);
         }
@@ -631,6 +632,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
     L->rep_slot_of = P.rep_slot_of;
     L->max_r = P.max_r;
     L->max_nchunk = P.max_nchunk;
+    L->max_cand = P.max_cand;
     L->max_nk = 1;
     for (const RepDev& r : P.reps) {
         L->max_nk = std::max(L->max_nk, r.nk);
@@ -693,6 +695,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
             sel.push_back(r);
             L->sel_head_host.push_back(i);
             L->sel_max_nchunk = std::max(L->sel_max_nchunk, r.nchunk);
+            L->sel_max_cand = std::max(L->sel_max_cand, r.hi - r.lo);
             L->sel_max_len = std::max(L->sel_max_len, (int)h.ctx);
         }
         L->n_sel = (int)sel.size();
@@ -907,6 +910,7 @@ static hc_status replan(hc_ctx* ctx, hc_layer* L, hipStream_t st)
     L->n_blocks = P.n_blocks;
     L->n_segs = L->n_partials = (int)P.segs.size();
     L->max_nchunk = P.max_nchunk;
+    L->max_cand = P.max_cand;
     L->appended_since_plan = 0;
     return HC_OK;
 }
@@ -938,14 +942,15 @@ static hc_status append_done(hc_ctx* ctx, hc_layer* L, hipStream_t st)
         h.ctx += 1;
         if (h.role == HC_ROLE_FULL) h.len += 1;
     }
-    int max_nchunk = 1;
+    int max_cand = 1;
     for (int i = 0; i < L->n_heads; ++i)
         if (L->rep_slot_of[i] >= 0) {
             const int slot = L->rep_slot_of[i];
             const int lo = L->rep_lo_host[slot], hi = L->hd_host[i].ctx - L->rep_recent_host[slot];
-            max_nchunk = std::max(max_nchunk, (hi - lo + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK);
+            max_cand = std::max(max_cand, hi - lo);
         }
-    L->max_nchunk = max_nchunk;
+    L->max_cand = max_cand;
+    L->max_nchunk = (max_cand + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
     ++L->total_appended;
     if (++L->appended_since_plan >= 64) return replan(ctx, L, st);
     return HC_OK;
@@ -1115,6 +1120,7 @@ extern "C" hc_status hc_prefill_init(hc_ctx* ctx, hc_layer* layer, const void* k
         call.outs = L->sel_outs;
         call.n_reps = L->n_sel;
         call.max_nchunk = L->sel_max_nchunk;
+        call.max_cand = L->sel_max_cand;
         call.max_nk = 1;
         s = hc_launch_monitor(ctx, 1, &call, 1, st);
         if (s != HC_OK) return s;

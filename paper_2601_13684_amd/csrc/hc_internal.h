@@ -14,6 +14,7 @@ constexpr int HC_D = 128;            // head dimension the kernels are written f
 constexpr int HC_UNIT_ROWS = 32;     // split-K granule: 4 waves x 8 rows
 constexpr int HC_SEL_CHUNK = 1024;   // candidates a workgroup or wave of the monitor's first passes takes at a time
 constexpr int HC_RADIX_BINS = 2048;  // bins of the monitor's histograms: 11 bits of a key, or of its distance from the smallest
+constexpr int HC_HIST_WORDS = HC_RADIX_BINS + 4;   // of a histogram in memory: a counter of its readers behind it
 constexpr int HC_SAMPLES = 4096;     // items of a long candidate range from which the monitor estimates its threshold
 constexpr int HC_MAX_SURVIVORS = 24576;   // survivors that a pivot's workspace holds
 
@@ -86,7 +87,7 @@ struct SatDev {
 
 struct hc_monitor_ws {
     int reps = 0;                  // pivots this copy has room for
-    uint32_t* hist = nullptr;      // [reps][HC_RADIX_BINS]: first-digit histogram of a long candidate range
+    uint32_t* hist = nullptr;      // [reps][HC_HIST_WORDS]: first-digit histogram of a long candidate range
     uint32_t* bitmap = nullptr;    // [reps][max_ctx/32]: baseline set, where it does not fit in LDS
     uint32_t* area = nullptr;      // [reps][area_words]: survivors of a long range, or histograms and counts of long lists
     bool dirty = true;             // histograms / bitmap not known to be clear (first call, or a call that failed midway)
@@ -139,7 +140,7 @@ struct hc_layer {
     int n_blocks, n_partials, n_segs;
     int n_reps, n_sats;
     int max_r;                     // largest r among satellites
-    int max_nchunk;
+    int max_nchunk, max_cand;      // of the longest candidate range of any pivot: chunks, candidates
     int max_nk;                    // largest number of distinct set sizes of a pivot
     int max_k_any = 1;             // largest set size of any pivot
     std::vector<int32_t> rep_slot_of;   // [B*Hkv]
@@ -150,7 +151,7 @@ struct hc_layer {
     long long total_appended = 0;       // tokens appended since creation
     // prefill-time initialisation: the heads that select (compressed heads by their own scores, pivots for their
     // baseline sets), one list each
-    int n_sel = 0, sel_max_nchunk = 1, sel_max_len = 1;
+    int n_sel = 0, sel_max_nchunk = 1, sel_max_cand = 1, sel_max_len = 1;
     int prefill_unfit_head = -1;        // a compressed head whose slots the selection cannot fill (list longer than max_k)
     RepDev* sel_reps = nullptr;
     OutDev* sel_outs = nullptr;
@@ -250,7 +251,7 @@ struct hc_monitor_call {
     // prefill-time selection runs over its own list of heads instead of the layer's pivots
     const RepDev* reps = nullptr;
     const OutDev* outs = nullptr;
-    int n_reps = 0, max_nchunk = 0, max_nk = 0;
+    int n_reps = 0, max_nchunk = 0, max_cand = 0, max_nk = 0;
     const void* arena = nullptr;   // the layer's K/V arena, for a layer that filters its pivot logits (nullptr: the one
                                    // its last attention call was given)
 };

@@ -13,13 +13,17 @@
 // of its items in LDS: threshold, ordered lists, |T ∩ baseline| through a bitmap in LDS, window, decision and
 // baseline update.  What reaches it:
 //   short candidate ranges   mon_select scores the candidates itself: one launch
-//   long ranges              mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact (the
+//   up to 64K candidates (32K beside the attention pass)
+//                            mon_score_hist (scores and their histogram; many workgroups per pivot), mon_direct (the lists straight
+//                            from the scores, no keys in LDS): two launches
+//   longer ranges            mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact (the
 //                            candidates that can be in the longest list, and few more), mon_select over those (a few
 //                            thousand): three launches
 //   long lists               mon_score_hist, mon_hist twice, mon_count, mon_write, mon_decide: six launches of many workgroups
 //   rows a filtering split pass kept
-//                            mon_sparse_score (their scores, one dense run), mon_select (with the long ranges' first two in
-//                            front of it where more rows are kept than it has room for): two launches, and behind them
+//                            mon_sparse_score (their scores, one dense run), mon_direct (mon_select where its LDS does not
+//                            suffice, with the long ranges' first two in front of it where more rows are kept than it has room
+//                            for): two launches, and behind them
 //                            two that normally find nothing to do, for a pivot whose check failed: rep_logits_kernel
 //                            (hc_attn.hip; all logits again, with their scores) and mon_select, which cuts the whole range
 //                            down by itself (a launch more for that would cost every step 3 us), or the six of long lists
@@ -27,12 +31,12 @@
 // them clear.)
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
-// histograms, counts, ordered write, decision): one 32K layer 27.4 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 33-36 instead of 81 us, the decode step of one 4K layer 29 instead of 49 us.
+// histograms, counts, ordered write, decision): one 32K layer 20.5 instead of 51.5 us per call, eight sequences of 9K to
+// 131K 33-36 instead of 81 us, the decode step of one 4K layer 28 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
-// registers, or 512 threads of at most 40 (mon_select's small form; no bound on waves per SIMD asks for so few, a
+// registers, or 512 threads of at most 40 (the small forms of mon_select and mon_direct; no bound on waves per SIMD asks for so few, a
 // test of the built kernels holds them to it).  In groups of eight heads the attention workgroups leave too little LDS for
 // mon_select's keys: its large form runs there, on a compute unit of its own (measured with four layers of 229,376 and lists
 // of 3,840: 266 us a step, 282 with the small form for as many as fit).  No local arrays (a kernel that needs scratch memory
@@ -55,7 +59,8 @@ __device__ __forceinline__ float key_score(uint32_t key)      // inverse of hc_s
 
 // Workspace of one layer of a batch (rep: pivot).
 struct Ws {
-    uint32_t* hist;      // [HC_RADIX_BINS]: first-digit histogram of a long range
+    uint32_t* hist;      // [HC_RADIX_BINS]: first-digit histogram of a long range, and behind it how many of mon_direct's
+                         // workgroups are through with it (HC_HIST_WORDS in all)
     uint32_t* bitmap;    // [max_ctx / 32]: baseline set, where it does not fit in LDS
     // one piece of memory, `area` words per pivot, that a call uses either for survivors ...
     uint64_t* mask;      // [max_chunks][HC_SEL_CHUNK / 64]: which candidates survive
@@ -71,7 +76,7 @@ struct Ws {
     __device__ Ws rep(int r) const
     {
         Ws w = *this;
-        w.hist += (size_t)r * HC_RADIX_BINS;
+        w.hist += (size_t)r * HC_HIST_WORDS;
         w.bitmap += (size_t)r * (max_ctx / 32);
         w.h2 += (size_t)r * area;
         w.h3 = w.h2 + HC_MAX_K_PER_REP * HC_RADIX_BINS;
@@ -206,11 +211,51 @@ __device__ __forceinline__ void find_digit(const uint32_t* hist, uint32_t k, uin
     count = lane_get(c, at);
 }
 
+// The same by a workgroup of NW waves, the answer in every thread: a wave sums its part of the digits (wave 0 the highest), one
+// barrier, then each finds part, lane and digit for itself, so that nothing has to be handed round.  (A wave by itself and
+// a barrier to tell the others took 0.2 us longer.)  part: LDS for NW words.
+template <int NW>
+__device__ __forceinline__ void find_digit_all(const uint32_t* hist, uint32_t* part, uint32_t k, uint32_t& digit, uint32_t& remaining, uint32_t& count)
+{
+    constexpr int PER = HC_RADIX_BINS / (NW * 64);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    auto span = [&](int w) { return hist + (HC_RADIX_BINS - (w * 64 + lane + 1) * PER); };      // a lane's digits, lane 0 the highest
+    uint32_t local = 0, tot;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) local += span(wv)[i];
+    tot = wave_sum(local);
+    if (lane == 0) part[wv] = tot;
+    __syncthreads();
+    const uint32_t mine = lane < NW ? part[lane] : 0u;
+    const uint32_t above = wave_exscan(mine, tot);
+    const uint64_t who = __builtin_amdgcn_ballot_w64(above < k && k <= above + mine);
+    const int w = who ? __builtin_ctzll(who) : 0;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) sum += c[i] = span(w)[i];
+    const uint32_t ab = lane_get(above, w) + wave_exscan(sum, tot);
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(ab < k && k <= ab + sum);
+    const int src = hit ? __builtin_ctzll(hit) : 0;
+    uint32_t before = lane_get(ab, src);
+    digit = (uint32_t)(HC_RADIX_BINS - (w * 64 + src + 1) * PER);
+    remaining = count = 0u;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+        const uint32_t here = lane_get(c[i], src);
+        if (before < k && k <= before + here) {
+            digit += (uint32_t)i;
+            remaining = k - before;
+            count = here;
+        }
+        before += here;
+    }
+}
+
 __global__ __launch_bounds__(256) void mon_prep(Ws ws)
 {
     const Ws w = ws.rep(blockIdx.y);
     const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < HC_RADIX_BINS; i += stride) w.hist[i] = 0u;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < HC_HIST_WORDS; i += stride) w.hist[i] = 0u;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < (size_t)ws.max_ctx / 32; i += stride) w.bitmap[i] = 0u;
 }
 
@@ -233,6 +278,17 @@ __device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j,
     }
     return hc_group_score<G>(l, lse, agg);
 }
+
+// ---- the histogram of a candidate range ----
+//
+// Scores are mostly probabilities, so the digits are spent on [2^-31, 2): 64 of them to an octave, each 1.1 to 1.6 % of a score
+// wide; the lowest takes everything below (negative scores and what is no number among them), the highest everything above.
+// The digit in which a list ends then holds a hundred or so of 32K candidates (of the key's first 11 bits, four to an
+// octave, thousands), unless scores are that close to each other.
+constexpr int FINE_BASE = (0x80000000u >> 17) + (96 << 6);      // the key of 2^-31, without its last 17 bits
+__device__ __forceinline__ uint32_t fine_digit(uint32_t key) { return (uint32_t)min(max((int)(key >> 17) - FINE_BASE, 0), HC_RADIX_BINS - 1); }
+__device__ __forceinline__ uint32_t fine_low(uint32_t digit) { return digit == 0u ? 0u : (digit + (uint32_t)FINE_BASE) << 17; }      // smallest key of a digit
+__device__ __forceinline__ uint32_t fine_last(uint32_t digit) { return digit == HC_RADIX_BINS - 1 ? 0xffffffffu : fine_low(digit + 1u) - 1u; }      // ... and the largest
 
 // ---- the survivors of a long range ----
 //
@@ -315,9 +371,9 @@ __device__ __forceinline__ void sample_threshold(uint32_t* sm_hist, uint32_t* sm
     row_out = sample_row(src * 64 + (bits ? __builtin_ctzll(bits) : 0), lo, n);
 }
 
-// Scores and first-digit histogram of a long candidate range.  A workgroup takes `span` consecutive chunks of
+// Scores and histogram of a long candidate range (over the first 11 bits of the keys unless mon_direct reads it).  A workgroup takes `span` consecutive chunks of
 // HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
-template <int G>
+template <int G, bool FINE>
 __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k)
 {
     __shared__ uint32_t sh[HC_RADIX_BINS];
@@ -333,7 +389,7 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
 #pragma unroll
     for (int g = 0; g < G; ++g) l[g] = (!scores_given && agg == HC_AGG_PROB) ? it.lse[(size_t)rd.bh * G + g] : 0.f;
     for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
-    if (long_lists) {                                // a slice each: the later histograms cleared, the baseline list to its bitmap
+    if (!FINE && long_lists) {                       // a slice each: the later histograms cleared, the baseline list to its bitmap
         const Ws w = it.ws.rep(rep);
         const int first = blockIdx.x * BLK + threadIdx.x, step = (rd.nchunk + span - 1) / span * BLK;
         const int lo = it.real_reps[rep].lo, hi = it.real_reps[rep].hi;
@@ -359,7 +415,8 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
             const int j = first + i * BLK + threadIdx.x;
             if (j < rd.hi) {
                 if (!scores_given) srow[j] = s[i];
-                atomicAdd(&sh[hc_score_key(s[i]) >> 21], 1u);
+                const uint32_t key = hc_score_key(s[i]);
+                atomicAdd(&sh[FINE ? fine_digit(key) : key >> 21], 1u);
             }
         }
     }
@@ -432,19 +489,34 @@ struct DriftCfg {
 
 // ---- the decision ----
 
-// Window update, decision, baseline update of a pivot, and the filter of the next step: by the whole workgroup (NT threads),
-// after the lists are written.  ring_of: thread i's word of the pivot's ring row; inter: |T ∩ baseline|; tmin: the
-// smallest list threshold, rows: how many rows the lists were taken from (both only for a filtering layer).
-template <int NT>
-__device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int rows, int k, const DriftCfg& cfg, int n_group, int32_t ring_of,
-                                       int32_t inter, uint32_t tmin, int32_t* sm_ring, int32_t& sm_med, int32_t& sm_trig)
+// What a decision needs of a pivot's ring row: how many values the window holds (the same in every lane), and value `lane`.
+struct RingRow {
+    int32_t count, value;
+};
+__device__ __forceinline__ RingRow ring_row(const MonItem& it, int bh, int window)
 {
-    const int tid = threadIdx.x;
+    const int32_t* rg = it.ring + (size_t)bh * (window + 1);
+    const int lane = threadIdx.x & 63;
+    RingRow r;
+    r.value = lane < window ? rg[1 + lane] : 0;
+    r.count = __builtin_amdgcn_readfirstlane(rg[0]);
+    return r;
+}
+
+// Window update, decision, baseline update of a pivot, and the filter of the next step: by the whole workgroup (NT threads),
+// after the lists are written.  inter: |T ∩ baseline|; tmin: the smallest list threshold, rows: how many rows the lists were
+// taken from (both only for a filtering layer), lse: of query head `lane` of the group (likewise).  Every wave decides for
+// itself, in registers (a window has at most 64 values, one to a lane), and the first writes it down: with the values and the
+// verdict passed through LDS, five barriers, this took 0.5 us longer.
+template <int NT>
+__device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int rows, int k, const DriftCfg& cfg, int n_group, const RingRow& row,
+                                       int32_t inter, uint32_t tmin, float lse)
+{
+    static_assert(HC_MAX_WINDOW <= 64, "a window's values, one to a lane");
+    const int tid = threadIdx.x, lane = tid & 63;
     int32_t* rg = it.ring + (size_t)bh * (cfg.window + 1);
     if (it.store_slot == -2) return;                 // the lists were all that was wanted
-    if (tid <= cfg.window) sm_ring[tid] = ring_of;
-    __syncthreads();
-    int cnt = sm_ring[0];
+    int cnt = row.count;
     if (cnt < 0 || cnt > cfg.window) cnt = 0;
     if (it.store_slot != -1) {
         // A buffered query of the window scored again at the test step (Algorithm 1): its overlap replaces
@@ -455,54 +527,52 @@ __device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int r
     }
     const int drop = cnt == cfg.window ? 1 : 0;      // sliding window: the oldest value leaves
     const int m = cnt - drop + 1;                    // values in the window after the push
-    // The lower median is found by ranking (no local arrays: they would live in scratch memory).
-    const int32_t value = tid < m ? (tid == m - 1 ? inter : sm_ring[1 + drop + tid]) : 0;
-    __syncthreads();
-    if (tid < m) sm_ring[tid] = value;
-    __syncthreads();
-    if (tid < m) {
-        const int32_t v = sm_ring[tid];
-        int rank = 0;
-        for (int j = 0; j < m; ++j) rank += sm_ring[j] < v || (sm_ring[j] == v && j < tid);
-        if (rank == (m - 1) / 2) sm_med = v;         // lower median
+    int32_t value = drop ? __shfl_down(row.value, 1) : row.value;
+    if (lane == m - 1) value = inter;
+    int rank = 0;
+    for (int j = 0; j < m; ++j) {                    // the lower median is found by ranking
+        const int32_t o = (int32_t)lane_get((uint32_t)value, j);
+        rank += o < value || (o == value && j < lane);
     }
-    __syncthreads();
-    if (tid < m) rg[1 + tid] = sm_ring[tid];
-    if (tid == 0) {
-        int trig = 0;
-        if (m == cfg.window) {
-            const long long med = sm_med, kl = k;
-            if (cfg.metric == HC_METRIC_OVERLAP)
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * kl;                     // med/k < tau
-            else
-                trig = med * cfg.tau_den < (long long)cfg.tau_num * (2 * kl - med);         // med/(2k-med) < tau
-        }
-        // the window restarts after a retrieval; a tumbling window after every test
-        rg[0] = (trig || (cfg.tumbling && m == cfg.window)) ? 0 : m;
-        it.inter[bh] = inter;
-        it.flag[bh] = trig;
-        sm_trig = trig;
-        if (it.counts) {
-            uint32_t* cn = it.counts + (size_t)rep * 4;
-            cn[0] += m == cfg.window;
-            cn[1] += (uint32_t)trig;
-            cn[2] += it.need_sense == 1;
-            cn[3] = it.need_sense == 0 ? (uint32_t)rows : 0xffffffffu;
+    const uint64_t middle = __builtin_amdgcn_ballot_w64(lane < m && rank == (m - 1) / 2);
+    const int32_t med = (int32_t)lane_get((uint32_t)value, middle ? __builtin_ctzll(middle) : 0);
+    bool trig = false;
+    if (m == cfg.window) {
+        const long long kl = k;
+        if (cfg.metric == HC_METRIC_OVERLAP)
+            trig = (long long)med * cfg.tau_den < (long long)cfg.tau_num * kl;                     // med/k < tau
+        else
+            trig = (long long)med * cfg.tau_den < (long long)cfg.tau_num * (2 * kl - med);         // med/(2k-med) < tau
+    }
+    if (tid < 64) {
+        if (lane < m) rg[1 + lane] = value;
+        if (lane == 0) {
+            // the window restarts after a retrieval; a tumbling window after every test
+            rg[0] = (trig || (cfg.tumbling && m == cfg.window)) ? 0 : m;
+            it.inter[bh] = inter;
+            it.flag[bh] = trig;
+            if (it.counts) {                         // (added without waiting for what was there)
+                uint32_t* cn = it.counts + (size_t)rep * 4;
+                atomicAdd(&cn[0], (uint32_t)(m == cfg.window));
+                atomicAdd(&cn[1], (uint32_t)trig);
+                atomicAdd(&cn[2], (uint32_t)(it.need_sense == 1));
+                cn[3] = it.need_sense == 0 ? (uint32_t)rows : 0xffffffffu;
+            }
         }
         if (it.filt) {
             // The filter of the next step's split pass: rows whose statistic, taken against this step's
             // log-sum-exp, stays below the smallest list threshold of this step divided by the margin are dropped.
             const float t = key_score(tmin);
-            RepFilter f;
-            f.cutsum = (t > 0.f && t < 1.0e30f && it.margin >= 1.f) ? (float)n_group * t / it.margin : 0.f;
-            for (int g = 0; g < 8; ++g) f.ref[g] = g < n_group ? it.lse[(size_t)bh * n_group + g] * 1.4426950408889634f : 0.f;
-            f.armed = 1;
-            for (int i = 0; i < 6; ++i) f.pad[i] = 0;
-            it.filt[rep] = f;
+            const float cutsum = (t > 0.f && t < 1.0e30f && it.margin >= 1.f) ? (float)n_group * t / it.margin : 0.f;
+            RepFilter* f = it.filt + rep;
+            if (lane < 8) f->ref[lane] = lane < n_group ? lse * 1.4426950408889634f : 0.f;
+            if (lane == 8) f->cutsum = cutsum;
+            if (lane == 9) f->armed = 1;
+            if (lane < 6) f->pad[lane] = 0;
         }
     }
-    __syncthreads();
-    if (sm_trig) {                                   // K_base <- K_t
+    if (trig) {                                      // K_base <- K_t
+        __syncthreads();                             // (the list is written)
         const int32_t* src = it.topk_idx + (size_t)bh * cfg.max_k;
         int32_t* base = it.base_idx + (size_t)bh * cfg.max_k;
         for (int i = tid; i < k; i += NT) base[i] = src[i];
@@ -576,8 +646,6 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
     __shared__ uint32_t sm_lo, sm_shift, sm_rem, sm_cnt, sm_tau, sm_need, sm_ties, sm_nlist;
     __shared__ uint32_t sm_min[NW], sm_max[NW], sm_hits[NW], sm_gt[NW], sm_eq[NW];
     __shared__ uint32_t sm_wsum[NW];
-    __shared__ int32_t sm_ring[HC_MAX_WINDOW + 1];
-    __shared__ int32_t sm_med, sm_trig;
 
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.x, ks = blockIdx.y;
@@ -597,11 +665,13 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;               // words of the baseline bitmap
     for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
     // what the decision needs from memory is asked for now
-    const int ring_of = deciding && it.store_slot != -2 && tid <= cfg.window ? it.ring[(size_t)rd.bh * (cfg.window + 1) + tid] : 0;
+    RingRow ring{0, 0};
+    if (deciding && it.store_slot != -2) ring = ring_row(it, rd.bh, cfg.window);
     const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
-    float ref_minus_lse = -INFINITY;                 // lane g: of query head g of the group, in log2 units
-    if (checks && lane < n_group) ref_minus_lse = it.filt[rep].ref[lane] - it.lse[(size_t)rd.bh * n_group + lane] * 1.4426950408889634f;
+    float ref_minus_lse = -INFINITY, lse_of = 0.f;   // lane g: of query head g of the group, the first in log2 units
+    if (deciding && it.filt && lane < n_group) lse_of = it.lse[(size_t)rd.bh * n_group + lane];
+    if (checks && lane < n_group) ref_minus_lse = it.filt[rep].ref[lane] - lse_of * 1.4426950408889634f;
     // the rows this list goes to, one to a lane
     uint32_t v_row = 0;
     int n_rows = -1;                                 // -1: too many for the lanes, looked up when they are needed
@@ -1074,7 +1144,431 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
     int32_t inter = 0;
 #pragma unroll
     for (int i = 0; i < NW; ++i) inter += (int32_t)sm_hits[i];
-    decide<NT>(it, rep, rd.bh, rd.hi, k, cfg, n_group, ring_of, inter, tmin, sm_ring, sm_med, sm_trig);
+    decide<NT>(it, rep, rd.bh, rd.hi, k, cfg, n_group, ring, inter, tmin, lse_of);
+}
+
+// ---- the selection straight from the scores ----
+//
+// For up to 64 K candidates (32 K beside the attention pass), and for the rows a filtering split pass kept: one workgroup per
+// pivot and set size, as mon_select, behind a launch that left the scores and their histogram.  The histogram names the digit
+// in which the list ends.  A wave then goes once through its run of the items, 1024 to a tile, 16 consecutive ones to a lane:
+// what lies above that digit is in the list, a bit per item (a compare and an add with carry each); what lies in it, a hundred
+// items or so, is ranked by counting in the order of the lists (score descending, index ascending), which leaves no ties to
+// resolve; and the list is written from the bits.  No keys are made, kept or moved.  Where the digit holds more than BAND items it
+// is cut again, over the scores.
+//
+// What bounds it is latency and issue: with 16 waves, an instruction that all of them execute takes 16 cycles of every SIMD.
+// (With the items 64 to a round, one to a lane, and ballots, going through 32K of them took 4.3 us of the launch.)
+// One pivot, three set sizes, us per call with the launch before it, scores spread out / within 2 % of each other / equal, and in
+// brackets by mon_compact and mon_select (and mon_score_hist): 10,000 candidates 17 / 21 / 23 (25 / 34 / 34), 32,768 21 / 30 / 35
+// (28 / 40 / 48), 65,000 26 / 43 / 54 (36 / 49 / 60).  The decode step of four 32K layers with a window of four: 125 us (145).
+constexpr int BAND = 512;                // items of the digit that can be ranked ...
+constexpr int RANKED = 128;              // ... without a histogram of their own
+constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
+
+template <int NT, bool MAP>
+__global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most)
+{
+    constexpr int NW = NT / 64, TILE = HC_SEL_CHUNK;
+    static_assert(TILE == 1024, "16 items to a lane");
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];       // [bufs][NW][TILE] scores, a bit per item, the baseline bitmap
+    __shared__ __attribute__((aligned(16))) uint32_t sm_hist[HC_RADIX_BINS];
+    __shared__ uint64_t sm_band[BAND];
+    __shared__ uint32_t sm_rank[RANKED], sm_part[NW], sm_count[NW], sm_eq[NW], sm_hits[NW], sm_nband, sm_nrank, sm_tau, sm_least, sm_most;
+
+    const MonItem& it = B.it[blockIdx.z];
+    const int rep = blockIdx.x, ks = blockIdx.y;
+    if (rep >= it.n_reps) return;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const Ws w = it.ws.rep(rep);
+    const RepDev rd = it.reps[rep];
+    const int need_of = it.need_sense >= 0 ? it.need[rep] : 0;
+    // (1 to 4: the pivot was handed on before it had a histogram; 5: by this launch's deciding workgroup)
+    if (ks >= rd.nk || (need_of != 0 && need_of != 5)) return;
+    const bool deciding = ks == 0;
+    const int max_ctx = it.ws.max_ctx;
+    // items are counted from a multiple of four positions, those from `first` to `end` - 1 are candidates
+    const int lo4 = rd.lo & ~3, first = rd.lo - lo4, end = min(rd.hi - lo4, most);     // (most: what the launch was sized for)
+    const float* srow = it.scores + (size_t)rep * max_ctx + lo4;
+    const int tiles = (end + TILE - 1) / TILE, per = (tiles + NW - 1) / NW;      // (at most DIRECT_TILES: the launch sees to it)
+    const int t0 = min(tiles, wv * per), t1 = min(tiles, t0 + per);
+
+    // everything from memory is asked for now
+    OutDev od{};
+    if (rd.out_count <= SEL_OUTS) od = it.outs[rd.out_begin + min(lane, rd.out_count - 1)];
+    const int k = it.reps[rep].k[ks];
+    int k_longest = 1;
+    for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
+    const int real_lo = it.real_reps[rep].lo & ~3, real_hi = it.real_reps[rep].hi;      // the bitmap is indexed by position
+    const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;
+    const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
+    const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
+    float ref_of = -INFINITY, lse_of = 0.f;          // lane g: of query head g of the group
+    if (deciding && it.filt && lane < n_group) lse_of = it.lse[(size_t)rd.bh * n_group + lane];
+    if (checks && lane < n_group) ref_of = it.filt[rep].ref[lane];
+    constexpr int HV = HC_RADIX_BINS / 4, HP = (HV + NT - 1) / NT;       // 16-byte pieces of the histogram, of a thread
+    uint4 h[HP];
+    if (!MAP) {
+#pragma unroll
+        for (int i = 0; i < HP; ++i) h[i] = reinterpret_cast<const uint4*>(w.hist)[min(i * NT + tid, HV - 1)];
+    }
+    RingRow ring{0, 0};
+    if (deciding && it.store_slot != -2) ring = ring_row(it, rd.bh, cfg.window);
+    // A tile goes straight to LDS, 16 bytes to a lane.  Lane o's items are pieces 4 o .. 4 o + 3 there, their order turned by o / 4, so
+    // that 16 lanes reading theirs find 16 different groups of banks.
+    auto buffer = [&](int t) { return dyn + ((t - t0) % bufs * NW + wv) * TILE; };
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int piece = (16 * j + (lane >> 2)) * 4 + ((lane & 3) ^ ((lane >> 4) & 3));
+            dma16(srow + min(t * TILE + piece * 4, (end - 1) & ~3), buffer(t) + j * 256);
+        }
+    };
+    for (int t = t0; t < min(t1, t0 + bufs); ++t) fetch(t);
+    // the rows this list goes to, one to a lane
+    uint32_t v_row = 0;
+    int n_rows = -1;                                 // -1: too many for the lanes, looked up when they are needed
+    if (rd.out_count <= SEL_OUTS) {
+        uint64_t rows = __builtin_amdgcn_ballot_w64(lane < rd.out_count && od.kslot == ks);
+        n_rows = __builtin_popcountll(rows);
+        for (int i = 0; rows != 0; ++i, rows &= rows - 1) {
+            const uint32_t row = lane_get((uint32_t)od.row, __builtin_ctzll(rows));
+            v_row = lane == i ? row : v_row;
+        }
+    }
+    uint32_t* sm_bits = dyn + bufs * NW * TILE;      // [tiles * 32]: chosen items
+    uint32_t* sm_bm = sm_bits + tiles * (TILE / 32);
+    constexpr int GROUP = NT == 512 ? 4 : 8;
+    const int32_t* base = it.base_idx + (size_t)rd.bh * cfg.max_k;
+    int j_base[GROUP];
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) j_base[u] = deciding && tid + u * NT < k ? base[tid + u * NT] : -1;
+    for (int i = tid; i < tiles * (TILE / 32) + bw; i += NT) sm_bits[i] = 0u;
+    if (tid < RANKED) sm_rank[tid] = 0u;
+    if (tid == 0) sm_nband = sm_nrank = 0u;
+    if (MAP) {
+        for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+    } else {
+#pragma unroll
+        for (int i = 0; i < HP; ++i)
+            if (i * NT + tid < HV) reinterpret_cast<uint4*>(sm_hist)[i * NT + tid] = h[i];
+    }
+    __syncthreads();
+    uint32_t ticket = 0;                             // (through with the histogram in memory; looked at in the end)
+    if (!MAP && tid == 0) ticket = atomicAdd(w.hist + HC_RADIX_BINS, 1u);
+    if (deciding) {                                  // baseline list -> bitmap
+        for (int i0 = tid;;) {
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u)
+                if (j_base[u] >= real_lo && j_base[u] < real_hi) atomicOr(&sm_bm[(j_base[u] - real_lo) >> 5], 1u << ((j_base[u] - real_lo) & 31));
+            i0 += GROUP * NT;
+            if (i0 - tid >= k) break;
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) j_base[u] = i0 + u * NT < k ? base[i0 + u * NT] : -1;
+        }
+    }
+    // tile t is in LDS and the wave may read it; and it has been read: its place may take the one `bufs` further on
+    auto arrived = [&](int t) {
+        if (t == t0 || bufs == 1 || t >= t0 + bufs) dma_wait();          // (at first: for all that are in flight)
+    };
+    auto leave = [&](int t) {
+        if (t + bufs < t1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+            fetch(t + bufs);
+        }
+    };
+    const int turn = (lane >> 2) & 3;
+    if (MAP) {                                       // few items, and digits of a few of them each: the histogram is made here
+        for (int t = t0; t < t1; ++t) {
+            arrived(t);
+            const float* tile = reinterpret_cast<const float*>(buffer(t));
+            const int left = end - t * TILE;
+#pragma unroll 4
+            for (int j = 0; j < 16; ++j) {           // (any order will do: this one finds all banks)
+                const int at = j * 64 + lane, i = (at & ~15) | ((((at >> 2) & 3) ^ ((at >> 6) & 3)) << 2) | (at & 3);
+                if (i < left) atomicAdd(&sm_hist[fine_digit(hc_score_key(tile[at]))], 1u);
+            }
+            leave(t);
+        }
+        if (per > bufs)
+            for (int t = t0; t < min(t1, t0 + bufs); ++t) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                fetch(t);
+            }
+        __syncthreads();
+    }
+
+    // ---- the digit in which the list ends: keys [lo, lo + wide], `count` items of which `rem` are in the list ----
+    uint32_t digit, rem, count, tmin = 0u;
+    if (deciding && it.filt && k_longest != k) {     // a bound from below will do for the filter
+        find_digit_all<NW>(sm_hist, sm_part, (uint32_t)k_longest, digit, rem, count);
+        tmin = fine_low(digit);
+        __syncthreads();
+    }
+    find_digit_all<NW>(sm_hist, sm_part, (uint32_t)k, digit, rem, count);
+    uint32_t lo = fine_low(digit), wide = fine_last(digit) - lo;         // (they do not reach beyond what was counted)
+    auto candidate = [&](int i) { return i >= first && i < end; };
+    while (count > BAND && wide != 0u) {             // (the same for every thread)
+        const uint32_t shift = wide < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(wide);      // wide >> shift < 2048
+        __syncthreads();
+        for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+        if (tid == 0) {
+            sm_least = 0xffffffffu;
+            sm_most = 0u;
+        }
+        __syncthreads();
+        uint32_t least = 0xffffffffu, greatest = 0u;
+        constexpr int U = NT == 512 ? 8 : 16;        // reads of a lane in flight
+        for (int i0 = t0 * TILE + lane; i0 < t1 * TILE; i0 += 64 * U) {
+            float x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = srow[min(i0 + u * 64, end - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t d = hc_score_key(x[u]) - lo;
+                const bool in = candidate(i0 + u * 64) && d <= wide;
+                least = in ? min(least, d) : least;
+                greatest = in ? max(greatest, d) : greatest;
+                const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+                const uint32_t one = m ? lane_get(d >> shift, __builtin_ctzll(m)) : 0u;
+                if (m == __builtin_amdgcn_ballot_w64(in && d >> shift == one)) {      // (equal scores: one sum instead of 64 in turn)
+                    if (m && lane == 0) atomicAdd(&sm_hist[one], (uint32_t)__builtin_popcountll(m));
+                } else if (in) {
+                    atomicAdd(&sm_hist[d >> shift], 1u);
+                }
+            }
+        }
+        least = ~wave_max(~least);
+        greatest = wave_max(greatest);
+        if (lane == 0) {
+            atomicMin(&sm_least, least);
+            atomicMax(&sm_most, greatest);
+        }
+        __syncthreads();
+        find_digit_all<NW>(sm_hist, sm_part, rem, digit, rem, count);
+        if (sm_least == sm_most) {                   // all equal: nothing left to cut
+            lo += sm_least;
+            wide = 0u;
+        } else {
+            wide = min((1u << shift) - 1u, wide - (digit << shift));
+            lo += digit << shift;
+        }
+    }
+
+    // ---- above it, in it, below it ----
+    uint32_t w0 = 0, w1 = 0;                         // a lane's items of tiles t0, t0 + 1 (16 bits each) and of t0 + 2, t0 + 3
+    const bool tied = count > BAND;                  // one key, more items than can be ranked
+    uint32_t e0 = 0, e1 = 0;                         // tied: the items with that key
+    // As floats the scores compare as their keys do, but for what is no number (below everything either way, unless `lo` is).
+    const bool plain = !tied && lo >= 0x80000000u && lo + wide < 0xff800000u;
+    const float f_lo = key_score(lo), f_hi = key_score(lo + wide + 1u);
+    for (int t = t0; t < t1; ++t) {
+        arrived(t);
+        const uint32_t* tile = buffer(t);
+        const int i0 = t * TILE + 16 * lane;
+        uint32_t above = 0, from = 0;
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            const float4 v = *reinterpret_cast<const float4*>(tile + lane * 16 + (q ^ turn) * 4);
+            const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int c = 3; c >= 0; --c) {
+                if (plain) {
+                    asm("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(above) : "s"(f_hi), "v"(x[c]) : "vcc");
+                    asm("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(from) : "s"(f_lo), "v"(x[c]) : "vcc");
+                } else {
+                    const uint32_t key = hc_score_key(x[c]);
+                    above = above + above + (key > lo + wide);
+                    from = from + from + (key >= lo);
+                }
+            }
+        }
+        // (of the lane's items, the candidates)
+        uint32_t valid = end - i0 >= 16 ? 0xffffu : end > i0 ? (1u << (end - i0)) - 1u : 0u;
+        if (first > i0) valid &= 0xffffu << (first - i0);
+        above &= valid;
+        uint32_t band = from & valid & ~above;
+        if (!tied) {
+            const int o = lane * 16;
+            for (; band != 0u; band &= band - 1u) {
+                const int c = __builtin_ctz(band);
+                const uint32_t at = atomicAdd(&sm_nband, 1u);
+                if (at < BAND)
+                    sm_band[at] = ((uint64_t)hc_score_key(__uint_as_float(tile[o + ((c >> 2) ^ turn) * 4 + (c & 3)])) << 32) | (uint32_t)~(i0 + c);
+            }
+        }
+        const int at = (t - t0) & 1 ? 16 : 0;
+        if (t - t0 < 2) {
+            w0 |= above << at;
+            e0 |= band << at;
+        } else {
+            w1 |= above << at;
+            e1 |= band << at;
+        }
+        leave(t);
+    }
+    // counts of a word's two tiles, in 16 bits each
+    auto counts = [](uint32_t x) { return (uint32_t)__builtin_popcount(x & 0xffffu) | (uint32_t)__builtin_popcount(x >> 16) << 16; };
+    auto total = [&]() { return wave_sum((uint32_t)(__builtin_popcount(w0) + __builtin_popcount(w1))); };
+    if (!tied) {
+        const uint32_t mine = total();
+        if (lane == 0) sm_count[wv] = mine;
+        __syncthreads();
+        auto choose = [&](uint64_t b) {
+            const int i = (int)~(uint32_t)b;
+            atomicOr(&sm_bits[i >> 5], 1u << (i & 31));
+            atomicAdd(&sm_count[(i / TILE) / per], 1u);
+        };
+        int m = (int)min(sm_nband, (uint32_t)BAND);
+        const uint64_t* list = sm_band;
+        if (m > RANKED) {                            // a histogram over the digit first (the tiles are done with: their place takes the rest)
+            uint64_t* rest = reinterpret_cast<uint64_t*>(dyn);
+            const uint32_t shift = wide < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(wide);
+            for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+            __syncthreads();
+            const uint64_t b = sm_band[min(tid, m - 1)];
+            const uint32_t d = ((uint32_t)(b >> 32) - lo) >> shift;
+            if (tid < m) atomicAdd(&sm_hist[d], 1u);
+            __syncthreads();
+            find_digit_all<NW>(sm_hist, sm_part, rem, digit, rem, count);
+            if (tid < m && d > digit) choose(b);
+            if (tid < m && d == digit) rest[atomicAdd(&sm_nrank, 1u)] = b;
+            __syncthreads();
+            list = rest;
+            m = (int)sm_nrank;
+        }
+        for (int m0 = 0; m0 < m; m0 += RANKED) {     // (once, unless hundreds are equal or nearly so)
+            // rank of the items m0 on: NT threads for all pairs
+            const int here = min(m - m0, RANKED), bits = here <= 1 ? 0 : 32 - __builtin_clz(here - 1);         // 2^bits >= here
+            const int item = tid & ((1 << bits) - 1), parts = NT >> bits, each = (m + parts - 1) / parts;
+            const int j0 = (tid >> bits) * each, j1 = min(m, j0 + each);
+            const uint64_t own = list[m0 + min(item, here - 1)];
+            uint32_t larger = 0;
+#pragma unroll 4
+            for (int j = j0; j < j1; ++j) larger += list[j] > own;
+            if (item < here && larger) atomicAdd(&sm_rank[item], larger);
+            __syncthreads();
+            if (tid < here) {
+                const uint64_t b = list[m0 + tid];
+                const uint32_t rank = sm_rank[tid];
+                if (rank < rem) choose(b);
+                if (rank == rem - 1u) sm_tau = (uint32_t)(b >> 32);
+                sm_rank[tid] = 0u;
+            }
+            __syncthreads();
+        }
+    } else {
+        // of the items with that key the first `rem`
+        uint32_t in0 = counts(e0), in1 = counts(e1), tot0, tot1;
+        in0 = wave_exscan(in0, tot0);
+        in1 = wave_exscan(in1, tot1);
+        if (lane == 0) sm_eq[wv] = (tot0 & 0xffffu) + (tot0 >> 16) + (tot1 & 0xffffu) + (tot1 >> 16);
+        __syncthreads();
+        uint32_t before = 0;
+        for (int i = 0; i < wv; ++i) before += sm_eq[i];
+        auto first_of = [&](uint32_t e, uint32_t ahead) {                // those of e's items that are among the first `rem`
+            const uint32_t take = rem > ahead ? rem - ahead : 0u;
+            if (take == 0u) return 0u;
+            while ((uint32_t)__builtin_popcount(e) > take) e &= ~(0x80000000u >> __builtin_clz(e));
+            return e;
+        };
+        const uint32_t b1 = before + (tot0 & 0xffffu), b2 = b1 + (tot0 >> 16), b3 = b2 + (tot1 & 0xffffu);
+        w0 |= first_of(e0 & 0xffffu, before + (in0 & 0xffffu)) | first_of(e0 & 0xffff0000u, b1 + (in0 >> 16));
+        w1 |= first_of(e1 & 0xffffu, b2 + (in1 & 0xffffu)) | first_of(e1 & 0xffff0000u, b3 + (in1 >> 16));
+        const uint32_t mine = total();
+        if (lane == 0) sm_count[wv] = mine;
+        if (tid == 0) sm_tau = lo;
+        __syncthreads();
+    }
+    const uint32_t tau = sm_tau;
+    if (k_longest == k) tmin = tau;
+
+    bool decided_elsewhere = false;
+    if (checks && cutsum > 0.f) {                    // the check of this step's filter: see mon_select
+        const float d = exp2f(ref_of - lse_of * 1.4426950408889634f);
+        float delta = 0.f;
+        for (int g = 0; g < n_group; ++g) delta = fmaxf(delta, __uint_as_float(lane_get(__float_as_uint(d), g)));
+        const float bound = cutsum / (float)n_group * delta * 1.0001f;
+        if (!(key_score(tmin) >= bound)) {
+            decided_elsewhere = true;
+            if (tid == 0) it.need[rep] = 5;
+        }
+    }
+
+    uint32_t hits = 0;
+    if (!decided_elsewhere) {
+        // ---- the list, and |T ∩ baseline|: item numbers to LDS (in the tiles' place), from there to the rows ----
+        uint32_t out = 0;
+        for (int i = 0; i < wv; ++i) out += sm_count[i];
+        const uint16_t* half = reinterpret_cast<const uint16_t*>(sm_bits);           // a lane's items of tile t: half[64 t + lane]
+        const int32_t* pmap = MAP ? it.pos_map + (size_t)rep * max_ctx + lo4 : nullptr;
+        const uint32_t room = (uint32_t)(bufs * NW * TILE);
+        for (uint32_t from = 0; from < (uint32_t)k; from += room) {      // (once, but for lists of more than 8,192 or 16,384)
+            uint32_t before = out;
+            for (int t = t0; t < t1; ++t) {
+                const uint32_t x = t - t0 < 2 ? w0 : w1;
+                uint32_t bits = ((t - t0) & 1 ? x >> 16 : x & 0xffffu) | half[t * 64 + lane], all;
+                uint32_t at = before - from + wave_exscan((uint32_t)__builtin_popcount(bits), all);
+                before += all;
+                const int i0 = t * TILE + 16 * lane;
+                if (!MAP && deciding && from == 0u)
+                    hits += (uint32_t)__builtin_popcount(bits & (i0 < end ? sm_bm[i0 >> 5] >> (i0 & 16) : 0u));      // (an item's number is its bit of the bitmap)
+                for (; bits != 0u; bits &= bits - 1u, ++at)
+                    if (at < room) dyn[at] = (uint32_t)(i0 + __builtin_ctz(bits));
+            }
+            if (!MAP && deciding && from == 0u) {
+                hits = wave_sum(hits);
+                if (lane == 0) sm_hits[wv] = hits;
+            }
+            __syncthreads();
+            const int n_out = (int)min((uint32_t)k - from, room);
+            for (int i0 = tid; i0 < n_out; i0 += GROUP * NT) {
+                int pos[GROUP];
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) pos[u] = min((int)dyn[min(i0 + u * NT, n_out - 1)], end - 1);        // (the limit keeps a corrupt state in bounds)
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) pos[u] = MAP ? pmap[pos[u]] : lo4 + pos[u];
+                if (MAP && deciding) {
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) {
+                        const int jj = min(max(pos[u], real_lo), real_hi - 1) - real_lo;
+                        if (i0 + u * NT < n_out) hits += (sm_bm[jj >> 5] >> (jj & 31)) & 1u;
+                    }
+                }
+                auto store = [&](int row) {
+                    int32_t* list = it.topk_idx + (size_t)row * cfg.max_k + from;
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u)
+                        if (i0 + u * NT < n_out) list[i0 + u * NT] = pos[u];
+                };
+                if (n_rows >= 0) {
+                    for (int o = 0; o < n_rows; ++o) store((int)lane_get(v_row, o));
+                } else {
+                    for (int o = 0; o < rd.out_count; ++o)
+                        if (it.outs[rd.out_begin + o].kslot == ks) store(it.outs[rd.out_begin + o].row);
+                }
+            }
+            if (from + room < (uint32_t)k) __syncthreads();
+        }
+    }
+    if (deciding && !decided_elsewhere) {
+        if (MAP) {
+            hits = wave_sum(hits);
+            if (lane == 0) sm_hits[wv] = hits;
+            __syncthreads();
+        }
+        int32_t inter = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) inter += (int32_t)sm_hits[i];
+        decide<NT>(it, rep, rd.bh, rd.hi, k, cfg, n_group, ring, inter, tmin, lse_of);
+    }
+    // ---- the next call finds the histogram clear: the last of the pivot's workgroups to have read it sees to it ----
+    if (!MAP && wv == 0 && __builtin_amdgcn_readfirstlane((int)ticket) == rd.nk - 1) {
+        for (int i = lane; i < HV; i += 64) reinterpret_cast<uint4*>(w.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (lane == 0) w.hist[HC_RADIX_BINS] = 0u;
+    }
 }
 
 // ---- long lists ----
@@ -1353,8 +1847,6 @@ __global__ __launch_bounds__(BLK, 8) void mon_write(MonBatch B, DriftCfg cfg, in
 // A workgroup per pivot, behind mon_write.
 __global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int n_group)
 {
-    __shared__ int32_t sm_ring[HC_MAX_WINDOW + 1];
-    __shared__ int32_t sm_med, sm_trig;
     __shared__ uint32_t sm_hits[NWAVE];
     const MonItem& it = B.it[blockIdx.y];
     const int rep = blockIdx.x, tid = threadIdx.x;
@@ -1363,7 +1855,9 @@ __global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int 
     const bool elsewhere = it.need_sense == 0 && it.need[rep] != 0;
     const RepDev rd = it.reps[rep];
     const Ws w = it.ws.rep(rep);
-    const int32_t ring_of = it.store_slot != -2 && tid <= cfg.window ? it.ring[(size_t)rd.bh * (cfg.window + 1) + tid] : 0;
+    RingRow ring{0, 0};
+    if (it.store_slot != -2) ring = ring_row(it, rd.bh, cfg.window);
+    const float lse_of = it.filt && (tid & 63) < n_group ? it.lse[(size_t)rd.bh * n_group + (tid & 63)] : 0.f;
     uint32_t h = 0;
     if (!elsewhere)
         for (int c = tid; c < chunks_from_lo4(rd); c += BLK) h += w.hits[c];
@@ -1378,8 +1872,7 @@ __global__ __launch_bounds__(BLK) void mon_decide(MonBatch B, DriftCfg cfg, int 
     uint32_t tmin = 0xffffffffu;
     if (it.filt)
         for (int ks = 0; ks < rd.nk; ++ks) tmin = min(tmin, w.sel[ks * 4]);
-    decide<BLK>(it, rep, rd.bh, rd.hi, rd.k[0], cfg, n_group, ring_of, (int32_t)(sm_hits[0] + sm_hits[1] + sm_hits[2] + sm_hits[3]), tmin, sm_ring, sm_med,
-                sm_trig);
+    decide<BLK>(it, rep, rd.bh, rd.hi, rd.k[0], cfg, n_group, ring, (int32_t)(sm_hits[0] + sm_hits[1] + sm_hits[2] + sm_hits[3]), tmin, lse_of);
 }
 
 // Scores of the rows a filtering split pass kept.  They lie segment by segment in the pivot's block of rep_logits
@@ -1488,6 +1981,35 @@ static bool select_small(const hc_ctx* ctx, int items)
     return ctx->beside_now && ctx->G < 8 && items <= SEL_KEYS(select_room<512>(ctx) / 4);
 }
 
+// mon_direct: up to as many items as its waves have bits for, if tiles and bitmaps fit in LDS beside what it declares.
+constexpr int DIRECT_STATIC = 14 * 1024;
+static int direct_threads(const hc_ctx* ctx) { return ctx->beside_now ? 512 : 1024; }
+static int direct_room(const hc_ctx* ctx)
+{
+    return (!ctx->beside_now ? 156 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - DIRECT_STATIC;
+}
+static int direct_bytes(const hc_ctx* ctx, int items, int bm_words, int bufs)
+{
+    const int tiles = (items + 3 + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;     // (items are counted from a multiple of four positions)
+    return 4 * (bufs * direct_threads(ctx) / 64 * HC_SEL_CHUNK + tiles * (HC_SEL_CHUNK / 32) + bm_words + 2);
+}
+static bool direct_fits(const hc_ctx* ctx, int items, int bm_words)
+{
+    return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 1) <= direct_room(ctx);
+}
+template <bool MAP>
+static hc_status launch_direct(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
+{
+    const int bufs = items + 3 > direct_threads(ctx) / 64 * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 2) <= direct_room(ctx) ? 2 : 1;
+    const unsigned lds = (unsigned)direct_bytes(ctx, items, bm_words, bufs);
+    if (direct_threads(ctx) == 512)
+        mon_direct<512, MAP><<<grid, dim3(512), hc_side_lds(ctx, (const void*)mon_direct<512, MAP>, lds), st>>>(B, dc, ctx->G, bufs, items + 3);
+    else
+        mon_direct<1024, MAP><<<grid, dim3(1024), hc_side_lds(ctx, (const void*)mon_direct<1024, MAP>, lds), st>>>(B, dc, ctx->G, bufs, items + 3);
+    HC_HIP(ctx, hipGetLastError());
+    return HC_OK;
+}
+
 // Launches mon_select over the batch, with LDS for want_keys items and a baseline bitmap of bm_words as far as it goes.
 template <int NT, int SRC>
 static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
@@ -1547,7 +2069,8 @@ static hc_status launch_long(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc,
 
 // Candidates up to which one workgroup per pivot does everything, from the scores on.  What lies against more is that
 // the exponentials of the scores are then made by one compute unit: at 32K candidates and a group of four this takes 18
-// of 44 us, where the three launches take 29 in all; at 4K it takes 3.5 us of 13, where two more launches cost 8.
+// of 44 us, where two launches take 21 in all; at 4K it takes 3.5 us of 13.5, two launches 14.5 (at 8K 16.4 and 15.3 with scores spread
+// out, 16.5 and 21 within 2 % of each other).
 constexpr int SELECT_DIRECT = 8192;
 // Survivors (as the sample would let through) up to which one workgroup per list beats the six launches of long lists, with
 // the sample in front of it where it is needed.  131,072 candidates, scores spread out / within 2 % / equal: a longest list of 8,192
@@ -1566,7 +2089,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
 {
     const hc_config& c = ctx->cfg;
     MonBatch B{};
-    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0, max_k = 1;
+    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0, max_k = 1, candidates = 0;
     bool armed = true;
     for (int i = 0; i < n; ++i) {
         const hc_monitor_call& x = *calls[i];
@@ -1588,7 +2111,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         it.store_slot = x.store_slot;
         it.need_sense = -1;
         if (!x.reps && x.store_slot == -1) it.counts = x.L->mon_counts;
-        int nchunk = x.reps ? x.max_nchunk : x.L->max_nchunk;
+        int nchunk = x.reps ? x.max_nchunk : x.L->max_nchunk, cand = x.reps ? x.max_cand : x.L->max_cand;
         max_real_chunk = std::max(max_real_chunk, nchunk);
         if (mode != 0) {
             const hc_layer* L = x.L;
@@ -1610,11 +2133,13 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
                 const int armed_cap = std::min(c.max_ctx, (ctx->filter_margin <= 1.5f ? 2 : 4) * L->max_k_any + 4096);
                 it.cap_rows = L->filter_armed ? armed_cap : c.max_ctx;
                 armed = armed && L->filter_armed;
+                cand = std::min(cand, it.cap_rows);
                 nchunk = std::min(nchunk, (it.cap_rows + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK);
             }
         }
         max_reps = std::max(max_reps, it.n_reps);
         max_nchunk = std::max(max_nchunk, nchunk);
+        candidates = std::max(candidates, cand);
         max_nk = std::max(max_nk, x.reps ? x.max_nk : x.L->max_nk);
         max_k = std::max(max_k, x.reps ? c.max_k : x.L->max_k_any);
         if (m.dirty && mode != 2) {     // a previous call that used this workspace copy did not run to its last kernel
@@ -1628,6 +2153,9 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     const dim3 gsel(max_reps, max_nk, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
+    // mon_direct wherever it has room: at every length and distribution it takes less than mon_compact and mon_select (see there).
+    // (candidates: of a filtering layer, what its launches are sized for)
+    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words);
     if (mode == 1) {
         // enough waves for a segment each of a long context's few hundred, no more workgroups than compute units
         const dim3 g(std::max(4, std::min(armed ? 32 : 128, (armed ? 256 : 1024) / pivots)), max_reps, n);
@@ -1640,7 +2168,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         HC_HIP(ctx, hipGetLastError());
     }
     if (mode != 0) scores_given = 1;                     // they are there from here on
-    const int candidates = max_nchunk * HC_SEL_CHUNK;
+    if (mode == 1 && direct) return launch_direct<true>(ctx, B, dc, gsel, candidates, bm_words, st);
     // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
     // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
     const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
@@ -1652,20 +2180,28 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     }
     int survivors, most;
     expected_survivors(max_k, candidates, &survivors, &most);
-    const bool long_lists = survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap;
+    const bool long_lists = !direct && (survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap);
     if (mode != 2 || long_lists) {
         // Chunks per workgroup, at most 8: about 2048 workgroups per launch (a call over eight sequences of 9K to 131K takes
         // 36 us with one chunk each, 37, 41, 50 with two, four, eight; one of 32K 28, 29, 32, 39), beside the attention pass
         // 512.  (The launches that stand by: few, long workgroups.)
         const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
-        switch (ctx->G) {
-        case 1: mon_score_hist<1><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<1>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
-        case 2: mon_score_hist<2><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<2>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
-        case 4: mon_score_hist<4><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<4>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
-        default: mon_score_hist<8><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<8>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k); break;
+#define HC_SCORE(GG, FINE)                                                                                                   \
+    mon_score_hist<GG, FINE><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, FINE>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k)
+        switch (ctx->G * 2 + direct) {
+        case 2: HC_SCORE(1, false); break;
+        case 3: HC_SCORE(1, true); break;
+        case 4: HC_SCORE(2, false); break;
+        case 5: HC_SCORE(2, true); break;
+        case 8: HC_SCORE(4, false); break;
+        case 9: HC_SCORE(4, true); break;
+        case 16: HC_SCORE(8, false); break;
+        default: HC_SCORE(8, true); break;
         }
+#undef HC_SCORE
         HC_HIP(ctx, hipGetLastError());
+        if (direct) return launch_direct<false>(ctx, B, dc, gsel, candidates, bm_words, st);
         if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
     }
     // The small form where all that may survive fits, and what is expected fits with the baseline bitmap (without the bitmap in LDS
@@ -1731,10 +2267,12 @@ hc_status hc_monitor_set_lds_limit()
 {
     // mon_select takes most of a compute unit's LDS, and beside the attention pass every kernel here reserves more
     // than half of it (hc_side_lds)
-    const void* fns[] = {(const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
+    const void* fns[] = {(const void*)mon_direct<512, false>, (const void*)mon_direct<512, true>, (const void*)mon_direct<1024, false>,
+                         (const void*)mon_direct<1024, true>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
                          (const void*)mon_compact, (const void*)mon_sparse_score<1>,
                          (const void*)mon_sparse_score<2>, (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>,
-                         (const void*)mon_score_hist<1>, (const void*)mon_score_hist<2>, (const void*)mon_score_hist<4>, (const void*)mon_score_hist<8>,
+                         (const void*)mon_score_hist<1, false>, (const void*)mon_score_hist<2, false>, (const void*)mon_score_hist<4, false>, (const void*)mon_score_hist<8, false>,
+                         (const void*)mon_score_hist<1, true>, (const void*)mon_score_hist<2, true>, (const void*)mon_score_hist<4, true>, (const void*)mon_score_hist<8, true>,
                          (const void*)mon_select<512, SRC_LOGITS, 1>, (const void*)mon_select<512, SRC_LOGITS, 2>,
                          (const void*)mon_select<512, SRC_LOGITS, 4>,
                          (const void*)mon_select<512, SRC_SCORES, 1>, (const void*)mon_select<512, SRC_SURVIVORS, 1>, (const void*)mon_select<512, SRC_RANGE, 1>,

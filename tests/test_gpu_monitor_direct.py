@@ -1,0 +1,100 @@
+"""The selection straight from the scores (8,193 to 65,533 candidates, 32,765 beside the attention pass) at the edges of what
+its workgroup takes: tiles of 1024 items, first candidates at any remainder of four, digits of every kind (the lowest, which takes
+what is below 2^-31, negative or no number, the highest, digits with more items than are ranked at once or at all), lists longer
+than its LDS.  Lists, overlaps and decisions bit for bit.  Run with `-m gpu` on an MI355X."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_13684_amd import binding as hc
+from paper_2601_13684_amd import inputs as I
+from paper_2601_13684_amd import runtime as R
+
+import test_gpu_parity as T
+from test_gpu_monitor_paths import one_pivot
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def draw(kind, N, rng):
+    x = {"spread": lambda: np.exp(rng.normal(size=N)) / N,
+         "tiny": lambda: np.exp(rng.normal(size=N)) * 1e-12,                     # all in the lowest digit
+         "large": lambda: np.exp(rng.normal(size=N)) * 1e3,                      # all in the highest
+         "signed": lambda: rng.normal(size=N),
+         "flat": lambda: np.exp(rng.normal(size=N) * 0.002) / N,                 # one or two digits
+         "ulps": lambda: (1.0 + rng.integers(0, 300, N) * 2.0 ** -23) / 8,       # one digit, 300 values
+         "band": lambda: np.where(np.arange(N) % 53 == 0, 0.25 + rng.random(N) * 1e-3, rng.random(N) / 8),      # hundreds in the digit
+         "equal": lambda: np.full(N, 0.25),
+         "zeros": lambda: np.where(rng.random(N) < 0.3, rng.random(N), np.where(rng.random(N) < 0.5, 0.0, -0.0))}
+    if kind == "special":
+        s = np.exp(rng.normal(size=N)).astype(np.float32)
+        for v in (np.nan, np.inf, -np.inf, -0.0):
+            s[rng.choice(N, N // 16, replace=False)] = v
+        return s
+    return x[kind]().astype(np.float32)
+
+
+@pytest.mark.parametrize("n,rs,sink,kind", [(8193, (700, 3), 5, "spread"), (8193, (8193, 1), 4, "signed"), (9215, (1024, 1023), 1, "band"), (9217, (2000,), 2, "tiny"),
+                                            (10241, (10000, 17), 3, "large"), (16384, (4097, 5), 0, "special"), (16385, (600, 1), 7, "ulps"), (20011, (12000, 300), 6, "zeros"),
+                                            (24576, (500, 513), 5, "flat"), (32765, (3000, 128, 129), 0, "spread"), (32768, (17000, 16384), 3, "spread"),
+                                            (32769, (2000, 40), 3, "equal"), (40001, (3999, 1), 2, "band"), (65533, (7000, 33, 1), 3, "spread"), (65533, (40000, 9), 1, "flat"),
+                                            (65533, (5000,), 3, "equal"), (65534, (5000, 7), 3, "spread")])
+def test_given_scores(n, rs, sink, kind):
+    T.say("monitor direct", n, rs, sink, kind)
+    N = n + sink + 7
+    spec = one_pivot(N, rs, sink=sink)
+    rng = np.random.default_rng(n + len(rs))
+    s = draw(kind, N, rng)
+    lo, hi = spec.cand_range(0, 0)
+    assert hi - lo == n
+    base = {(0, 0): torch.from_numpy(np.sort(rng.choice(np.arange(lo, hi), spec.k_mon(0, 0), replace=False)).astype(np.int32))}
+    ctx, gpu, base_all = T.monitor_case(spec, {(0, 0): s}, base)
+    s = np.where(np.isnan(s), np.float32(-np.inf), s)       # the oracle takes no NaN; no list here reaches down to them
+    for call in range(3):                       # what a call leaves behind in the workspace does not reach the next
+        T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
+        gpu.base_idx[0, :len(base_all[(0, 0)])] = base_all[(0, 0)].to(DEV)
+        gpu.ring.zero_()
+        gpu.monitor(scores_given=True)
+        torch.cuda.synchronize()
+    T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
+    gpu.close()
+    ctx.close()
+
+
+# beside the attention pass, with a side stream: the 512-thread form up to its limit, and kept rows with a map to their
+# positions, the monitored list shorter than the longest
+@pytest.mark.parametrize("N,margin,k_mon", [(9001, 0.0, 0), (32768 + 317, 0.0, 0), (32768 + 320, 0.0, 0), (60001, 1.25, 0), (60001, 1.25, 300), (100003, 1.5, 0)])
+def test_beside_the_attention_pass_like_alone(N, margin, k_mon):
+    T.say("monitor direct beside", N, margin, k_mon)
+    tables = []
+    for beside in (True, False):
+        ws = [I.make_workload(2, layer=l, N=N) for l in range(2)]
+        for w in ws if k_mon else ():
+            heads = w.spec.heads[0]
+            heads[:] = [dataclasses.replace(h, k_mon=k_mon) if h.role == I.ROLE_FULL else h for h in heads]
+        ctx = R.Context(R.make_config(ws[0].spec), DEV, filter_margin=margin)
+        lists = [I.initial_lists(w.spec) for w in ws]
+        layers = [R.LayerRuntime(ctx, w.spec, w.data, *l, own_scratch=True) for w, l in zip(ws, lists)]
+        q = torch.zeros((2, 1, 32, 128), dtype=torch.bfloat16, device=DEV)
+        io = R.make_step_io(layers, q)
+        side = torch.cuda.Stream()
+        seen = []
+        for t in range(5):
+            q.copy_(torch.stack([w.schedule.next() for w in ws]).to(DEV))
+            if beside:
+                hc.hc_decode_step(ctx.handle, io, 2, None, side, 1)
+            else:
+                for lay, x in zip(layers, q):
+                    lay.step(x)
+            torch.cuda.synchronize()
+            seen.append([x.cpu().numpy().copy() for lay in layers for x in (lay.topk_idx, lay.base_idx, lay.ring, lay.inter, lay.flag, lay.slot_pos, lay.out)])
+        tables.append(seen)
+        for lay in layers:
+            lay.close()
+        ctx.close()
+    for t, (a, b) in enumerate(zip(*tables)):
+        for i, (x, y) in enumerate(zip(a, b)):
+            np.testing.assert_array_equal(x, y, err_msg=f"step {t} table {i}")

@@ -90,3 +90,10 @@ def test_side_kernels_fit_beside_two_attention_workgroups(kernels):
     for part in small:
         for n, k in of(kernels, part).items():
             assert k["regs"] * k["threads"] // 256 <= left, (n, k)
+
+
+def test_direct_selection_fits_beside_two_attention_workgroups(kernels):
+    for n, k in of(kernels, "mon_directILi512E").items():
+        assert k["regs"] * k["threads"] // 256 <= SIMD_REGS - 2 * 216, (n, k)
+    for n, k in of(kernels, "mon_direct").items():               # what its launches allow for
+        assert k["lds"] <= 14 * 1024, (n, k)
