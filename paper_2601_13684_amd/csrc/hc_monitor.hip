@@ -12,7 +12,7 @@
 // everything after the scores is ONE kernel, mon_select, with one workgroup per pivot and set size that keeps the keys
 // of its items in LDS: threshold, ordered lists, |T ∩ baseline| through a bitmap in LDS, window, decision and
 // baseline update.  What reaches it:
-//   short candidate ranges   mon_select scores the candidates itself: one launch
+//   short candidate ranges   mon_direct scores the candidates itself: one launch
 //   up to 64K candidates (32K beside the attention pass)
 //                            mon_score_hist (scores and their histogram; many workgroups per pivot), mon_direct (the lists straight
 //                            from the scores, no keys in LDS): two launches
@@ -32,7 +32,7 @@
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
 // histograms, counts, ordered write, decision): one 32K layer 20.5 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 33-36 instead of 81 us, the decode step of one 4K layer 28 instead of 49 us.
+// 131K 33-36 instead of 81 us, the decode step of one 4K layer 27 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
@@ -261,9 +261,8 @@ __global__ __launch_bounds__(256) void mon_prep(Ws ws)
 
 // Score of candidate j from the G scaled logits of its row (rep_logits is [ctx][G] per pivot).
 template <int G>
-__device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j, const float (&lse)[G], int agg)
+__device__ __forceinline__ void load_row(const float* __restrict__ lrow, int j, float (&l)[G])
 {
-    float l[G];
     if (G == 1) {
         l[0] = lrow[j];
     } else if (G == 2) {
@@ -276,6 +275,12 @@ __device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j,
             l[4 * q] = v.x; l[4 * q + 1] = v.y; l[4 * q + 2] = v.z; l[4 * q + 3] = v.w;
         }
     }
+}
+template <int G>
+__device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j, const float (&lse)[G], int agg)
+{
+    float l[G];
+    load_row<G>(lrow, j, l);
     return hc_group_score<G>(l, lse, agg);
 }
 
@@ -582,9 +587,8 @@ __device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int r
 // ---- the selection ----
 //
 // One workgroup per pivot and set size (blockIdx.y); the one of set size 0, the monitored list, also takes the
-// decision.  Items are the pivot's candidates in position order: SRC_LOGITS scores them from the stored logits,
-// SRC_SCORES finds their scores in place (given by the caller, or of the rows a filtering split pass kept, whose
-// positions pos_map names), SRC_SURVIVORS takes what mon_compact left, SRC_RANGE cuts the range down itself.  Their keys are kept in LDS: `cap` of them;
+// decision.  Items are the pivot's candidates in position order: SRC_SCORES finds their scores in place (of the rows a
+// filtering split pass kept, whose positions pos_map names, or of a short range), SRC_SURVIVORS takes what mon_compact left, SRC_RANGE cuts the range down itself.  Their keys are kept in LDS: `cap` of them;
 // items beyond that are read again from the scores in every pass, so that any number of items is handled.  (Survivors
 // that are fewer than the longest list or do not all fit, about one sample in a million, are given up for the range.)
 //
@@ -598,7 +602,7 @@ __device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int r
 // used, and set sizes go to workgroups of their own because the passes behind the histogram cost the same for each
 // of them (one workgroup for all: 97 us for 16,700 rows and three set sizes with 256 threads; one each: 43; with 512
 // threads of half the registers, two waves per SIMD: 28).
-enum { SRC_LOGITS = 0, SRC_SCORES = 1, SRC_SURVIVORS = 2, SRC_RANGE = 3 };
+enum { SRC_SCORES = 1, SRC_SURVIVORS = 2, SRC_RANGE = 3 };
 constexpr int SEL_LIST = 128;        // members of a threshold bin that are ranked by counting
 
 constexpr int SEL_KEYS(int words) { return words / 264 * 256; }           // keys, with their masks, that fit in so many words (whole 256s)
@@ -636,7 +640,7 @@ __device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n,
     }
 }
 
-template <int NT, int SRC, int G>
+template <int NT, int SRC>
 __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
 {
     constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
@@ -765,26 +769,7 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
         kmin = min(kmin, key);
         kmax = max(kmax, key);
     };
-    if (SRC == SRC_LOGITS) {
-        const float* lrow = it.rep_logits + (size_t)rep * G * max_ctx;
-        float l[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) l[g] = cfg.agg == HC_AGG_PROB ? it.lse[(size_t)rd.bh * G + g] : 0.f;
-        constexpr int U = (NT == 512 ? 2 : 4) / (G >= 8 ? 2 : 1);
-        for (int i0 = tid; i0 < n; i0 += U * NT) {
-            float s[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) s[u] = score_of<G>(lrow, rd.lo + min(i0 + u * NT, n - 1), l, cfg.agg);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * NT;
-                if (i < n) {
-                    if (deciding || !fits) srow[rd.lo + i] = s[u];
-                    put(i, hc_score_key(s[u]));
-                }
-            }
-        }
-    } else if (SRC >= SRC_SURVIVORS && surv) {
+    if (SRC >= SRC_SURVIVORS && surv) {
         // the survivors' rows of the range, then in their places their keys; the positions go to a table
         for (int m = m_begin; m < m_end; ++m)
             for (uint64_t bits = w.mask[m]; bits != 0; bits &= bits - 1) sm_key[first_item++] = (uint32_t)(m * 64 + __builtin_ctzll(bits));
@@ -1150,8 +1135,9 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 // ---- the selection straight from the scores ----
 //
 // For up to 64 K candidates (32 K beside the attention pass), and for the rows a filtering split pass kept: one workgroup per
-// pivot and set size, as mon_select, behind a launch that left the scores and their histogram.  The histogram names the digit
-// in which the list ends.  A wave then goes once through its run of the items, 1024 to a tile, 16 consecutive ones to a lane:
+// pivot and set size, as mon_select, behind a launch that left the scores and their histogram (DIRECT_HIST), behind
+// mon_sparse_score (DIRECT_MAP: kept rows), or by itself over a short range (DIRECT_LOGITS, or DIRECT_SCORES where the scores
+// are given).  The histogram names the digit in which the list ends.  A wave then goes once through its run of the items, 1024 to a tile, 16 consecutive ones to a lane:
 // what lies above that digit is in the list, a bit per item (a compare and an add with carry each); what lies in it, a hundred
 // items or so, is ranked by counting in the order of the lists (score descending, index ascending), which leaves no ties to
 // resolve; and the list is written from the bits.  No keys are made, kept or moved.  Where the digit holds more than BAND items it
@@ -1161,15 +1147,18 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 // (With the items 64 to a round, one to a lane, and ballots, going through 32K of them took 4.3 us of the launch.)
 // One pivot, three set sizes, us per call with the launch before it, scores spread out / within 2 % of each other / equal, and in
 // brackets by mon_compact and mon_select (and mon_score_hist): 10,000 candidates 17 / 21 / 23 (25 / 34 / 34), 32,768 21 / 30 / 35
-// (28 / 40 / 48), 65,000 26 / 43 / 54 (36 / 49 / 60).  The decode step of four 32K layers with a window of four: 125 us (145).
+// (28 / 40 / 48), 65,000 26 / 43 / 54 (36 / 49 / 60).  By itself, 4,096 candidates 12.2 / 12.3 / 12.0 (mon_select over keys 13.4 / 13.7 /
+// 11.7), 8,192 15.4 / 15.2 / 14.3 (16.5 / 16.6 / 16.2).  The decode step of four 32K layers with a window of four: 125 us (145).
 constexpr int BAND = 512;                // items of the digit that can be ranked ...
 constexpr int RANKED = 128;              // ... without a histogram of their own
 constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
 
-template <int NT, bool MAP>
+enum { DIRECT_HIST = 0, DIRECT_MAP = 1, DIRECT_SCORES = 2, DIRECT_LOGITS = 3 };
+template <int NT, int SRC, int G>
 __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most)
 {
     constexpr int NW = NT / 64, TILE = HC_SEL_CHUNK;
+    constexpr bool MAP = SRC == DIRECT_MAP, HERE = SRC != DIRECT_HIST;   // HERE: the histogram is made by this workgroup
     static_assert(TILE == 1024, "16 items to a lane");
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];       // [bufs][NW][TILE] scores, a bit per item, the baseline bitmap
     __shared__ __attribute__((aligned(16))) uint32_t sm_hist[HC_RADIX_BINS];
@@ -1182,14 +1171,16 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const Ws w = it.ws.rep(rep);
     const RepDev rd = it.reps[rep];
-    const int need_of = it.need_sense >= 0 ? it.need[rep] : 0;
+    const int need_of = MAP ? it.need[rep] : 0;
     // (1 to 4: the pivot was handed on before it had a histogram; 5: by this launch's deciding workgroup)
     if (ks >= rd.nk || (need_of != 0 && need_of != 5)) return;
     const bool deciding = ks == 0;
     const int max_ctx = it.ws.max_ctx;
-    // items are counted from a multiple of four positions, those from `first` to `end` - 1 are candidates
-    const int lo4 = rd.lo & ~3, first = rd.lo - lo4, end = min(rd.hi - lo4, most);     // (most: what the launch was sized for)
-    const float* srow = it.scores + (size_t)rep * max_ctx + lo4;
+    // items are counted from a multiple of four positions (where they are read 16 bytes at a time), those from `first` to `end` - 1 are
+    // candidates
+    constexpr int ALIGN = SRC == DIRECT_LOGITS ? ~0 : ~3;
+    const int lo4 = rd.lo & ALIGN, first = rd.lo - lo4, end = min(rd.hi - lo4, most);     // (most: what the launch was sized for)
+    float* srow = it.scores + (size_t)rep * max_ctx + lo4;
     const int tiles = (end + TILE - 1) / TILE, per = (tiles + NW - 1) / NW;      // (at most DIRECT_TILES: the launch sees to it)
     const int t0 = min(tiles, wv * per), t1 = min(tiles, t0 + per);
 
@@ -1199,7 +1190,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const int k = it.reps[rep].k[ks];
     int k_longest = 1;
     for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
-    const int real_lo = it.real_reps[rep].lo & ~3, real_hi = it.real_reps[rep].hi;      // the bitmap is indexed by position
+    const int real_lo = it.real_reps[rep].lo & ALIGN, real_hi = it.real_reps[rep].hi;      // the bitmap is indexed by position
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;
     const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
@@ -1208,7 +1199,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     if (checks && lane < n_group) ref_of = it.filt[rep].ref[lane];
     constexpr int HV = HC_RADIX_BINS / 4, HP = (HV + NT - 1) / NT;       // 16-byte pieces of the histogram, of a thread
     uint4 h[HP];
-    if (!MAP) {
+    if (!HERE) {
 #pragma unroll
         for (int i = 0; i < HP; ++i) h[i] = reinterpret_cast<const uint4*>(w.hist)[min(i * NT + tid, HV - 1)];
     }
@@ -1224,7 +1215,21 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
             dma16(srow + min(t * TILE + piece * 4, (end - 1) & ~3), buffer(t) + j * 256);
         }
     };
-    for (int t = t0; t < min(t1, t0 + bufs); ++t) fetch(t);
+    if (SRC != DIRECT_LOGITS)
+        for (int t = t0; t < min(t1, t0 + bufs); ++t) fetch(t);
+    // logits: item tid + u NT of each round of U NT (the first round's are asked for now)
+    constexpr int U = SRC != DIRECT_LOGITS ? 1 : (NT == 512 ? 2 : 4) / (G >= 8 ? 2 : 1);
+    const float* lrow = SRC == DIRECT_LOGITS ? it.rep_logits + ((size_t)rep * max_ctx + lo4) * G : nullptr;
+    float row[U][G], lse_g[G];
+    auto rows = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_row<G>(lrow, min(i0 + u * NT, end - 1), row[u]);
+    };
+    if (SRC == DIRECT_LOGITS) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) lse_g[g] = cfg.agg == HC_AGG_PROB ? it.lse[(size_t)rd.bh * G + g] : 0.f;
+        rows(tid);
+    }
     // the rows this list goes to, one to a lane
     uint32_t v_row = 0;
     int n_rows = -1;                                 // -1: too many for the lanes, looked up when they are needed
@@ -1245,8 +1250,12 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     for (int u = 0; u < GROUP; ++u) j_base[u] = deciding && tid + u * NT < k ? base[tid + u * NT] : -1;
     for (int i = tid; i < tiles * (TILE / 32) + bw; i += NT) sm_bits[i] = 0u;
     if (tid < RANKED) sm_rank[tid] = 0u;
-    if (tid == 0) sm_nband = sm_nrank = 0u;
-    if (MAP) {
+    if (tid == 0) {
+        sm_nband = sm_nrank = 0u;
+        sm_least = 0xffffffffu;
+        sm_most = 0u;
+    }
+    if (HERE) {
         for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
     } else {
 #pragma unroll
@@ -1255,7 +1264,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     }
     __syncthreads();
     uint32_t ticket = 0;                             // (through with the histogram in memory; looked at in the end)
-    if (!MAP && tid == 0) ticket = atomicAdd(w.hist + HC_RADIX_BINS, 1u);
+    if (!HERE && tid == 0) ticket = atomicAdd(w.hist + HC_RADIX_BINS, 1u);
     if (deciding) {                                  // baseline list -> bitmap
         for (int i0 = tid;;) {
 #pragma unroll
@@ -1269,17 +1278,72 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     }
     // tile t is in LDS and the wave may read it; and it has been read: its place may take the one `bufs` further on
     auto arrived = [&](int t) {
+        if (SRC == DIRECT_LOGITS) return;
         if (t == t0 || bufs == 1 || t >= t0 + bufs) dma_wait();          // (at first: for all that are in flight)
     };
     auto leave = [&](int t) {
-        if (t + bufs < t1) {
+        if (SRC != DIRECT_LOGITS && t + bufs < t1) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
             fetch(t + bufs);
         }
     };
     const int turn = (lane >> 2) & 3;
-    if (MAP) {                                       // few items, and digits of a few of them each: the histogram is made here
+    // Where the histogram is made of all candidates its digits are spread over what there is of keys, 2048 for [k_lo, k_hi].  (Digits
+    // of fixed width took 4 us longer for scores within 2 % of each other: all items in one or two of them, then cut again.)
+    uint32_t k_lo = 0, k_hi = 0, k_shift = 0;
+    if (SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES) {
+        uint32_t least = 0xffffffffu, greatest = 0u;
+        // (every tile is at its number's place: a tile to a wave)
+        auto item_at = [&](int at) { return (at & ~15) | ((((at >> 2) & 3) ^ ((at >> 6) & 3)) << 2) | (at & 3); };
+        if (SRC == DIRECT_LOGITS) {
+            for (int i0 = tid; i0 < end; i0 += U * NT) {
+                float x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] = hc_group_score<G>(row[u], lse_g, cfg.agg);
+                if (i0 - tid + U * NT < end) rows(i0 + U * NT);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = i0 + u * NT;
+                    if (i < end) {
+                        const uint32_t key = hc_score_key(x[u]);
+                        if (deciding) srow[i] = x[u];
+                        dyn[item_at(i)] = __float_as_uint(x[u]);
+                        least = min(least, key);
+                        greatest = max(greatest, key);
+                    }
+                }
+            }
+        } else {
+            if (t0 < t1) arrived(t0);
+            __syncthreads();
+            for (int at = tid; at < tiles * TILE; at += NT) {
+                const int i = item_at(at);
+                const uint32_t key = hc_score_key(__uint_as_float(dyn[at]));
+                if (i >= first && i < end) {
+                    least = min(least, key);
+                    greatest = max(greatest, key);
+                }
+            }
+        }
+        least = ~wave_max(~least);
+        greatest = wave_max(greatest);
+        if (lane == 0) {
+            atomicMin(&sm_least, least);
+            atomicMax(&sm_most, greatest);
+        }
+        __syncthreads();
+        k_lo = sm_least;
+        k_hi = sm_most;
+        const uint32_t range = k_hi - k_lo;
+        k_shift = range < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(range);
+        if (range != 0u)
+            for (int at = tid; at < tiles * TILE; at += NT) {
+                const int i = item_at(at);
+                if (i >= first && i < end) atomicAdd(&sm_hist[(hc_score_key(__uint_as_float(dyn[at])) - k_lo) >> k_shift], 1u);
+            }
+        __syncthreads();
+    } else if (HERE) {                               // few items, and digits of a few of them each: the histogram is made here
         for (int t = t0; t < t1; ++t) {
             arrived(t);
             const float* tile = reinterpret_cast<const float*>(buffer(t));
@@ -1287,7 +1351,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
 #pragma unroll 4
             for (int j = 0; j < 16; ++j) {           // (any order will do: this one finds all banks)
                 const int at = j * 64 + lane, i = (at & ~15) | ((((at >> 2) & 3) ^ ((at >> 6) & 3)) << 2) | (at & 3);
-                if (i < left) atomicAdd(&sm_hist[fine_digit(hc_score_key(tile[at]))], 1u);
+                if (i < left && (MAP || t * TILE + i >= first)) atomicAdd(&sm_hist[fine_digit(hc_score_key(tile[at]))], 1u);
             }
             leave(t);
         }
@@ -1302,13 +1366,22 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
 
     // ---- the digit in which the list ends: keys [lo, lo + wide], `count` items of which `rem` are in the list ----
     uint32_t digit, rem, count, tmin = 0u;
+    auto find = [&](uint32_t k_of) {
+        if ((SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES) && k_lo == k_hi) {
+            digit = 0u;
+            rem = k_of;
+            count = (uint32_t)(end - first);
+        } else {
+            find_digit_all<NW>(sm_hist, sm_part, k_of, digit, rem, count);
+        }
+        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? k_lo + (digit << k_shift) : fine_low(digit);
+    };
     if (deciding && it.filt && k_longest != k) {     // a bound from below will do for the filter
-        find_digit_all<NW>(sm_hist, sm_part, (uint32_t)k_longest, digit, rem, count);
-        tmin = fine_low(digit);
+        tmin = find((uint32_t)k_longest);
         __syncthreads();
     }
-    find_digit_all<NW>(sm_hist, sm_part, (uint32_t)k, digit, rem, count);
-    uint32_t lo = fine_low(digit), wide = fine_last(digit) - lo;         // (they do not reach beyond what was counted)
+    uint32_t lo = find((uint32_t)k);                 // (digits do not reach beyond what was counted in them)
+    uint32_t wide = SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? min((1u << k_shift) - 1u, k_hi - lo) : fine_last(digit) - lo;
     auto candidate = [&](int i) { return i >= first && i < end; };
     while (count > BAND && wide != 0u) {             // (the same for every thread)
         const uint32_t shift = wide < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(wide);      // wide >> shift < 2048
@@ -1320,13 +1393,16 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         }
         __syncthreads();
         uint32_t least = 0xffffffffu, greatest = 0u;
-        constexpr int U = NT == 512 ? 8 : 16;        // reads of a lane in flight
-        for (int i0 = t0 * TILE + lane; i0 < t1 * TILE; i0 += 64 * U) {
-            float x[U];
+        constexpr int R = SRC == DIRECT_LOGITS ? 4 : NT == 512 ? 8 : 16;         // reads of a lane in flight
+        for (int i0 = t0 * TILE + lane; i0 < t1 * TILE; i0 += 64 * R) {
+            float x[R];
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = srow[min(i0 + u * 64, end - 1)];
+            for (int u = 0; u < R; ++u) {
+                const int i = min(i0 + u * 64, end - 1);
+                x[u] = SRC == DIRECT_LOGITS ? __uint_as_float(dyn[(i & ~15) | ((((i >> 2) & 3) ^ ((i >> 6) & 3)) << 2) | (i & 3)]) : srow[i];
+            }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < R; ++u) {
                 const uint32_t d = hc_score_key(x[u]) - lo;
                 const bool in = candidate(i0 + u * 64) && d <= wide;
                 least = in ? min(least, d) : least;
@@ -1565,7 +1641,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         decide<NT>(it, rep, rd.bh, rd.hi, k, cfg, n_group, ring, inter, tmin, lse_of);
     }
     // ---- the next call finds the histogram clear: the last of the pivot's workgroups to have read it sees to it ----
-    if (!MAP && wv == 0 && __builtin_amdgcn_readfirstlane((int)ticket) == rd.nk - 1) {
+    if (!HERE && wv == 0 && __builtin_amdgcn_readfirstlane((int)ticket) == rd.nk - 1) {
         for (int i = lane; i < HV; i += 64) reinterpret_cast<uint4*>(w.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
         if (lane == 0) w.hist[HC_RADIX_BINS] = 0u;
     }
@@ -1997,15 +2073,30 @@ static bool direct_fits(const hc_ctx* ctx, int items, int bm_words)
 {
     return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 1) <= direct_room(ctx);
 }
-template <bool MAP>
+template <int SRC>
 static hc_status launch_direct(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
 {
     const int bufs = items + 3 > direct_threads(ctx) / 64 * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 2) <= direct_room(ctx) ? 2 : 1;
     const unsigned lds = (unsigned)direct_bytes(ctx, items, bm_words, bufs);
-    if (direct_threads(ctx) == 512)
-        mon_direct<512, MAP><<<grid, dim3(512), hc_side_lds(ctx, (const void*)mon_direct<512, MAP>, lds), st>>>(B, dc, ctx->G, bufs, items + 3);
-    else
-        mon_direct<1024, MAP><<<grid, dim3(1024), hc_side_lds(ctx, (const void*)mon_direct<1024, MAP>, lds), st>>>(B, dc, ctx->G, bufs, items + 3);
+#define HC_DIRECT(NT, GG)                                                                                                    \
+    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, items + 3)
+    const bool small = direct_threads(ctx) == 512;
+    if constexpr (SRC != DIRECT_LOGITS) {
+        if (small) HC_DIRECT(512, 1);                                // (the group size only matters where logits are read)
+        else HC_DIRECT(1024, 1);
+    } else {
+        switch (ctx->G * 2 + small) {
+        case 2: HC_DIRECT(1024, 1); break;
+        case 3: HC_DIRECT(512, 1); break;
+        case 4: HC_DIRECT(1024, 2); break;
+        case 5: HC_DIRECT(512, 2); break;
+        case 8: HC_DIRECT(1024, 4); break;
+        case 9: HC_DIRECT(512, 4); break;
+        case 16: HC_DIRECT(1024, 8); break;
+        default: HC_DIRECT(512, 8); break;
+        }
+    }
+#undef HC_DIRECT
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
@@ -2015,19 +2106,7 @@ template <int NT, int SRC>
 static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
 {
     const unsigned lds = (unsigned)std::min((long long)select_room<NT>(ctx), ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
-#define HC_SELECT(GG)                                                                                                        \
-    mon_select<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4))
-    if constexpr (SRC != SRC_LOGITS) {
-        HC_SELECT(1);                                                // (the group size only matters where logits are read)
-    } else {
-        switch (ctx->G) {
-        case 1: HC_SELECT(1); break;
-        case 2: HC_SELECT(2); break;
-        case 4: HC_SELECT(4); break;
-        default: if constexpr (NT == 1024) HC_SELECT(8); break;
-        }
-    }
-#undef HC_SELECT
+    mon_select<NT, SRC><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4));
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
@@ -2069,8 +2148,8 @@ static hc_status launch_long(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc,
 
 // Candidates up to which one workgroup per pivot does everything, from the scores on.  What lies against more is that
 // the exponentials of the scores are then made by one compute unit: at 32K candidates and a group of four this takes 18
-// of 44 us, where two launches take 21 in all; at 4K it takes 3.5 us of 13.5, two launches 14.5 (at 8K 16.4 and 15.3 with scores spread
-// out, 16.5 and 21 within 2 % of each other).
+// of 44 us, where two launches take 21 in all.  One launch and two, us: 12.2 and 14.5 at 4K, at 8K 15.3 and 15.3 with scores spread
+// out, 15.2 and 21 within 2 % of each other.
 constexpr int SELECT_DIRECT = 8192;
 // Survivors (as the sample would let through) up to which one workgroup per list beats the six launches of long lists, with
 // the sample in front of it where it is needed.  131,072 candidates, scores spread out / within 2 % / equal: a longest list of 8,192
@@ -2168,15 +2247,18 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         HC_HIP(ctx, hipGetLastError());
     }
     if (mode != 0) scores_given = 1;                     // they are there from here on
-    if (mode == 1 && direct) return launch_direct<true>(ctx, B, dc, gsel, candidates, bm_words, st);
+    if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, B, dc, gsel, candidates, bm_words, st);
     // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
     // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
     const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
     const bool few = mode == 1 && armed && (select_small(ctx, kept) || (!(ctx->beside_now && ctx->G < 8) && kept <= SEL_KEYS(select_room<1024>(ctx) / 4)));
+    // (a tile to a wave; given scores are read from a multiple of four positions on)
+    if (mode == 0 && candidates <= SELECT_DIRECT && (!scores_given || candidates + 3 <= direct_threads(ctx) / 64 * HC_SEL_CHUNK))
+        return scores_given ? launch_direct<DIRECT_SCORES>(ctx, B, dc, gsel, candidates, bm_words, st)
+                            : launch_direct<DIRECT_LOGITS>(ctx, B, dc, gsel, candidates, bm_words, st);
     if (few || candidates <= SELECT_DIRECT) {
         const bool small = few ? select_small(ctx, kept) : select_small(ctx, candidates);
-        return scores_given ? launch_select<SRC_SCORES>(ctx, B, dc, gsel, candidates, bm_words, small, st)
-                            : launch_select<SRC_LOGITS>(ctx, B, dc, gsel, candidates, bm_words, small, st);
+        return launch_select<SRC_SCORES>(ctx, B, dc, gsel, candidates, bm_words, small, st);
     }
     int survivors, most;
     expected_survivors(max_k, candidates, &survivors, &most);
@@ -2201,7 +2283,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         }
 #undef HC_SCORE
         HC_HIP(ctx, hipGetLastError());
-        if (direct) return launch_direct<false>(ctx, B, dc, gsel, candidates, bm_words, st);
+        if (direct) return launch_direct<DIRECT_HIST>(ctx, B, dc, gsel, candidates, bm_words, st);
         if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
     }
     // The small form where all that may survive fits, and what is expected fits with the baseline bitmap (without the bitmap in LDS
@@ -2267,18 +2349,17 @@ hc_status hc_monitor_set_lds_limit()
 {
     // mon_select takes most of a compute unit's LDS, and beside the attention pass every kernel here reserves more
     // than half of it (hc_side_lds)
-    const void* fns[] = {(const void*)mon_direct<512, false>, (const void*)mon_direct<512, true>, (const void*)mon_direct<1024, false>,
-                         (const void*)mon_direct<1024, true>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
+    const void* fns[] = {(const void*)mon_direct<512, DIRECT_HIST, 1>, (const void*)mon_direct<512, DIRECT_MAP, 1>, (const void*)mon_direct<512, DIRECT_SCORES, 1>,
+                         (const void*)mon_direct<512, DIRECT_LOGITS, 1>, (const void*)mon_direct<512, DIRECT_LOGITS, 2>, (const void*)mon_direct<512, DIRECT_LOGITS, 4>,
+                         (const void*)mon_direct<512, DIRECT_LOGITS, 8>, (const void*)mon_direct<1024, DIRECT_HIST, 1>, (const void*)mon_direct<1024, DIRECT_MAP, 1>,
+                         (const void*)mon_direct<1024, DIRECT_SCORES, 1>, (const void*)mon_direct<1024, DIRECT_LOGITS, 1>, (const void*)mon_direct<1024, DIRECT_LOGITS, 2>,
+                         (const void*)mon_direct<1024, DIRECT_LOGITS, 4>, (const void*)mon_direct<1024, DIRECT_LOGITS, 8>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
                          (const void*)mon_compact, (const void*)mon_sparse_score<1>,
                          (const void*)mon_sparse_score<2>, (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>,
                          (const void*)mon_score_hist<1, false>, (const void*)mon_score_hist<2, false>, (const void*)mon_score_hist<4, false>, (const void*)mon_score_hist<8, false>,
                          (const void*)mon_score_hist<1, true>, (const void*)mon_score_hist<2, true>, (const void*)mon_score_hist<4, true>, (const void*)mon_score_hist<8, true>,
-                         (const void*)mon_select<512, SRC_LOGITS, 1>, (const void*)mon_select<512, SRC_LOGITS, 2>,
-                         (const void*)mon_select<512, SRC_LOGITS, 4>,
-                         (const void*)mon_select<512, SRC_SCORES, 1>, (const void*)mon_select<512, SRC_SURVIVORS, 1>, (const void*)mon_select<512, SRC_RANGE, 1>,
-                         (const void*)mon_select<1024, SRC_LOGITS, 1>, (const void*)mon_select<1024, SRC_LOGITS, 2>,
-                         (const void*)mon_select<1024, SRC_LOGITS, 4>, (const void*)mon_select<1024, SRC_LOGITS, 8>,
-                         (const void*)mon_select<1024, SRC_SCORES, 1>, (const void*)mon_select<1024, SRC_SURVIVORS, 1>, (const void*)mon_select<1024, SRC_RANGE, 1>};
+                         (const void*)mon_select<512, SRC_SCORES>, (const void*)mon_select<512, SRC_SURVIVORS>, (const void*)mon_select<512, SRC_RANGE>,
+                         (const void*)mon_select<1024, SRC_SCORES>, (const void*)mon_select<1024, SRC_SURVIVORS>, (const void*)mon_select<1024, SRC_RANGE>};
     for (const void* fn : fns)
         if (hc_allow_lds(fn) != hipSuccess) return HC_EHIP;
     return HC_OK;

@@ -98,3 +98,36 @@ def test_beside_the_attention_pass_like_alone(N, margin, k_mon):
     for t, (a, b) in enumerate(zip(*tables)):
         for i, (x, y) in enumerate(zip(a, b)):
             np.testing.assert_array_equal(x, y, err_msg=f"step {t} table {i}")
+
+
+# short ranges, scored by the selection itself or given: one item to a list, all of them, ends of tiles, all groups of heads
+@pytest.mark.parametrize("n,rs,sink,G", [(9, (9, 1), 1, 4), (63, (5, 62), 2, 1), (1024, (1024, 3), 3, 2), (1025, (700, 1), 0, 8), (4097, (4000, 513, 1), 5, 4),
+                                         (8191, (8191, 129), 2, 8), (8192, (600, 511), 3, 1), (8192, (2000, 8192), 1, 2)])
+@pytest.mark.parametrize("kind", ["spread", "flat", "equal"])
+def test_short_ranges_from_logits_and_given(n, rs, sink, G, kind):
+    T.say("monitor direct short", n, rs, sink, G, kind)
+    N = n + sink + 7
+    spec = one_pivot(N, rs, sink=sink)
+    spec = I.LayerSpec(B=1, Hq=G * spec.Hkv, Hkv=spec.Hkv, D=128, ctx=[N], heads=spec.heads)
+    rng = np.random.default_rng(n + G)
+    lo, hi = spec.cand_range(0, 0)
+    base = {(0, 0): torch.from_numpy(np.sort(rng.choice(np.arange(lo, hi), spec.k_mon(0, 0), replace=False)).astype(np.int32))}
+    logits = torch.from_numpy((rng.normal(size=(N, G)) * {"spread": 1.5, "flat": 0.003, "equal": 0.0}[kind]).astype(np.float32)).to(DEV)
+    ctx, gpu, base_all = T.monitor_case(spec, {(0, 0): np.zeros(N, np.float32)}, base)
+    gpu.rep_logits[0, :N] = logits
+    gpu.lse.fill_(float(np.log(N)) + 1.0)
+    gpu.base_idx[0, :len(base_all[(0, 0)])] = base_all[(0, 0)].to(DEV)
+    gpu.ring.zero_()
+    gpu.monitor()
+    torch.cuda.synchronize()
+    s = gpu.scores[0, :N].cpu().numpy().copy()
+    want = torch.exp(logits.double() - gpu.lse.double()[0, 0]).mean(1).cpu().numpy()
+    np.testing.assert_allclose(s[lo:hi], want[lo:hi], rtol=1e-5)
+    T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)          # the lists of the scores it wrote
+    gpu.base_idx[0, :len(base_all[(0, 0)])] = base_all[(0, 0)].to(DEV)
+    gpu.ring.zero_()
+    gpu.monitor(scores_given=True)
+    torch.cuda.synchronize()
+    T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
+    gpu.close()
+    ctx.close()
