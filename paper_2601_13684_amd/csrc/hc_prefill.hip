@@ -10,8 +10,8 @@
 //   prefill_score_kernel   group mean of the softmax weights, then the pooling window           (below)
 //   selection              the monitor's, lists only                                            (hc_monitor.hip)
 //   prefill_place_kernel   rows of the resident positions -> the heads' blocks in the arena; baseline sets,
-//                          slot maps and rings                                                  (below)
-//   prefill_offload_kernel satellites' rows -> the pinned host tier, K row then V row per position (below)
+//                          slot maps and rings; beside it satellites' rows -> the pinned host tier, K row then
+//                          V row per position                                                   (below)
 #include "hc_internal.h"
 
 namespace {
@@ -86,20 +86,48 @@ __global__ __launch_bounds__(PF_BLK) void prefill_score_kernel(const RepDev* __r
     }
 }
 
+// The host tier's block of a satellite is [ctx][2][D]: piece idx of the block is piece idx % 16 of the K row
+// (idx / 16 even) or V row (odd) of position idx / 32, so the stores of a wave are 1 KB contiguous.
+// Workgroup `part` of `parts` of a satellite.
+__device__ __forceinline__ void offload(const HeadDev* __restrict__ heads, const PreSrc* __restrict__ src, const uint4* __restrict__ kv_prefill,
+                                        uint4* __restrict__ tier, int bh, int part, int parts)
+{
+    const HeadDev hd = heads[bh];
+    const PreSrc s = src[bh];
+    const long long pieces = (long long)hd.ctx * 32;
+    uint4* dst = tier + (size_t)hd.tier_off / 8;
+    for (long long idx = (long long)part * PF_BLK + threadIdx.x; idx < pieces; idx += (long long)parts * PF_BLK) {
+        const int pos = (int)(idx >> 5), piece = (int)(idx & 31);
+        const size_t from = (size_t)(piece >= 16 ? s.v_off : s.k_off) / 8 + (size_t)pos * 16 + (piece & 15);
+        dst[idx] = kv_prefill[from];
+    }
+}
+
 // Slot i of a compressed head holds: i < sink: position i; then the last `recent` positions in order; then
 // the selected positions in ascending order.  A full head holds all of its positions.  A workgroup takes
-// tiles of 32 slots (1024 16-byte pieces; a row, K then V, is 32 consecutive pieces), tile x, x + gridDim.x,
+// tiles of 32 slots (1024 16-byte pieces; a row, K then V, is 32 consecutive pieces), tile x, x + per_head,
 // ... of its head; a thread moves four pieces of a tile, all four loads issued before the first store, so
 // that a long head's copy has 16 KB per workgroup in flight.  Source rows are read once and destination
 // rows are not read again by this call: streaming loads and stores.
+//
+// The first n_off workgroups are the offload's (none without a tier): bound by the host link, it waits for no selection, so that
+// it runs beside the rows' placing, which takes 20 us by itself at 32K.  (A workgroup per compute unit leaves room for the others'
+// and writes at the link's rate.  A layer of 32K with its offload: 1854 us, 1857 with two or four per unit, 1884 with a launch of
+// its own behind this one.)
 __global__ __launch_bounds__(PF_BLK) void prefill_place_kernel(const HeadDev* __restrict__ heads, const PreSrc* __restrict__ src,
                                                                const RepDev* __restrict__ reps, const int32_t* __restrict__ rep_slot_of,
                                                                const uint4* __restrict__ kv_prefill, uint4* __restrict__ arena,
                                                                const int32_t* __restrict__ topk_idx, int32_t* __restrict__ base_idx,
                                                                int32_t* __restrict__ slot_pos, int32_t* __restrict__ ring, int max_k,
-                                                               int window)
+                                                               int window, int per_head, const SatDev* __restrict__ sats,
+                                                               uint4* __restrict__ tier, int n_off, int per_sat)
 {
-    const int bh = blockIdx.y;
+    const int b = (int)blockIdx.x - n_off;
+    if (b < 0) {
+        offload(heads, src, kv_prefill, tier, sats[blockIdx.x / per_sat].bh, blockIdx.x % per_sat, per_sat);
+        return;
+    }
+    const int bh = b / per_head, x = b % per_head;
     const HeadDev hd = heads[bh];
     const PreSrc s = src[bh];
     const int32_t* list = topk_idx + (size_t)bh * max_k;
@@ -110,7 +138,7 @@ __global__ __launch_bounds__(PF_BLK) void prefill_place_kernel(const HeadDev* __
     const bool isv = piece >= 16;
     const size_t from0 = (size_t)(isv ? s.v_off : s.k_off) / 8 + (piece & 15);
     const size_t to0 = (size_t)(isv ? hd.v_off : hd.k_off) / 8 + (piece & 15);
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    for (int tile = x; tile < tiles; tile += per_head) {
         u32x4 v[4];
         int slot[4];
 #pragma unroll
@@ -128,7 +156,7 @@ __global__ __launch_bounds__(PF_BLK) void prefill_place_kernel(const HeadDev* __
         for (int u = 0; u < 4; ++u)
             if (slot[u] < hd.len) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(arena) + to0 + (size_t)slot[u] * 16);
     }
-    if (blockIdx.x != 0) return;
+    if (x != 0) return;
     // tables: the ring starts empty; a satellite's slot map names what its retrieved slots hold; a pivot's
     // baseline set is its own list
     for (int i = threadIdx.x; i <= window; i += PF_BLK) ring[(size_t)bh * (window + 1) + i] = 0;
@@ -138,24 +166,6 @@ __global__ __launch_bounds__(PF_BLK) void prefill_place_kernel(const HeadDev* __
     if (full && rep_slot_of[bh] >= 0) {
         const int k = reps[rep_slot_of[bh]].k[0];
         for (int i = threadIdx.x; i < k; i += PF_BLK) base_idx[(size_t)bh * max_k + i] = list[i];
-    }
-}
-
-// The host tier's block of a satellite is [ctx][2][D]: piece idx of the block is piece idx % 16 of the K row
-// (idx / 16 even) or V row (odd) of position idx / 32, so the stores of a wave are 1 KB contiguous.
-__global__ __launch_bounds__(PF_BLK) void prefill_offload_kernel(const HeadDev* __restrict__ heads, const SatDev* __restrict__ sats,
-                                                                 const PreSrc* __restrict__ src, const uint4* __restrict__ kv_prefill,
-                                                                 uint4* __restrict__ tier)
-{
-    const int bh = sats[blockIdx.y].bh;
-    const HeadDev hd = heads[bh];
-    const PreSrc s = src[bh];
-    const long long pieces = (long long)hd.ctx * 32;
-    uint4* dst = tier + (size_t)hd.tier_off / 8;
-    for (long long idx = (long long)blockIdx.x * PF_BLK + threadIdx.x; idx < pieces; idx += (long long)gridDim.x * PF_BLK) {
-        const int pos = (int)(idx >> 5), piece = (int)(idx & 31);
-        const size_t from = (size_t)(piece >= 16 ? s.v_off : s.k_off) / 8 + (size_t)pos * 16 + (piece & 15);
-        dst[idx] = kv_prefill[from];
     }
 }
 
@@ -213,15 +223,12 @@ hc_status hc_launch_prefill_place(hc_ctx* ctx, const hc_layer* L, const void* kv
     // context to budget, so a share per head by count would leave the chip to the few long heads' workgroups.
     const int max_tiles = (max_len + 31) / 32;
     const int per_head = std::max(1, std::min((max_tiles + 3) / 4, 2048));
-    prefill_place_kernel<<<dim3(per_head, L->n_heads), dim3(PF_BLK), 0, st>>>(L->heads, L->pre_src, L->reps, L->rep_slot_dev,
-                                                                               (const uint4*)kv_prefill, (uint4*)arena, topk_idx, base_idx,
-                                                                               slot_pos, ring, c.max_k, c.window);
+    const int per_sat = tier && L->n_sats > 0 ? std::max(1, std::min((max_ctx * 32 + PF_BLK * 8 - 1) / (PF_BLK * 8), std::max(1, ctx->n_cu / L->n_sats))) : 1;
+    const int n_off = tier ? per_sat * L->n_sats : 0;
+    prefill_place_kernel<<<dim3(n_off + per_head * L->n_heads), dim3(PF_BLK), 0, st>>>(L->heads, L->pre_src, L->reps, L->rep_slot_dev,
+                                                                                        (const uint4*)kv_prefill, (uint4*)arena, topk_idx, base_idx,
+                                                                                        slot_pos, ring, c.max_k, c.window, per_head, L->sats,
+                                                                                        (uint4*)tier, n_off, per_sat);
     HC_HIP(ctx, hipGetLastError());
-    if (tier && L->n_sats > 0) {
-        const int per_sat = std::max(1, std::min((max_ctx * 32 + PF_BLK * 8 - 1) / (PF_BLK * 8), std::max(1, 8 * ctx->n_cu / L->n_sats)));
-        prefill_offload_kernel<<<dim3(per_sat, L->n_sats), dim3(PF_BLK), 0, st>>>(L->heads, L->sats, L->pre_src, (const uint4*)kv_prefill,
-                                                                                   (uint4*)tier);
-        HC_HIP(ctx, hipGetLastError());
-    }
     return HC_OK;
 }
