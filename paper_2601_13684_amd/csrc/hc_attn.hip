@@ -919,7 +919,9 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
 // loads are independent and issued together.  (Four small workgroups per query head instead of one of 1024
 // threads: they find room beside the monitor's kernels sooner.)
 // The layers of a hc_decode_step group are combined with one launch (blockIdx.z picks the layer): a launch of its own
-// behind every layer's split pass is mostly latency, 4.5 us and a gap in which the compute units stand empty.
+// behind every layer's split pass is mostly latency, 4.5 us and a gap in which the compute units stand empty.  For the same
+// reason it copies the queries that a re-scored window keeps (a launch of its own for that: 2.7 us and a gap; four 32K layers
+// in two groups 136 instead of 131 us a step).
 constexpr int CQ = 8;                       // column quads (of 32) per workgroup
 constexpr int COMBINE_BLK = 32 * CQ;
 struct CombineItem {
@@ -928,6 +930,8 @@ struct CombineItem {
     const float* part_ml;
     float* out;
     float* lse;
+    const uint4* q;              // the step's queries ...
+    uint4* q_window;             // ... and where a re-scored window keeps them (nullptr: nowhere)
 };
 struct CombineBatch {
     CombineItem it[HC_MAX_GROUP];
@@ -947,6 +951,7 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(CombineBatch 
     const int bh = blockIdx.x / G, g = blockIdx.x % G;
     const HeadDev hd = heads[bh];
     const int tid = threadIdx.x, dq = (tid % CQ) + CQ * blockIdx.y, pl = tid / CQ;
+    if (item.q_window && blockIdx.y == 0 && tid < HC_D / 8) item.q_window[(size_t)blockIdx.x * (HC_D / 8) + tid] = item.q[(size_t)blockIdx.x * (HC_D / 8) + tid];
     const int n = hd.part_count;
     const float2* ml = reinterpret_cast<const float2*>(part_ml);
     const float4* pa = reinterpret_cast<const float4*>(part_acc);
@@ -1212,7 +1217,7 @@ static hc_status launch_any(hc_ctx* ctx, const hc_layer* L, const void* arena, c
     const hc_status s = split_any(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
     if (s != HC_OK) return s;
     CombineBatch batch{};
-    batch.it[0] = CombineItem{L->heads, part_acc, part_ml, out, lse};
+    batch.it[0] = CombineItem{L->heads, part_acc, part_ml, out, lse, nullptr, nullptr};
     return combine_any(ctx, batch, 1, L->n_heads, st);
 }
 
@@ -1250,7 +1255,7 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
             (void)flush();
             return s;
         }
-        batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse};
+        batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse, (const uint4*)x.q, (uint4*)x.q_window};
     }
     return flush();
 }

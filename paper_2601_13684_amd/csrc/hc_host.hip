@@ -1343,8 +1343,6 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         SideWork& w = work[cur];
         w.n_mon = w.n_gat = w.n_test = 0;
         w.all_filtered = true;
-        const void* push_src[HC_MAX_GROUP];
-        void* push_dst[HC_MAX_GROUP];
         hc_layer* push_layer[HC_MAX_GROUP];
         int n_push = 0;
         // the tokens of the group's layers enter their caches with one launch, ahead of the group's attention
@@ -1373,32 +1371,29 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
             const hc_layer_io& x = io[l];
             hc_layer* L = x.layer;
             const bool side = L->n_reps > 0 && x.scores != nullptr;
+            void* q_window = nullptr;
             if (side) {
                 w.mon[w.n_mon] = hc_monitor_call{L, x.rep_logits, x.lse, x.scores, x.topk_idx, x.base_idx, x.ring, x.inter, x.flag};
                 w.mon[w.n_mon++].arena = x.kv_arena;
                 L->last_arena = x.kv_arena;
                 w.all_filtered = w.all_filtered && hc_layer_filtered(ctx, L);
                 if (rescored) {
-                    push_src[n_push] = x.q;
-                    push_layer[n_push] = L;
-                    push_dst[n_push++] = (char*)x.q_window + (size_t)L->window_slot * ctx->cfg.B * ctx->cfg.Hq * HC_D * 2;
+                    push_layer[n_push++] = L;
+                    q_window = (char*)x.q_window + (size_t)L->window_slot * ctx->cfg.B * ctx->cfg.Hq * HC_D * 2;
                     if (L->window_slot == ctx->cfg.window - 1)
                         w.test_job[w.n_test++] = RescoreJob{L, x.kv_arena, x.q_window, x.base_idx, x.ring, x.rescore_work};
                 }
                 if (x.host_tier && L->n_sats > 0)
                     w.gat[w.n_gat++] = hc_gather_call{L, x.host_tier, x.topk_idx, x.flag, const_cast<void*>(x.kv_arena), x.slot_pos};
             }
-            att[l - g0] = hc_attn_call{L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr};
+            att[l - g0] = hc_attn_call{L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr, q_window};
         }
-        if (result == HC_OK) result = hc_launch_attn(ctx, g1 - g0, att, ms);
-        // The queries go into the window buffers on the main stream: the caller may overwrite q as soon
-        // as this call returns, in main-stream order, while the side stream may still be behind.  A layer's
+        // The queries go into the window buffers on the main stream, with the combine pass: the caller may overwrite q as
+        // soon as this call returns, in main-stream order, while the side stream may still be behind.  A layer's
         // count of steps inside its window moves on once its query is in the buffer.
-        if (result == HC_OK && n_push > 0) {
-            result = hc_launch_rescore_push(ctx, n_push, push_src, push_dst, ms);
-            if (result == HC_OK)
-                for (int i = 0; i < n_push; ++i) push_layer[i]->window_slot = (push_layer[i]->window_slot + 1) % ctx->cfg.window;
-        }
+        if (result == HC_OK) result = hc_launch_attn(ctx, g1 - g0, att, ms);
+        if (result == HC_OK)
+            for (int i = 0; i < n_push; ++i) push_layer[i]->window_slot = (push_layer[i]->window_slot + 1) % ctx->cfg.window;
         if (result != HC_OK) w.n_mon = 0;              // this group's side work is dropped; the previous group's still goes out
         if (w.n_mon > 0) {
             w.Lg = io[g1 - 1].layer;

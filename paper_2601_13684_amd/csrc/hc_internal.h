@@ -270,6 +270,7 @@ struct hc_attn_call {
     float* out;
     float* lse;
     float* rep_logits;     // or nullptr
+    void* q_window = nullptr;   // where the combine pass leaves a copy of q (16-byte aligned), or nullptr
 };
 hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st);
 hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out,
