@@ -23,6 +23,9 @@
  *     synchronise, allocate or copy from the host, so they may be captured in a HIP graph.
  *     Results are valid once the stream (or done_event) has completed.  Trigger decisions
  *     stay in device memory (flag); the host may read them later.
+ *     A captured hc_rep_topk_drift may be replayed over contexts that hc_append_kv has grown since, as long as no
+ *     pivot's candidates pass the next multiple of 1,024 above the longest range at capture, nor 65,533 if that was at
+ *     most 65,533 (in place of both 16,381 if it was at most 8,192); capture it again before they do.
  *   - One hc_ctx per host thread; calls on one ctx are not re-entrant, and two hot-path calls
  *     that use the same workspace (two hc_decode_attn, or two hc_rep_topk_drift) must be
  *     ordered by the caller's streams.  A decode_attn and a rep_topk_drift may overlap.

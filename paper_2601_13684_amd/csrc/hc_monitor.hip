@@ -378,14 +378,16 @@ __device__ __forceinline__ void sample_threshold(uint32_t* sm_hist, uint32_t* sm
 
 // Scores and histogram of a long candidate range (over the first 11 bits of the keys unless mon_direct reads it).  A workgroup takes `span` consecutive chunks of
 // HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
+// most: as many candidates as mon_direct will go through (a captured call may find more than when it was launched).
 template <int G, bool FINE>
-__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k)
+__global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k, int most)
 {
     __shared__ uint32_t sh[HC_RADIX_BINS];
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
-    const RepDev rd = it.reps[rep];
+    RepDev rd = it.reps[rep];
+    if (FINE) rd.hi = min(rd.hi, rd.lo + most);
     const int c0 = blockIdx.x * span, c1 = min(c0 + span, rd.nchunk);
     if (c0 >= rd.nchunk) return;
     float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
@@ -1155,7 +1157,7 @@ constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
 
 enum { DIRECT_HIST = 0, DIRECT_MAP = 1, DIRECT_SCORES = 2, DIRECT_LOGITS = 3 };
 template <int NT, int SRC, int G>
-__global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most)
+__global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most, int bm_words)
 {
     constexpr int NW = NT / 64, TILE = HC_SEL_CHUNK;
     constexpr bool MAP = SRC == DIRECT_MAP, HERE = SRC != DIRECT_HIST;   // HERE: the histogram is made by this workgroup
@@ -1179,7 +1181,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     // items are counted from a multiple of four positions (where they are read 16 bytes at a time), those from `first` to `end` - 1 are
     // candidates
     constexpr int ALIGN = SRC == DIRECT_LOGITS ? ~0 : ~3;
-    const int lo4 = rd.lo & ALIGN, first = rd.lo - lo4, end = min(rd.hi - lo4, most);     // (most: what the launch was sized for)
+    const int lo4 = rd.lo & ALIGN, first = rd.lo - lo4, end = min(rd.hi - rd.lo, most) + first;     // (most: what the launch was sized for)
     float* srow = it.scores + (size_t)rep * max_ctx + lo4;
     const int tiles = (end + TILE - 1) / TILE, per = (tiles + NW - 1) / NW;      // (at most DIRECT_TILES: the launch sees to it)
     const int t0 = min(tiles, wv * per), t1 = min(tiles, t0 + per);
@@ -1190,7 +1192,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const int k = it.reps[rep].k[ks];
     int k_longest = 1;
     for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
-    const int real_lo = it.real_reps[rep].lo & ALIGN, real_hi = it.real_reps[rep].hi;      // the bitmap is indexed by position
+    const int real_lo = it.real_reps[rep].lo & ALIGN, real_hi = min(it.real_reps[rep].hi, real_lo + bm_words * 32);      // the bitmap is indexed by position
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;
     const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
@@ -2064,22 +2066,34 @@ static int direct_room(const hc_ctx* ctx)
 {
     return (!ctx->beside_now ? 156 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - DIRECT_STATIC;
 }
-static int direct_bytes(const hc_ctx* ctx, int items, int bm_words, int bufs)
+// Candidates a launch goes through.  A captured call is replayed over contexts that have grown since, so a launch takes whole tiles:
+// one to a wave, or up to the end of the last chunk that mon_score_hist takes (items are counted from a multiple of four
+// positions, so that the last three may not fit).
+static int direct_most(const hc_ctx* ctx, int src, int items)
 {
-    const int tiles = (items + 3 + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;     // (items are counted from a multiple of four positions)
+    const int tile_each = direct_threads(ctx) / 64 * HC_SEL_CHUNK;
+    if (src == DIRECT_LOGITS) return tile_each;
+    if (src == DIRECT_SCORES) return tile_each - 3;
+    return std::min((items + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK * HC_SEL_CHUNK, DIRECT_TILES * tile_each - 3);
+}
+static int direct_bytes(const hc_ctx* ctx, int most, int bm_words, int bufs)
+{
+    const int tiles = (most + 3 + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
     return 4 * (bufs * direct_threads(ctx) / 64 * HC_SEL_CHUNK + tiles * (HC_SEL_CHUNK / 32) + bm_words + 2);
 }
 static bool direct_fits(const hc_ctx* ctx, int items, int bm_words)
 {
-    return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 1) <= direct_room(ctx);
+    return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, direct_most(ctx, DIRECT_HIST, items), bm_words, 1) <= direct_room(ctx);
 }
 template <int SRC>
 static hc_status launch_direct(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
 {
-    const int bufs = items + 3 > direct_threads(ctx) / 64 * HC_SEL_CHUNK && direct_bytes(ctx, items, bm_words, 2) <= direct_room(ctx) ? 2 : 1;
-    const unsigned lds = (unsigned)direct_bytes(ctx, items, bm_words, bufs);
+    const int most = direct_most(ctx, SRC, items);
+    bm_words = SRC == DIRECT_MAP ? bm_words + 1 : std::max(bm_words, (most + 3 + 31) / 32);      // (positions are counted from a multiple of four; a candidate's number is its bit)
+    const int bufs = SRC < DIRECT_SCORES && items + 3 > direct_threads(ctx) / 64 * HC_SEL_CHUNK && direct_bytes(ctx, most, bm_words, 2) <= direct_room(ctx) ? 2 : 1;
+    const unsigned lds = (unsigned)direct_bytes(ctx, most, bm_words, bufs);
 #define HC_DIRECT(NT, GG)                                                                                                    \
-    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, items + 3)
+    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words)
     const bool small = direct_threads(ctx) == 512;
     if constexpr (SRC != DIRECT_LOGITS) {
         if (small) HC_DIRECT(512, 1);                                // (the group size only matters where logits are read)
@@ -2236,6 +2250,8 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     // (candidates: of a filtering layer, what its launches are sized for)
     const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words);
     if (mode == 1) {
+        if (direct)                                      // (more rows than it goes through, in a captured call: the dense chain's)
+            for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(ctx, DIRECT_MAP, candidates));
         // enough waves for a segment each of a long context's few hundred, no more workgroups than compute units
         const dim3 g(std::max(4, std::min(armed ? 32 : 128, (armed ? 256 : 1024) / pivots)), max_reps, n);
         switch (ctx->G) {
@@ -2270,7 +2286,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
 #define HC_SCORE(GG, FINE)                                                                                                   \
-    mon_score_hist<GG, FINE><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, FINE>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k)
+    mon_score_hist<GG, FINE><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, FINE>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(ctx, DIRECT_HIST, candidates))
         switch (ctx->G * 2 + direct) {
         case 2: HC_SCORE(1, false); break;
         case 3: HC_SCORE(1, true); break;

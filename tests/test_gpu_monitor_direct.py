@@ -131,3 +131,51 @@ def test_short_ranges_from_logits_and_given(n, rs, sink, G, kind):
     T.compare_monitor(spec, gpu, {(0, 0): s}, base_all)
     gpu.close()
     ctx.close()
+
+
+# a captured call finds more candidates than when it was captured: up to 16,381 where one launch takes them from the logits
+# or the scores, up to the end of the last chunk of 1024 where two do
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("n,upto", [(4090, (4091, 4093, 4094, 4098, 6000)), (8190, (8192, 8193, 8194, 9300)), (20001, (20004, 20005, 20070, 20480)),
+                                    (32760, (32763, 32764, 32768))])
+def test_captured_call_and_a_context_that_grows(n, upto, given):
+    T.say("monitor direct captured, growing", n, given)
+    N, grow = n + 12, upto[-1] - n
+    spec = one_pivot(N, (1500, 77))
+    ctx = R.Context(R.make_config(spec, growth=grow), DEV)
+    g = torch.Generator().manual_seed(n)
+    data = I.LayerData({(0, h): torch.zeros((N, 128), dtype=torch.bfloat16) for h in range(spec.Hkv)},
+                       {(0, h): torch.zeros((N, 128), dtype=torch.bfloat16) for h in range(spec.Hkv)}, {})
+    gpu = R.LayerRuntime(ctx, spec, data, *I.initial_lists(spec), growth=grow)
+    gpu.rep_logits.copy_(torch.randn(gpu.rep_logits.shape, generator=g) * 1.5)
+    gpu.lse.fill_(float(np.log(N)) + 1.0)
+    scores = torch.exp(gpu.rep_logits.double() - gpu.lse.double()[0, 0]).mean(2).float()
+    token = torch.zeros((1, spec.Hkv, 128), dtype=torch.bfloat16, device=DEV)
+    gpu.monitor(scores_given=given)                              # (leaves the workspace clear)
+    cap = torch.cuda.Stream()
+    cap.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(cap):
+        with torch.cuda.graph(graph, stream=cap):
+            gpu.monitor(scores_given=given)
+    torch.cuda.synchronize()
+    for now in (n,) + upto:
+        while spec.ctx[0] < now + 12:
+            gpu.append(token, token)
+            spec.ctx[0] += 1
+        lo, hi = spec.cand_range(0, 0)
+        assert hi - lo == now
+        base = {(0, 0): torch.arange(hi - spec.k_mon(0, 0), hi, dtype=torch.int32)}       # (the newest candidates)
+        for call in (graph.replay, graph.replay, lambda: gpu.monitor(scores_given=given)):
+            gpu.base_idx[0, :len(base[(0, 0)])] = base[(0, 0)].to(DEV)
+            gpu.ring.zero_()
+            gpu.topk_idx.fill_(-1)
+            if given:
+                gpu.scores.copy_(scores)
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            np.testing.assert_allclose(gpu.scores[0, lo:hi].cpu().numpy(), scores[0, lo:hi].cpu().numpy(), rtol=1e-5)
+            T.compare_monitor(spec, gpu, {(0, 0): gpu.scores[0].cpu().numpy().copy()}, base)
+    gpu.close()
+    ctx.close()
