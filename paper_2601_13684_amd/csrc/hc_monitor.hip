@@ -1165,7 +1165,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];       // [bufs][NW][TILE] scores, a bit per item, the baseline bitmap
     __shared__ __attribute__((aligned(16))) uint32_t sm_hist[HC_RADIX_BINS];
     __shared__ uint64_t sm_band[BAND];
-    __shared__ uint32_t sm_rank[RANKED], sm_part[NW], sm_count[NW], sm_eq[NW], sm_hits[NW], sm_nband, sm_nrank, sm_tau, sm_least, sm_most;
+    __shared__ uint32_t sm_rank[RANKED], sm_part[NW], sm_count[NW], sm_eq[NW], sm_hits[NW], sm_nband, sm_nrank, sm_tau, sm_least, sm_most, sm_own[4];
 
     const MonItem& it = B.it[blockIdx.z];
     const int rep = blockIdx.x, ks = blockIdx.y;
@@ -1194,10 +1194,10 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
     const int real_lo = it.real_reps[rep].lo & ALIGN, real_hi = min(it.real_reps[rep].hi, real_lo + bm_words * 32);      // the bitmap is indexed by position
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;
-    const bool checks = deciding && it.need_sense == 0 && it.filt != nullptr;
+    const bool checks = MAP && deciding && it.need_sense == 0 && it.filt != nullptr;      // (a filter's rows come with a map)
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
     float ref_of = -INFINITY, lse_of = 0.f;          // lane g: of query head g of the group
-    if (deciding && it.filt && lane < n_group) lse_of = it.lse[(size_t)rd.bh * n_group + lane];
+    if (checks && lane < n_group) lse_of = it.lse[(size_t)rd.bh * n_group + lane];
     if (checks && lane < n_group) ref_of = it.filt[rep].ref[lane];
     constexpr int HV = HC_RADIX_BINS / 4, HP = (HV + NT - 1) / NT;       // 16-byte pieces of the histogram, of a thread
     uint4 h[HP];
@@ -1378,14 +1378,36 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         }
         return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? k_lo + (digit << k_shift) : fine_low(digit);
     };
-    if (deciding && it.filt && k_longest != k) {     // a bound from below will do for the filter
-        tmin = find((uint32_t)k_longest);
+    auto width = [&](uint32_t from) {                // (digits do not reach beyond what was counted in them)
+        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? min((1u << k_shift) - 1u, k_hi - from) : fine_last(digit) - from;
+    };
+    uint32_t lo = find((uint32_t)k), wide = width(lo);
+    // The filter's threshold is the smallest of all lists, to one part in 65,536: the edge of its digit would let more rows through,
+    // and the lowest digit has no number at its edge, so that the check would fail at every step.
+    bool for_filter = checks && k_longest != k;
+    if (for_filter) {
+        if (tid == 0) {                              // (this list's digit, meanwhile in LDS)
+            sm_own[0] = lo;
+            sm_own[1] = wide;
+            sm_own[2] = rem;
+            sm_own[3] = count;
+        }
         __syncthreads();
+        lo = find((uint32_t)k_longest);
+        wide = width(lo);
     }
-    uint32_t lo = find((uint32_t)k);                 // (digits do not reach beyond what was counted in them)
-    uint32_t wide = SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? min((1u << k_shift) - 1u, k_hi - lo) : fine_last(digit) - lo;
     auto candidate = [&](int i) { return i >= first && i < end; };
-    while (count > BAND && wide != 0u) {             // (the same for every thread)
+    for (;;) {                                       // (the same for every thread)
+        if (for_filter ? wide < 128u : count <= BAND || wide == 0u) {
+            if (!for_filter) break;
+            for_filter = false;
+            tmin = lo;
+            lo = sm_own[0];
+            wide = sm_own[1];
+            rem = sm_own[2];
+            count = sm_own[3];
+            continue;
+        }
         const uint32_t shift = wide < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(wide);      // wide >> shift < 2048
         __syncthreads();
         for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
@@ -1395,7 +1417,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         }
         __syncthreads();
         uint32_t least = 0xffffffffu, greatest = 0u;
-        constexpr int R = SRC == DIRECT_LOGITS ? 4 : NT == 512 ? 8 : 16;         // reads of a lane in flight
+        constexpr int R = SRC == DIRECT_LOGITS || (MAP && NT == 512) ? 4 : NT == 512 ? 8 : 16;         // reads of a lane in flight
         for (int i0 = t0 * TILE + lane; i0 < t1 * TILE; i0 += 64 * R) {
             float x[R];
 #pragma unroll

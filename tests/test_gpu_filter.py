@@ -2,6 +2,8 @@
 logits that can reach a list, the monitor selects among them, checks on the device that no dropped row could have
 mattered, and otherwise redoes the pivot from all of its logits.  Whatever path a step takes, lists, overlaps, flags
 and refilled rows must be those of the oracle (which knows nothing of any filter).  Run with `-m gpu`."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -193,3 +195,42 @@ def test_side_lds_argument_range():
         with pytest.raises(hc.HcError):
             hc.hc_set_side_lds(ctx.handle, bad)
     ctx.close()
+
+
+@pytest.mark.parametrize("N,k_mon,scale", [(60001, 300, 20.0), (60001, 300, 1.0), (20011, 100, 20.0), (60001, 0, 20.0)])
+def test_filter_where_the_longest_list_is_not_the_monitored_one(N, k_mon, scale):
+    """Sharp attention (scale 20: the longest list ends below 2^-31) with a monitored list that is shorter than the longest: the
+    filter's threshold is the longest list's, exactly, so an unchanged query never falls back, and keeps the rows that reach the
+    threshold divided by the margin.  Lists and tables like those without the filter."""
+    say("filter, longest list not monitored", N, k_mon, scale)
+    tables, kept = [], []
+    for margin in (1.25, 0.0):
+        w = I.make_workload(2, N=N)
+        if k_mon:
+            w.spec.heads[0][:] = [dataclasses.replace(h, k_mon=k_mon) if h.role == I.ROLE_FULL else h for h in w.spec.heads[0]]
+        ctx = R.Context(R.make_config(w.spec), DEV, filter_margin=margin)
+        lay = R.LayerRuntime(ctx, w.spec, w.data, *I.initial_lists(w.spec), own_scratch=True)
+        q = (w.schedule.next().float() * scale).to(torch.bfloat16).to(DEV)
+        seen = []
+        for t in range(4):
+            lay.step(q)
+            torch.cuda.synchronize()
+            seen.append([x.cpu().numpy().copy() for x in (lay.topk_idx, lay.base_idx, lay.ring, lay.inter, lay.flag, lay.slot_pos, lay.out)])
+            for p in w.spec.reps(0):
+                c = lay.monitor_counts(0, p)
+                if margin:
+                    assert c["fallbacks"] == 0, (t, p, c)
+                    kept.append(c["kept"])
+                else:
+                    lo, hi = w.spec.cand_range(0, p)
+                    s = lay.scores[lay.rep_slot(0, p), lo:hi].cpu().numpy()
+                    kth = np.sort(s)[::-1][max(w.spec.r(0, h) for h in w.spec.satellites(0, p)) - 1]
+                    assert (kth < 2.0 ** -31) == (scale > 1.0), kth
+                    if t > 0:                        # (the statistic's rounding may move a row or two across the cut)
+                        assert abs(kept[t * len(w.spec.reps(0)) + w.spec.reps(0).index(p)] - int((s >= kth / 1.25).sum())) <= 2
+        tables.append(seen)
+        lay.close()
+        ctx.close()
+    for t, (a, b) in enumerate(zip(*tables)):
+        for i, (x, y) in enumerate(zip(a, b)):
+            np.testing.assert_array_equal(x, y, err_msg=f"step {t} table {i}")
