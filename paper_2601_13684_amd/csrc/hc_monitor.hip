@@ -286,14 +286,31 @@ __device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j,
 
 // ---- the histogram of a candidate range ----
 //
-// Scores are mostly probabilities, so the digits are spent on [2^-31, 2): 64 of them to an octave, each 1.1 to 1.6 % of a score
-// wide; the lowest takes everything below (negative scores and what is no number among them), the highest everything above.
-// The digit in which a list ends then holds a hundred or so of 32K candidates (of the key's first 11 bits, four to an
-// octave, thousands), unless scores are that close to each other.
-constexpr int FINE_BASE = (0x80000000u >> 17) + (96 << 6);      // the key of 2^-31, without its last 17 bits
-__device__ __forceinline__ uint32_t fine_digit(uint32_t key) { return (uint32_t)min(max((int)(key >> 17) - FINE_BASE, 0), HC_RADIX_BINS - 1); }
-__device__ __forceinline__ uint32_t fine_low(uint32_t digit) { return digit == 0u ? 0u : (digit + (uint32_t)FINE_BASE) << 17; }      // smallest key of a digit
-__device__ __forceinline__ uint32_t fine_last(uint32_t digit) { return digit == HC_RADIX_BINS - 1 ? 0xffffffffu : fine_low(digit + 1u) - 1u; }      // ... and the largest
+// 2048 digits, narrow ones for where a list usually ends, wide ones on either side.  Probabilities (HC_AGG_PROB): 64 to an octave
+// over [2^-23, 2^-7), each 1.1 to 1.6 % of a score wide, 16 over [2^-79, 2^-23) and [2^-7, 2); the lowest takes everything below (negative
+// scores and what is no number among them), the highest everything above.  The digit in which a list ends then holds a
+// hundred or so of 32K candidates (of the key's first 11 bits, four to an octave, thousands), unless scores are that close to
+// each other; where sharp attention makes scores small they are far apart.  Mean logits (HC_AGG_LOGIT): digits of 1/64 over
+// [-12, 12), of 1/8 from -44 to 44.
+template <int MID, int LOW, int SHIFT>
+struct Digits {                                      // x: number of a narrow digit, 0 .. MID - 1 the narrow ones
+    static __device__ __forceinline__ uint32_t of(int x)
+    {
+        return (uint32_t)min(max(LOW + (min(x, 0) >> SHIFT) + min(max(x, 0), MID) + (max(x - MID, 0) >> SHIFT), 0), HC_RADIX_BINS - 1);
+    }
+    static __device__ __forceinline__ int first(int digit) { return digit < LOW ? (digit - LOW) << SHIFT : digit < LOW + MID ? digit - LOW : MID + ((digit - LOW - MID) << SHIFT); }
+};
+typedef Digits<1024, 896, 2> FineDigits;
+typedef Digits<1536, 256, 3> LinearDigits;
+constexpr int FINE_BASE = (0x80000000u >> 17) + (104 << 6);     // the key of 2^-23, without its last 17 bits
+__device__ __forceinline__ uint32_t fine_digit(uint32_t key) { return FineDigits::of((int)(key >> 17) - FINE_BASE); }
+__device__ __forceinline__ uint32_t linear_digit(float s) { return LinearDigits::of((int)fminf(fmaxf(floorf(s * 64.f), -4096.f), 4096.f) + 768); }
+__device__ __forceinline__ uint32_t digit_low(uint32_t digit, bool linear)                // smallest key of a digit ...
+{
+    if (digit == 0u) return 0u;
+    return linear ? hc_score_key((float)(LinearDigits::first((int)digit) - 768) / 64.f) : (uint32_t)(FineDigits::first((int)digit) + FINE_BASE) << 17;
+}
+__device__ __forceinline__ uint32_t digit_last(uint32_t digit, bool linear) { return digit == HC_RADIX_BINS - 1 ? 0xffffffffu : digit_low(digit + 1u, linear) - 1u; }      // ... and the largest
 
 // ---- the survivors of a long range ----
 //
@@ -376,10 +393,11 @@ __device__ __forceinline__ void sample_threshold(uint32_t* sm_hist, uint32_t* sm
     row_out = sample_row(src * 64 + (bits ? __builtin_ctzll(bits) : 0), lo, n);
 }
 
-// Scores and histogram of a long candidate range (over the first 11 bits of the keys unless mon_direct reads it).  A workgroup takes `span` consecutive chunks of
+// Scores and histogram of a long candidate range (over the first 11 bits of the keys, or the digits that mon_direct reads).  A workgroup takes `span` consecutive chunks of
 // HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
 // most: as many candidates as mon_direct will go through (a captured call may find more than when it was launched).
-template <int G, bool FINE>
+enum { HIST_KEYS = 0, HIST_FINE = 1, HIST_LINEAR = 2 };
+template <int G, int HIST>
 __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k, int most)
 {
     __shared__ uint32_t sh[HC_RADIX_BINS];
@@ -387,7 +405,7 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
     const int rep = blockIdx.y;
     if (rep >= it.n_reps || mon_skip(it, rep)) return;
     RepDev rd = it.reps[rep];
-    if (FINE) rd.hi = min(rd.hi, rd.lo + most);
+    if (HIST != HIST_KEYS) rd.hi = min(rd.hi, rd.lo + most);
     const int c0 = blockIdx.x * span, c1 = min(c0 + span, rd.nchunk);
     if (c0 >= rd.nchunk) return;
     float* srow = it.scores + (size_t)rep * it.ws.max_ctx;
@@ -396,7 +414,7 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
 #pragma unroll
     for (int g = 0; g < G; ++g) l[g] = (!scores_given && agg == HC_AGG_PROB) ? it.lse[(size_t)rd.bh * G + g] : 0.f;
     for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK) sh[i] = 0u;
-    if (!FINE && long_lists) {                       // a slice each: the later histograms cleared, the baseline list to its bitmap
+    if (HIST == HIST_KEYS && long_lists) {                       // a slice each: the later histograms cleared, the baseline list to its bitmap
         const Ws w = it.ws.rep(rep);
         const int first = blockIdx.x * BLK + threadIdx.x, step = (rd.nchunk + span - 1) / span * BLK;
         const int lo = it.real_reps[rep].lo, hi = it.real_reps[rep].hi;
@@ -423,7 +441,7 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
             if (j < rd.hi) {
                 if (!scores_given) srow[j] = s[i];
                 const uint32_t key = hc_score_key(s[i]);
-                atomicAdd(&sh[FINE ? fine_digit(key) : key >> 21], 1u);
+                atomicAdd(&sh[HIST == HIST_LINEAR ? linear_digit(s[i]) : HIST == HIST_FINE ? fine_digit(key) : key >> 21], 1u);
             }
         }
     }
@@ -1147,9 +1165,12 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 //
 // What bounds it is latency and issue: with 16 waves, an instruction that all of them execute takes 16 cycles of every SIMD.
 // (With the items 64 to a round, one to a lane, and ballots, going through 32K of them took 4.3 us of the launch.)
-// One pivot, three set sizes, us per call with the launch before it, scores spread out / within 2 % of each other / equal, and in
-// brackets by mon_compact and mon_select (and mon_score_hist): 10,000 candidates 17 / 21 / 23 (25 / 34 / 34), 32,768 21 / 30 / 35
-// (28 / 40 / 48), 65,000 26 / 43 / 54 (36 / 49 / 60).  By itself, 4,096 candidates 12.2 / 12.3 / 12.0 (mon_select over keys 13.4 / 13.7 /
+// One pivot, three set sizes, us per call with the launch before it, and in brackets by mon_compact and mon_select (and
+// mon_score_hist).  Given scores spread out / within 2 % of each other / equal: 10,000 candidates 15 / 19 / 19 (23 / 33 / 34), 32,768 19 /
+// 24 / 25 (25 / 37 / 43), 65,000 25 / 33 / 37 (32 / 35 / 57).  Mean logits (HC_AGG_LOGIT) of any offset, spread out / within 0.1 %: 10,000
+// 16 / 20 (24-27 / 27), 32,768 21 / 25-29 (27-40 / 40-43), 65,000 27-29 / 35-43 (35-49 / 48-53).  Given scores that are not what HC_AGG_PROB
+// makes of logits, negative or above 2, end in a digit without an edge: 10,000 20 (23), 32,768 26-28 (25), 65,000 37-41 (32-34).  By
+// itself, 4,096 candidates 12.2 / 12.3 / 12.0 (mon_select over keys 13.4 / 13.7 /
 // 11.7), 8,192 15.4 / 15.2 / 14.3 (16.5 / 16.6 / 16.2).  The decode step of four 32K layers with a window of four: 125 us (145).
 constexpr int BAND = 512;                // items of the digit that can be ranked ...
 constexpr int RANKED = 128;              // ... without a histogram of their own
@@ -1368,6 +1389,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
 
     // ---- the digit in which the list ends: keys [lo, lo + wide], `count` items of which `rem` are in the list ----
     uint32_t digit, rem, count, tmin = 0u;
+    const bool linear = SRC == DIRECT_HIST && cfg.agg == HC_AGG_LOGIT;
     auto find = [&](uint32_t k_of) {
         if ((SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES) && k_lo == k_hi) {
             digit = 0u;
@@ -1376,10 +1398,10 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         } else {
             find_digit_all<NW>(sm_hist, sm_part, k_of, digit, rem, count);
         }
-        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? k_lo + (digit << k_shift) : fine_low(digit);
+        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? k_lo + (digit << k_shift) : digit_low(digit, linear);
     };
     auto width = [&](uint32_t from) {                // (digits do not reach beyond what was counted in them)
-        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? min((1u << k_shift) - 1u, k_hi - from) : fine_last(digit) - from;
+        return SRC == DIRECT_LOGITS || SRC == DIRECT_SCORES ? min((1u << k_shift) - 1u, k_hi - from) : digit_last(digit, linear) - from;
     };
     uint32_t lo = find((uint32_t)k), wide = width(lo);
     // The filter's threshold is the smallest of all lists, to one part in 65,536: the edge of its digit would let more rows through,
@@ -1396,11 +1418,15 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         lo = find((uint32_t)k_longest);
         wide = width(lo);
     }
-    auto candidate = [&](int i) { return i >= first && i < end; };
+    // A digit with more items than can be ranked is cut again: its smallest and largest key are looked for first, then what
+    // lies between is counted in 2048 parts.  (Counted in parts of the digit's width at once, equal ones summed over a wave because they
+    // are in each other's way, an item to a lane: 32,768 items within 2 % of each other 27.8 us a call, equal 33.3; this way 23.6 and
+    // 24.9.  65,800: 41.2 and 52.4; 32.6 and 36.9.)
+    bool measured = false;
     for (;;) {                                       // (the same for every thread)
         if (for_filter ? wide < 128u : count <= BAND || wide == 0u) {
             if (!for_filter) break;
-            for_filter = false;
+            for_filter = measured = false;
             tmin = lo;
             lo = sm_own[0];
             wide = sm_own[1];
@@ -1410,50 +1436,85 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
         }
         const uint32_t shift = wide < HC_RADIX_BINS ? 0u : 21u - (uint32_t)__builtin_clz(wide);      // wide >> shift < 2048
         __syncthreads();
-        for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
-        if (tid == 0) {
+        if (measured) {
+            for (int i = tid; i < HC_RADIX_BINS; i += NT) sm_hist[i] = 0u;
+        } else if (tid == 0) {
             sm_least = 0xffffffffu;
             sm_most = 0u;
         }
         __syncthreads();
         uint32_t least = 0xffffffffu, greatest = 0u;
-        constexpr int R = SRC == DIRECT_LOGITS || (MAP && NT == 512) ? 4 : NT == 512 ? 8 : 16;         // reads of a lane in flight
-        for (int i0 = t0 * TILE + lane; i0 < t1 * TILE; i0 += 64 * R) {
-            float x[R];
+        // (positive numbers compare as their bits do; the tiles are still in LDS unless a wave has more of them than buffers; any order will do)
+        auto pass = [&](auto raw, auto here) {
+            constexpr bool RAW = decltype(raw)::value, LDS = decltype(here)::value;
+            constexpr int R = SRC == DIRECT_LOGITS || NT == 512 ? (MAP ? 1 : 2) : 4;     // reads of a lane in flight
+            const uint32_t from = RAW ? lo & 0x7fffffffu : lo;
+#pragma unroll 1
+            for (int t = t0; t < t1; ++t) {
+                const bool whole = t * TILE >= first && (t + 1) * TILE <= end;
+#pragma unroll 1
+                for (int p0 = 4 * lane; p0 < TILE; p0 += 256 * R) {
+                    float4 v[R];
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int i = min(i0 + u * 64, end - 1);
-                x[u] = SRC == DIRECT_LOGITS ? __uint_as_float(dyn[(i & ~15) | ((((i >> 2) & 3) ^ ((i >> 6) & 3)) << 2) | (i & 3)]) : srow[i];
-            }
+                    for (int u = 0; u < R; ++u) {
+                        if (LDS) v[u] = *reinterpret_cast<const float4*>(buffer(t) + p0 + 256 * u);
+                        else v[u] = *reinterpret_cast<const float4*>(srow + min(t * TILE + p0 + 256 * u, (end - 1) & ~3));
+                    }
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const uint32_t d = hc_score_key(x[u]) - lo;
-                const bool in = candidate(i0 + u * 64) && d <= wide;
-                least = in ? min(least, d) : least;
-                greatest = in ? max(greatest, d) : greatest;
-                const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-                const uint32_t one = m ? lane_get(d >> shift, __builtin_ctzll(m)) : 0u;
-                if (m == __builtin_amdgcn_ballot_w64(in && d >> shift == one)) {      // (equal scores: one sum instead of 64 in turn)
-                    if (m && lane == 0) atomicAdd(&sm_hist[one], (uint32_t)__builtin_popcountll(m));
-                } else if (in) {
-                    atomicAdd(&sm_hist[d >> shift], 1u);
+                    for (int u = 0; u < R; ++u) {
+                        const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                        uint32_t d[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) d[c] = (RAW ? __float_as_uint(x[c]) : hc_score_key(x[c])) - from;
+                        if (!whole) {
+                            const int p = p0 + 256 * u, i = t * TILE + (LDS ? (p & ~15) | ((p ^ (p >> 4)) & 12) : p);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (i + c < first || i + c >= end) d[c] = 0xffffffffu;       // (no candidate; wide is less)
+                        }
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            if (measured) {
+                                if (d[c] <= wide) atomicAdd(&sm_hist[d[c] >> shift], 1u);
+                            } else {
+                                least = min(least, d[c]);
+                                greatest = d[c] <= wide ? max(greatest, d[c]) : greatest;
+                            }
+                        }
+                    }
                 }
             }
-        }
-        least = ~wave_max(~least);
-        greatest = wave_max(greatest);
-        if (lane == 0) {
-            atomicMin(&sm_least, least);
-            atomicMax(&sm_most, greatest);
-        }
-        __syncthreads();
-        find_digit_all<NW>(sm_hist, sm_part, rem, digit, rem, count);
-        if (sm_least == sm_most) {                   // all equal: nothing left to cut
-            lo += sm_least;
-            wide = 0u;
+        };
+        const bool raw = lo > 0x80000000u && lo + wide < 0xff800000u;
+        if constexpr (SRC == DIRECT_LOGITS) {
+            pass(std::false_type{}, std::true_type{});
+        } else if constexpr (NT == 512) {            // (more forms would take registers)
+            pass(std::false_type{}, std::false_type{});
+        } else if (per <= bufs) {
+            arrived(t0);
+            if (raw) pass(std::true_type{}, std::true_type{});
+            else pass(std::false_type{}, std::true_type{});
         } else {
+            if (raw) pass(std::true_type{}, std::false_type{});
+            else pass(std::false_type{}, std::false_type{});
+        }
+        if (!measured) {
+            least = ~wave_max(~least);
+            greatest = wave_max(greatest);
+            if (lane == 0) {
+                atomicMin(&sm_least, least);
+                atomicMax(&sm_most, greatest);
+            }
+            __syncthreads();
+            lo += sm_least;
+            wide = sm_least <= sm_most ? sm_most - sm_least : 0u;        // (there is one, unless the histogram is not of these scores)
+            measured = true;
+        } else {
+            __syncthreads();
+            find_digit_all<NW>(sm_hist, sm_part, rem, digit, rem, count);
             wide = min((1u << shift) - 1u, wide - (digit << shift));
             lo += digit << shift;
+            measured = false;
         }
     }
 
@@ -2307,17 +2368,21 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         // 512.  (The launches that stand by: few, long workgroups.)
         const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
-#define HC_SCORE(GG, FINE)                                                                                                   \
-    mon_score_hist<GG, FINE><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, FINE>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(ctx, DIRECT_HIST, candidates))
-        switch (ctx->G * 2 + direct) {
-        case 2: HC_SCORE(1, false); break;
-        case 3: HC_SCORE(1, true); break;
-        case 4: HC_SCORE(2, false); break;
-        case 5: HC_SCORE(2, true); break;
-        case 8: HC_SCORE(4, false); break;
-        case 9: HC_SCORE(4, true); break;
-        case 16: HC_SCORE(8, false); break;
-        default: HC_SCORE(8, true); break;
+#define HC_SCORE(GG, HIST)                                                                                                   \
+    mon_score_hist<GG, HIST><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, HIST>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(ctx, DIRECT_HIST, candidates))
+        switch (ctx->G * 4 + (!direct ? HIST_KEYS : c.agg == HC_AGG_LOGIT ? HIST_LINEAR : HIST_FINE)) {
+        case 4: HC_SCORE(1, HIST_KEYS); break;
+        case 5: HC_SCORE(1, HIST_FINE); break;
+        case 6: HC_SCORE(1, HIST_LINEAR); break;
+        case 8: HC_SCORE(2, HIST_KEYS); break;
+        case 9: HC_SCORE(2, HIST_FINE); break;
+        case 10: HC_SCORE(2, HIST_LINEAR); break;
+        case 16: HC_SCORE(4, HIST_KEYS); break;
+        case 17: HC_SCORE(4, HIST_FINE); break;
+        case 18: HC_SCORE(4, HIST_LINEAR); break;
+        case 32: HC_SCORE(8, HIST_KEYS); break;
+        case 33: HC_SCORE(8, HIST_FINE); break;
+        default: HC_SCORE(8, HIST_LINEAR); break;
         }
 #undef HC_SCORE
         HC_HIP(ctx, hipGetLastError());
@@ -2394,8 +2459,9 @@ hc_status hc_monitor_set_lds_limit()
                          (const void*)mon_direct<1024, DIRECT_LOGITS, 4>, (const void*)mon_direct<1024, DIRECT_LOGITS, 8>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
                          (const void*)mon_compact, (const void*)mon_sparse_score<1>,
                          (const void*)mon_sparse_score<2>, (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>,
-                         (const void*)mon_score_hist<1, false>, (const void*)mon_score_hist<2, false>, (const void*)mon_score_hist<4, false>, (const void*)mon_score_hist<8, false>,
-                         (const void*)mon_score_hist<1, true>, (const void*)mon_score_hist<2, true>, (const void*)mon_score_hist<4, true>, (const void*)mon_score_hist<8, true>,
+                         (const void*)mon_score_hist<1, HIST_KEYS>, (const void*)mon_score_hist<2, HIST_KEYS>, (const void*)mon_score_hist<4, HIST_KEYS>, (const void*)mon_score_hist<8, HIST_KEYS>,
+                         (const void*)mon_score_hist<1, HIST_FINE>, (const void*)mon_score_hist<2, HIST_FINE>, (const void*)mon_score_hist<4, HIST_FINE>, (const void*)mon_score_hist<8, HIST_FINE>,
+                         (const void*)mon_score_hist<1, HIST_LINEAR>, (const void*)mon_score_hist<2, HIST_LINEAR>, (const void*)mon_score_hist<4, HIST_LINEAR>, (const void*)mon_score_hist<8, HIST_LINEAR>,
                          (const void*)mon_select<512, SRC_SCORES>, (const void*)mon_select<512, SRC_SURVIVORS>, (const void*)mon_select<512, SRC_RANGE>,
                          (const void*)mon_select<1024, SRC_SCORES>, (const void*)mon_select<1024, SRC_SURVIVORS>, (const void*)mon_select<1024, SRC_RANGE>};
     for (const void* fn : fns)

@@ -179,3 +179,70 @@ def test_captured_call_and_a_context_that_grows(n, upto, given):
             T.compare_monitor(spec, gpu, {(0, 0): gpu.scores[0].cpu().numpy().copy()}, base)
     gpu.close()
     ctx.close()
+
+
+# scores that the call computes itself, over both kinds of digits: mean logits of one head are the logits as they are, so that every
+# distribution reaches the linear ones; softmax weights at the edges of narrow and wide digits and far below them
+@pytest.mark.parametrize("n,rs,sink,kind", [(8193, (700, 3), 5, "special"), (9217, (2000, 8000), 2, "signed"), (16385, (600, 1), 7, "large"), (20011, (12000, 300), 6, "zeros"),
+                                            (24576, (500, 513), 5, "ulps"), (32768, (17000, 1000), 3, "flat"), (65533, (7000, 33, 1), 3, "signed"), (65533, (7000, 33), 1, "equal"),
+                                            (40001, (3999, 1), 2, "logits"), (65533, (7000, 60000), 2, "logits"), (32768, (3776, 20000, 32000), 3, "weights"),
+                                            (65533, (300, 40000, 65000), 2, "weights"), (10000, (1000, 9999), 1, "edges")])
+def test_computed_scores(n, rs, sink, kind):
+    T.say("monitor direct computed", n, rs, sink, kind)
+    N = n + sink + 7
+    spec = one_pivot(N, rs, sink=sink)
+    agg = I.AGG_PROB if kind in ("weights", "edges") else I.AGG_LOGIT
+    spec = I.LayerSpec(B=1, Hq=spec.Hkv, Hkv=spec.Hkv, D=128, ctx=[N], heads=spec.heads, agg=agg)
+    rng = np.random.default_rng(n + len(rs))
+    if kind == "logits":                        # both ends of the linear digits' range and beyond, narrow and wide ones
+        logits = (rng.normal(size=N) * 25).astype(np.float32)
+    elif kind == "weights":                     # sharp attention: from 1 down to nothing
+        logits = (rng.normal(size=N) * 30 - 60).astype(np.float32)
+    elif kind == "edges":                       # a power of two each, one value in a thousand off by little
+        logits = (np.log(2.0) * rng.integers(-90, 3, N) + (rng.random(N) < 1e-3) * rng.normal(size=N) * 1e-6).astype(np.float32)
+    else:
+        logits = draw(kind, N, rng)
+    lo, hi = spec.cand_range(0, 0)
+    base = {(0, 0): torch.from_numpy(np.sort(rng.choice(np.arange(lo, hi), spec.k_mon(0, 0), replace=False)).astype(np.int32))}
+    ctx, gpu, base_all = T.monitor_case(spec, {(0, 0): np.zeros(N, np.float32)}, base)
+    gpu.rep_logits[0, :N, 0] = torch.from_numpy(logits).to(DEV)
+    gpu.lse.zero_()
+    for call in range(2):
+        gpu.base_idx[0, :len(base_all[(0, 0)])] = base_all[(0, 0)].to(DEV)
+        gpu.ring.zero_()
+        gpu.monitor()
+        torch.cuda.synchronize()
+        s = gpu.scores[0, :N].cpu().numpy().copy()
+        if agg == I.AGG_LOGIT:
+            np.testing.assert_array_equal(s[lo:hi], logits[lo:hi])
+        T.compare_monitor(spec, gpu, {(0, 0): np.where(np.isnan(s), np.float32(-np.inf), s)}, base_all)
+    gpu.close()
+    ctx.close()
+
+
+def test_time_does_not_depend_on_the_offset():
+    """Mean logits around 8, around -8 and close to each other take less than twice what mean logits around 0 take (measured at 65,480
+    candidates: 1.0, 1.1 and 1.3 to 1.6 times; 2.6, 2.8 and 3.6 times over digits made for probabilities)."""
+    N = 65800
+    heads = one_pivot(N, (8192, 4096, 2048), sink=64, recent=256).heads
+    spec = I.LayerSpec(B=1, Hq=16, Hkv=4, D=128, ctx=[N], heads=heads, agg=I.AGG_LOGIT)
+    ctx, gpu, _ = T.monitor_case(spec, {(0, 0): np.zeros(N, np.float32)}, I.initial_lists(spec)[1])
+    noise = torch.randn((N, 4), generator=torch.Generator().manual_seed(2)).to(DEV)
+    us = {}
+    for scale, mean in ((1.5, 0.0), (1.5, 8.0), (1.5, -8.0), (0.01, 8.0), (0.01, -8.0)):
+        gpu.rep_logits[0, :N] = noise * scale + mean
+        gpu.monitor()
+        best = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                gpu.monitor()
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b) / 20 * 1e3)
+        us[scale, mean] = min(best)
+    gpu.close()
+    ctx.close()
+    T.say("monitor time by offset", {k: round(v, 1) for k, v in us.items()})
+    assert max(us.values()) < 2 * us[1.5, 0.0], us
