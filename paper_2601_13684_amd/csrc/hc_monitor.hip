@@ -2168,6 +2168,17 @@ static bool direct_fits(const hc_ctx* ctx, int items, int bm_words)
 {
     return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, direct_most(ctx, DIRECT_HIST, items), bm_words, 1) <= direct_room(ctx);
 }
+// Lists that mon_direct writes in several pieces, going through its bits for each (a piece has 16,384 entries there, alone): whether
+// the six launches of long lists take less.  One list, us by them / by mon_direct, scores spread out and within 2 % of each other: 32,000 of
+// 40,000 candidates 54 54 / 45 51, 36,000 61 62 / 61 67; of 50,000 26,000 entries 46 45 / 45 46, 32,000 49 50 / 44 51, 36,000 51 51 / 54 61;
+// of 58,000 16,000 40 41 / 31 38, 20,000 42 42 / 38 46, 26,000 43 43 / 49 51; of 65,480 16,000 40 40 / 31 39, 20,000 41 42 / 45 45, 60,000 62 63 /
+// 98 106.  Each further list adds 5 us to the six and nothing to mon_direct: lists of 20,000, 10,000 and 5,000 of 65,480 54 54 / 44 45, of
+// 36,000, 20,000 and 9,000 60 60 / 55 64, of 50,000 63 64 / 54 61.  (Beside the
+// attention pass its ranges are shorter: steps of four layers of 31,000 with lists of 22,000 and 8,000 194 us by the six, 146.)
+static bool direct_outlasted(const hc_ctx* ctx, int items, int max_k, int max_nk)
+{
+    return !ctx->beside_now && max_k > 16384 && !(max_nk >= 3 ? max_k <= 40960 : max_k <= 32768 && items <= 51200);
+}
 template <int SRC>
 static hc_status launch_direct(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
 {
@@ -2329,9 +2340,10 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     const dim3 gsel(max_reps, max_nk, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
-    // mon_direct wherever it has room: at every length and distribution it takes less than mon_compact and mon_select (see there).
-    // (candidates: of a filtering layer, what its launches are sized for)
-    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words);
+    // mon_direct where it has room and the lists are not too long for it.  (candidates: of a filtering layer, what its launches are
+    // sized for)
+    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words) &&
+                        !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk));
     if (mode == 1) {
         if (direct)                                      // (more rows than it goes through, in a captured call: the dense chain's)
             for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(ctx, DIRECT_MAP, candidates));
