@@ -296,7 +296,8 @@ template <int MID, int LOW, int SHIFT>
 struct Digits {                                      // x: number of a narrow digit, 0 .. MID - 1 the narrow ones
     static __device__ __forceinline__ uint32_t of(int x)
     {
-        return (uint32_t)min(max(LOW + (min(x, 0) >> SHIFT) + min(max(x, 0), MID) + (max(x - MID, 0) >> SHIFT), 0), HC_RADIX_BINS - 1);
+        const int y = min(max(x, x >> SHIFT), (x + ((1 << SHIFT) - 1) * MID) >> SHIFT);      // (below 0 and above MID the flatter line)
+        return (uint32_t)min(max(y + LOW, 0), HC_RADIX_BINS - 1);
     }
     static __device__ __forceinline__ int first(int digit) { return digit < LOW ? (digit - LOW) << SHIFT : digit < LOW + MID ? digit - LOW : MID + ((digit - LOW - MID) << SHIFT); }
 };
