@@ -209,9 +209,11 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     if (total == 0) return;
     const int tid = threadIdx.x, wv = uniform(tid >> 6), lane = tid & 63;
     // List rows to a task: where there are at least twice as many workgroups as satellites, such that every task has a workgroup of
-    // its own; otherwise half a workgroup's, so that those who get two tasks or three are evenly busy (steps of six sequences,
-    // 72 satellites, 48 workgroups: 245.5 us, with tasks of two workgroups' rows 247.5, of one's 249).
-    const int by = 2 * fired <= n_wgs ? n_wgs - fired : 2 * n_wgs, share = (total + by - 1) / by;
+    // its own; otherwise half a workgroup's, so that those who get two tasks or three are evenly busy, but 256 at least: a task makes its
+    // satellite's whole plan, 7 us, about what 256 rows of a list take.  (Calls over satellites of 16,384, lists a quarter new, by 48
+    // workgroups.  24, 27, 36, 42 satellites, lists of 80 to 140: 16, 17, 19, 21 us, without the lower bound 16, 26, 28, 28; of 310 to
+    // 610: 37, 45, 49, 63, without 37, 44, 57, 59, with 512 37, 40, 49, 70.  Tasks of a workgroup's rows: 22, 22, 24, 25 and 45, 46, 56, 58.)
+    const int by = 2 * fired <= n_wgs ? n_wgs - fired : 2 * n_wgs, share = max((total + by - 1) / by, 2 * fired <= n_wgs ? 1 : 256);
     if (wv == 0) {                                   // rows -> first task (one for each of a satellite's workgroups)
         int before = 0;
 #pragma unroll 1
