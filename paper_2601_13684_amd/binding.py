@@ -194,7 +194,7 @@ def hc_set_logit_filter(ctx: int, margin: float, min_candidates: int = 0) -> Non
     _check(lib().hc_set_logit_filter(ctx, float(margin), int(min_candidates)), "hc_set_logit_filter", ctx)
 
 
-def hc_set_gather_shape(ctx: int, workgroups: int = 96, threads: int = 256) -> None:
+def hc_set_gather_shape(ctx: int, workgroups: int = 0, threads: int = 256) -> None:
     _check(lib().hc_set_gather_shape(ctx, workgroups, threads), "hc_set_gather_shape", ctx)
 
 

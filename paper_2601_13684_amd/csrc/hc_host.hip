@@ -223,8 +223,8 @@ extern "C" hc_status hc_set_side_lds(hc_ctx* ctx, int32_t bytes)
 extern "C" hc_status hc_set_gather_shape(hc_ctx* ctx, int32_t workgroups, int32_t threads)
 {
     if (!ctx_ok(ctx)) return HC_ESTATE;
-    if (workgroups < 1 || workgroups > 4096 || (threads != 64 && threads != 128 && threads != 256))
-        return hc_fail(ctx, HC_EINVAL, "hc_set_gather_shape: 1..4096 workgroups of 64, 128 or 256 threads");
+    if (workgroups < 0 || workgroups > 4096 || (threads != 64 && threads != 128 && threads != 256))
+        return hc_fail(ctx, HC_EINVAL, "hc_set_gather_shape: 0 (automatic) or 1..4096 workgroups of 64, 128 or 256 threads");
     ctx->gather_workgroups = workgroups;
     ctx->gather_threads = threads;
     return HC_OK;

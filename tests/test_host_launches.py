@@ -81,3 +81,21 @@ def test_a_failed_launch_leaves_the_layers_before_it_combined(fake):
         names = [(l[0], int(l[3])) for l in log()]
         assert sum("attn_split" in n for n, z in names) == 4 and [z for n, z in names if "attn_combine" in n] == [4], names
     """)
+
+
+def test_the_gather_shape_goes_back_to_automatic(fake):
+    """A set launch shape holds alone and on the side stream; with 0 workgroups each has its own default again."""
+    run(fake, """
+        ctx = context(30000, 6000)
+        layers = [layer(ctx, 30000, 6000) for _ in range(2)]
+        def grids():
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), 2, 1, None, C.c_void_p(77)) == 0
+            assert L.hc_decode_step(ctx, io_of(layers[:1]), 1, 1, None, None) == 0
+            return [int(l[1]) for l in log() if "gather" in l[0]]
+        first = grids()
+        assert first == [48, 48, 96], first
+        assert L.hc_set_gather_shape(ctx, 30, 64) == 0 and grids() == [30, 30, 30]
+        assert L.hc_set_gather_shape(ctx, 0, 256) == 0 and grids() == first
+        assert L.hc_set_gather_shape(ctx, -1, 256) == hc.HC_EINVAL and L.hc_set_gather_shape(ctx, 4097, 256) == hc.HC_EINVAL
+    """)
