@@ -441,9 +441,9 @@ hc_status hc_layer_set_window_slot(hc_layer* layer, int32_t slot);
  * (1..HC_MAX_GROUP; 8 measured best at 32 layers of 224K): the group's appended tokens (k_new / v_new) in
  * one launch, the group's attentions, then one cross-stream event, then ONE batched monitor and ONE
  * batched gather for the whole group, which overlap the attention of the following groups; with
- * HC_WINDOW_RESCORED also one launch that buffers the group's queries (on main_stream: q may be
+ * HC_WINDOW_RESCORED the attentions' last launch also buffers the group's queries (on main_stream: q may be
  * overwritten as soon as the call returns) and, at the window's last step, the re-scoring passes of the
- * whole group ahead of its monitor.  The attention of a layer at the next call waits for that layer's side work of this call, so
+ * whole group run ahead of its monitor.  The attention of a layer at the next call waits for that layer's side work of this call, so
  * a refill decided at step t is used from step t+1.  Launching from native code keeps the host ahead
  * of the GPU.  All buffers are the caller's, as in the three calls; scores == NULL (or a layer without
  * pivots) skips monitor and gather for that layer; host_tier == NULL skips the gather.  Layers whose

@@ -1244,9 +1244,7 @@ extern "C" hc_status hc_rescore_window(hc_ctx* ctx, hc_layer* layer, const void*
     layer->window_slot = (slot + 1) % ctx->cfg.window;
     hipStream_t st = (hipStream_t)stream;
     const size_t q_bytes = (size_t)ctx->cfg.B * ctx->cfg.Hq * HC_D * 2;
-    const void* src = q;
-    void* dst = (char*)q_window + (size_t)slot * q_bytes;
-    s = hc_launch_rescore_push(ctx, 1, &src, &dst, st);
+    s = hc_launch_rescore_push(ctx, q, (char*)q_window + (size_t)slot * q_bytes, st);
     if (s != HC_OK || slot != ctx->cfg.window - 1) return s;
     const RescoreJob job{layer, kv_arena, q_window, base_idx, ring, work};
     return rescore_passes(ctx, 1, &job, st);
@@ -1254,7 +1252,7 @@ extern "C" hc_status hc_rescore_window(hc_ctx* ctx, hc_layer* layer, const void*
 
 // One decode step over a stack of layers, launched from native code so that the host keeps ahead of the
 // GPU.  Layers are taken in groups: the attention of a group's layers on the main stream; then, on the
-// side stream, ONE batched monitor and ONE batched gather for the whole group (five or six launches per group, more
+// side stream, ONE batched monitor and ONE batched gather for the whole group (two to five launches per group, more
 // for long lists, instead of per layer: these kernels are latency-bound, so a batch costs little more GPU time than
 // one layer, and the host stays ahead).  They overlap the attention of the following groups.  One event
 // pair per group keeps the host cost of the cross-stream ordering small.  The attention of a layer

@@ -325,7 +325,7 @@ struct hc_rescore_layout {
 };
 int hc_rescore_items_per_pass(const hc_ctx* ctx);
 hc_rescore_layout hc_rescore_plan(const hc_ctx* ctx, const hc_layer* L);
-hc_status hc_launch_rescore_push(hc_ctx* ctx, int n, const void* const* q, void* const* dst, hipStream_t st);
+hc_status hc_launch_rescore_push(hc_ctx* ctx, const void* q, void* window, hipStream_t st);
 struct hc_logits_job {
     const hc_layer* L;
     const RepDev* reps;        // the heads to score against, n_heads of them; max_len: the longest

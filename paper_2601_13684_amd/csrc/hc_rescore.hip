@@ -279,17 +279,10 @@ __global__ __launch_bounds__(RS_LSE_BLK) void rescore_lse_kernel(RescoreBatch ba
     }
 }
 
-// The current queries of up to HC_MAX_GROUP layers go into their window buffers with one launch.
-struct PushBatch {
-    const uint4* src[HC_MAX_GROUP];
-    uint4* dst[HC_MAX_GROUP];
-    int n16;
-};
-__global__ __launch_bounds__(RS_BLK) void rescore_push_kernel(PushBatch B)
+// The current queries go into a layer's window buffer (hc_rescore_window; in hc_decode_step the combine pass copies them).
+__global__ __launch_bounds__(RS_BLK) void rescore_push_kernel(const uint4* __restrict__ q, uint4* __restrict__ window, int n16)
 {
-    const uint4* __restrict__ s = B.src[blockIdx.y];
-    uint4* __restrict__ d = B.dst[blockIdx.y];
-    for (int i = blockIdx.x * RS_BLK + threadIdx.x; i < B.n16; i += gridDim.x * RS_BLK) d[i] = s[i];
+    for (int i = blockIdx.x * RS_BLK + threadIdx.x; i < n16; i += gridDim.x * RS_BLK) window[i] = q[i];
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -324,16 +317,10 @@ hc_rescore_layout hc_rescore_plan(const hc_ctx* ctx, const hc_layer* L)
     return o;
 }
 
-hc_status hc_launch_rescore_push(hc_ctx* ctx, int n, const void* const* q, void* const* dst, hipStream_t st)
+hc_status hc_launch_rescore_push(hc_ctx* ctx, const void* q, void* window, hipStream_t st)
 {
-    if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "query push of %d layers", n);
-    PushBatch B{};
-    for (int i = 0; i < n; ++i) {
-        B.src[i] = (const uint4*)q[i];
-        B.dst[i] = (uint4*)dst[i];
-    }
-    B.n16 = ctx->cfg.B * ctx->cfg.Hq * HC_D * 2 / 16;
-    rescore_push_kernel<<<dim3(std::max(1, std::min(8, B.n16 / RS_BLK)), n), dim3(RS_BLK), 0, st>>>(B);
+    const int n16 = ctx->cfg.B * ctx->cfg.Hq * HC_D * 2 / 16;
+    rescore_push_kernel<<<dim3(std::max(1, std::min(8, n16 / RS_BLK))), dim3(RS_BLK), 0, st>>>((const uint4*)q, (uint4*)window, n16);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
