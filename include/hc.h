@@ -27,8 +27,11 @@
  *     pivot's candidates pass the next multiple of 1,024 above the longest range at capture, nor 65,533 if that was at
  *     most 65,533 (in place of both 16,381 if it was at most 8,192); capture it again before they do.
  *   - One hc_ctx per host thread; calls on one ctx are not re-entrant, and two hot-path calls
- *     that use the same workspace (two hc_decode_attn, or two hc_rep_topk_drift) must be
- *     ordered by the caller's streams.  A decode_attn and a rep_topk_drift may overlap.
+ *     that use the same workspace (two hc_decode_attn, two hc_rep_topk_drift, or two
+ *     hc_gather_retrieve with a slot map, of whatever layers) must be ordered by the caller's
+ *     streams.  A decode_attn, a rep_topk_drift and a gather_retrieve may overlap.  (The refill counts
+ *     its workgroups in the context: after two with a slot map that did overlap, later ones of
+ *     that context are not reliable either.)
  *   - Arguments are validated on the host before anything is launched.
  *
  * Index-list tables (topk_idx, base_idx) have one row of max_k int32 per (b, KV head):

@@ -24,7 +24,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int GATHER_PASSES = 4;     // host reads a lane of gather_kernel has in flight
 constexpr int PLAN_THREADS = 256;
 
-// One layer of a batched call (blockIdx.z picks the layer).
+// One layer of a batched call (gather_plan_kernel: blockIdx.z picks the layer; the others go through the satellites of all).
 struct GatherItem {
     const SatDev* sats;
     const HeadDev* heads;
@@ -36,7 +36,7 @@ struct GatherItem {
     int32_t* pair_slot;     // [B*Hkv][max_k] workspace: the slots to overwrite ...
     int32_t* pair_pos;      // [B*Hkv][max_k]            ... and the positions that go there
     int32_t* npairs;        // [B*Hkv]
-    int32_t* done;          // [B*Hkv] workgroups that are through with a satellite's slot map; zero between launches
+    int32_t* done;          // [B*Hkv] workgroups that are through with a satellite's slot map; zero between launches, which must not overlap
     int n_sats, pad;
 };
 struct GatherBatch {
