@@ -508,7 +508,7 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
         // attention pass: within what its workgroups leave of a compute unit's), one launch plans and moves; otherwise
         // a plan by binary search, a workgroup per satellite, and gather_kernel behind it (a list of 7,872: 43 us + 55).
         const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16 + entry_words(n * max_sats) * 4;
-        const unsigned room = !ctx->beside_now ? 150 * 1024 : ctx->G == 8 ? 55 * 1024 : ctx->side_pad_now ? 108 * 1024 : 75 * 1024;
+        const unsigned room = (!ctx->beside_now ? 156 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - 256;
         if (maps <= room) {
             if (ctx->beside_now)
                 gather_plan_bitmap_kernel<512><<<dim3(nwg), dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, n, max_sats, max_k, thr);

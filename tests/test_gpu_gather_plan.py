@@ -146,3 +146,7 @@ def test_time_does_not_jump_with_one_satellite_more():
         ctx.close()
     print("gather time", {k: round(v, 1) for k, v in us.items()}, flush=True)
     assert us[25] < 1.3 * us[24], us
+
+
+def test_the_longest_context_whose_bitmaps_fit():
+    test_plan_and_moved_rows(634048, 3000)

@@ -99,3 +99,28 @@ def test_the_gather_shape_goes_back_to_automatic(fake):
         assert L.hc_set_gather_shape(ctx, 0, 256) == 0 and grids() == first
         assert L.hc_set_gather_shape(ctx, -1, 256) == hc.HC_EINVAL and L.hc_set_gather_shape(ctx, 4097, 256) == hc.HC_EINVAL
     """)
+
+
+@pytest.mark.parametrize("G,N", [(4, 306816), (8, 224896)])
+def test_the_longest_context_whose_refill_is_planned_by_bitmaps(fake, G, N):
+    """Beside the attention pass: bitmaps of 75 KB (groups of eight heads: 55 KB) with their masks, next to which the satellites' first
+    rows still find room."""
+    run(fake, f"""
+        names = []
+        def long_layer(ctx, N):
+            descs = (hc.hc_head_desc * 4)()
+            for h in range(4):
+                descs[h] = hc.hc_head_desc(k_off=h * (1 << 28), v_off=h * (1 << 28) + (1 << 27), tier_off=h * (1 << 28), ctx=N, len=N if h == 0 else 312,
+                                           role=0 if h == 0 else 1, rep=-1 if h == 0 else 0, sink=0 if h == 0 else 5, recent=0 if h == 0 else 7, k_mon=0, cap=0)
+            out = C.c_void_p()
+            assert L.hc_layer_create(ctx, descs, C.byref(out)) == 0, L.hc_last_error(ctx)
+            return out.value
+        for n in ({N}, {N} + 8192):
+            ctx = context(n, 300, G={G})
+            layers = [long_layer(ctx, n) for _ in range(2)]
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), 2, 1, None, C.c_void_p(77)) == 0
+            names.append([l[0] for l in log() if "gather" in l[0]])
+        assert all("plan_bitmap" in x for x in names[0]) and len(names[0]) == 2, names
+        assert not any("plan_bitmap" in x for x in names[1]) and len(names[1]) == 4, names
+    """)
