@@ -234,3 +234,62 @@ def test_filter_where_the_longest_list_is_not_the_monitored_one(N, k_mon, scale)
     for t, (a, b) in enumerate(zip(*tables)):
         for i, (x, y) in enumerate(zip(a, b)):
             np.testing.assert_array_equal(x, y, err_msg=f"step {t} table {i}")
+
+
+@pytest.mark.parametrize("kind,budgets", [("equal", (9000, 3000)), ("near", (9000, 3000)), ("near", (13000, 500)), ("groups", (9000, 3000)), ("groups", (2000, 700))])
+def test_kept_rows_whose_scores_are_equal_or_nearly_so(kind, budgets):
+    """A third more rows than the longest list stand out and score the same, almost the same, or the same in groups of 800: the digit of
+    the kept rows' histogram in which a list ends holds thousands, up to 512 of which are ranked.  Lists long enough that a wave
+    has more tiles of kept rows than it has buffers.  With the filter beside the attention pass like without it, never falling
+    back."""
+    say("filter, kept rows", kind, budgets)
+    N, n_out = 40011, budgets[0] * 4 // 3
+    heads = [I.HeadSpec(I.ROLE_FULL), I.HeadSpec(I.ROLE_FULL)] + \
+            [I.HeadSpec(I.ROLE_SATELLITE, rep=j % 2, sink=5, recent=7, budget=12 + r) for j, r in enumerate(budgets + budgets[::-1])]
+    spec = I.LayerSpec(B=1, Hq=4 * len(heads), Hkv=len(heads), D=128, ctx=[N], heads=[heads])
+    g = torch.Generator(device=DEV)
+    g.manual_seed(budgets[0])
+    q = torch.randn((1, spec.Hkv, 1, 128), generator=g, device=DEV).expand(1, spec.Hkv, 4, 128).reshape(1, spec.Hq, 128).to(torch.bfloat16)
+    datas = []
+    for l in range(2):
+        data = I.LayerData()
+        for h in range(spec.Hkv):
+            K = 0.1 * torch.randn((N, 128), generator=g, device=DEV)
+            at = 5 + torch.randperm(N - 12, generator=g, device=DEV)[:n_out]
+            u = q[0, 4 * h].float()
+            u = u / u.norm()
+            if kind == "near":
+                K[at] = 4.0 * u + 0.01 * torch.randn((n_out, 128), generator=g, device=DEV)
+            elif kind == "groups":
+                K[at] = (4.0 + 0.005 * (torch.arange(n_out, device=DEV) // 800))[:, None] * u
+            else:
+                K[at] = 4.0 * u
+            data.K[(0, h)] = K.to(torch.bfloat16)
+            data.V[(0, h)] = torch.randn((N, 128), generator=g, device=DEV).to(torch.bfloat16)
+        datas.append(data)
+    tables = []
+    for margin in (1.25, 0.0):
+        ctx = R.Context(R.make_config(spec), DEV, filter_margin=margin)
+        layers = [R.LayerRuntime(ctx, spec, d, *I.initial_lists(spec), host_tier=False, own_scratch=True) for d in datas]
+        side = torch.cuda.Stream()
+        seen = []
+        qq = torch.stack([q, q])
+        for t in range(4):
+            if margin:
+                hc.hc_decode_step(ctx.handle, R.make_step_io(layers, qq), 2, None, side, 1)
+            else:
+                for lay in layers:
+                    lay.step(q)
+            torch.cuda.synchronize()
+            seen.append([x.cpu().numpy().copy() for lay in layers for x in (lay.topk_idx, lay.base_idx, lay.ring, lay.inter, lay.flag, lay.out)])
+            for lay in layers if margin else ():
+                for p in (0, 1):
+                    c = lay.monitor_counts(0, p)
+                    assert c["fallbacks"] == 0 and (t == 0 or c["kept"] == n_out), (t, p, c)
+        tables.append(seen)
+        for lay in layers:
+            lay.close()
+        ctx.close()
+    for t, (a, b) in enumerate(zip(*tables)):
+        for i, (x, y) in enumerate(zip(a, b)):
+            np.testing.assert_array_equal(x, y, err_msg=f"step {t} table {i}")
