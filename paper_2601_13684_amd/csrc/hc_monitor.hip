@@ -21,9 +21,9 @@
 //                            thousand): three launches
 //   long lists               mon_score_hist, mon_hist twice, mon_count, mon_write, mon_decide: six launches of many workgroups
 //   rows a filtering split pass kept
-//                            mon_sparse_score (their scores, one dense run), mon_direct (mon_select where its LDS does not
-//                            suffice, with the long ranges' first two in front of it where more rows are kept than it has room
-//                            for): two launches, and behind them
+//                            mon_sparse_score (their scores, one dense run), mon_direct (mon_select beside the attention pass for
+//                            lists of up to 4,096, and where mon_direct's LDS does not suffice, with the long ranges' first
+//                            two in front of it where more rows are kept than it has room for): two launches, and behind them
 //                            two that normally find nothing to do, for a pivot whose check failed: rep_logits_kernel
 //                            (hc_attn.hip; all logits again, with their scores) and mon_select, which cuts the whole range
 //                            down by itself (a launch more for that would cost every step 3 us), or the six of long lists
@@ -2341,10 +2341,17 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     const dim3 gsel(max_reps, max_nk, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
+    // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
+    // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
+    const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
+    const bool few = mode == 1 && armed && (select_small(ctx, kept) || (!(ctx->beside_now && ctx->G < 8) && kept <= SEL_KEYS(select_room<1024>(ctx) / 4)));
     // mon_direct where it has room and the lists are not too long for it.  (candidates: of a filtering layer, what its launches are
-    // sized for)
+    // sized for.)  Beside the attention pass, where a read takes many times as long, not for the kept rows of short lists: few waves
+    // then have a tile, and the rows' positions are one read more behind the selection.  Steps of four layers, contexts of 66,000 to 123,000, a
+    // drift at every step, us by mon_select / mon_direct: longest list 1,728, three and six sequences 277 278 / 424 425; 3,776 297 314 /
+    // 459 480; 5,824 343 345 / 536 536; 7,872 478 467 / 596 594 (the kernel itself, 3,776, six sequences: 59 and 97).
     const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words) &&
-                        !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk));
+                        !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk)) && !(ctx->beside_now && few && max_k <= 4096);
     if (mode == 1) {
         if (direct)                                      // (more rows than it goes through, in a captured call: the dense chain's)
             for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(ctx, DIRECT_MAP, candidates));
@@ -2360,10 +2367,6 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     }
     if (mode != 0) scores_given = 1;                     // they are there from here on
     if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, B, dc, gsel, candidates, bm_words, st);
-    // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
-    // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
-    const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
-    const bool few = mode == 1 && armed && (select_small(ctx, kept) || (!(ctx->beside_now && ctx->G < 8) && kept <= SEL_KEYS(select_room<1024>(ctx) / 4)));
     // (a tile to a wave; given scores are read from a multiple of four positions on)
     if (mode == 0 && candidates <= SELECT_DIRECT && (!scores_given || candidates + 3 <= direct_threads(ctx) / 64 * HC_SEL_CHUNK))
         return scores_given ? launch_direct<DIRECT_SCORES>(ctx, B, dc, gsel, candidates, bm_words, st)

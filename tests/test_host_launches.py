@@ -124,3 +124,23 @@ def test_the_longest_context_whose_refill_is_planned_by_bitmaps(fake, G, N):
         assert all("plan_bitmap" in x for x in names[0]) and len(names[0]) == 2, names
         assert not any("plan_bitmap" in x for x in names[1]) and len(names[1]) == 4, names
     """)
+
+
+@pytest.mark.parametrize("r,kernel", [(300, "mon_selectILi512ELi1E"), (4096, "mon_selectILi512ELi1E"), (4097, "mon_directILi512ELi1E"), (9000, "mon_directILi512ELi1E")])
+def test_what_selects_among_the_kept_rows_beside_the_attention_pass(fake, r, kernel):
+    """Once the filter is set: mon_select for lists of up to 4,096, mon_direct for longer ones; alone mon_direct for both."""
+    run(fake, f"""
+        ctx = context(70000, {r})
+        assert L.hc_set_logit_filter(ctx, C.c_float(1.25), 0) == 0
+        layers = [layer(ctx, 70000, {r}) for _ in range(2)]
+        for side in (77, 77, None):
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), 2, 1, None, C.c_void_p(side)) == 0
+            names = [l[0] for l in log() if "mon_" in l[0] and "ELi3" not in l[0]]
+            if side is None:
+                assert sum("mon_directILi1024ELi1E" in n for n in names) == 2, names
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io_of(layers), 2, 1, None, C.c_void_p(77)) == 0
+        names = [l[0] for l in log() if "mon_" in l[0]]
+        assert sum("{kernel}" in n for n in names) == 2 and len(names) == 6, names
+    """)
