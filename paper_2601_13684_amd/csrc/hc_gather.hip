@@ -200,13 +200,16 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     const int n_ent = n_items * max_sats, n_wgs = (int)gridDim.x;
     int* sm_first = reinterpret_cast<int*>(dyn);     // [n_ent + 1]
     uint32_t* sm_words = dyn + entry_words(n_ent);
+    const bool plan_only = NT == 1024 && movers == 0;        // (a task to a satellite, whether its pivot fired or not)
     int total = 0, fired = 0;
-    entry_rows(B, n_ent, max_sats, [](const GatherItem&, const SatDev& sd) { return sd.r; }, [&](int e, int rows) {
-        if (threadIdx.x < 64 && e < n_ent) sm_first[e] = rows;
-        total += uniform(__builtin_amdgcn_readlane(wave_incl(rows), 63));
-        fired += __builtin_popcountll(__builtin_amdgcn_ballot_w64(rows > 0));
-    });
-    if (total == 0) return;
+    if (!plan_only) {
+        entry_rows(B, n_ent, max_sats, [](const GatherItem&, const SatDev& sd) { return sd.r; }, [&](int e, int rows) {
+            if (threadIdx.x < 64 && e < n_ent) sm_first[e] = rows;
+            total += uniform(__builtin_amdgcn_readlane(wave_incl(rows), 63));
+            fired += __builtin_popcountll(__builtin_amdgcn_ballot_w64(rows > 0));
+        });
+        if (total == 0) return;
+    }
     const int tid = threadIdx.x, wv = uniform(tid >> 6), lane = tid & 63;
     // List rows to a task: where there are at least twice as many workgroups as satellites, such that every task has a workgroup of
     // its own; otherwise half a workgroup's, so that those who get two tasks or three are evenly busy, but 256 at least: a task makes its
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     // workgroups.  24, 27, 36, 42 satellites, lists of 80 to 140: 16, 17, 19, 21 us, without the lower bound 16, 26, 28, 28; of 310 to
     // 610: 37, 45, 49, 63, without 37, 44, 57, 59, with 512 37, 40, 49, 70.  Tasks of a workgroup's rows: 22, 22, 24, 25 and 45, 46, 56, 58.)
     const int by = 2 * fired <= n_wgs ? n_wgs - fired : 2 * n_wgs, share = max((total + by - 1) / by, 2 * fired <= n_wgs ? 1 : 256);
-    if (wv == 0) {                                   // rows -> first task (one for each of a satellite's workgroups)
+    if (!plan_only && wv == 0) {                     // rows -> first task (one for each of a satellite's workgroups)
         int before = 0;
 #pragma unroll 1
         for (int base = 0; base < n_ent; base += 64) {
@@ -225,17 +228,23 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         if (lane == 0) sm_first[n_ent] = before;
     }
     __syncthreads();
-    const int tasks = uniform(sm_first[n_ent]);
+    const int tasks = plan_only ? n_ent : uniform(sm_first[n_ent]);
 #pragma unroll 1
     for (int task = blockIdx.x; task < tasks; task += n_wgs) {           // (the same for the whole workgroup)
-        int e = 0;
-        for (int hi = n_ent; hi - e > 1;) {          // the last entry whose tasks begin at or before this one
-            const int mid = (e + hi) >> 1;
-            if (uniform(sm_first[mid]) <= task) e = mid;
-            else hi = mid;
+        int e = 0, part = 0, parts = 1;
+        if (plan_only) {
+            e = task;
+        } else {
+            for (int hi = n_ent; hi - e > 1;) {      // the last entry whose tasks begin at or before this one
+                const int mid = (e + hi) >> 1;
+                if (uniform(sm_first[mid]) <= task) e = mid;
+                else hi = mid;
+            }
+            part = task - uniform(sm_first[e]);
+            parts = uniform(sm_first[e + 1]) - uniform(sm_first[e]);
         }
-        const int part = task - uniform(sm_first[e]), parts = uniform(sm_first[e + 1]) - uniform(sm_first[e]);
         const GatherItem& it = B.it[e / max_sats];
+        if (plan_only && (e % max_sats >= it.n_sats || it.flag[it.sats[e % max_sats].rep_bh] == 0)) continue;
         const int bh = uniform(it.sats[e % max_sats].bh), r = uniform(it.sats[e % max_sats].r), first_slot = uniform(it.sats[e % max_sats].first_slot);
         const HeadDev& hd = it.heads[bh];
         const uint32_t ctx = (uint32_t)uniform(hd.ctx);
@@ -345,6 +354,11 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         if (sm_last)
 #pragma unroll 1
             for (int k = tid; k < pairs; k += NT) sp[pslot[k]] = ppos[k];
+        if (plan_only) {
+            if (tid == 0) it.npairs[bh] = pairs;
+            __syncthreads();
+            continue;
+        }
         const int k_begin = (int)((long long)pairs * part / parts), k_end = (int)((long long)pairs * (part + 1) / parts);
         move_rows<2>(it, hd, first_slot, r, pslot, ppos, k_begin, k_end, movers);
         __syncthreads();                             // (the next satellite takes over the LDS and the workspace's pairs)
@@ -468,7 +482,7 @@ __global__ __launch_bounds__(256, 8) void gather_kernel(GatherBatch B, int n_ite
 
 }   // namespace
 
-hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipStream_t st)
+hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool may_overlap, hipStream_t st)
 {
     if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "gather batch of %d layers", n);
     GatherBatch B{};
@@ -509,16 +523,25 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipS
         // a plan by binary search, a workgroup per satellite, and gather_kernel behind it (a list of 7,872: 43 us + 55).
         const unsigned maps = ((unsigned)ctx->cfg.max_ctx / 32 * 2 + 4) * 4 + (unsigned)((max_k + 63) / 64) * 16 + entry_words(n * max_sats) * 4;
         const unsigned room = (!ctx->beside_now ? 156 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - 256;
-        if (maps <= room) {
+        // Many satellites, and perhaps another stream's attention pass on the GPU (a call by itself): the plan first, then gather_kernel,
+        // whose workgroups are small enough to leave attention's their places.  By itself this takes the same from 48
+        // satellites on; refills of whole lists of 66 / 96 satellites, 0.8 and 1.1 ms, made eight attention launches beside them 283 / 280 us
+        // longer this way, 531 / 634 in one launch; of 48 265 and 361, but there one launch is 5 % faster, and of 24 161 and 187.
+        const bool apart = may_overlap && n * max_sats > 48;
+        if (maps <= room && apart) {
+            gather_plan_bitmap_kernel<1024><<<dim3(std::min(n * max_sats, 256)), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 0);
+            HC_HIP(ctx, hipGetLastError());
+        } else if (maps <= room) {
             if (ctx->beside_now)
                 gather_plan_bitmap_kernel<512><<<dim3(nwg), dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, n, max_sats, max_k, thr);
             else
                 gather_plan_bitmap_kernel<1024><<<dim3(nwg), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 2 * thr);
             HC_HIP(ctx, hipGetLastError());
             return HC_OK;
+        } else {
+            gather_plan_kernel<<<dim3(1, max_sats, n), dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
+            HC_HIP(ctx, hipGetLastError());
         }
-        gather_plan_kernel<<<dim3(1, max_sats, n), dim3(PLAN_THREADS), hc_side_lds(ctx, (const void*)gather_plan_kernel, (unsigned)lds), st>>>(B, max_k);
-        HC_HIP(ctx, hipGetLastError());
     }
     gather_kernel<<<dim3(nwg), dim3(thr), hc_side_lds(ctx, (const void*)gather_kernel, 0), st>>>(B, n, max_sats, max_k);
     HC_HIP(ctx, hipGetLastError());

@@ -843,7 +843,7 @@ extern "C" hc_status hc_gather_retrieve(hc_ctx* ctx, const hc_layer* layer, cons
     if (wait_event) HC_HIP(ctx, hipStreamWaitEvent(st, (hipEvent_t)wait_event, 0));
     if (layer->n_sats > 0) {
         const hc_gather_call call{layer, host_tier, topk_idx, flag, kv_arena, slot_pos};
-        const hc_status s = hc_launch_gather(ctx, 1, &call, st);
+        const hc_status s = hc_launch_gather(ctx, 1, &call, true, st);
         if (s != HC_OK) return s;
     }
     if (done_event) HC_HIP(ctx, hipEventRecord((hipEvent_t)done_event, st));
@@ -1322,7 +1322,7 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         // (groups of eight heads: the split pass takes 52 KB of LDS per workgroup, two do not fit beside the reservation)
         ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
-        if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, run);
+        if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, false, run);
         ctx->side_pad_now = ctx->beside_now = false;
         if (ss) {
             // recorded even after a failed launch, so that no later call waits on a stale event

@@ -285,7 +285,8 @@ struct hc_rep_logits_call {
 };
 hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st);
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st);
-hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, hipStream_t st);
+// may_overlap: another stream of the caller's may run the attention pass meanwhile (in hc_decode_step it is known)
+hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool may_overlap, hipStream_t st);
 hc_status hc_gather_set_lds_limit();     // once per process, at context creation
 hc_status hc_monitor_set_lds_limit();
 hc_status hc_attn_set_lds_limit();
