@@ -200,7 +200,7 @@ hc_status hc_layer_filter_view(const hc_layer* layer, const int32_t** kept_pos, 
 
 /* Tuning knob: launch shape of the gather kernel: at most `workgroups` workgroups (1..4096) of `threads` threads (64,
  * 128 or 256); a workgroup has at most threads / 8 positions in flight.  Default 0 x 256; 0 workgroups: 96, on the side
- * stream of hc_decode_step 48.  What matters is how the host
+ * stream of hc_decode_step 48 unless a group of up to four layers has more than 24 satellites.  What matters is how the host
  * reads, which take microseconds each, are spread over the compute units: the attention pass's loads on a unit queue
  * behind them. */
 hc_status hc_set_gather_shape(hc_ctx* ctx, int32_t workgroups, int32_t threads);

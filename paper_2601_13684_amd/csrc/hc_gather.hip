@@ -506,12 +506,14 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool
     // that hosts gather waves has its memory pipeline filled with reads that take microseconds, behind which the
     // attention waves on the same unit queue (measured at the 224K shape with 16 workgroups per satellite in a
     // batch of 8 layers: the attention launch that ran beside a refill took 400 us instead of 45).  One refill of 2.6 MB by
-    // itself with 32, 48, 64, 96, 160 workgroups: 60, 57, 57, 57, 54 us; steps of four layers, six sequences, with it on the side
-    // stream: 279, 279, 280, 282, 284 us.
+    // itself with 32, 48, 64, 96, 160 workgroups: 60, 57, 57, 57, 54 us.  Beside the attention pass 48; but groups of up to four
+    // layers with many satellites have little attention to hide a refill behind.  Steps with a drift at each, contexts of 66,000 to
+    // 123,000, us with 48 / 96: groups of two layers, 36 satellites 290 282, 48 347 339, 72 590 575, 192 883 859; of four, 96 satellites 852
+    // 857, whole-list jumps 947 914; of eight, 48 satellites (32 layers of 131,072) 34.4 and 35.9 a layer, of 229,376 47.5 and 48.2.
     long long rows_max = 0;
     for (int i = 0; i < n; ++i) rows_max += (long long)calls[i].L->n_sats * calls[i].L->max_r;
     const int thr = ctx->gather_threads, in_flight = thr / 32 * GATHER_PASSES;
-    const int most = ctx->gather_workgroups > 0 ? ctx->gather_workgroups : ctx->beside_now ? 48 : 96;
+    const int most = ctx->gather_workgroups > 0 ? ctx->gather_workgroups : ctx->beside_now && (n > 4 || 2 * n * max_sats <= 48) ? 48 : 96;
     const int nwg = (int)std::max<long long>(1, std::min<long long>(most, (rows_max + in_flight - 1) / in_flight));
     if (any_delta) {
         for (int i = 0; i < n; ++i)

@@ -144,3 +144,19 @@ def test_what_selects_among_the_kept_rows_beside_the_attention_pass(fake, r, ker
         names = [l[0] for l in log() if "mon_" in l[0]]
         assert sum("{kernel}" in n for n in names) == 2 and len(names) == 6, names
     """)
+
+
+def test_workgroups_of_a_refill_beside_the_attention_pass(fake):
+    """48 where few satellites or many layers share a launch, 96 for groups of up to four layers with more than 24 satellites."""
+    run(fake, """
+        def gathers(n_heads, group, layers_n):
+            ctx = context(30000, 600, n=n_heads)
+            layers = [layer(ctx, 30000, 600, n=n_heads) for _ in range(layers_n)]
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), layers_n, group, None, C.c_void_p(77)) == 0
+            return [int(l[1]) for l in log() if "gather" in l[0]]
+        assert gathers(13, 2, 4) == [48, 48]          # 24 satellites
+        assert gathers(14, 2, 4) == [96, 96]          # 26
+        assert gathers(8, 4, 8) == [96, 96]           # 28
+        assert gathers(8, 5, 10) == [48, 48]          # 35 in a group of five
+    """)
