@@ -190,7 +190,8 @@ __device__ __forceinline__ void move_rows(const GatherItem& it, const HeadDev& h
 // ballots.  The plan is a chain of latencies: list and slot map are asked for together, at the start.
 // Six lists of 704 to 7,872 entries, a quarter new, 2.6 MB over the link (45 us at its rate): 54 us, 66 in two launches (a plan
 // by a workgroup per satellite, 11 us, then the rows, 54).  A launch that finds nothing to do takes 4 us.
-template <int NT>
+// PLAN: the plan alone, a task to a satellite, whether its pivot fired or not; gather_kernel moves the rows.
+template <int NT, bool PLAN>
 __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int n_items, int max_sats, int max_k, int movers)
 {
     constexpr int NW = NT / 64, U = NT == 512 ? 4 : 8;
@@ -200,9 +201,8 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     const int n_ent = n_items * max_sats, n_wgs = (int)gridDim.x;
     int* sm_first = reinterpret_cast<int*>(dyn);     // [n_ent + 1]
     uint32_t* sm_words = dyn + entry_words(n_ent);
-    const bool plan_only = NT == 1024 && movers == 0;        // (a task to a satellite, whether its pivot fired or not)
     int total = 0, fired = 0;
-    if (!plan_only) {
+    if (!PLAN) {
         entry_rows(B, n_ent, max_sats, [](const GatherItem&, const SatDev& sd) { return sd.r; }, [&](int e, int rows) {
             if (threadIdx.x < 64 && e < n_ent) sm_first[e] = rows;
             total += uniform(__builtin_amdgcn_readlane(wave_incl(rows), 63));
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
     // workgroups.  24, 27, 36, 42 satellites, lists of 80 to 140: 16, 17, 19, 21 us, without the lower bound 16, 26, 28, 28; of 310 to
     // 610: 37, 45, 49, 63, without 37, 44, 57, 59, with 512 37, 40, 49, 70.  Tasks of a workgroup's rows: 22, 22, 24, 25 and 45, 46, 56, 58.)
     const int by = 2 * fired <= n_wgs ? n_wgs - fired : 2 * n_wgs, share = max((total + by - 1) / by, 2 * fired <= n_wgs ? 1 : 256);
-    if (!plan_only && wv == 0) {                     // rows -> first task (one for each of a satellite's workgroups)
+    if (!PLAN && wv == 0) {                     // rows -> first task (one for each of a satellite's workgroups)
         int before = 0;
 #pragma unroll 1
         for (int base = 0; base < n_ent; base += 64) {
@@ -228,11 +228,11 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         if (lane == 0) sm_first[n_ent] = before;
     }
     __syncthreads();
-    const int tasks = plan_only ? n_ent : uniform(sm_first[n_ent]);
+    const int tasks = PLAN ? n_ent : uniform(sm_first[n_ent]);
 #pragma unroll 1
     for (int task = blockIdx.x; task < tasks; task += n_wgs) {           // (the same for the whole workgroup)
         int e = 0, part = 0, parts = 1;
-        if (plan_only) {
+        if (PLAN) {
             e = task;
         } else {
             for (int hi = n_ent; hi - e > 1;) {      // the last entry whose tasks begin at or before this one
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
             parts = uniform(sm_first[e + 1]) - uniform(sm_first[e]);
         }
         const GatherItem& it = B.it[e / max_sats];
-        if (plan_only && (e % max_sats >= it.n_sats || it.flag[it.sats[e % max_sats].rep_bh] == 0)) continue;
+        if (PLAN && (e % max_sats >= it.n_sats || it.flag[it.sats[e % max_sats].rep_bh] == 0)) continue;
         const int bh = uniform(it.sats[e % max_sats].bh), r = uniform(it.sats[e % max_sats].r), first_slot = uniform(it.sats[e % max_sats].first_slot);
         const HeadDev& hd = it.heads[bh];
         const uint32_t ctx = (uint32_t)uniform(hd.ctx);
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         if (sm_last)
 #pragma unroll 1
             for (int k = tid; k < pairs; k += NT) sp[pslot[k]] = ppos[k];
-        if (plan_only) {
+        if (PLAN) {
             if (tid == 0) it.npairs[bh] = pairs;
             __syncthreads();
             continue;
@@ -531,13 +531,13 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool
         // longer this way, 531 / 634 in one launch; of 48 265 and 361, but there one launch is 5 % faster, and of 24 161 and 187.
         const bool apart = may_overlap && n * max_sats > 48;
         if (maps <= room && apart) {
-            gather_plan_bitmap_kernel<1024><<<dim3(std::min(n * max_sats, 256)), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 0);
+            gather_plan_bitmap_kernel<1024, true><<<dim3(std::min(n * max_sats, 256)), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 0);
             HC_HIP(ctx, hipGetLastError());
         } else if (maps <= room) {
             if (ctx->beside_now)
-                gather_plan_bitmap_kernel<512><<<dim3(nwg), dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512>, maps), st>>>(B, n, max_sats, max_k, thr);
+                gather_plan_bitmap_kernel<512, false><<<dim3(nwg), dim3(512), hc_side_lds(ctx, (const void*)gather_plan_bitmap_kernel<512, false>, maps), st>>>(B, n, max_sats, max_k, thr);
             else
-                gather_plan_bitmap_kernel<1024><<<dim3(nwg), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 2 * thr);
+                gather_plan_bitmap_kernel<1024, false><<<dim3(nwg), dim3(1024), maps, st>>>(B, n, max_sats, max_k, 2 * thr);
             HC_HIP(ctx, hipGetLastError());
             return HC_OK;
         } else {
@@ -554,8 +554,9 @@ hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool
 // reserve more than half of a compute unit's LDS (hc_side_lds)
 hc_status hc_gather_set_lds_limit()
 {
-    if (hc_allow_lds((const void*)gather_plan_bitmap_kernel<512>) != hipSuccess ||
-        hc_allow_lds((const void*)gather_plan_bitmap_kernel<1024>) != hipSuccess) return HC_EHIP;
+    if (hc_allow_lds((const void*)gather_plan_bitmap_kernel<512, false>) != hipSuccess ||
+        hc_allow_lds((const void*)gather_plan_bitmap_kernel<1024, false>) != hipSuccess ||
+        hc_allow_lds((const void*)gather_plan_bitmap_kernel<1024, true>) != hipSuccess) return HC_EHIP;
     if (hc_allow_lds((const void*)gather_plan_kernel) != hipSuccess || hc_allow_lds((const void*)gather_kernel) != hipSuccess) return HC_EHIP;
     return HC_OK;
 }
