@@ -64,7 +64,7 @@ def main():
                     "than this do not filter (the filtered monitor costs more launches, which a short context does not earn back)")
     ap.add_argument("--side-lds", type=int, default=-1, help="KB of LDS every side-stream workgroup reserves (hc_set_side_lds; tuning; "
                     "-1: the library's default of 81, 0: none)")
-    ap.add_argument("--gather-shape", default="", help="workgroups,threads of the gather kernel (tuning; default 96,256, on the side stream 48,256)")
+    ap.add_argument("--gather-shape", default="", help="workgroups,threads of the gather kernel (tuning; default 0,256: 96 workgroups, on the side stream 48 or 96)")
     ap.add_argument("--group", type=int, default=0, help="layers per cross-stream sync group in step mode (0: half of the "
                     "stack, at most 8, so that the side work of all but the last group overlaps later groups' attention)")
     ap.add_argument("--serial", action="store_true", help="monitor and gather on the main stream (no overlap)")

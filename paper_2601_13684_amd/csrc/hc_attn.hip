@@ -920,8 +920,8 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
 // threads: they find room beside the monitor's kernels sooner.)
 // The layers of a hc_decode_step group are combined with one launch (blockIdx.z picks the layer): a launch of its own
 // behind every layer's split pass is mostly latency, 4.5 us and a gap in which the compute units stand empty.  For the same
-// reason it copies the queries that a re-scored window keeps (a launch of its own for that: 2.7 us and a gap; four 32K layers
-// in two groups 136 instead of 131 us a step).
+// reason it copies the queries that a re-scored window keeps (a launch of its own for that: 3 us and a gap per
+// group, less than what steps with a window differ by from run to run).
 constexpr int CQ = 8;                       // column quads (of 32) per workgroup
 constexpr int COMBINE_BLK = 32 * CQ;
 struct CombineItem {

@@ -32,7 +32,7 @@
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
 // histograms, counts, ordered write, decision): one 32K layer 20.5 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 33-36 instead of 81 us, the decode step of one 4K layer 27 instead of 49 us.
+// 131K 33-36 instead of 81 us, the decode step of one 4K layer 25.7 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
@@ -1172,7 +1172,7 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 // 16 / 20 (24-27 / 27), 32,768 21 / 25-29 (27-40 / 40-43), 65,000 27-29 / 35-43 (35-49 / 48-53).  Given scores that are not what HC_AGG_PROB
 // makes of logits, negative or above 2, end in a digit without an edge: 10,000 20 (23), 32,768 26-28 (25), 65,000 37-41 (32-34).  By
 // itself, 4,096 candidates 12.2 / 12.3 / 12.0 (mon_select over keys 13.4 / 13.7 /
-// 11.7), 8,192 15.4 / 15.2 / 14.3 (16.5 / 16.6 / 16.2).  The decode step of four 32K layers with a window of four: 125 us (145).
+// 11.7), 8,192 15.4 / 15.2 / 14.3 (16.5 / 16.6 / 16.2).  Steps of four 32K layers with a drift at each, overlapped: 105 us (120).
 constexpr int BAND = 512;                // items of the digit that can be ranked ...
 constexpr int RANKED = 128;              // ... without a histogram of their own
 constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
