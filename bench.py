@@ -297,8 +297,8 @@ def main():
     ms_per_step = (t1 - t0) * 1e3 / K
     us_per_layer = ms_per_step * 1e3 / L
 
-    # ---- kernel-timing pass: the same steps launched the same way, with one event pair attached to every
-    # split-pass dispatch by the library (a captured graph cannot carry them: that mode is timed eagerly) ----
+    # ---- kernel-timing pass: the same steps with one event pair attached by the library to every split-pass dispatch; every
+    # layer's is a launch of its own then (a captured graph cannot carry them: that mode is timed eagerly) ----
     n_pairs = 0 if args.no_kernel_timing else K * L
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_pairs)]
     for a, b in evs:

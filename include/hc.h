@@ -220,7 +220,8 @@ hc_status hc_set_side_lds(hc_ctx* ctx, int32_t bytes);
 /* Measurement hook: hands the library n pairs of hipEvent_t (host arrays of handles, copied).  The
  * next n launches of the split-pass kernel, from hc_decode_attn or hc_decode_step, attach pair i to
  * their i-th dispatch, so that hipEventElapsedTime(ev_begin[i], ev_end[i]) is that kernel's execution
- * time alone, as a profiler's kernel trace reports it.  After n launches, or with n = 0, no events
+ * time alone, as a profiler's kernel trace reports it.  While pairs are left every layer has a launch of its own
+ * (otherwise layers of a hc_decode_step group may share one).  After n launches, or with n = 0, no events
  * are recorded.  The events are the caller's; they are only recorded, never waited on or destroyed. */
 hc_status hc_set_timing_events(hc_ctx* ctx, void* const* ev_begin, void* const* ev_end, int32_t n);
 

@@ -434,14 +434,9 @@ struct FilterArgs {
 // 32 query + 64 accumulator registers, and two workgroups keep 64 KB in flight, which measurement shows is enough.
 // Groups of eight have a kernel of their own below.)
 template <int G, bool FILT>
-__global__ __launch_bounds__(256, 2) void attn_split_kernel(const uint16_t* __restrict__ arena,
-                                                                    const uint16_t* __restrict__ q,
-                                                                    const BlkDev* __restrict__ blks,
-                                                                    const SegDev* __restrict__ segs,
-                                                                    float* __restrict__ part_acc,
-                                                                    float* __restrict__ part_ml,
-                                                                    float* __restrict__ rep_logits, int max_ctx,
-                                                                    unsigned long long* __restrict__ stamps, FilterArgs fa)
+__device__ __forceinline__ void split_rows(const uint16_t* __restrict__ arena, const uint16_t* __restrict__ q, const BlkDev* __restrict__ blks,
+                                           const SegDev* __restrict__ segs, float* __restrict__ part_acc, float* __restrict__ part_ml,
+                                           float* __restrict__ rep_logits, int max_ctx, unsigned long long* __restrict__ stamps, const FilterArgs& fa)
 {
     __shared__ float sm_m[4][G];
     __shared__ float sm_Z[16][G];
@@ -665,11 +660,9 @@ __device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b)      // 
 }
 
 template <bool FILT>
-__global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __restrict__ arena, const uint16_t* __restrict__ q,
-                                                             const BlkDev* __restrict__ blks, const SegDev* __restrict__ segs,
-                                                             float* __restrict__ part_acc, float* __restrict__ part_ml,
-                                                             float* __restrict__ rep_logits, int max_ctx,
-                                                             unsigned long long* __restrict__ stamps, FilterArgs fa)
+__device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, const uint16_t* __restrict__ q, const BlkDev* __restrict__ blks,
+                                            const SegDev* __restrict__ segs, float* __restrict__ part_acc, float* __restrict__ part_ml,
+                                            float* __restrict__ rep_logits, int max_ctx, unsigned long long* __restrict__ stamps, const FilterArgs& fa)
 {
     __shared__ float sm_m[4][G8];
     __shared__ float sm_Z[16][G8];
@@ -914,6 +907,48 @@ __global__ __launch_bounds__(256, 2) void attn_split8_kernel(const uint16_t* __r
     }
 }
 
+// One layer of a launch of the split pass, and what a launch takes: a layer, or the layers of a group one behind the other
+// (blockIdx.y picks the layer).  A launch by itself loses about 5 us to its start, its first loads and its unequal finish; here the
+// workgroups of a layer start where those of the layer before it end, on a compute unit whose other workgroup is streaming.  Us, a
+// launch for each layer / one for the group: a step of four layers of 224K in groups of two 221 / 217 (252 / 245 where the side
+// stream shares the hardware queue), of six sequences 256 / 252; per layer-step of 32 layers in groups of eight, 224K 47.5 / 44.1, 128K
+// with refills at most steps 34.5 / 29.6, sixteen sequences, groups of four, 158 / 154.
+struct SplitItem {
+    const uint16_t* arena;
+    const uint16_t* q;
+    const BlkDev* blks;
+    const SegDev* segs;
+    float* part_acc;
+    float* part_ml;
+    float* rep_logits;           // or nullptr
+    FilterArgs fa;
+    int n_blocks;
+};
+struct SplitOne {
+    SplitItem it;
+    __device__ __forceinline__ const SplitItem& item() const { return it; }
+    __device__ __forceinline__ bool idle() const { return false; }
+};
+struct SplitGroup {
+    SplitItem it[HC_MAX_GROUP];
+    __device__ __forceinline__ const SplitItem& item() const { return it[blockIdx.y]; }
+    __device__ __forceinline__ bool idle() const { return (int)blockIdx.x >= it[blockIdx.y].n_blocks; }
+};
+template <int G, bool FILT, class Args>
+__global__ __launch_bounds__(256, 2) void attn_split_kernel(Args a, int max_ctx, unsigned long long* __restrict__ stamps)
+{
+    if (a.idle()) return;
+    const SplitItem& it = a.item();
+    split_rows<G, FILT>(it.arena, it.q, it.blks, it.segs, it.part_acc, it.part_ml, it.rep_logits, max_ctx, stamps, it.fa);
+}
+template <bool FILT, class Args>
+__global__ __launch_bounds__(256, 2) void attn_split8_kernel(Args a, int max_ctx, unsigned long long* __restrict__ stamps)
+{
+    if (a.idle()) return;
+    const SplitItem& it = a.item();
+    split_rows8<FILT>(it.arena, it.q, it.blks, it.segs, it.part_acc, it.part_ml, it.rep_logits, max_ctx, stamps, it.fa);
+}
+
 // Second pass: out = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) Z_s over the partials of one head.
 // One workgroup per (b, query head, quarter of the columns): 32 partial lanes x CQ column quads; every thread's
 // loads are independent and issued together.  (Four small workgroups per query head instead of one of 1024
@@ -1108,9 +1143,8 @@ __global__ __launch_bounds__(256, G >= 8 ? 4 : 8) void rep_logits_kernel(RepLogi
     }
 }
 
-template <int G>
-hc_status launch_split(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* rep_logits, hipStream_t st, float* part_acc,
-                       float* part_ml)
+template <int G, class Args>
+hc_status launch_split(hc_ctx* ctx, const Args& a, int n, int n_blocks, bool filtered, hipStream_t st)
 {
     // The optional timing events are attached to the kernel's own dispatch, so that their distance is the
     // kernel's execution time (what a profiler's kernel trace reports), not launch latency plus execution.
@@ -1120,23 +1154,18 @@ hc_status launch_split(hc_ctx* ctx, const hc_layer* L, const void* arena, const 
         ev_end = ctx->timing[ctx->timing_next].second;
         ++ctx->timing_next;
     }
-    const bool filtered = rep_logits != nullptr && hc_layer_filtered(ctx, L);
-    const FilterArgs fa{L->filt, L->reps, L->surv_pos, L->seg_cnt, L->q_keep};
-#define HC_LAUNCH(KERNEL)                                                                                         \
-    hipExtLaunchKernelGGL(KERNEL, dim3(L->n_blocks), dim3(256), 0, st, ev_begin, ev_end, 0,                      \
-                          (const uint16_t*)arena, (const uint16_t*)q, (const BlkDev*)L->blks,                    \
-                          (const SegDev*)L->segs, part_acc, part_ml, rep_logits, ctx->cfg.max_ctx,                 \
-                          ctx->tune_stamps, fa)
+#define HC_LAUNCH(KERNEL) \
+    hipExtLaunchKernelGGL(KERNEL, dim3(n_blocks, n), dim3(256), 0, st, ev_begin, ev_end, 0, a, (int)ctx->cfg.max_ctx, ctx->tune_stamps)
     if constexpr (G == 8) {
         if (filtered)
-            HC_LAUNCH((attn_split8_kernel<true>));
+            HC_LAUNCH((attn_split8_kernel<true, Args>));
         else
-            HC_LAUNCH((attn_split8_kernel<false>));
+            HC_LAUNCH((attn_split8_kernel<false, Args>));
     } else {
         if (filtered)
-            HC_LAUNCH((attn_split_kernel<G, true>));
+            HC_LAUNCH((attn_split_kernel<G, true, Args>));
         else
-            HC_LAUNCH((attn_split_kernel<G, false>));
+            HC_LAUNCH((attn_split_kernel<G, false, Args>));
     }
 #undef HC_LAUNCH
     HC_HIP(ctx, hipGetLastError());
@@ -1188,17 +1217,31 @@ hc_status hc_attn_static_scratch(hc_ctx* ctx, float** base)
     return HC_OK;
 }
 
-static hc_status split_any(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* rep_logits, hipStream_t st,
-                           float* part_acc, float* part_ml)
+template <class Args>
+static hc_status split_any(hc_ctx* ctx, const Args& a, int n, int n_blocks, bool filtered, hipStream_t st)
 {
     switch (ctx->G) {
-    case 1: return launch_split<1>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
-    case 2: return launch_split<2>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
-    case 4: return launch_split<4>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
-    case 8: return launch_split<8>(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    case 1: return launch_split<1>(ctx, a, n, n_blocks, filtered, st);
+    case 2: return launch_split<2>(ctx, a, n, n_blocks, filtered, st);
+    case 4: return launch_split<4>(ctx, a, n, n_blocks, filtered, st);
+    case 8: return launch_split<8>(ctx, a, n, n_blocks, filtered, st);
     }
     return hc_fail(ctx, HC_ESHAPE, "unsupported group size");
 }
+
+static SplitItem split_item(const hc_attn_call& x, float* part_acc, float* part_ml)
+{
+    const hc_layer* L = x.L;
+    return SplitItem{(const uint16_t*)x.arena, (const uint16_t*)x.q, L->blks, L->segs, part_acc, part_ml, x.rep_logits,
+                     FilterArgs{L->filt, L->reps, L->surv_pos, L->seg_cnt, L->q_keep}, L->n_blocks};
+}
+
+static bool split_filtered(const hc_ctx* ctx, const hc_attn_call& x) { return x.rep_logits != nullptr && hc_layer_filtered(ctx, x.L); }
+
+// Whether a layer may share its launch of the split pass with its neighbours of the group: if its workgroups fill the GPU.
+// (Shorter passes would gain as well, but keep a launch of their own: one that fails leaves the layers before it combined, layer by
+// layer.  Of a shared launch that fails, none of its layers is.  A caller that times the passes has a launch for each layer.)
+static bool split_together(const hc_ctx* ctx, const hc_layer* L) { return L->n_blocks >= ctx->wg_per_cu * ctx->n_cu && ctx->timing_next >= ctx->timing.size(); }
 
 static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
 {
@@ -1214,7 +1257,8 @@ static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int 
 static hc_status launch_any(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out, float* lse,
                             float* rep_logits, hipStream_t st, float* part_acc, float* part_ml)
 {
-    const hc_status s = split_any(ctx, L, arena, q, rep_logits, st, part_acc, part_ml);
+    const hc_attn_call call{L, arena, q, out, lse, rep_logits};
+    const hc_status s = split_any(ctx, SplitOne{split_item(call, part_acc, part_ml)}, 1, L->n_blocks, split_filtered(ctx, call), st);
     if (s != HC_OK) return s;
     CombineBatch batch{};
     batch.it[0] = CombineItem{L->heads, part_acc, part_ml, out, lse, nullptr, nullptr};
@@ -1231,11 +1275,22 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
         if ((size_t)calls[i].L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
     const size_t acc_floats = ctx->part_slots * ctx->G * HC_D, ml_floats = ctx->part_slots * ctx->G * 2;
     CombineBatch batch{};
-    int m = 0, n_heads = 0;
-    auto flush = [&]() -> hc_status {
-        const hc_status s = m > 0 ? combine_any(ctx, batch, m, n_heads, st) : HC_OK;
-        m = 0;
+    SplitGroup group;
+    int m = 0, gathered = 0, blocks = 0, n_heads = 0;     // layers of the batch: split and gathered, of these gathered for one launch
+    bool filtered = false;
+    auto split = [&]() -> hc_status {                     // the gathered layers' launch
+        if (gathered == 0) return HC_OK;
+        const hc_status s = gathered == 1 ? split_any(ctx, SplitOne{group.it[0]}, 1, blocks, filtered, st)
+                                          : split_any(ctx, group, gathered, blocks, filtered, st);
+        if (s != HC_OK) m -= gathered;
+        gathered = blocks = 0;
         return s;
+    };
+    auto flush = [&]() -> hc_status {
+        const hc_status a = split();
+        const hc_status b = m > 0 ? combine_any(ctx, batch, m, n_heads, st) : HC_OK;
+        m = 0;
+        return a != HC_OK ? a : b;
     };
     for (int i = 0; i < n; ++i) {
         const hc_attn_call& x = calls[i];
@@ -1248,14 +1303,27 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
             const hc_status s = flush();
             if (s != HC_OK) return s;
         }
+        const bool together = split_together(ctx, x.L);
+        if (gathered > 0 && (!together || filtered != split_filtered(ctx, x))) {
+            const hc_status s = split();
+            if (s != HC_OK) {
+                (void)flush();
+                return s;
+            }
+        }
         float* acc = m == 0 ? ctx->part_acc : ctx->part_more + (m - 1) * acc_floats;
         float* ml = m == 0 ? ctx->part_ml : ctx->part_more + (ctx->part_copies - 1) * acc_floats + (m - 1) * ml_floats;
-        const hc_status s = split_any(ctx, x.L, x.arena, x.q, x.rep_logits, st, acc, ml);
-        if (s != HC_OK) {
-            (void)flush();
-            return s;
-        }
         batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse, (const uint4*)x.q, (uint4*)x.q_window};
+        group.it[gathered++] = split_item(x, acc, ml);
+        blocks = std::max(blocks, x.L->n_blocks);
+        filtered = split_filtered(ctx, x);
+        if (!together) {
+            const hc_status s = split();
+            if (s != HC_OK) {
+                (void)flush();
+                return s;
+            }
+        }
     }
     return flush();
 }

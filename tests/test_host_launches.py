@@ -160,3 +160,31 @@ def test_workgroups_of_a_refill_beside_the_attention_pass(fake):
         assert gathers(8, 4, 8) == [96, 96]           # 28
         assert gathers(8, 5, 10) == [48, 48]          # 35 in a group of five
     """)
+
+
+def test_long_layers_of_a_group_share_a_launch_of_the_split_pass(fake):
+    """Layers whose pass fills the GPU: one launch for the group; a short layer between them, or buffers that two of them share, part
+    it; with timing events set every layer has its own; if the shared launch fails, the layers before it are combined."""
+    run(fake, """
+        ctx = context(70000, 300)
+        long = [layer(ctx, 70000, 300) for _ in range(4)]
+        short = layer(ctx, 5000, 300)
+        def splits(layers, io=None):
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io or io_of(layers), len(layers), 8, None, None) == 0
+            return [int(l[2]) for l in log() if "attn_split" in l[0]], [int(l[3]) for l in log() if "attn_combine" in l[0]]
+        assert splits(long) == ([4], [4])
+        assert splits(long[:1]) == ([1], [1])
+        assert splits(long[:2] + [short] + long[2:]) == ([2, 1, 2], [5])
+        io = io_of(long)
+        io[2].out = io[1].out
+        assert splits(long, io) == ([2, 2], [2, 2])
+        ev = (C.c_void_p * 4)(1, 2, 3, 4)
+        assert L.hc_set_timing_events(ctx, ev, ev, 4) == 0
+        assert splits(long) == ([1, 1, 1, 1], [4])
+        assert splits(long) == ([4], [4])
+        fake.fake_reset(3)                           # the third launch: the two long layers behind the short one
+        assert L.hc_decode_step(ctx, io_of(long[:2] + [short] + long[2:]), 5, 8, None, None) == hc.HC_EHIP
+        names = [(l[0], int(l[2]), int(l[3])) for l in log()]
+        assert [y for n, y, z in names if "attn_split" in n] == [2, 1] and "attn_combine" in names[2][0] and names[2][2] == 3 and len(names) == 3, names
+    """)
