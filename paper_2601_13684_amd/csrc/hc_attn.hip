@@ -1238,10 +1238,14 @@ static SplitItem split_item(const hc_attn_call& x, float* part_acc, float* part_
 
 static bool split_filtered(const hc_ctx* ctx, const hc_attn_call& x) { return x.rep_logits != nullptr && hc_layer_filtered(ctx, x.L); }
 
-// Whether a layer may share its launch of the split pass with its neighbours of the group: if its workgroups fill the GPU.
+// Whether a layer may share its launch of the split pass with its neighbours of the group: if it has two granules of rows and more to
+// a compute unit.
 // (Shorter passes would gain as well, but keep a launch of their own: one that fails leaves the layers before it combined, layer by
 // layer.  Of a shared launch that fails, none of its layers is.  A caller that times the passes has a launch for each layer.)
-static bool split_together(const hc_ctx* ctx, const hc_layer* L) { return L->n_blocks >= ctx->wg_per_cu * ctx->n_cu && ctx->timing_next >= ctx->timing.size(); }
+static bool split_together(const hc_ctx* ctx, const hc_layer* L)
+{
+    return L->total_rows >= 2 * HC_UNIT_ROWS * (int64_t)ctx->n_cu && ctx->timing_next >= ctx->timing.size();
+}
 
 static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
 {

@@ -9,6 +9,8 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <numeric>
+#include <queue>
 #include <new>
 #include <utility>
 
@@ -348,8 +350,57 @@ struct ErrBuf {
     }
 };
 
+// Short passes (fewer than SHORT_SHARE granules of rows to a workgroup): how many workgroups every head gets, so that none of
+// them crosses from one head to the next, which costs it 2 us (a state merged and written, another one opened, loads that wait
+// for descriptors), as long as 4 to 6 granules.  A workgroup takes a granule in about 0.5 us where memory is not the bound; a
+// second one on its compute unit costs it 1.7 us.  So: shares of the fewest granules with which every workgroup has a compute unit
+// to itself, or, where sharing one makes them more than 2 granules shorter, with which two share it (then as many workgroups as there is room
+// for, the spare ones to the heads with the longest shares).  Groups of eight heads, whose workgroups keep the vector units and
+// the matrix cores busier, have a compute unit to themselves up to SHORT_SHARE.  us per call, before (equal shares across head boundaries, at
+// least 4 granules) / now: two KV heads, one of them full, 4K 9.1 / 7.6, 8K 9.5 / 8.1, 12K 10.4 / 8.8; eight KV heads, two full, 8K 12.2 / 9.6, 16K
+// 13.8 / 10.8, 32K 15.7 / 14.4, 64K 21.8 / 20.6; groups of eight heads, 24K 13.8 / 13.0, 48K 19.9 / 17.4, 96K 27.7 / 26.6.
+constexpr int64_t SHORT_SHARE = 16;
+static std::vector<int64_t> short_shares(const hc_head_desc* hd, int nh, int64_t n_cu, int64_t limit, int group)
+{
+    std::vector<int64_t> units(nh), n(nh);
+    int64_t longest = 1;
+    for (int i = 0; i < nh; ++i) longest = std::max(longest, units[i] = (hd[i].len + HC_UNIT_ROWS - 1) / HC_UNIT_ROWS);
+    auto workgroups = [&](int64_t share) {
+        int64_t sum = 0;
+        for (int i = 0; i < nh; ++i) sum += (units[i] + share - 1) / share;
+        return sum;
+    };
+    auto smallest = [&](int64_t most) {                // share with which there are no more workgroups than that
+        int64_t a = 1, b = longest;
+        while (a < b) {
+            const int64_t m = (a + b) / 2;
+            if (workgroups(m) <= most) b = m;
+            else a = m + 1;
+        }
+        return a;
+    };
+    if (nh > limit) return {};
+    int64_t share = smallest(limit), spare = 0;
+    const int64_t alone = nh <= n_cu ? smallest(std::min(n_cu, limit)) : INT64_MAX;
+    if (alone != INT64_MAX && (group >= 8 || alone <= share + 2)) share = alone;
+    else spare = limit - workgroups(share);
+    for (int i = 0; i < nh; ++i) n[i] = (units[i] + share - 1) / share;
+    typedef std::pair<double, int> Long;               // granules to a workgroup, head
+    std::priority_queue<Long> by_share;
+    for (int i = 0; i < nh && spare > 0; ++i) by_share.push(Long((double)units[i] / n[i], i));
+    for (; spare > 0; --spare) {
+        const int i = by_share.top().second;
+        if (n[i] >= units[i]) break;
+        by_share.pop();
+        ++n[i];
+        by_share.push(Long((double)units[i] / n[i], i));
+    }
+    return n;
+}
+
+// (short_limit: no more workgroups than that for a short pass)
 static hc_status make_plan(const hc_config& cfg, const hc_head_desc* hd, int n_cu, int wg_per_cu, const float* share_weights,
-                           Plan& P, const ErrBuf& E)
+                           Plan& P, const ErrBuf& E, int64_t short_limit = INT64_MAX)
 {
     const int nh = cfg.B * cfg.Hkv;
     const int max_reps = std::max(1, nh / 2);
@@ -480,12 +531,16 @@ static hc_status make_plan(const hc_config& cfg, const hc_head_desc* hd, int n_c
         H.tail_seg = H.tail_blk = -1;
         H.pad = 0;
     }
-    const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(max_blocks, total_units / min_units));
+    int nb = (int)std::max<int64_t>(1, std::min<int64_t>(max_blocks, total_units / min_units));
+    std::vector<int64_t> of_head;                      // short passes: every head's workgroups
+    if (total_units >= 2 * min_units && total_units < SHORT_SHARE * max_blocks)
+        of_head = short_shares(hd, nh, n_cu, std::min(short_limit, std::min<int64_t>(max_blocks, std::max<int64_t>(HC_STATIC_MAX_PARTIALS, nb))), cfg.Hq / cfg.Hkv);
+    if (!of_head.empty()) nb = (int)std::accumulate(of_head.begin(), of_head.end(), (int64_t)0);
     P.n_blocks = nb;
     P.blk_seg.assign(nb + 1, 0);
     // Long passes whose workgroups come in whole groups of one per die and dispatch slot get shares
     // weighted by the class the share runs on (share l runs on die (l % 16) / 2, slot l % 2).
-    const bool weighted = share_weights != nullptr && nb % 16 == 0 && total_units >= 16 * (int64_t)nb;   // >= 512 rows per workgroup
+    const bool weighted = of_head.empty() && share_weights != nullptr && nb % 16 == 0 && total_units >= 16 * (int64_t)nb;   // >= 512 rows per workgroup
 
     std::vector<int64_t> head_first(nh + 1, 0);        // first granule of every head
     for (int i = 0; i < nh; ++i) head_first[i + 1] = head_first[i] + (hd[i].len + HC_UNIT_ROWS - 1) / HC_UNIT_ROWS;
@@ -511,7 +566,14 @@ static hc_status make_plan(const hc_config& cfg, const hc_head_desc* hd, int n_c
 
     // share boundaries [lo, hi) in granules
     std::vector<int64_t> lo(nb), hi(nb);
-    {
+    if (!of_head.empty()) {
+        int l = 0;
+        for (int i = 0; i < nh; ++i)
+            for (int64_t j = 0, u = head_first[i + 1] - head_first[i]; j < of_head[i]; ++j, ++l) {
+                lo[l] = head_first[i] + u * j / of_head[i];
+                hi[l] = head_first[i] + u * (j + 1) / of_head[i];
+            }
+    } else {
         double total_w = 0;
         for (int l = 0; l < nb; ++l) total_w += weighted ? share_weights[l % 16] : 1.0;
         double acc_w = 0;
@@ -641,6 +703,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
     L->n_reps = (int)P.reps.size();
     L->n_sats = (int)P.sats.size();
     L->n_blocks = P.n_blocks;
+    L->total_rows = P.total_rows;
     L->n_segs = L->n_partials = (int)P.segs.size();
     L->hd_host.assign(hd, hd + L->n_heads);
     for (int i = 0; i < L->n_heads; ++i) L->ctx0_host.push_back(hd[i].ctx);
@@ -884,7 +947,7 @@ static hc_status replan(hc_ctx* ctx, hc_layer* L, hipStream_t st)
 {
     Plan P;
     hc_status s = make_plan(ctx->cfg, L->hd_host.data(), ctx->n_cu, ctx->wg_per_cu, ctx->share_weights, P,
-                            ErrBuf{ctx->err, sizeof ctx->err});
+                            ErrBuf{ctx->err, sizeof ctx->err}, L->blk_capacity);
     if (s != HC_OK) return s;
     if (P.n_blocks > L->blk_capacity || (int)P.segs.size() > L->seg_capacity || (int)P.reps.size() != L->n_reps)
         return hc_fail(ctx, HC_ESTATE, "internal: a rebalanced plan does not fit the layer");
@@ -908,6 +971,7 @@ static hc_status replan(hc_ctx* ctx, hc_layer* L, hipStream_t st)
     if (b_reps) HC_HIP(ctx, hipMemcpyAsync(L->reps, stage + o_reps, b_reps, hipMemcpyHostToDevice, st));
     HC_HIP(ctx, hipEventRecord(L->plan_copied[which], st));
     L->n_blocks = P.n_blocks;
+    L->total_rows = P.total_rows;
     L->n_segs = L->n_partials = (int)P.segs.size();
     L->max_nchunk = P.max_nchunk;
     L->max_cand = P.max_cand;

@@ -138,6 +138,7 @@ struct hc_layer {
     hc_ctx* ctx;
     int n_heads;
     int n_blocks, n_partials, n_segs;
+    int64_t total_rows;            // of all heads, when the plan was made
     int n_reps, n_sats;
     int max_r;                     // largest r among satellites
     int max_nchunk, max_cand;      // of the longest candidate range of any pivot: chunks, candidates
