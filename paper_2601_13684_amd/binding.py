@@ -151,9 +151,16 @@ def _p(x: Ptr) -> Optional[int]:
     return int(x)
 
 
+def _raw_stream() -> int:
+    """The current stream's handle.  torch's own accessor of the bare handle where there is one: the Stream object that
+    torch.cuda.current_stream makes on the way costs a microsecond a call."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+
+
 def _stream(s) -> Optional[int]:
     if s is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream()
     if isinstance(s, torch.cuda.Stream):
         return s.cuda_stream
     return int(s)

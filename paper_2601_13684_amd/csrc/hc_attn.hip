@@ -968,13 +968,19 @@ struct CombineItem {
     const uint4* q;              // the step's queries ...
     uint4* q_window;             // ... and where a re-scored window keeps them (nullptr: nowhere)
 };
+// (One layer's launch takes one layer's arguments: the host copies every byte of them to device memory, 0.4 us a KB.)
+struct CombineOne {
+    CombineItem it;
+    __device__ __forceinline__ const CombineItem& item() const { return it; }
+};
 struct CombineBatch {
     CombineItem it[HC_MAX_GROUP];
+    __device__ __forceinline__ const CombineItem& item() const { return it[blockIdx.z]; }
 };
-template <int G>
-__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(CombineBatch batch)
+template <int G, class Args>
+__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
 {
-    const CombineItem& item = batch.it[blockIdx.z];
+    const CombineItem& item = batch.item();
     const HeadDev* __restrict__ heads = item.heads;
     const float* __restrict__ part_acc = item.part_acc;
     const float* __restrict__ part_ml = item.part_ml;
@@ -1175,7 +1181,8 @@ hc_status launch_split(hc_ctx* ctx, const Args& a, int n, int n_blocks, bool fil
 template <int G>
 hc_status launch_combine(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
 {
-    attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ, n), dim3(COMBINE_BLK), 0, st>>>(batch);
+    if (n == 1) attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(CombineOne{batch.it[0]});
+    else attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ, n), dim3(COMBINE_BLK), 0, st>>>(batch);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
