@@ -176,6 +176,43 @@ __device__ __forceinline__ void move_rows(const GatherItem& it, const HeadDev& h
     }
 }
 
+// Pairs c0 .. c1 - 1 of a satellite's plan to slot[] and pos[]: a wave compacts its rounds r0 .. r1 - 1 of the masks, whose first free slot
+// and fresh position are numbers at_free and at_fresh.  want: the list's entries of the first U rounds, read again if `again`.
+template <int U, int NT>
+__device__ __forceinline__ void write_pairs(int32_t* slot, int32_t* pos, int c0, int c1, const int32_t* list, uint32_t (&want)[U], bool again, bool over, int r,
+                                            int r0, int r1, const uint64_t* free_mask, const uint64_t* fresh_mask, uint32_t at_free, uint32_t at_fresh)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t n = (uint32_t)(c1 - c0);
+    if (over) {
+#pragma unroll 1
+        for (int i = tid; i < (int)n; i += NT) {
+            slot[i] = c0 + i;
+            pos[i] = list[c0 + i];
+        }
+        return;
+    }
+    at_free -= (uint32_t)c0;
+    at_fresh -= (uint32_t)c0;
+#pragma unroll 1
+    for (int q0 = r0; q0 < r1; q0 += U) {
+        if (again) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) want[u] = (uint32_t)list[min((q0 + u) * 64 + lane, r - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q0 + u >= r1) break;
+            const uint64_t mf = free_mask[q0 + u], mn = fresh_mask[q0 + u], below = (1ull << lane) - 1ull;
+            const uint32_t a = at_free + (uint32_t)__builtin_popcountll(mf & below), b = at_fresh + (uint32_t)__builtin_popcountll(mn & below);
+            if (((mf >> lane) & 1u) && a < n) slot[a] = (q0 + u) * 64 + lane;
+            if (((mn >> lane) & 1u) && b < n) pos[b] = (int32_t)want[u];
+            at_free += (uint32_t)__builtin_popcountll(mf);
+            at_fresh += (uint32_t)__builtin_popcountll(mn);
+        }
+    }
+}
+
 // Which slots of a satellite hold positions that left the list (free), which positions of the list are not resident (fresh);
 // the k-th free slot takes the k-th fresh position.  And the move of those rows, in the same launch: the satellites that are to be
 // refilled get workgroups in proportion to their lists (so that the time does not depend on how unequal these are, and a launch
@@ -190,6 +227,9 @@ __device__ __forceinline__ void move_rows(const GatherItem& it, const HeadDev& h
 // ballots.  The plan is a chain of latencies: list and slot map are asked for together, at the start.
 // Six lists of 704 to 7,872 entries, a quarter new, 2.6 MB over the link (45 us at its rate): 54 us, 66 in two launches (a plan
 // by a workgroup per satellite, 11 us, then the rows, 54).  A launch that finds nothing to do takes 4 us.
+// A workgroup's share of the pairs stays in LDS, in the place of the bitmaps: written to memory and read back (all pairs, by every
+// workgroup of the satellite) they cost a round trip and a wait for the stores in front of the first row.  us, through memory / LDS: one list of
+// 320 10.3 / 9.7, six of 420 to 640 15.1 / 13.8, 42 of 600 to 2,300 123 / 120.6, the six lists above 54.6 / 54.0.
 // PLAN: the plan alone, a task to a satellite, whether its pivot fired or not; gather_kernel moves the rows.
 template <int NT, bool PLAN>
 __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, int n_items, int max_sats, int max_k, int movers)
@@ -255,8 +295,6 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         uint64_t* fresh_mask = free_mask + rounds;                                                   // [rounds]: list entries no slot holds
         const int32_t* list = it.topk_idx + (size_t)bh * max_k;
         int32_t* sp = it.slot_pos + (size_t)bh * max_k;
-        int32_t* pslot = it.pair_slot + (size_t)bh * max_k;
-        int32_t* ppos = it.pair_pos + (size_t)bh * max_k;
         // a wave takes a run of rounds of 64, U of them at a time; the first U stay in registers
         const int per = (rounds + NW - 1) / NW, r0 = min(rounds, wv * per), r1 = min(rounds, r0 + per);
         auto load = [&](uint32_t (&p)[U], const int32_t* src, int q0) {
@@ -309,11 +347,8 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
             sm_cnt[1][wv] = n_fresh;
         }
         __syncthreads();                             // (this workgroup has read the slot map)
-        if (tid == 0) {
-            int32_t* done = it.done + bh;
-            sm_last = parts == 1 || atomicAdd(done, 1) == parts - 1;
-            if (sm_last && parts > 1) *done = 0;
-        }
+        int ticket = 0;
+        if (!PLAN && tid == 0 && parts > 1) ticket = atomicAdd(it.done + bh, 1);
         uint32_t at_free = 0, at_fresh = 0, tot_free = 0, tot_fresh = 0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -326,42 +361,59 @@ __global__ __launch_bounds__(NT) void gather_plan_bitmap_kernel(GatherBatch B, i
         at_fresh = (uint32_t)uniform((int)at_fresh);
         tot_free = (uint32_t)uniform((int)tot_free);
         tot_fresh = (uint32_t)uniform((int)tot_fresh);
-        // the pairs (the same from every workgroup of this satellite)
         const bool over = tot_free != tot_fresh;     // the slot map does not describe a set of r distinct positions: start over from the list
         const int pairs = over ? r : (int)tot_free;
-        if (over) {
-#pragma unroll 1
-            for (int i = tid; i < r; i += NT) {
-                pslot[i] = i;
-                ppos[i] = list[i];
-            }
-        } else {
-#pragma unroll 1
-            for (int q0 = r0; q0 < r1; q0 += U) {
-                if (per > U) load(want, list, q0);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (q0 + u >= r1) break;
-                    const uint64_t mf = free_mask[q0 + u], mn = fresh_mask[q0 + u], below = (1ull << lane) - 1ull;
-                    if ((mf >> lane) & 1u) pslot[at_free + __builtin_popcountll(mf & below)] = (q0 + u) * 64 + lane;
-                    if ((mn >> lane) & 1u) ppos[at_fresh + __builtin_popcountll(mn & below)] = (int32_t)want[u];
-                    at_free += (uint32_t)__builtin_popcountll(mf);
-                    at_fresh += (uint32_t)__builtin_popcountll(mn);
-                }
-            }
-        }
-        __syncthreads();                             // the pairs are complete (and visible to the whole workgroup)
-        if (sm_last)
+        if constexpr (PLAN) {
+            int32_t* pslot = it.pair_slot + (size_t)bh * max_k;
+            int32_t* ppos = it.pair_pos + (size_t)bh * max_k;
+            write_pairs<U, NT>(pslot, ppos, 0, pairs, list, want, per > U, over, r, r0, r1, free_mask, fresh_mask, at_free, at_fresh);
+            __syncthreads();                         // the pairs are complete (and visible to the whole workgroup)
 #pragma unroll 1
             for (int k = tid; k < pairs; k += NT) sp[pslot[k]] = ppos[k];
-        if (PLAN) {
             if (tid == 0) it.npairs[bh] = pairs;
             __syncthreads();
-            continue;
+        } else {
+            // this workgroup's share of the pairs, in the bitmaps' place (as many at a time as there are words to a bitmap)
+            int32_t* slot = reinterpret_cast<int32_t*>(sm_words);
+            int32_t* pos = slot + words;
+            const int k_begin = (int)((long long)pairs * part / parts), k_end = (int)((long long)pairs * (part + 1) / parts);
+            auto own = [&](int c0, bool again) __attribute__((always_inline)) {
+                write_pairs<U, NT>(slot, pos, c0, min(k_end, c0 + words), list, want, per > U || again, over, r, r0, r1, free_mask, fresh_mask, at_free, at_fresh);
+            };
+            own(k_begin, false);
+            if (tid == 0) {
+                sm_last = parts > 1 && ticket == parts - 1;
+                if (sm_last) it.done[bh] = 0;
+            }
+            __syncthreads();
+            if (sm_last) {                           // everyone has read the slot map: bring it up to date
+#pragma unroll 1
+                for (int c0 = 0; c0 < pairs; c0 += words) {
+                    const int c1 = min(pairs, c0 + words);
+                    write_pairs<U, NT>(slot, pos, c0, c1, list, want, true, over, r, r0, r1, free_mask, fresh_mask, at_free, at_fresh);
+                    __syncthreads();
+#pragma unroll 1
+                    for (int k = tid; k < c1 - c0; k += NT) sp[slot[k]] = pos[k];
+                    __syncthreads();
+                }
+                own(k_begin, true);
+                __syncthreads();
+            }
+#pragma unroll 1
+            for (int c0 = k_begin; c0 < k_end; c0 += words) {
+                if (c0 != k_begin) {
+                    own(c0, true);
+                    __syncthreads();
+                }
+                const int n = min(k_end - c0, words);
+                if (parts == 1)
+#pragma unroll 1
+                    for (int k = tid; k < n; k += NT) sp[slot[k]] = pos[k];
+                move_rows<2>(it, hd, first_slot, r, slot, pos, 0, n, movers);
+                __syncthreads();
+            }
+            __syncthreads();                         // (the next satellite takes over the LDS)
         }
-        const int k_begin = (int)((long long)pairs * part / parts), k_end = (int)((long long)pairs * (part + 1) / parts);
-        move_rows<2>(it, hd, first_slot, r, pslot, ppos, k_begin, k_end, movers);
-        __syncthreads();                             // (the next satellite takes over the LDS and the workspace's pairs)
     }
 }
 
