@@ -304,7 +304,13 @@ struct Digits {                                      // x: number of a narrow di
 typedef Digits<1024, 896, 2> FineDigits;
 typedef Digits<1536, 256, 3> LinearDigits;
 constexpr int FINE_BASE = (0x80000000u >> 17) + (104 << 6);     // the key of 2^-23, without its last 17 bits
-__device__ __forceinline__ uint32_t fine_digit(uint32_t key) { return FineDigits::of((int)(key >> 17) - FINE_BASE); }
+// FineDigits::of the score's key, in a third of the instructions: negative scores and what is no number end in the lowest digit, as 0
+// does, and the piecewise line is the middle one of three.
+__device__ __forceinline__ uint32_t fine_digit(float s)
+{
+    const int x = (int)(__float_as_uint(fmaxf(s, 0.f)) >> 17) + (0x4000 - FINE_BASE + 896), y = (x >> 2) + (896 - 896 / 4);
+    return (uint32_t)min(max(min(max(x, y), y + (1024 - 1024 / 4)), 0), HC_RADIX_BINS - 1);
+}
 __device__ __forceinline__ uint32_t linear_digit(float s) { return LinearDigits::of((int)fminf(fmaxf(floorf(s * 64.f), -4096.f), 4096.f) + 768); }
 __device__ __forceinline__ uint32_t digit_low(uint32_t digit, bool linear)                // smallest key of a digit ...
 {
@@ -441,8 +447,7 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
             const int j = first + i * BLK + threadIdx.x;
             if (j < rd.hi) {
                 if (!scores_given) srow[j] = s[i];
-                const uint32_t key = hc_score_key(s[i]);
-                atomicAdd(&sh[HIST == HIST_LINEAR ? linear_digit(s[i]) : HIST == HIST_FINE ? fine_digit(key) : key >> 21], 1u);
+                atomicAdd(&sh[HIST == HIST_LINEAR ? linear_digit(s[i]) : HIST == HIST_FINE ? fine_digit(s[i]) : hc_score_key(s[i]) >> 21], 1u);
             }
         }
     }
@@ -1211,10 +1216,13 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     // everything from memory is asked for now
     OutDev od{};
     if (rd.out_count <= SEL_OUTS) od = it.outs[rd.out_begin + min(lane, rd.out_count - 1)];
-    const int k = it.reps[rep].k[ks];
-    int k_longest = 1;
-    for (int i = 0; i < rd.nk; ++i) k_longest = max(k_longest, it.reps[rep].k[i]);      // (indexing the register copy would spill it)
-    const int real_lo = it.real_reps[rep].lo & ALIGN, real_hi = min(it.real_reps[rep].hi, real_lo + bm_words * 32);      // the bitmap is indexed by position
+    int k = rd.k[0], k_longest = 1;
+#pragma unroll
+    for (int i = 0; i < HC_MAX_K_PER_REP; ++i) {     // (a loop over memory would be a chain of reads, a variable index would spill the copy)
+        if (i == ks) k = rd.k[i];
+        if (i < rd.nk) k_longest = max(k_longest, rd.k[i]);
+    }
+    const int real_lo = (MAP ? it.real_reps[rep].lo : rd.lo) & ALIGN, real_hi = min(MAP ? it.real_reps[rep].hi : rd.hi, real_lo + bm_words * 32);      // the bitmap is indexed by position
     const int bw = deciding ? (real_hi - real_lo + 31) / 32 : 0;
     const bool checks = MAP && deciding && it.need_sense == 0 && it.filt != nullptr;      // (a filter's rows come with a map)
     const float cutsum = checks ? it.filt[rep].cutsum : 0.f;
@@ -1368,14 +1376,27 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
             }
         __syncthreads();
     } else if (HERE) {                               // few items, and digits of a few of them each: the histogram is made here
+        // (issue bound: 12,700 rows took 4.7 us of the launch with key, digit and place of an item in 28 instructions; with 11 of them
+        // 3.2, a step of four layers of 224K on one stream 255 -> 251 us)
         for (int t = t0; t < t1; ++t) {
             arrived(t);
             const float* tile = reinterpret_cast<const float*>(buffer(t));
             const int left = end - t * TILE;
+            if (left >= TILE) {                      // (any order will do)
+#pragma unroll 1
+                for (int j = 0; j < 4; ++j) {
+                    const float4 v = *reinterpret_cast<const float4*>(tile + (j * 64 + lane) * 4);
+                    atomicAdd(&sm_hist[fine_digit(v.x)], 1u);
+                    atomicAdd(&sm_hist[fine_digit(v.y)], 1u);
+                    atomicAdd(&sm_hist[fine_digit(v.z)], 1u);
+                    atomicAdd(&sm_hist[fine_digit(v.w)], 1u);
+                }
+            } else {
 #pragma unroll 4
-            for (int j = 0; j < 16; ++j) {           // (any order will do: this one finds all banks)
-                const int at = j * 64 + lane, i = (at & ~15) | ((((at >> 2) & 3) ^ ((at >> 6) & 3)) << 2) | (at & 3);
-                if (i < left && (MAP || t * TILE + i >= first)) atomicAdd(&sm_hist[fine_digit(hc_score_key(tile[at]))], 1u);
+                for (int j = 0; j < 16; ++j) {
+                    const int at = j * 64 + lane, i = (at & ~15) | ((((at >> 2) & 3) ^ ((at >> 6) & 3)) << 2) | (at & 3);
+                    if (i < left) atomicAdd(&sm_hist[fine_digit(tile[at])], 1u);
+                }
             }
             leave(t);
         }
