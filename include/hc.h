@@ -394,8 +394,8 @@ int32_t hc_layer_context(const hc_layer* layer, int32_t b);
  * hc_prefill_work_bytes bytes, 256-byte aligned, scratch (hc_prefill_work_layout says where the selecting
  * heads' logits [n][max_ctx][G], scores [n][max_ctx] and the lse [B*Hq] are left, and which table row
  * each selecting head is; head_of needs room for B*Hkv entries).
- * Set-up call: synchronises the stream once (a small table goes to the device), then enqueues.  Must
- * precede any hc_append_kv on the layer. */
+ * Enqueue-only (k_src_off and v_src_off are read before it returns).  Must precede any hc_append_kv on the
+ * layer. */
 size_t hc_prefill_work_bytes(const hc_ctx* ctx, const hc_layer* layer);
 hc_status hc_prefill_work_layout(const hc_ctx* ctx, const hc_layer* layer, int32_t* n_selecting, int32_t* head_of,
                                  size_t* logits_off, size_t* scores_off, size_t* lse_off);

@@ -1165,9 +1165,10 @@ extern "C" hc_status hc_prefill_init(hc_ctx* ctx, hc_layer* layer, const void* k
         src[(size_t)i] = PreSrc{k_src_off[i], v_src_off[i]};
     }
     hipStream_t st = (hipStream_t)stream;
-    // (pageable source: the copy has left the host buffer when the call returns)
-    HC_HIP(ctx, hipMemcpyAsync(L->pre_src, src.data(), src.size() * sizeof(PreSrc), hipMemcpyHostToDevice, st));
-    HC_HIP(ctx, hipStreamSynchronize(st));
+    {
+        const hc_status s = hc_launch_prefill_src(ctx, L, src.data(), st);
+        if (s != HC_OK) return s;
+    }
     char* wb = (char*)work;
     if (L->n_sel > 0) {
         float* logits = (float*)(wb + lay.logits_off);

@@ -349,6 +349,7 @@ struct hc_prefill_layout {
     size_t logits_off, scores_off, lse_off, part_off, scratch_off, bytes;
 };
 hc_prefill_layout hc_prefill_plan(const hc_ctx* ctx, const hc_layer* L);
+hc_status hc_launch_prefill_src(hc_ctx* ctx, const hc_layer* L, const PreSrc* src, hipStream_t st);      // src: host memory, read before the call returns
 hc_status hc_launch_prefill_scores(hc_ctx* ctx, const hc_layer* L, const float* logits, const float* lse, float* scores, int pool,
                                    hipStream_t st);
 hc_status hc_launch_prefill_place(hc_ctx* ctx, const hc_layer* L, const void* kv_prefill, void* arena, void* tier,

@@ -12,6 +12,8 @@
 //   prefill_place_kernel   rows of the resident positions -> the heads' blocks in the arena; baseline sets,
 //                          slot maps and rings; beside it satellites' rows -> the pinned host tier, K row then
 //                          V row per position                                                   (below)
+#include <algorithm>
+
 #include "hc_internal.h"
 
 namespace {
@@ -20,6 +22,19 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PF_BLK = 256;
 constexpr int PF_CHUNK = 1024;       // positions per workgroup of the score kernel
+
+// Where the heads' rows of the prefill stage are, from a launch's arguments to the layer's table.  (A copy from the caller's memory
+// has to be waited for before the call may return: the GPU then stands idle behind every call, and the host waits for the whole of the
+// layer before, 1.8 ms at 32K.  us per call, with the copy / this way: 2K, two heads 61 / 49, 8K 506 / 494, 32K 1855 / 1842.)
+constexpr int SRC_HEADS = 128;
+struct SrcBatch {
+    PreSrc at[SRC_HEADS];
+};
+__global__ __launch_bounds__(SRC_HEADS) void prefill_src_kernel(SrcBatch batch, PreSrc* __restrict__ src, int n)
+{
+    const int i = threadIdx.x;
+    if (i < n) src[i] = batch.at[i];
+}
 
 // score[j] = (1/P) sum_{|d| <= P/2} a[j+d],  a[i] = (1/G) sum_g exp(l[i][g] - lse[g]) (or the mean logit), a = 0
 // outside [0, ctx).  A workgroup stages a[] of its chunk and the halo in LDS, so every a[i] is computed once
@@ -200,6 +215,18 @@ hc_prefill_layout hc_prefill_plan(const hc_ctx* ctx, const hc_layer* L)
     off += pf_align(2 * (size_t)c.B * c.Hkv * 4);
     o.bytes = off;
     return o;
+}
+
+hc_status hc_launch_prefill_src(hc_ctx* ctx, const hc_layer* L, const PreSrc* src, hipStream_t st)
+{
+    for (int i = 0; i < L->n_heads; i += SRC_HEADS) {
+        SrcBatch batch{};
+        const int n = std::min(SRC_HEADS, L->n_heads - i);
+        std::copy(src + i, src + i + n, batch.at);
+        prefill_src_kernel<<<dim3(1), dim3(SRC_HEADS), 0, st>>>(batch, L->pre_src + i, n);
+        HC_HIP(ctx, hipGetLastError());
+    }
+    return HC_OK;
 }
 
 hc_status hc_launch_prefill_scores(hc_ctx* ctx, const hc_layer* L, const float* logits, const float* lse, float* scores, int pool,
