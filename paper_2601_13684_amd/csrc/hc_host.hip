@@ -332,6 +332,7 @@ struct Plan {
     std::vector<SatDev> sats;
     std::vector<int32_t> rep_slot_of;
     int n_blocks = 0, max_r = 0, max_nchunk = 1, max_cand = 1;
+    bool weighted = false;             // the shares are weighted by die and dispatch slot
     int64_t total_rows = 0;
 };
 
@@ -541,6 +542,7 @@ static hc_status make_plan(const hc_config& cfg, const hc_head_desc* hd, int n_c
     // Long passes whose workgroups come in whole groups of one per die and dispatch slot get shares
     // weighted by the class the share runs on (share l runs on die (l % 16) / 2, slot l % 2).
     const bool weighted = of_head.empty() && share_weights != nullptr && nb % 16 == 0 && total_units >= 16 * (int64_t)nb;   // >= 512 rows per workgroup
+    P.weighted = weighted;
 
     std::vector<int64_t> head_first(nh + 1, 0);        // first granule of every head
     for (int i = 0; i < nh; ++i) head_first[i + 1] = head_first[i] + (hd[i].len + HC_UNIT_ROWS - 1) / HC_UNIT_ROWS;
@@ -704,6 +706,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
     L->n_sats = (int)P.sats.size();
     L->n_blocks = P.n_blocks;
     L->total_rows = P.total_rows;
+    L->weighted = P.weighted;
     L->n_segs = L->n_partials = (int)P.segs.size();
     L->hd_host.assign(hd, hd + L->n_heads);
     for (int i = 0; i < L->n_heads; ++i) L->ctx0_host.push_back(hd[i].ctx);
@@ -976,6 +979,7 @@ static hc_status replan(hc_ctx* ctx, hc_layer* L, hipStream_t st)
     HC_HIP(ctx, hipEventRecord(L->plan_copied[which], st));
     L->n_blocks = P.n_blocks;
     L->total_rows = P.total_rows;
+    L->weighted = P.weighted;
     L->n_segs = L->n_partials = (int)P.segs.size();
     L->max_nchunk = P.max_nchunk;
     L->max_cand = P.max_cand;
@@ -1051,9 +1055,7 @@ extern "C" hc_status hc_layer_tune(hc_ctx* ctx, hc_layer* layer, const void* kv_
     if (rounds < 1 || rounds > 16) return hc_fail(ctx, HC_EINVAL, "hc_layer_tune: rounds 1..16");
     hc_layer* L = layer;
     const int nb = L->n_blocks;
-    int64_t total_units = 0;
-    for (const hc_head_desc& h : L->hd_host) total_units += (h.len + HC_UNIT_ROWS - 1) / HC_UNIT_ROWS;
-    if (nb % 16 != 0 || total_units < 16 * (int64_t)nb) return HC_OK;        // shares of this plan are not weighted
+    if (!L->weighted) return HC_OK;        // shares of this plan are not weighted
     hipStream_t st = (hipStream_t)stream;
     unsigned long long* dev = nullptr;
     HC_HIP(ctx, hipMalloc((void**)&dev, (size_t)nb * 2 * sizeof(unsigned long long)));

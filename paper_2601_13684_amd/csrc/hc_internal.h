@@ -139,6 +139,7 @@ struct hc_layer {
     int n_heads;
     int n_blocks, n_partials, n_segs;
     int64_t total_rows;            // of all heads, when the plan was made
+    bool weighted = false;         // the plan's shares are weighted by die and dispatch slot
     int n_reps, n_sats;
     int max_r;                     // largest r among satellites
     int max_nchunk, max_cand;      // of the longest candidate range of any pivot: chunks, candidates

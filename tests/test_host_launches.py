@@ -188,3 +188,23 @@ def test_long_layers_of_a_group_share_a_launch_of_the_split_pass(fake):
         names = [(l[0], int(l[2]), int(l[3])) for l in log()]
         assert [y for n, y, z in names if "attn_split" in n] == [2, 1] and "attn_combine" in names[2][0] and names[2][2] == 3 and len(names) == 3, names
     """)
+
+
+def test_a_short_pass_of_a_group_of_eight_is_not_tuned(fake):
+    """Its plan has no weights to measure, whatever its number of workgroups and their length (one to a compute unit, of up to 31
+    granules): hc_layer_tune leaves it as it is."""
+    run(fake, """
+        seen = 0
+        for N in range(137000, 138000, 100):
+            ctx = context(N, 300, G=8)
+            x = layer(ctx, N, 300)
+            nb = L.hc_layer_num_workgroups(x)
+            assert nb <= 256
+            if nb % 16 == 0 and N // 32 >= 16 * nb:
+                seen += 1
+                before = [C.c_float(0) for _ in range(16)]
+                fake.fake_reset(0)
+                assert L.hc_layer_tune(ctx, x, C.c_void_p(1 << 40), C.c_void_p(1 << 41), C.c_void_p(1 << 42), C.c_void_p(1 << 43), None, 2, None) == 0
+                assert log() == []
+        assert seen
+    """)
