@@ -13,7 +13,7 @@
 // of its items in LDS: threshold, ordered lists, |T ∩ baseline| through a bitmap in LDS, window, decision and
 // baseline update.  What reaches it:
 //   short candidate ranges   mon_direct scores the candidates itself: one launch
-//   up to 64K candidates (32K beside the attention pass)
+//   up to 64K candidates (beside the attention pass 32K, and for few lists 64K)
 //                            mon_score_hist (scores and their histogram; many workgroups per pivot), mon_direct (the lists straight
 //                            from the scores, no keys in LDS): two launches
 //   longer ranges            mon_score_hist (scores, first-digit histogram; many workgroups per pivot), mon_compact (the
@@ -1160,7 +1160,7 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 
 // ---- the selection straight from the scores ----
 //
-// For up to 64 K candidates (32 K beside the attention pass), and for the rows a filtering split pass kept: one workgroup per
+// For up to 64 K candidates (beside the attention pass 32 K, for few lists 64 K), and for the rows a filtering split pass kept: one workgroup per
 // pivot and set size, as mon_select, behind a launch that left the scores and their histogram (DIRECT_HIST), behind
 // mon_sparse_score (DIRECT_MAP: kept rows), or by itself over a short range (DIRECT_LOGITS, or DIRECT_SCORES where the scores
 // are given).  The histogram names the digit in which the list ends.  A wave then goes once through its run of the items, 1024 to a tile, 16 consecutive ones to a lane:
@@ -2166,29 +2166,39 @@ static bool select_small(const hc_ctx* ctx, int items)
 
 // mon_direct: up to as many items as its waves have bits for, if tiles and bitmaps fit in LDS beside what it declares.
 constexpr int DIRECT_STATIC = 14 * 1024;
-static int direct_threads(const hc_ctx* ctx) { return ctx->beside_now ? 512 : 1024; }
-static int direct_room(const hc_ctx* ctx)
+// Its two forms.  Beside the attention pass the small one fits next to two attention workgroups on a compute unit, but goes through
+// 32 K candidates only.  For up to 64 K of an unfiltered layer the large one, which fits next to one of them (as long as it keeps
+// one buffer of tiles), beats the survivors' three launches while lists are few.  Steps of four layers in groups of two, us by three launches / this way: one
+// sequence (12 lists) of 36,000 114 / 101, 48K 124 / 108, 60,000 118 / 110, in groups of eight heads 36,000 160 / 143, 50,000 125 / 110; three (18 lists, a layer to a
+// group) 111 / 109; two (24 lists) 106-120 / 111-113; four (48 lists, whose workgroups attention's then wait for) 174 / 187.  (For up to 32 K the small form and
+// the large one take the same.)
+struct DirectForm {
+    int threads, room;           // room: dynamic LDS of a workgroup, bytes
+};
+static DirectForm direct_form(const hc_ctx* ctx, int mode, int items, int lists)
 {
-    return (!ctx->beside_now ? 156 * 1024 : ctx->G == 8 ? 56 * 1024 : ctx->side_pad_now ? 110 * 1024 : 76 * 1024) - DIRECT_STATIC;
+    if (!ctx->beside_now) return {1024, 156 * 1024 - DIRECT_STATIC};
+    if (mode == 0 && !ctx->side_pad_now && items + 3 > 512 / 64 * DIRECT_TILES * HC_SEL_CHUNK && lists <= 20) return {1024, (ctx->G == 8 ? 106 : 116) * 1024 - DIRECT_STATIC};
+    return {512, (ctx->G == 8 ? 56 : ctx->side_pad_now ? 110 : 76) * 1024 - DIRECT_STATIC};
 }
 // Candidates a launch goes through.  A captured call is replayed over contexts that have grown since, so a launch takes whole tiles:
 // one to a wave, or up to the end of the last chunk that mon_score_hist takes (items are counted from a multiple of four
 // positions, so that the last three may not fit).
-static int direct_most(const hc_ctx* ctx, int src, int items)
+static int direct_most(const DirectForm& f, int src, int items)
 {
-    const int tile_each = direct_threads(ctx) / 64 * HC_SEL_CHUNK;
+    const int tile_each = f.threads / 64 * HC_SEL_CHUNK;
     if (src == DIRECT_LOGITS) return tile_each;
     if (src == DIRECT_SCORES) return tile_each - 3;
     return std::min((items + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK * HC_SEL_CHUNK, DIRECT_TILES * tile_each - 3);
 }
-static int direct_bytes(const hc_ctx* ctx, int most, int bm_words, int bufs)
+static int direct_bytes(const DirectForm& f, int most, int bm_words, int bufs)
 {
     const int tiles = (most + 3 + HC_SEL_CHUNK - 1) / HC_SEL_CHUNK;
-    return 4 * (bufs * direct_threads(ctx) / 64 * HC_SEL_CHUNK + tiles * (HC_SEL_CHUNK / 32) + bm_words + 2);
+    return 4 * (bufs * f.threads / 64 * HC_SEL_CHUNK + tiles * (HC_SEL_CHUNK / 32) + bm_words + 2);
 }
-static bool direct_fits(const hc_ctx* ctx, int items, int bm_words)
+static bool direct_fits(const DirectForm& f, int items, int bm_words)
 {
-    return items + 3 <= direct_threads(ctx) / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(ctx, direct_most(ctx, DIRECT_HIST, items), bm_words, 1) <= direct_room(ctx);
+    return items + 3 <= f.threads / 64 * DIRECT_TILES * HC_SEL_CHUNK && direct_bytes(f, direct_most(f, DIRECT_HIST, items), bm_words, 1) <= f.room;
 }
 // Lists that mon_direct writes in several pieces, going through its bits for each (a piece has 16,384 entries there, alone): whether
 // the six launches of long lists take less.  One list, us by them / by mon_direct, scores spread out and within 2 % of each other: 32,000 of
@@ -2202,15 +2212,15 @@ static bool direct_outlasted(const hc_ctx* ctx, int items, int max_k, int max_nk
     return !ctx->beside_now && max_k > 16384 && !(max_nk >= 3 ? max_k <= 40960 : max_k <= 32768 && items <= 51200);
 }
 template <int SRC>
-static hc_status launch_direct(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
+static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
 {
-    const int most = direct_most(ctx, SRC, items);
+    const int most = direct_most(f, SRC, items);
     bm_words = SRC == DIRECT_MAP ? bm_words + 1 : std::max(bm_words, (most + 3 + 31) / 32);      // (positions are counted from a multiple of four; a candidate's number is its bit)
-    const int bufs = SRC < DIRECT_SCORES && items + 3 > direct_threads(ctx) / 64 * HC_SEL_CHUNK && direct_bytes(ctx, most, bm_words, 2) <= direct_room(ctx) ? 2 : 1;
-    const unsigned lds = (unsigned)direct_bytes(ctx, most, bm_words, bufs);
+    const int bufs = SRC < DIRECT_SCORES && items + 3 > f.threads / 64 * HC_SEL_CHUNK && direct_bytes(f, most, bm_words, 2) <= f.room ? 2 : 1;
+    const unsigned lds = (unsigned)direct_bytes(f, most, bm_words, bufs);
 #define HC_DIRECT(NT, GG)                                                                                                    \
     mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words)
-    const bool small = direct_threads(ctx) == 512;
+    const bool small = f.threads == 512;
     if constexpr (SRC != DIRECT_LOGITS) {
         if (small) HC_DIRECT(512, 1);                                // (the group size only matters where logits are read)
         else HC_DIRECT(1024, 1);
@@ -2371,11 +2381,12 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     // then have a tile, and the rows' positions are one read more behind the selection.  Steps of four layers, contexts of 66,000 to 123,000, a
     // drift at every step, us by mon_select / mon_direct: longest list 1,728, three and six sequences 277 278 / 424 425; 3,776 297 314 /
     // 459 480; 5,824 343 345 / 536 536; 7,872 478 467 / 596 594 (the kernel itself, 3,776, six sequences: 59 and 97).
-    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(ctx, candidates, bm_words) &&
+    const DirectForm form = direct_form(ctx, mode, candidates, pivots * max_nk);
+    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(form, candidates, bm_words) &&
                         !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk)) && !(ctx->beside_now && few && max_k <= 4096);
     if (mode == 1) {
         if (direct)                                      // (more rows than it goes through, in a captured call: the dense chain's)
-            for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(ctx, DIRECT_MAP, candidates));
+            for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(form, DIRECT_MAP, candidates));
         // enough waves for a segment each of a long context's few hundred, no more workgroups than compute units
         const dim3 g(std::max(4, std::min(armed ? 32 : 128, (armed ? 256 : 1024) / pivots)), max_reps, n);
         switch (ctx->G) {
@@ -2387,11 +2398,11 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         HC_HIP(ctx, hipGetLastError());
     }
     if (mode != 0) scores_given = 1;                     // they are there from here on
-    if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, B, dc, gsel, candidates, bm_words, st);
+    if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, form, B, dc, gsel, candidates, bm_words, st);
     // (a tile to a wave; given scores are read from a multiple of four positions on)
-    if (mode == 0 && candidates <= SELECT_DIRECT && (!scores_given || candidates + 3 <= direct_threads(ctx) / 64 * HC_SEL_CHUNK))
-        return scores_given ? launch_direct<DIRECT_SCORES>(ctx, B, dc, gsel, candidates, bm_words, st)
-                            : launch_direct<DIRECT_LOGITS>(ctx, B, dc, gsel, candidates, bm_words, st);
+    if (mode == 0 && candidates <= SELECT_DIRECT && (!scores_given || candidates + 3 <= form.threads / 64 * HC_SEL_CHUNK))
+        return scores_given ? launch_direct<DIRECT_SCORES>(ctx, form, B, dc, gsel, candidates, bm_words, st)
+                            : launch_direct<DIRECT_LOGITS>(ctx, form, B, dc, gsel, candidates, bm_words, st);
     if (few || candidates <= SELECT_DIRECT) {
         const bool small = few ? select_small(ctx, kept) : select_small(ctx, candidates);
         return launch_select<SRC_SCORES>(ctx, B, dc, gsel, candidates, bm_words, small, st);
@@ -2406,7 +2417,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         const int span = mode == 2 ? 32 : ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, (pivots * max_nchunk) / (ctx->beside_now ? 512 : 2048)));
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
 #define HC_SCORE(GG, HIST)                                                                                                   \
-    mon_score_hist<GG, HIST><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, HIST>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(ctx, DIRECT_HIST, candidates))
+    mon_score_hist<GG, HIST><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, HIST>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(form, DIRECT_HIST, candidates))
         switch (ctx->G * 4 + (!direct ? HIST_KEYS : c.agg == HC_AGG_LOGIT ? HIST_LINEAR : HIST_FINE)) {
         case 4: HC_SCORE(1, HIST_KEYS); break;
         case 5: HC_SCORE(1, HIST_FINE); break;
@@ -2423,7 +2434,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         }
 #undef HC_SCORE
         HC_HIP(ctx, hipGetLastError());
-        if (direct) return launch_direct<DIRECT_HIST>(ctx, B, dc, gsel, candidates, bm_words, st);
+        if (direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, candidates, bm_words, st);
         if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
     }
     // The small form where all that may survive fits, and what is expected fits with the baseline bitmap (without the bitmap in LDS

@@ -208,3 +208,17 @@ def test_a_short_pass_of_a_group_of_eight_is_not_tuned(fake):
                 assert log() == []
         assert seen
     """)
+
+
+@pytest.mark.parametrize("N,n,kernel", [(32777, 4, "mon_directILi512ELi0E"), (32778, 4, "mon_directILi1024ELi0E"), (65545, 4, "mon_directILi1024ELi0E"),
+                                        (65600, 4, "mon_selectILi512ELi2E")])
+def test_what_selects_among_long_ranges_beside_the_attention_pass(fake, N, n, kernel):
+    """Unfiltered, few lists: mon_direct's small form up to 32,765 candidates (N - 12), its large one up to 65,533."""
+    run(fake, f"""
+        ctx = context({N}, 300, n={n})
+        layers = [layer(ctx, {N}, 300, n={n}) for _ in range(2)]
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io_of(layers), 2, 1, None, C.c_void_p(77)) == 0
+        names = [l[0] for l in log() if "mon_" in l[0]]
+        assert sum("{kernel}" in n for n in names) == 2, names
+    """)
