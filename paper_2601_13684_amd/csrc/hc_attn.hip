@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "hc_internal.h"
+#include "hc_score.h"
 
 namespace {
 
@@ -977,10 +978,10 @@ struct CombineBatch {
     CombineItem it[HC_MAX_GROUP];
     __device__ __forceinline__ const CombineItem& item() const { return it[blockIdx.z]; }
 };
-template <int G, class Args>
-__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
+// Workgroup (head, quarter): quarter of the columns of query head `head` of all.
+template <int G>
+__device__ __forceinline__ void combine_head(const CombineItem& item, int head, int quarter)
 {
-    const CombineItem& item = batch.item();
     const HeadDev* __restrict__ heads = item.heads;
     const float* __restrict__ part_acc = item.part_acc;
     const float* __restrict__ part_ml = item.part_ml;
@@ -989,10 +990,10 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
     __shared__ float sm_max[COMBINE_BLK / 64];
     __shared__ float4 sm_acc[32][CQ];
     __shared__ float sm_z[32];
-    const int bh = blockIdx.x / G, g = blockIdx.x % G;
+    const int bh = head / G, g = head % G;
     const HeadDev hd = heads[bh];
-    const int tid = threadIdx.x, dq = (tid % CQ) + CQ * blockIdx.y, pl = tid / CQ;
-    if (item.q_window && blockIdx.y == 0 && tid < HC_D / 8) item.q_window[(size_t)blockIdx.x * (HC_D / 8) + tid] = item.q[(size_t)blockIdx.x * (HC_D / 8) + tid];
+    const int tid = threadIdx.x, dq = (tid % CQ) + CQ * quarter, pl = tid / CQ;
+    if (item.q_window && quarter == 0 && tid < HC_D / 8) item.q_window[(size_t)head * (HC_D / 8) + tid] = item.q[(size_t)head * (HC_D / 8) + tid];
     const int n = hd.part_count;
     const float2* ml = reinterpret_cast<const float2*>(part_ml);
     const float4* pa = reinterpret_cast<const float4*>(part_acc);
@@ -1032,7 +1033,7 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const float wgt = (s0 + 32 * u < n) ? __builtin_amdgcn_exp2f(mz[u].x - M) : 0.f;
-            z += wgt * mz[u].y;
+            z = fmaf(wgt, mz[u].y, z);
             acc.x += wgt * a[u].x;
             acc.y += wgt * a[u].y;
             acc.z += wgt * a[u].z;
@@ -1050,9 +1051,109 @@ __global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
             a += col[i * 4 * CQ];
             zz += sm_z[i];
         }
-        out[(size_t)blockIdx.x * HC_D + 4 * CQ * blockIdx.y + tid] = a / zz;
-        if (tid == 0 && blockIdx.y == 0) lse[blockIdx.x] = (M + __builtin_amdgcn_logf(zz)) * LN2;
+        out[(size_t)head * HC_D + 4 * CQ * quarter + tid] = a / zz;
+        if (tid == 0 && quarter == 0) lse[head] = (M + __builtin_amdgcn_logf(zz)) * LN2;
     }
+}
+
+template <int G, class Args>
+__global__ __launch_bounds__(COMBINE_BLK) void attn_combine_kernel(Args batch)
+{
+    combine_head<G>(batch.item(), blockIdx.x, blockIdx.y);
+}
+
+// The same with the scores of the pivots' candidates and their histogram, which the side work of an unfiltered layer begins with, made on the
+// way: the first n_reps * wgs workgroups of a layer take `span` chunks of a pivot's range each.  They do not wait for the
+// combine pass's log-sum-exp but make it from the partial results themselves, by the same sums in the same order.
+struct ScoreItem {
+    const RepDev* reps;
+    const float* rep_logits;
+    float* scores;               // or nullptr: none for this layer
+    uint32_t* hist;
+    int n_reps;
+};
+struct CombineScoreBatch {
+    CombineItem it[HC_MAX_GROUP];
+    ScoreItem sc[HC_MAX_GROUP];
+};
+static_assert(COMBINE_BLK == SCORE_BLK, "both halves of the launch");
+template <int G, int HIST>
+__global__ __launch_bounds__(SCORE_BLK) void attn_combine_score_kernel(CombineScoreBatch batch, int n_score, int wgs, int span, int agg, int most, int max_ctx)
+{
+    __shared__ uint32_t sh[HC_RADIX_BINS];
+    __shared__ float sm_zz[G][32], sm_M[G];
+    const CombineItem& item = batch.it[blockIdx.z];
+    if ((int)blockIdx.x >= n_score) {
+        combine_head<G>(item, ((int)blockIdx.x - n_score) / (32 / CQ), ((int)blockIdx.x - n_score) % (32 / CQ));
+        return;
+    }
+    const ScoreItem& sc = batch.sc[blockIdx.z];
+    const int rep = (int)blockIdx.x / wgs;
+    if (!sc.scores || rep >= sc.n_reps) return;
+    RepDev rd = sc.reps[rep];
+    if (HIST != HIST_KEYS) rd.hi = min(rd.hi, rd.lo + most);
+    const int c0 = (int)blockIdx.x % wgs * span, c1 = min(c0 + span, rd.nchunk), tid = threadIdx.x;
+    if (c0 >= rd.nchunk) return;
+    const float* lrow = sc.rep_logits + (size_t)rep * G * max_ctx;
+    float* srow = sc.scores + (size_t)rep * max_ctx;
+    // the first chunk's logits are asked for before the log-sum-exp is known
+    float row[SCORE_PER_THREAD][G], l[G];
+    auto rows = [&](int ch) {
+#pragma unroll
+        for (int i = 0; i < SCORE_PER_THREAD; ++i) load_row<G>(lrow, min(rd.lo + ch * HC_SEL_CHUNK + i * SCORE_BLK + tid, rd.hi - 1), row[i]);
+    };
+    rows(c0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) l[g] = 0.f;
+    for (int i = tid; i < HC_RADIX_BINS; i += SCORE_BLK) sh[i] = 0u;
+    if (agg == HC_AGG_PROB) {                        // (see combine_head)
+        const HeadDev& hd = item.heads[rd.bh];
+        const float2* ml = reinterpret_cast<const float2*>(item.part_ml) + (size_t)hd.part_begin * G;
+        const int n = hd.part_count, g = tid / 32, pl = tid % 32;
+        if (g < G) {
+            constexpr int U = 8;
+            float2 mz[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) mz[u] = ml[(size_t)(pl + 32 * u < n ? pl + 32 * u : 0) * G + g];
+            float M = M_INIT;
+#pragma unroll
+            for (int u = 0; u < U; ++u) M = fmaxf(M, mz[u].x);
+            for (int s = pl + 32 * U; s < n; s += 32) M = fmaxf(M, ml[(size_t)s * G + g].x);
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+            float z = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) z = fmaf(pl + 32 * u < n ? __builtin_amdgcn_exp2f(mz[u].x - M) : 0.f, mz[u].y, z);
+            for (int s = pl + 32 * U; s < n; s += 32) {
+                const float2 t = ml[(size_t)s * G + g];
+                z = fmaf(__builtin_amdgcn_exp2f(t.x - M), t.y, z);
+            }
+            sm_zz[g][pl] = z;
+            if (pl == 0) sm_M[g] = M;
+        }
+        __syncthreads();
+        if (tid < G) {
+            float zz = 0.f;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) zz += sm_zz[tid][i];
+            sm_zz[tid][0] = (sm_M[tid] + __builtin_amdgcn_logf(zz)) * LN2;
+        }
+    }
+    __syncthreads();
+    if (agg == HC_AGG_PROB) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) l[g] = sm_zz[g][0];
+    }
+    for (int ch = c0;;) {
+        float x[SCORE_PER_THREAD];
+#pragma unroll
+        for (int i = 0; i < SCORE_PER_THREAD; ++i) x[i] = hc_group_score<G>(row[i], l, agg);
+        count_scores<HIST>(sh, srow, rd.lo + ch * HC_SEL_CHUNK, rd.hi, x);
+        if (++ch >= c1) break;
+        rows(ch);
+    }
+    __syncthreads();
+    flush_counts(sc.hist + (size_t)rep * HC_HIST_WORDS, sh);
 }
 
 // The pivots' logits over again, every row, into the dense [ctx][G] layout: what the monitor falls back on when
@@ -1179,9 +1280,29 @@ hc_status launch_split(hc_ctx* ctx, const Args& a, int n, int n_blocks, bool fil
 }
 
 template <int G>
-hc_status launch_combine(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
+hc_status launch_combine(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, const ScoreItem* sc, const hc_score_plan* plan, hipStream_t st)
 {
-    if (n == 1) attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(CombineOne{batch.it[0]});
+    bool any = false;
+    int reps = 0;
+    for (int i = 0; i < n; ++i)
+        if (sc && sc[i].scores) {
+            any = true;
+            reps = std::max(reps, sc[i].n_reps);
+        }
+    if (any) {
+        CombineScoreBatch both{};
+        for (int i = 0; i < n; ++i) {
+            both.it[i] = batch.it[i];
+            both.sc[i] = sc[i];
+        }
+        // (a chunk to a workgroup as long as these are no more than two to a compute unit)
+        const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, reps * n * plan->max_nchunk / (2 * ctx->n_cu)));
+        const int wgs = (plan->max_nchunk + span - 1) / span, n_score = reps * wgs;
+        const dim3 grid(n_score + n_heads * G * (32 / CQ), 1, n);
+        if (!plan->direct) attn_combine_score_kernel<G, HIST_KEYS><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
+        else if (ctx->cfg.agg == HC_AGG_LOGIT) attn_combine_score_kernel<G, HIST_LINEAR><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
+        else attn_combine_score_kernel<G, HIST_FINE><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
+    } else if (n == 1) attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(CombineOne{batch.it[0]});
     else attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ, n), dim3(COMBINE_BLK), 0, st>>>(batch);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
@@ -1254,13 +1375,13 @@ static bool split_together(const hc_ctx* ctx, const hc_layer* L)
     return L->total_rows >= 2 * HC_UNIT_ROWS * (int64_t)ctx->n_cu && ctx->timing_next >= ctx->timing.size();
 }
 
-static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st)
+static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st, const ScoreItem* sc = nullptr, const hc_score_plan* plan = nullptr)
 {
     switch (ctx->G) {
-    case 1: return launch_combine<1>(ctx, batch, n, n_heads, st);
-    case 2: return launch_combine<2>(ctx, batch, n, n_heads, st);
-    case 4: return launch_combine<4>(ctx, batch, n, n_heads, st);
-    case 8: return launch_combine<8>(ctx, batch, n, n_heads, st);
+    case 1: return launch_combine<1>(ctx, batch, n, n_heads, sc, plan, st);
+    case 2: return launch_combine<2>(ctx, batch, n, n_heads, sc, plan, st);
+    case 4: return launch_combine<4>(ctx, batch, n, n_heads, sc, plan, st);
+    case 8: return launch_combine<8>(ctx, batch, n, n_heads, sc, plan, st);
     }
     return hc_fail(ctx, HC_ESHAPE, "unsupported group size");
 }
@@ -1276,7 +1397,7 @@ static hc_status launch_any(hc_ctx* ctx, const hc_layer* L, const void* arena, c
     return combine_any(ctx, batch, 1, L->n_heads, st);
 }
 
-hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st)
+hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st, const hc_score_plan* plan)
 {
     if (n < 1 || n > HC_MAX_GROUP) return hc_fail(ctx, HC_EINVAL, "attention batch of %d layers", n);
     // Every layer of the batch leaves its partial results in a copy of the workspace of its own, as far as there are
@@ -1286,6 +1407,7 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
         if ((size_t)calls[i].L->n_partials > ctx->part_slots) return hc_fail(ctx, HC_ESTATE, "split-K workspace smaller than the plan");
     const size_t acc_floats = ctx->part_slots * ctx->G * HC_D, ml_floats = ctx->part_slots * ctx->G * 2;
     CombineBatch batch{};
+    ScoreItem sc[HC_MAX_GROUP];
     SplitGroup group;
     int m = 0, gathered = 0, blocks = 0, n_heads = 0;     // layers of the batch: split and gathered, of these gathered for one launch
     bool filtered = false;
@@ -1299,7 +1421,7 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
     };
     auto flush = [&]() -> hc_status {
         const hc_status a = split();
-        const hc_status b = m > 0 ? combine_any(ctx, batch, m, n_heads, st) : HC_OK;
+        const hc_status b = m > 0 ? combine_any(ctx, batch, m, n_heads, st, sc, plan) : HC_OK;
         m = 0;
         return a != HC_OK ? a : b;
     };
@@ -1324,6 +1446,7 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
         }
         float* acc = m == 0 ? ctx->part_acc : ctx->part_more + (m - 1) * acc_floats;
         float* ml = m == 0 ? ctx->part_ml : ctx->part_more + (ctx->part_copies - 1) * acc_floats + (m - 1) * ml_floats;
+        sc[m] = ScoreItem{x.L->reps, x.rep_logits, x.scores, x.L->score_hist, x.L->n_reps};
         batch.it[m++] = CombineItem{x.L->heads, acc, ml, x.out, x.lse, (const uint4*)x.q, (uint4*)x.q_window};
         group.it[gathered++] = split_item(x, acc, ml);
         blocks = std::max(blocks, x.L->n_blocks);

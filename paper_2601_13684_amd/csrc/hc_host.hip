@@ -311,6 +311,7 @@ static void layer_free(hc_layer* L)
     (void)hipFree(L->need);
     (void)hipFree(L->q_keep);
     (void)hipFree(L->mon_counts);
+    (void)hipFree(L->score_hist);
     if (L->ev_attn) (void)hipEventDestroy(L->ev_attn);
     if (L->ev_side) (void)hipEventDestroy(L->ev_side);
     for (int i = 0; i < 2; ++i) {
@@ -767,6 +768,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
         L->n_sel = (int)sel.size();
         if (st == HC_OK) st = upload(ctx, sel, &L->sel_reps);
         if (st == HC_OK) st = upload(ctx, outs, &L->sel_outs);
+        if (st == HC_OK) st = upload(ctx, std::vector<uint32_t>((size_t)L->n_reps * HC_HIST_WORDS, 0u), &L->score_hist);
         if (st == HC_OK) st = upload(ctx, std::vector<PreSrc>(), &L->pre_src, (size_t)L->n_heads);
         if (st == HC_OK) st = upload(ctx, P.rep_slot_of, &L->rep_slot_dev);
     }
@@ -1393,6 +1395,8 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         // (groups of eight heads: the split pass takes 52 KB of LDS per workgroup, two do not fit beside the reservation)
         ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
+        for (int i = 0; i < w.n_mon && st == HC_OK; ++i)
+            if (w.mon[i].scored) const_cast<hc_layer*>(w.mon[i].L)->hist_dirty = false;
         if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, false, run);
         ctx->side_pad_now = ctx->beside_now = false;
         if (ss) {
@@ -1404,6 +1408,12 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         w.n_mon = 0;
         return st;
     };
+    bool own_scores = true;                     // no two layers share (a part of) a buffer of scores
+    for (int l = 0; l < n_layers && own_scores; ++l)
+        for (int m = 0; m < l && own_scores; ++m) {
+            const float *a = io[l].scores, *b = io[m].scores;
+            own_scores = !a || !b || a + (size_t)io[l].layer->n_reps * ctx->cfg.max_ctx <= b || b + (size_t)io[m].layer->n_reps * ctx->cfg.max_ctx <= a;
+        }
     hipEvent_t last_waited = nullptr;
     int cur = 0;
     hc_status result = HC_OK;
@@ -1457,10 +1467,28 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
             }
             att[l - g0] = hc_attn_call{L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr, q_window};
         }
+        // Unfiltered layers of a middle length: their scores are made with the combine pass, a launch less for their side work, which
+        // such steps wait for.  (Not into a buffer that another layer uses as well.)
+        hc_score_plan plan;
+        ctx->beside_now = ss != nullptr;
+        ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
+        const bool scored = result == HC_OK && w.n_mon > 0 && own_scores && hc_monitor_reads_scores(ctx, w.n_mon, w.mon, &plan);
+        ctx->side_pad_now = ctx->beside_now = false;
+        bool clear = scored;
+        for (int i = 0; i < w.n_mon; ++i) clear = clear && !w.mon[i].L->hist_dirty;
+        if (clear)
+            for (int i = 0, l = g0; l < g1; ++l) {
+                if (i == w.n_mon || io[l].layer != w.mon[i].L) continue;
+                hc_monitor_call& m = w.mon[i++];
+                if (hc_layer_filtered(ctx, m.L)) continue;
+                m.scored = true;
+                att[l - g0].scores = m.scores;
+                const_cast<hc_layer*>(m.L)->hist_dirty = true;            // until its selection has been launched
+            }
         // The queries go into the window buffers on the main stream, with the combine pass: the caller may overwrite q as
         // soon as this call returns, in main-stream order, while the side stream may still be behind.  A layer's
         // count of steps inside its window moves on once its query is in the buffer.
-        if (result == HC_OK) result = hc_launch_attn(ctx, g1 - g0, att, ms);
+        if (result == HC_OK) result = hc_launch_attn(ctx, g1 - g0, att, ms, &plan);
         if (result == HC_OK)
             for (int i = 0; i < n_push; ++i) push_layer[i]->window_slot = (push_layer[i]->window_slot + 1) % ctx->cfg.window;
         if (result != HC_OK) w.n_mon = 0;              // this group's side work is dropped; the previous group's still goes out

@@ -185,6 +185,8 @@ struct hc_layer {
     int32_t* need = nullptr;       // [n_reps] != 0: the check of this step's filter failed, the dense passes take over
     uint16_t* q_keep = nullptr;    // [n_reps][G][D] the pivots' queries of the last attention call
     uint32_t* mon_counts = nullptr;// [n_reps][4] tests, triggers, steps decided by the dense fallback, rows kept at the last step
+    uint32_t* score_hist = nullptr;// [n_reps][HC_HIST_WORDS] histograms of scores made with the combine pass; clear between steps
+    bool hist_dirty = false;       // not known to be clear (a step that failed midway)
     const void* last_arena = nullptr;   // the arena of the last attention call with pivot logits (the fallback reads K from it)
     bool filter_armed = false;     // a monitor call has set the filter: the selection passes are launched for few rows
     hipEvent_t ev_attn = nullptr;  // hc_decode_step: this layer's attention has been enqueued / its side work is done
@@ -256,7 +258,14 @@ struct hc_monitor_call {
     int n_reps = 0, max_nchunk = 0, max_cand = 0, max_nk = 0;
     const void* arena = nullptr;   // the layer's K/V arena, for a layer that filters its pivot logits (nullptr: the one
                                    // its last attention call was given)
+    bool scored = false;           // the combine pass has made the scores, and their histogram in L->score_hist
 };
+// What the combine pass needs to make scores: candidates that are gone through, and chunks of the longest range.
+struct hc_score_plan {
+    int most, max_nchunk;
+    bool direct;                   // for mon_direct (else the histogram is over the keys, and all candidates are gone through)
+};
+bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* calls, hc_score_plan* plan);
 struct hc_gather_call {
     const hc_layer* L;
     const void* tier;
@@ -273,8 +282,9 @@ struct hc_attn_call {
     float* lse;
     float* rep_logits;     // or nullptr
     void* q_window = nullptr;   // where the combine pass leaves a copy of q (16-byte aligned), or nullptr
+    float* scores = nullptr;    // where it leaves the candidates' scores (their histogram in L->score_hist), or nullptr
 };
-hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st);
+hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStream_t st, const hc_score_plan* plan = nullptr);     // plan: if any call has scores
 hc_status hc_launch_attn_static(hc_ctx* ctx, const hc_layer* L, const void* arena, const void* q, float* out,
                                 float* lse, float* rep_logits, hipStream_t st);
 hc_status hc_attn_static_scratch(hc_ctx* ctx, float** base);     // at context creation, with the context's device current

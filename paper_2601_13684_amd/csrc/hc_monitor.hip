@@ -45,11 +45,11 @@
 #include <cmath>
 
 #include "hc_internal.h"
+#include "hc_score.h"
 
 namespace {
 
-constexpr int BLK = 256;
-constexpr int PER_THREAD = HC_SEL_CHUNK / BLK;   // candidates of a chunk per thread
+constexpr int BLK = SCORE_BLK;
 constexpr int NWAVE = BLK / 64;
 
 __device__ __forceinline__ float key_score(uint32_t key)      // inverse of hc_score_key
@@ -259,59 +259,6 @@ __global__ __launch_bounds__(256) void mon_prep(Ws ws)
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < (size_t)ws.max_ctx / 32; i += stride) w.bitmap[i] = 0u;
 }
 
-// Score of candidate j from the G scaled logits of its row (rep_logits is [ctx][G] per pivot).
-template <int G>
-__device__ __forceinline__ void load_row(const float* __restrict__ lrow, int j, float (&l)[G])
-{
-    if (G == 1) {
-        l[0] = lrow[j];
-    } else if (G == 2) {
-        const float2 v = reinterpret_cast<const float2*>(lrow)[j];
-        l[0] = v.x; l[1] = v.y;
-    } else {
-#pragma unroll
-        for (int q = 0; q < G / 4; ++q) {
-            const float4 v = reinterpret_cast<const float4*>(lrow)[(size_t)j * (G / 4) + q];
-            l[4 * q] = v.x; l[4 * q + 1] = v.y; l[4 * q + 2] = v.z; l[4 * q + 3] = v.w;
-        }
-    }
-}
-template <int G>
-__device__ __forceinline__ float score_of(const float* __restrict__ lrow, int j, const float (&lse)[G], int agg)
-{
-    float l[G];
-    load_row<G>(lrow, j, l);
-    return hc_group_score<G>(l, lse, agg);
-}
-
-// ---- the histogram of a candidate range ----
-//
-// 2048 digits, narrow ones for where a list usually ends, wide ones on either side.  Probabilities (HC_AGG_PROB): 64 to an octave
-// over [2^-23, 2^-7), each 1.1 to 1.6 % of a score wide, 16 over [2^-79, 2^-23) and [2^-7, 2); the lowest takes everything below (negative
-// scores and what is no number among them), the highest everything above.  The digit in which a list ends then holds a
-// hundred or so of 32K candidates (of the key's first 11 bits, four to an octave, thousands), unless scores are that close to
-// each other; where sharp attention makes scores small they are far apart.  Mean logits (HC_AGG_LOGIT): digits of 1/64 over
-// [-12, 12), of 1/8 from -44 to 44.
-template <int MID, int LOW, int SHIFT>
-struct Digits {                                      // x: number of a narrow digit, 0 .. MID - 1 the narrow ones
-    static __device__ __forceinline__ uint32_t of(int x)
-    {
-        const int y = min(max(x, x >> SHIFT), (x + ((1 << SHIFT) - 1) * MID) >> SHIFT);      // (below 0 and above MID the flatter line)
-        return (uint32_t)min(max(y + LOW, 0), HC_RADIX_BINS - 1);
-    }
-    static __device__ __forceinline__ int first(int digit) { return digit < LOW ? (digit - LOW) << SHIFT : digit < LOW + MID ? digit - LOW : MID + ((digit - LOW - MID) << SHIFT); }
-};
-typedef Digits<1024, 896, 2> FineDigits;
-typedef Digits<1536, 256, 3> LinearDigits;
-constexpr int FINE_BASE = (0x80000000u >> 17) + (104 << 6);     // the key of 2^-23, without its last 17 bits
-// FineDigits::of the score's key, in a third of the instructions: negative scores and what is no number end in the lowest digit, as 0
-// does, and the piecewise line is the middle one of three.
-__device__ __forceinline__ uint32_t fine_digit(float s)
-{
-    const int x = (int)(__float_as_uint(fmaxf(s, 0.f)) >> 17) + (0x4000 - FINE_BASE + 896), y = (x >> 2) + (896 - 896 / 4);
-    return (uint32_t)min(max(min(max(x, y), y + (1024 - 1024 / 4)), 0), HC_RADIX_BINS - 1);
-}
-__device__ __forceinline__ uint32_t linear_digit(float s) { return LinearDigits::of((int)fminf(fmaxf(floorf(s * 64.f), -4096.f), 4096.f) + 768); }
 __device__ __forceinline__ uint32_t digit_low(uint32_t digit, bool linear)                // smallest key of a digit ...
 {
     if (digit == 0u) return 0u;
@@ -403,7 +350,6 @@ __device__ __forceinline__ void sample_threshold(uint32_t* sm_hist, uint32_t* sm
 // Scores and histogram of a long candidate range (over the first 11 bits of the keys, or the digits that mon_direct reads).  A workgroup takes `span` consecutive chunks of
 // HC_SEL_CHUNK candidates: the histogram in LDS is cleared and flushed once for all of them.
 // most: as many candidates as mon_direct will go through (a captured call may find more than when it was launched).
-enum { HIST_KEYS = 0, HIST_FINE = 1, HIST_LINEAR = 2 };
 template <int G, int HIST>
 __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_given, int agg, int span, int long_lists, int max_k, int most)
 {
@@ -435,26 +381,17 @@ __global__ __launch_bounds__(BLK) void mon_score_hist(MonBatch B, int scores_giv
     __syncthreads();
     for (int ch = c0; ch < c1; ++ch) {
         const int first = rd.lo + ch * HC_SEL_CHUNK;
-        float s[PER_THREAD];
+        float x[SCORE_PER_THREAD];
 #pragma unroll
-        for (int i = 0; i < PER_THREAD; ++i) {       // candidate first + i*BLK + t: coalesced, loads independent
+        for (int i = 0; i < SCORE_PER_THREAD; ++i) {       // candidate first + i*BLK + t: coalesced, loads independent
             const int j = first + i * BLK + threadIdx.x;
-            s[i] = 0.f;
-            if (j < rd.hi) s[i] = scores_given ? srow[j] : score_of<G>(lrow, j, l, agg);
+            x[i] = 0.f;
+            if (j < rd.hi) x[i] = scores_given ? srow[j] : score_of<G>(lrow, j, l, agg);
         }
-#pragma unroll
-        for (int i = 0; i < PER_THREAD; ++i) {
-            const int j = first + i * BLK + threadIdx.x;
-            if (j < rd.hi) {
-                if (!scores_given) srow[j] = s[i];
-                atomicAdd(&sh[HIST == HIST_LINEAR ? linear_digit(s[i]) : HIST == HIST_FINE ? fine_digit(s[i]) : hc_score_key(s[i]) >> 21], 1u);
-            }
-        }
+        count_scores<HIST>(sh, scores_given ? nullptr : srow, first, rd.hi, x);
     }
     __syncthreads();
-    uint32_t* h1 = it.ws.rep(rep).hist;
-    for (int i = threadIdx.x; i < HC_RADIX_BINS; i += BLK)
-        if (sh[i]) atomicAdd(&h1[i], sh[i]);
+    flush_counts(it.ws.rep(rep).hist, sh);
 }
 
 // The survivors are kept as one bit per candidate: nothing to reserve, little to write, few bits for mon_select to read.  A wave
@@ -2366,12 +2303,14 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
             HC_HIP(ctx, hipGetLastError());
         }
         m.dirty = true;
+        if (x.scored) it.ws.hist = x.L->score_hist;      // (not what is cleared above)
     }
     if (max_reps == 0) return HC_OK;
     const DriftCfg dc{c.window, c.metric, c.tau_num, c.tau_den, c.max_k, c.window_mode != HC_WINDOW_SLIDING, c.agg};
     const dim3 gsel(max_reps, max_nk, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
+    const bool scored = mode == 0 && calls[0]->scored;       // (by all of the batch, or none)
     // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
     // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
     const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
@@ -2397,6 +2336,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         }
         HC_HIP(ctx, hipGetLastError());
     }
+    if (scored && direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, candidates, bm_words, st);
     if (mode != 0) scores_given = 1;                     // they are there from here on
     if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, form, B, dc, gsel, candidates, bm_words, st);
     // (a tile to a wave; given scores are read from a multiple of four positions on)
@@ -2410,7 +2350,8 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     int survivors, most;
     expected_survivors(max_k, candidates, &survivors, &most);
     const bool long_lists = !direct && (survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap);
-    if (mode != 2 || long_lists) {
+    if (scored && long_lists) return hc_fail(ctx, HC_ESTATE, "internal: scores and histogram for a selection that reads neither");
+    if (!scored && (mode != 2 || long_lists)) {
         // Chunks per workgroup, at most 8: about 2048 workgroups per launch (a call over eight sequences of 9K to 131K takes
         // 36 us with one chunk each, 37, 41, 50 with two, four, eight; one of 32K 28, 29, 32, 39), beside the attention pass
         // 512.  (The launches that stand by: few, long workgroups.)
@@ -2450,6 +2391,41 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B, limit);
     HC_HIP(ctx, hipGetLastError());
     return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, std::max(most, limit), bm_words, small, st);
+}
+
+// Whether the combine pass of a group's attention makes the scores and histograms of its unfiltered layers (with the context set as for the
+// monitor call that follows: the same choice of what selects).  Up to 64 K candidates a step waits for its side chain (two
+// groups of two 32K layers: the main stream by itself 49 us a step, the chains 85), which then begins with the selection: a launch and
+// its reads less.  us per step, mon_score_hist on the side stream / with the combine pass: four layers 16K 85 / 79, 32K 99 / 85, 48K 106 / 98, 60,000 110-152 /
+// 99-142, one of 10,000 33.2 / 28.5, of 32K 41.4 / 36.8; twelve sequences of 9,000 to 31,000, two layers 155 / 136.  Where mon_compact and mon_select take
+// the lists (more than 20 of them) as long as the group's attention is short, here up to 1600 rows to a compute unit (36 us of
+// reading): eight layers of 36,000 in groups of four 141 / 129, four sequences, a layer to a group 115 / 105; of 60,000, two and a half times the
+// rows, 150 / 155.  Longer contexts wait for the attention.
+bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* calls, hc_score_plan* plan)
+{
+    int m = 0, reps = 0, nk = 1, k = 1, nchunk = 0, candidates = 0;
+    int64_t rows = 0;
+    for (int i = 0; i < n; ++i) {
+        const hc_layer* L = calls[i].L;
+        rows += L->total_rows;
+        if (hc_layer_filtered(ctx, L)) continue;
+        ++m;
+        reps = std::max(reps, L->n_reps);
+        nk = std::max(nk, L->max_nk);
+        k = std::max(k, L->max_k_any);
+        nchunk = std::max(nchunk, L->max_nchunk);
+        candidates = std::max(candidates, L->max_cand);
+    }
+    const DirectForm form = direct_form(ctx, 0, candidates, reps * m * nk);
+    if (candidates <= SELECT_DIRECT || candidates + 3 > 1024 / 64 * DIRECT_TILES * HC_SEL_CHUNK) return false;
+    const bool direct = direct_fits(form, candidates, nchunk * (HC_SEL_CHUNK / 32)) && !direct_outlasted(ctx, candidates, k, nk);
+    if (!direct) {
+        int survivors, most;
+        expected_survivors(k, candidates, &survivors, &most);
+        if (survivors > SELECT_SURVIVORS || most > ctx->sv_cap || rows > 1600 * (int64_t)ctx->n_cu) return false;
+    }
+    *plan = hc_score_plan{direct_most(form, DIRECT_HIST, candidates), nchunk, direct};
+    return true;
 }
 
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st)

@@ -1,0 +1,117 @@
+"""hc_decode_step makes the scores of unfiltered layers of a middle length with the combine pass: the same bits as by hc_decode_attn,
+hc_rep_topk_drift and hc_gather_retrieve one after the other.  Run with `-m gpu` on an MI355X."""
+import pytest
+import torch
+
+from paper_2601_13684_amd import binding as hc
+from paper_2601_13684_amd import inputs as I
+from paper_2601_13684_amd import runtime as R
+
+pytestmark = pytest.mark.gpu
+DEV, D = "cuda:0", 128
+
+
+def make(G, ctxs, n_full, lists, agg, window=1, window_mode=0, layers=2, seed=0):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(sum(ctxs) + G + seed)
+    hkv, made = n_full + len(lists), []
+    for _ in range(layers):
+        heads = [[I.HeadSpec(I.ROLE_FULL) for _ in range(n_full)] +
+                 [I.HeadSpec(I.ROLE_SATELLITE, rep=j % n_full, sink=3, recent=6, budget=9 + r) for j, r in enumerate(lists)] for _ in ctxs]
+        spec = I.LayerSpec(B=len(ctxs), Hq=G * hkv, Hkv=hkv, D=D, ctx=list(ctxs), heads=heads, window=window, window_mode=window_mode, agg=agg)
+        data, retrieved, base = I.LayerData(), {}, {}
+        for b, n in enumerate(ctxs):
+            for h in range(hkv):
+                data.K[(b, h)], data.V[(b, h)] = (torch.randn((n, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+            for j, r in enumerate(lists):
+                retrieved[(b, n_full + j)] = torch.randperm(n - 9, generator=g, device=DEV)[:r].sort().values.int() + 3
+            for p in range(n_full):
+                k = spec.k_mon(b, p)
+                base[(b, p)] = torch.randperm(n - 9, generator=g, device=DEV)[:k].sort().values.int() + 3
+        made.append((spec, data, retrieved, base))
+    qs = [torch.randn((layers, len(ctxs), G * hkv, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(3)]
+    return made, qs
+
+
+def run(made, qs, how, group=1, side=None, **kw):
+    ctx = R.Context(R.make_config(made[0][0]), DEV, **kw)
+    layers = [R.LayerRuntime(ctx, *m, own_scratch=True) for m in made]
+    seen = []
+    for q in qs:
+        if how == "step":
+            hc.hc_decode_step(ctx.handle, R.make_step_io(layers, q), len(layers), None, side, group)
+        else:
+            for x, one in zip(layers, q):
+                x.attn(one)
+            for x in layers:
+                x.monitor()
+                x.gather()
+        torch.cuda.synchronize()
+        for x in layers:
+            seen += [t.clone() for t in (x.out, x.lse, x.topk_idx, x.base_idx, x.ring, x.inter, x.flag, x.slot_pos, x.arena)]
+            for b in range(x.spec.B):
+                for p in x.spec.reps(b):
+                    lo, hi = x.spec.cand_range(b, p)
+                    seen.append(x.scores[x.rep_slot(b, p), lo:hi].clone())
+    for x in layers:
+        x.close()
+    ctx.close()
+    return seen
+
+
+def same(a, b):
+    assert len(a) == len(b)
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), i
+
+
+# 9 positions are no candidates.  8,193 candidates, the first range with a histogram; one full head with hundreds of partial results; 65,533 alone; a batch
+# with a short sequence; mean logits; lists that one launch does not write at a time
+@pytest.mark.parametrize("G,ctxs,n_full,lists,agg", [(4, (8202,), 2, (300, 64), I.AGG_PROB), (4, (16384,), 1, (512,), I.AGG_PROB), (1, (40000,), 1, (700,), I.AGG_PROB),
+                                                     (2, (33001, 700, 9001), 2, (300, 64), I.AGG_PROB), (8, (30003,), 2, (2000, 64), I.AGG_PROB), (4, (65542,), 1, (1000, 64), I.AGG_PROB),
+                                                     (4, (20001,), 2, (300, 64), I.AGG_LOGIT), (8, (12001, 9000), 1, (300,), I.AGG_LOGIT), (4, (32777,), 1, (16500,), I.AGG_PROB)])
+def test_a_step_like_the_three_calls(G, ctxs, n_full, lists, agg):
+    print("scores with the combine pass", G, ctxs, lists, agg, flush=True)
+    made, qs = make(G, ctxs, n_full, lists, agg)
+    want = run(made, qs, "calls")
+    same(run(made, qs, "step"), want)
+    same(run(made, qs, "step", group=2), want)
+    same(run(made, qs, "step", side=torch.cuda.Stream()), want)
+
+
+def test_more_lists_than_one_launch_takes():
+    """Beside the attention pass, eight pivots of three lists each and a range that needs the large form: by survivors."""
+    made, qs = make(4, (36000,) + (9000,) * 7, 1, (300, 64, 33), I.AGG_PROB)
+    same(run(made, qs, "step", side=torch.cuda.Stream()), run(made, qs, "calls"))
+
+
+def test_layers_of_a_group_that_filter_and_that_do_not():
+    """The filter is on for contexts from 30,000 candidates: one layer's scores come with the combine pass, the other's from the kept rows."""
+    short, qs = make(4, (20001,), 1, (300,), I.AGG_PROB, layers=1)
+    long, _ = make(4, (40001,), 1, (300,), I.AGG_PROB, layers=1)
+    both = [long[0], short[0]]
+    qs = [torch.cat([q, q.flip(-1)]) for q in qs]
+    kw = dict(filter_margin=1.25, filter_min_candidates=30000)
+    a, b = run(both, qs, "step", group=2, **kw), run(both, qs, "calls", **kw)
+    n = len(a) // (2 * len(qs))
+    for i, (x, y) in enumerate(zip(a, b)):
+        if i % n < 9 or (i // n) % 2:                # (a filtered layer's scores are of rows, not of positions)
+            assert torch.equal(x, y), i
+
+
+def test_layers_that_share_a_buffer_of_scores():
+    """On one stream, logits their own: their scores are made behind the other's selection, as ever."""
+    made, qs = make(4, (20001,), 1, (300,), I.AGG_PROB)
+    want = run(made, qs, "calls")
+    ctx = R.Context(R.make_config(made[0][0]), DEV)
+    layers = [R.LayerRuntime(ctx, *m, own_scratch=True) for m in made]
+    layers[1].scores = layers[0].scores
+    for q in qs:
+        hc.hc_decode_step(ctx.handle, R.make_step_io(layers, q), 2, None, None, 1)
+    torch.cuda.synchronize()
+    per = len(want) // len(qs) // 2
+    for l, x in enumerate(layers):
+        for i, t in enumerate((x.out, x.lse, x.topk_idx, x.base_idx, x.ring, x.inter, x.flag, x.slot_pos, x.arena)):
+            assert torch.equal(t, want[-2 * per + l * per + i]), (l, i)
+        x.close()
+    ctx.close()

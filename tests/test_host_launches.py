@@ -222,3 +222,40 @@ def test_what_selects_among_long_ranges_beside_the_attention_pass(fake, N, n, ke
         names = [l[0] for l in log() if "mon_" in l[0]]
         assert sum("{kernel}" in n for n in names) == 2, names
     """)
+
+
+@pytest.mark.parametrize("N,kernel,scored", [(8204, "mon_directILi1024ELi3E", False), (8205, "mon_directILi1024ELi0E", True),
+                                             (65545, "mon_directILi1024ELi0E", True), (65546, "mon_selectILi1024ELi2E", False)])
+def test_which_steps_score_with_the_combine_pass(fake, N, kernel, scored):
+    """Ranges that mon_direct takes from a histogram: no launch of mon_score_hist, and none where it makes the scores itself or takes more."""
+    run(fake, f"""
+        ctx = context({N}, 300)
+        layers = [layer(ctx, {N}, 300) for _ in range(2)]
+        for t in range(2):
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), 2, 2, None, None) == 0
+            names = [l[0] for l in log()]
+            assert sum("attn_combine_score" in n for n in names) == {int(scored)} and sum("attn_combine" in n for n in names) == 1, names
+            assert sum("{kernel}" in n for n in names) == 1, names
+            assert sum("mon_score_hist" in n for n in names) == {int(not scored and "select" in kernel)}, names
+    """)
+
+
+def test_a_step_that_failed_does_not_count_scores_twice(fake):
+    """The selection's launch fails: the layers' histograms are not known to be clear, so the steps that follow do without them."""
+    run(fake, """
+        ctx = context(20000, 300)
+        layers = [layer(ctx, 20000, 300) for _ in range(2)]
+        def names():
+            return [l[0] for l in log()]
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io_of(layers), 2, 2, None, None) == 0
+        first = names()
+        at = [i for i, n in enumerate(first) if "mon_direct" in n][0]
+        assert any("attn_combine_score" in n for n in first[:at])
+        fake.fake_reset(at + 1 - sum("mon_prep" in n for n in first))
+        assert L.hc_decode_step(ctx, io_of(layers), 2, 2, None, None) == hc.HC_EHIP and any("attn_combine_score" in n for n in names()) and not any("mon_direct" in n for n in names())
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io_of(layers), 2, 2, None, None) == 0
+        assert not any("attn_combine_score" in n for n in names()) and any("mon_score_hist" in n for n in names()), names()
+    """)
