@@ -978,6 +978,10 @@ struct CombineBatch {
     CombineItem it[HC_MAX_GROUP];
     __device__ __forceinline__ const CombineItem& item() const { return it[blockIdx.z]; }
 };
+// The 32 partial lanes' sums are added in fours of eight, these as a tree: an addend is rounded 10 times at most instead of 31.  Mean error against
+// 64 bits over 12 inputs, in a row / this way: a layer of 4K 1.64e-7 / 1.55e-7 (1.60e-7 in a row with a quarter of the workgroups), 32K 1.77e-7 / 1.74e-7.
+__device__ __forceinline__ float sum4(const float (&x)[4]) { return (x[0] + x[1]) + (x[2] + x[3]); }
+
 // Workgroup (head, quarter): quarter of the columns of query head `head` of all.
 template <int G>
 __device__ __forceinline__ void combine_head(const CombineItem& item, int head, int quarter)
@@ -1045,13 +1049,18 @@ __device__ __forceinline__ void combine_head(const CombineItem& item, int head, 
     __syncthreads();
     if (tid < 4 * CQ) {     // column tid of this workgroup's 4 CQ: quad tid / 4, component tid % 4
         const float* col = reinterpret_cast<const float*>(&sm_acc[0][0]) + tid;
-        float a = 0.f, zz = 0.f;
+        float as[4], zs[4];
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            a += col[i * 4 * CQ];
-            zz += sm_z[i];
+        for (int q = 0; q < 4; ++q) {
+            as[q] = zs[q] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                as[q] += col[(8 * q + i) * 4 * CQ];
+                zs[q] += sm_z[8 * q + i];
+            }
         }
-        out[(size_t)head * HC_D + 4 * CQ * quarter + tid] = a / zz;
+        const float zz = sum4(zs);
+        out[(size_t)head * HC_D + 4 * CQ * quarter + tid] = sum4(as) / zz;
         if (tid == 0 && quarter == 0) lse[head] = (M + __builtin_amdgcn_logf(zz)) * LN2;
     }
 }
@@ -1133,10 +1142,14 @@ __global__ __launch_bounds__(SCORE_BLK) void attn_combine_score_kernel(CombineSc
         }
         __syncthreads();
         if (tid < G) {
-            float zz = 0.f;
+            float q[4];
 #pragma unroll
-            for (int i = 0; i < 32; ++i) zz += sm_zz[tid][i];
-            sm_zz[tid][0] = (sm_M[tid] + __builtin_amdgcn_logf(zz)) * LN2;
+            for (int u = 0; u < 4; ++u) {
+                q[u] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[u] += sm_zz[tid][8 * u + i];
+            }
+            sm_zz[tid][0] = (sm_M[tid] + __builtin_amdgcn_logf(sum4(q))) * LN2;
         }
     }
     __syncthreads();
