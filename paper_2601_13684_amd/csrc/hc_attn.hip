@@ -1383,9 +1383,17 @@ static bool split_filtered(const hc_ctx* ctx, const hc_attn_call& x) { return x.
 // a compute unit.
 // (Shorter passes would gain as well, but keep a launch of their own: one that fails leaves the layers before it combined, layer by
 // layer.  Of a shared launch that fails, none of its layers is.  A caller that times the passes has a launch for each layer.)
-static bool split_together(const hc_ctx* ctx, const hc_layer* L)
+// Layers that leave all of their pivots' logits, for the side stream to read beside the next group's attention, share one up to 1400 rows to a
+// compute unit only, and two of them by themselves up to 64 K candidates.  Beyond, the side chains, which find room as a launch ends, are what such
+// steps wait for.  us per step, a launch each / shared: two layers to a group 32K 95 / 86, 64K 131 / 123, 95K 181 / 178, 100K 217 / 225, 125K 207 / 206; four and
+// more 90K 445 / 393, 100K 248 / 249, 131K 340 / 315, 160K 384 / 367, 200K 405 / 453, 224K 450 / 505; six sequences of 12,000 to 81,000 320 / 329.  With the filter little is left to the side
+// stream (four of 224K 214 / 208), but in groups of eight heads, whose attention leaves no room beside it: 131K 171 / 187, 224K 561 / 590, eight 781 / 803.
+static bool split_together(const hc_ctx* ctx, const hc_attn_call& x, int n)
 {
-    return L->total_rows >= 2 * HC_UNIT_ROWS * (int64_t)ctx->n_cu && ctx->timing_next >= ctx->timing.size();
+    const int64_t rows = x.L->total_rows, n_cu = ctx->n_cu;
+    if (rows < 2 * HC_UNIT_ROWS * n_cu || ctx->timing_next < ctx->timing.size()) return false;
+    if (x.rep_logits == nullptr) return true;
+    return split_filtered(ctx, x) ? ctx->G < 8 : rows <= 1400 * n_cu && (n > 2 || x.L->max_cand <= 65536);
 }
 
 static hc_status combine_any(hc_ctx* ctx, const CombineBatch& batch, int n, int n_heads, hipStream_t st, const ScoreItem* sc = nullptr, const hc_score_plan* plan = nullptr)
@@ -1449,7 +1457,7 @@ hc_status hc_launch_attn(hc_ctx* ctx, int n, const hc_attn_call* calls, hipStrea
             const hc_status s = flush();
             if (s != HC_OK) return s;
         }
-        const bool together = split_together(ctx, x.L);
+        const bool together = split_together(ctx, x, n);
         if (gathered > 0 && (!together || filtered != split_filtered(ctx, x))) {
             const hc_status s = split();
             if (s != HC_OK) {
