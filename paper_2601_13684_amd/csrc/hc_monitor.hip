@@ -32,7 +32,7 @@
 //
 // Measured on MI355X against a radix select in six launches over all candidates (score and histogram, two more
 // histograms, counts, ordered write, decision): one 32K layer 19.8 instead of 51.5 us per call, eight sequences of 9K to
-// 131K 33-36 instead of 81 us, the decode step of one 4K layer 25.7 instead of 49 us.
+// 131K 33-36 instead of 81 us, the decode step of one 4K layer 23.3 instead of 49 us.
 //
 // Beside the attention pass (hc_decode_step's side stream) a workgroup has to find room on a compute unit that holds
 // two attention workgroups, whose registers (at most 216 a lane) leave 80 per lane of a SIMD: 256 threads of at most 80
