@@ -451,8 +451,9 @@ hc_status hc_layer_set_window_slot(hc_layer* layer, int32_t slot);
  * a refill decided at step t is used from step t+1.  Launching from native code keeps the host ahead
  * of the GPU.  All buffers are the caller's, as in the three calls; scores == NULL (or a layer without
  * pivots) skips monitor and gather for that layer; host_tier == NULL skips the gather.  Layers whose
- * monitors overlap other layers' attention need their own rep_logits, scores, lse, out.  rep_logits, lse, out and, for
- * layers without the filter, scores are written in main_stream order.  The context
+ * monitors overlap other layers' attention need their own rep_logits, scores, lse, out.  out and lse are written in main_stream
+ * order, and so are rep_logits but for pivots whose filter check fails, which the side work makes again; scores, the index tables, ring,
+ * inter, flag and slot_pos are written in side_stream order (main_stream order where everything is handled there).  The context
  * holds one selection workspace per position in a group; hc_rep_topk_drift uses the first, so a direct
  * call must be stream-ordered with this call's side work.  Every layer's arguments are checked before the first
  * launch, so a refused call leaves every layer as it was.  Enqueue-only; not meant for graph capture

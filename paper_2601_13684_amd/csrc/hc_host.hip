@@ -312,6 +312,7 @@ static void layer_free(hc_layer* L)
     (void)hipFree(L->q_keep);
     (void)hipFree(L->mon_counts);
     (void)hipFree(L->score_hist);
+    (void)hipFree(L->score_buf);
     if (L->ev_attn) (void)hipEventDestroy(L->ev_attn);
     if (L->ev_side) (void)hipEventDestroy(L->ev_side);
     for (int i = 0; i < 2; ++i) {
@@ -769,6 +770,7 @@ extern "C" hc_status hc_layer_create(hc_ctx* ctx, const hc_head_desc* hd, hc_lay
         if (st == HC_OK) st = upload(ctx, sel, &L->sel_reps);
         if (st == HC_OK) st = upload(ctx, outs, &L->sel_outs);
         if (st == HC_OK) st = upload(ctx, std::vector<uint32_t>((size_t)L->n_reps * HC_HIST_WORDS, 0u), &L->score_hist);
+        if (st == HC_OK && P.max_cand <= HC_SCORED_MOST) st = upload(ctx, std::vector<float>(), &L->score_buf, (size_t)L->n_reps * ctx->cfg.max_ctx);
         if (st == HC_OK) st = upload(ctx, std::vector<PreSrc>(), &L->pre_src, (size_t)L->n_heads);
         if (st == HC_OK) st = upload(ctx, P.rep_slot_of, &L->rep_slot_dev);
     }
@@ -1408,12 +1410,6 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         w.n_mon = 0;
         return st;
     };
-    bool own_scores = true;                     // no two layers share (a part of) a buffer of scores
-    for (int l = 0; l < n_layers && own_scores; ++l)
-        for (int m = 0; m < l && own_scores; ++m) {
-            const float *a = io[l].scores, *b = io[m].scores;
-            own_scores = !a || !b || a + (size_t)io[l].layer->n_reps * ctx->cfg.max_ctx <= b || b + (size_t)io[m].layer->n_reps * ctx->cfg.max_ctx <= a;
-        }
     hipEvent_t last_waited = nullptr;
     int cur = 0;
     hc_status result = HC_OK;
@@ -1468,11 +1464,13 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
             att[l - g0] = hc_attn_call{L, x.kv_arena, x.q, x.out, x.lse, side ? x.rep_logits : nullptr, q_window};
         }
         // Unfiltered layers of a middle length: their scores are made with the combine pass, a launch less for their side work, which
-        // such steps wait for.  (Not into a buffer that another layer uses as well.)
+        // such steps wait for.  The caller's buffers are the side work's, in its stream's order, as in every other step: what a caller has put
+        // there to read them, and other side work that uses them, may be behind this attention.  So the scores go to a buffer of the layer's, and
+        // the selection copies them.  (A step of one group does its side work right behind its attention: straight to the caller's.)
         hc_score_plan plan;
         ctx->beside_now = ss != nullptr;
         ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
-        const bool scored = result == HC_OK && w.n_mon > 0 && own_scores && hc_monitor_reads_scores(ctx, w.n_mon, w.mon, &plan);
+        const bool scored = result == HC_OK && w.n_mon > 0 && hc_monitor_reads_scores(ctx, w.n_mon, w.mon, &plan);
         ctx->side_pad_now = ctx->beside_now = false;
         bool clear = scored;
         for (int i = 0; i < w.n_mon; ++i) clear = clear && !w.mon[i].L->hist_dirty;
@@ -1482,6 +1480,10 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
                 hc_monitor_call& m = w.mon[i++];
                 if (hc_layer_filtered(ctx, m.L)) continue;
                 m.scored = true;
+                if (n_layers > layers_per_group) {
+                    m.copy_to = m.scores;
+                    m.scores = m.L->score_buf;
+                }
                 att[l - g0].scores = m.scores;
                 const_cast<hc_layer*>(m.L)->hist_dirty = true;            // until its selection has been launched
             }

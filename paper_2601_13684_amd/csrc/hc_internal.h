@@ -17,6 +17,7 @@ constexpr int HC_RADIX_BINS = 2048;  // bins of the monitor's histograms: 11 bit
 constexpr int HC_HIST_WORDS = HC_RADIX_BINS + 4;   // of a histogram in memory: a counter of its readers behind it
 constexpr int HC_SAMPLES = 4096;     // items of a long candidate range from which the monitor estimates its threshold
 constexpr int HC_MAX_SURVIVORS = 24576;   // survivors that a pivot's workspace holds
+constexpr int HC_SCORED_MOST = 65533;      // candidates of a range whose scores the combine pass may make: what mon_direct goes through
 
 // One KV head as the kernels see it.
 struct HeadDev {
@@ -187,6 +188,7 @@ struct hc_layer {
     uint32_t* mon_counts = nullptr;// [n_reps][4] tests, triggers, steps decided by the dense fallback, rows kept at the last step
     uint32_t* score_hist = nullptr;// [n_reps][HC_HIST_WORDS] histograms of scores made with the combine pass; clear between steps
     bool hist_dirty = false;       // not known to be clear (a step that failed midway)
+    float* score_buf = nullptr;    // [n_reps][max_ctx] these scores, until the side work has run (nullptr: the ranges are too long for them)
     const void* last_arena = nullptr;   // the arena of the last attention call with pivot logits (the fallback reads K from it)
     bool filter_armed = false;     // a monitor call has set the filter: the selection passes are launched for few rows
     hipEvent_t ev_attn = nullptr;  // hc_decode_step: this layer's attention has been enqueued / its side work is done
@@ -259,6 +261,7 @@ struct hc_monitor_call {
     const void* arena = nullptr;   // the layer's K/V arena, for a layer that filters its pivot logits (nullptr: the one
                                    // its last attention call was given)
     bool scored = false;           // the combine pass has made the scores, and their histogram in L->score_hist
+    float* copy_to = nullptr;      // ... and the selection copies them here
 };
 // What the combine pass needs to make scores: candidates that are gone through, and chunks of the longest range.
 struct hc_score_plan {

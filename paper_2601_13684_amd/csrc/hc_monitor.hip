@@ -96,7 +96,10 @@ struct MonItem {
     Ws ws;
     const RepDev* reps;
     const OutDev* outs;
-    const float* rep_logits;
+    union {
+        const float* rep_logits;
+        float* copy_to;           // scores that the combine pass made: where the selection copies them (nullptr: they are the caller's already)
+    };
     const float* lse;
     float* scores;
     int32_t* topk_idx;
@@ -127,6 +130,27 @@ struct MonItem {
 struct MonBatch {
     MonItem it[HC_MAX_GROUP];
 };
+
+// Scores of a pivot's candidates to the caller's buffer: part of `parts`, by a workgroup of NT threads.  (16 bytes to a lane; both
+// rows begin at a multiple of 16 bytes.)
+template <int NT>
+__device__ __forceinline__ void copy_scores(const MonItem& it, int rep, int lo, int hi, int part, int parts)
+{
+    const float* __restrict__ from = it.scores + (size_t)rep * it.ws.max_ctx;
+    float* __restrict__ to = it.copy_to + (size_t)rep * it.ws.max_ctx;
+#pragma unroll 4
+    for (int j = (lo & ~3) + (part * NT + (int)threadIdx.x) * 4; j < hi; j += parts * NT * 4) {
+        const float4 v = *reinterpret_cast<const float4*>(from + j);
+        if (j >= lo && j + 4 <= hi) {
+            *reinterpret_cast<float4*>(to + j) = v;
+        } else {
+            const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (j + c >= lo && j + c < hi) to[j + c] = x[c];
+        }
+    }
+}
 
 __device__ __forceinline__ bool mon_skip(const MonItem& it, int rep)
 {
@@ -565,6 +589,7 @@ __device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int r
 // used, and set sizes go to workgroups of their own because the passes behind the histogram cost the same for each
 // of them (one workgroup for all: 97 us for 16,700 rows and three set sizes with 256 threads; one each: 43; with 512
 // threads of half the registers, two waves per SIMD: 28).
+// (Behind the `lists` rows of the grid that are set sizes there may be workgroups that copy scores: see copy_scores.)
 enum { SRC_SCORES = 1, SRC_SURVIVORS = 2, SRC_RANGE = 3 };
 constexpr int SEL_LIST = 128;        // members of a threshold bin that are ranked by counting
 
@@ -604,7 +629,7 @@ __device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n,
 }
 
 template <int NT, int SRC>
-__global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words)
+__global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words, int lists)
 {
     constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -620,7 +645,10 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     const int max_ctx = it.ws.max_ctx;
     const RepDev rd = it.reps[rep];
-    if (ks >= rd.nk) return;
+    if (ks >= rd.nk) {
+        if (SRC == SRC_SURVIVORS && ks >= lists) copy_scores<NT>(it, rep, rd.lo, rd.hi, ks - lists, (int)gridDim.y - lists);
+        return;
+    }
     const bool deciding = ks == 0;
     const Ws w = it.ws.rep(rep);
     const int32_t* pmap = it.pos_map ? it.pos_map + (size_t)rep * max_ctx : nullptr;
@@ -1118,10 +1146,11 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
 constexpr int BAND = 512;                // items of the digit that can be ranked ...
 constexpr int RANKED = 128;              // ... without a histogram of their own
 constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
+static_assert(HC_SCORED_MOST + 3 == 1024 / 64 * DIRECT_TILES * HC_SEL_CHUNK, "what the large form goes through");
 
 enum { DIRECT_HIST = 0, DIRECT_MAP = 1, DIRECT_SCORES = 2, DIRECT_LOGITS = 3 };
 template <int NT, int SRC, int G>
-__global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most, int bm_words)
+__global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most, int bm_words, int lists)
 {
     constexpr int NW = NT / 64, TILE = HC_SEL_CHUNK;
     constexpr bool MAP = SRC == DIRECT_MAP, HERE = SRC != DIRECT_HIST;   // HERE: the histogram is made by this workgroup
@@ -1139,6 +1168,10 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const RepDev rd = it.reps[rep];
     const int need_of = MAP ? it.need[rep] : 0;
     // (1 to 4: the pivot was handed on before it had a histogram; 5: by this launch's deciding workgroup)
+    if (SRC == DIRECT_HIST && ks >= lists) {
+        copy_scores<NT>(it, rep, rd.lo, min(rd.hi, rd.lo + most), ks - lists, (int)gridDim.y - lists);
+        return;
+    }
     if (ks >= rd.nk || (need_of != 0 && need_of != 5)) return;
     const bool deciding = ks == 0;
     const int max_ctx = it.ws.max_ctx;
@@ -2149,14 +2182,14 @@ static bool direct_outlasted(const hc_ctx* ctx, int items, int max_k, int max_nk
     return !ctx->beside_now && max_k > 16384 && !(max_nk >= 3 ? max_k <= 40960 : max_k <= 32768 && items <= 51200);
 }
 template <int SRC>
-static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int items, int bm_words, hipStream_t st)
+static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int lists, int items, int bm_words, hipStream_t st)
 {
     const int most = direct_most(f, SRC, items);
     bm_words = SRC == DIRECT_MAP ? bm_words + 1 : std::max(bm_words, (most + 3 + 31) / 32);      // (positions are counted from a multiple of four; a candidate's number is its bit)
     const int bufs = SRC < DIRECT_SCORES && items + 3 > f.threads / 64 * HC_SEL_CHUNK && direct_bytes(f, most, bm_words, 2) <= f.room ? 2 : 1;
     const unsigned lds = (unsigned)direct_bytes(f, most, bm_words, bufs);
 #define HC_DIRECT(NT, GG)                                                                                                    \
-    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words)
+    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words, lists)
     const bool small = f.threads == 512;
     if constexpr (SRC != DIRECT_LOGITS) {
         if (small) HC_DIRECT(512, 1);                                // (the group size only matters where logits are read)
@@ -2180,20 +2213,20 @@ static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch&
 
 // Launches mon_select over the batch, with LDS for want_keys items and a baseline bitmap of bm_words as far as it goes.
 template <int NT, int SRC>
-static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, hipStream_t st)
+static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int lists, int want_keys, int bm_words, hipStream_t st)
 {
     const unsigned lds = (unsigned)std::min((long long)select_room<NT>(ctx), ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
-    mon_select<NT, SRC><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4));
+    mon_select<NT, SRC><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4), lists);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
 
 template <int SRC>
-static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int want_keys, int bm_words, bool small,
+static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int lists, int want_keys, int bm_words, bool small,
                                hipStream_t st)
 {
-    return small ? launch_select_nt<512, SRC>(ctx, B, dc, grid, want_keys, bm_words, st)
-                 : launch_select_nt<1024, SRC>(ctx, B, dc, grid, want_keys, bm_words, st);
+    return small ? launch_select_nt<512, SRC>(ctx, B, dc, grid, lists, want_keys, bm_words, st)
+                 : launch_select_nt<1024, SRC>(ctx, B, dc, grid, lists, want_keys, bm_words, st);
 }
 
 // Items that the sample lets through for a longest list of k out of n candidates: expected, and with room for its spread.
@@ -2245,7 +2278,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
 {
     const hc_config& c = ctx->cfg;
     MonBatch B{};
-    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0, max_k = 1, candidates = 0;
+    int max_reps = 0, max_nk = 1, max_nchunk = 0, max_real_chunk = 0, max_k = 1, candidates = 0, copiers = 0;
     bool armed = true;
     for (int i = 0; i < n; ++i) {
         const hc_monitor_call& x = *calls[i];
@@ -2303,11 +2336,15 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
             HC_HIP(ctx, hipGetLastError());
         }
         m.dirty = true;
-        if (x.scored) it.ws.hist = x.L->score_hist;      // (not what is cleared above)
+        if (x.scored) {
+            it.ws.hist = x.L->score_hist;                // (not what is cleared above)
+            it.copy_to = x.copy_to;
+            if (x.copy_to) copiers = (max_real_chunk + 31) / 32;       // (a workgroup of its own to 32 K scores)
+        }
     }
     if (max_reps == 0) return HC_OK;
     const DriftCfg dc{c.window, c.metric, c.tau_num, c.tau_den, c.max_k, c.window_mode != HC_WINDOW_SLIDING, c.agg};
-    const dim3 gsel(max_reps, max_nk, n);
+    const dim3 gsel(max_reps, max_nk + copiers, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
     const bool scored = mode == 0 && calls[0]->scored;       // (by all of the batch, or none)
@@ -2336,16 +2373,16 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         }
         HC_HIP(ctx, hipGetLastError());
     }
-    if (scored && direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, candidates, bm_words, st);
+    if (scored && direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, max_nk, candidates, bm_words, st);
     if (mode != 0) scores_given = 1;                     // they are there from here on
-    if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, form, B, dc, gsel, candidates, bm_words, st);
+    if (mode == 1 && direct) return launch_direct<DIRECT_MAP>(ctx, form, B, dc, gsel, max_nk, candidates, bm_words, st);
     // (a tile to a wave; given scores are read from a multiple of four positions on)
     if (mode == 0 && candidates <= SELECT_DIRECT && (!scores_given || candidates + 3 <= form.threads / 64 * HC_SEL_CHUNK))
-        return scores_given ? launch_direct<DIRECT_SCORES>(ctx, form, B, dc, gsel, candidates, bm_words, st)
-                            : launch_direct<DIRECT_LOGITS>(ctx, form, B, dc, gsel, candidates, bm_words, st);
+        return scores_given ? launch_direct<DIRECT_SCORES>(ctx, form, B, dc, gsel, max_nk, candidates, bm_words, st)
+                            : launch_direct<DIRECT_LOGITS>(ctx, form, B, dc, gsel, max_nk, candidates, bm_words, st);
     if (few || candidates <= SELECT_DIRECT) {
         const bool small = few ? select_small(ctx, kept) : select_small(ctx, candidates);
-        return launch_select<SRC_SCORES>(ctx, B, dc, gsel, candidates, bm_words, small, st);
+        return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nk, candidates, bm_words, small, st);
     }
     int survivors, most;
     expected_survivors(max_k, candidates, &survivors, &most);
@@ -2375,7 +2412,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         }
 #undef HC_SCORE
         HC_HIP(ctx, hipGetLastError());
-        if (direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, candidates, bm_words, st);
+        if (direct) return launch_direct<DIRECT_HIST>(ctx, form, B, dc, gsel, max_nk, candidates, bm_words, st);
         if (long_lists) return launch_long(ctx, B, dc, n, max_reps, max_nk, max_nchunk, span, st);
     }
     // The small form where all that may survive fits, and what is expected fits with the baseline bitmap (without the bitmap in LDS
@@ -2386,11 +2423,11 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     // How many may survive by the first digit alone: the sample takes 11 us, mon_select as long for 10,000 more items (131,072
     // candidates, a longest list of 8,192: 34, 35, 35, 39, 41, 46 us with 0, 2,000, ... 10,000 more, 46 with the sample).
     const int limit = std::max(survivors, std::min(survivors + 10000, fit));
-    if (mode == 2) return launch_select<SRC_RANGE>(ctx, B, dc, gsel, std::max(most, 8192), bm_words, small, st);
+    if (mode == 2) return launch_select<SRC_RANGE>(ctx, B, dc, gsel, max_nk, std::max(most, 8192), bm_words, small, st);
     const int wg = std::max(1, std::min((max_nchunk + NWAVE - 1) / NWAVE, std::max(4, 1024 / pivots)));
     mon_compact<<<dim3(wg, max_reps, n), dim3(BLK), hc_side_lds(ctx, (const void*)mon_compact, 0), st>>>(B, limit);
     HC_HIP(ctx, hipGetLastError());
-    return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, std::max(most, limit), bm_words, small, st);
+    return launch_select<SRC_SURVIVORS>(ctx, B, dc, gsel, max_nk, std::max(most, limit), bm_words, small, st);
 }
 
 // Whether the combine pass of a group's attention makes the scores and histograms of its unfiltered layers (with the context set as for the
@@ -2400,7 +2437,8 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
 // 99-142, one of 10,000 33.2 / 28.5, of 32K 41.4 / 36.8; twelve sequences of 9,000 to 31,000, two layers 155 / 136.  Where mon_compact and mon_select take
 // the lists (more than 20 of them) as long as the group's attention is short, here up to 1600 rows to a compute unit (36 us of
 // reading): eight layers of 36,000 in groups of four 141 / 129, four sequences, a layer to a group 115 / 105; of 60,000, two and a half times the
-// rows, 150 / 155.  Longer contexts wait for the attention.
+// rows, 150 / 155.  Longer contexts wait for the attention.  (Of steps with a side stream the copy to the caller's buffer takes back 0.5 to 1 us, where
+// mon_select takes the lists 2 to 3: eight layers of 36,000 128.5 / 131, four sequences 101 / 104.)
 bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* calls, hc_score_plan* plan)
 {
     int m = 0, reps = 0, nk = 1, k = 1, nchunk = 0, candidates = 0;
@@ -2415,9 +2453,10 @@ bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* ca
         k = std::max(k, L->max_k_any);
         nchunk = std::max(nchunk, L->max_nchunk);
         candidates = std::max(candidates, L->max_cand);
+        if (!L->score_buf) return false;             // (made when its ranges were longer)
     }
     const DirectForm form = direct_form(ctx, 0, candidates, reps * m * nk);
-    if (candidates <= SELECT_DIRECT || candidates + 3 > 1024 / 64 * DIRECT_TILES * HC_SEL_CHUNK) return false;
+    if (candidates <= SELECT_DIRECT || candidates > HC_SCORED_MOST) return false;
     const bool direct = direct_fits(form, candidates, nchunk * (HC_SEL_CHUNK / 32)) && !direct_outlasted(ctx, candidates, k, nk);
     if (!direct) {
         int survivors, most;

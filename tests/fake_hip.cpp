@@ -6,25 +6,31 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
 
 static std::map<const void*, std::string> names;
 static std::string log_text;
+static std::map<std::string, size_t> first_size;             // of a kernel's first argument, where the test has said so
+static std::vector<std::string> first_args;                  // of the launches in the log
 static long fail_at = 0, taken = 0;
 static hipError_t last_error = hipSuccess;
 static struct { dim3 grid, block; size_t shared; hipStream_t stream; } config;
 
-static hipError_t launch(const void* fn, dim3 g, dim3 b, size_t shared, hipStream_t st)
+static hipError_t launch(const void* fn, dim3 g, dim3 b, void** args, size_t shared, hipStream_t st)
 {
     if (fail_at > 0 && --fail_at == 0) return last_error = hipErrorLaunchFailure;
     log_text += names[fn] + " " + std::to_string(g.x) + " " + std::to_string(g.y) + " " + std::to_string(g.z) + " " + std::to_string(b.x) + " " +
                 std::to_string(shared) + " " + std::to_string((size_t)st) + "\n";
+    first_args.emplace_back((const char*)args[0], first_size.count(names[fn]) ? first_size[names[fn]] : 0);
     return hipSuccess;
 }
 
 extern "C" {
 const char* fake_log() { return log_text.c_str(); }
-void fake_reset(long fail) { log_text.clear(); fail_at = fail; last_error = hipSuccess; }
+void fake_reset(long fail) { log_text.clear(); first_args.clear(); fail_at = fail; last_error = hipSuccess; }
 long fake_bytes() { return taken; }
+void fake_first_size(const char* kernel, long bytes) { first_size[kernel] = (size_t)bytes; }
+long fake_first_arg(long launch, void* to) { memcpy(to, first_args[launch].data(), first_args[launch].size()); return (long)first_args[launch].size(); }
 
 void** __hipRegisterFatBinary(const void*) { return (void**)calloc(1, 8); }
 void __hipUnregisterFatBinary(void**) {}
@@ -36,8 +42,8 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shared, hipStream
     *g = config.grid; *b = config.block; *shared = config.shared; *st = config.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* fn, dim3 g, dim3 b, void**, size_t shared, hipStream_t st) { return launch(fn, g, b, shared, st); }
-hipError_t hipExtLaunchKernel(const void* fn, dim3 g, dim3 b, void**, size_t shared, hipStream_t st, hipEvent_t, hipEvent_t, int) { return launch(fn, g, b, shared, st); }
+hipError_t hipLaunchKernel(const void* fn, dim3 g, dim3 b, void** args, size_t shared, hipStream_t st) { return launch(fn, g, b, args, shared, st); }
+hipError_t hipExtLaunchKernel(const void* fn, dim3 g, dim3 b, void** args, size_t shared, hipStream_t st, hipEvent_t, hipEvent_t, int) { return launch(fn, g, b, args, shared, st); }
 hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipMalloc(void** p, size_t n) { taken += (long)n; return (*p = calloc(1, n)) ? hipSuccess : hipErrorOutOfMemory; }

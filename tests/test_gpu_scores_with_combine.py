@@ -115,3 +115,67 @@ def test_layers_that_share_a_buffer_of_scores():
             assert torch.equal(t, want[-2 * per + l * per + i]), (l, i)
         x.close()
     ctx.close()
+
+
+def touched(x):
+    """Where the layer's scores may have been written: its pivots' candidates."""
+    m = torch.zeros_like(x.scores, dtype=torch.bool)
+    for b in range(x.spec.B):
+        for p in x.spec.reps(b):
+            lo, hi = x.spec.cand_range(b, p)
+            m[x.rep_slot(b, p), lo:hi] = True
+    return m
+
+
+# one workgroup per list, its small and its large form, and the lists by survivors (36,000: more than 20 lists); ranges that begin
+# and end beside a multiple of four positions
+@pytest.mark.parametrize("ctxs,lists,layers,group", [((20001,), (300, 64), 4, 2), ((40002,), (300, 64), 4, 2), ((36003,) + (9000,) * 7, (300, 64, 33), 2, 1),
+                                                     ((9003, 16387, 700), (300,), 4, 2)])
+def test_a_reader_on_the_side_stream(ctxs, lists, layers, group):
+    """What is put on the side stream between two steps finds the scores of the step before it, however late it runs, and two calls that
+    share their layers' buffers of scores do not get in each other's way.  Nothing but candidates is written."""
+    made, qs = make(4, ctxs, 1, lists, I.AGG_PROB, layers=layers)
+    ctx = R.Context(R.make_config(made[0][0]), DEV)
+
+    def stack():
+        xs = [R.LayerRuntime(ctx, *m, own_scratch=True) for m in made]
+        for x in xs:
+            x.scores.fill_(-7.0)
+        return xs
+
+    apart, cut = stack(), stack()
+    for a, b in zip(cut[:layers // 2], cut[layers // 2:]):
+        b.scores = a.scores
+    side = torch.cuda.Stream()
+    want, have, last = [], [], []
+    for q in qs:
+        for x, one in zip(apart, q):
+            x.attn(one)
+            x.monitor()
+            x.gather()
+        torch.cuda.synchronize()
+        want += [x.scores.clone() for x in apart]
+        last = [t.clone() for x in apart for t in (x.out, x.lse, x.topk_idx, x.base_idx, x.inter, x.flag, x.slot_pos, x.arena)]
+    for x, w in zip(apart, want[-layers:]):
+        assert (w[~touched(x)] == -7.0).all()
+    again = stack()
+    torch.cuda.synchronize()
+    for q in qs:
+        hc.hc_decode_step(ctx.handle, R.make_step_io(again, q), layers, None, side, group)
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(2_000_000)             # later than the next step's attention
+            have += [x.scores.clone() for x in again]
+    torch.cuda.synchronize()
+    same(have, want)
+    same([t for x in again for t in (x.out, x.lse, x.topk_idx, x.base_idx, x.inter, x.flag, x.slot_pos, x.arena)], last)
+    half = layers // 2
+    for q in qs:
+        io = R.make_step_io(cut, q)
+        parts = [(type(io[0]) * half)(*io[i * half:(i + 1) * half]) for i in range(2)]
+        for p in parts:
+            hc.hc_decode_step(ctx.handle, p, half, None, side, max(1, group // 2))
+    torch.cuda.synchronize()
+    same([t for x in cut for t in (x.out, x.lse, x.topk_idx, x.base_idx, x.inter, x.flag, x.slot_pos, x.arena)], last)
+    for x in apart + cut + again:
+        x.close()
+    ctx.close()

@@ -259,3 +259,43 @@ def test_a_step_that_failed_does_not_count_scores_twice(fake):
         assert L.hc_decode_step(ctx, io_of(layers), 2, 2, None, None) == 0
         assert not any("attn_combine_score" in n for n in names()) and any("mon_score_hist" in n for n in names()), names()
     """)
+
+
+def first_argument_sizes():
+    """Bytes of every kernel's first argument, from the library's own metadata."""
+    import msgpack
+    from test_kernel_resources import LIB, code_objects, notes
+    with open(LIB, "rb") as f:
+        blob = f.read()
+    return {k[".name"]: k[".args"][0][".size"] for obj in code_objects(blob) for desc in notes(obj) for k in msgpack.unpackb(desc)["amdhsa.kernels"] if k[".args"]}
+
+
+@pytest.mark.parametrize("N,L,group,kernel", [(20000, 4, 2, "mon_directILi512ELi0E"), (40000, 4, 2, "mon_directILi1024ELi0E"), (36000, 16, 8, "mon_compact"),
+                                              (5000, 4, 2, "mon_directILi512ELi3E"), (70000, 4, 2, "mon_compact")])
+def test_the_scores_buffer_is_the_side_streams(fake, N, L, group, kernel):
+    """Nothing on the main stream is given the caller's scores, whatever makes them: what else a caller puts on the side stream to read them, or
+    another call's side work that uses the buffer, is in order with the side work alone."""
+    run(fake, f"""
+        for name, size in {first_argument_sizes()!r}.items():
+            fake.fake_first_size(name.encode(), size)
+        def layer3():
+            descs = (hc.hc_head_desc * 4)()
+            for h, ln in enumerate(({N}, 312, 212, 112)):
+                descs[h] = hc.hc_head_desc(k_off=h * (1 << 26), v_off=h * (1 << 26) + (1 << 25), tier_off=h * (1 << 27), ctx={N}, len=ln, role=int(h > 0),
+                                           rep=-1 if h == 0 else 0, sink=5 * (h > 0), recent=7 * (h > 0), k_mon=0, cap=0)
+            out = C.c_void_p()
+            assert L.hc_layer_create(ctx, descs, C.byref(out)) == 0, L.hc_last_error(ctx)
+            return out.value
+        ctx = context({N}, 300)
+        io = io_of([layer3() for _ in range({L})])
+        fake.fake_reset(0)
+        assert L.hc_decode_step(ctx, io, {L}, {group}, None, C.c_void_p(77)) == 0
+        assert any("{kernel}" in l[0] for l in log()), log()
+        reads = {{0: 0, 77: 0}}
+        for i, l in enumerate(log()):
+            words = (C.c_uint64 * 1024)()
+            n = fake.fake_first_arg(C.c_long(i), words)
+            assert n > 0
+            reads[int(l[-1])] += sum(x.scores == w for w in words[:n // 8] for x in io)
+        assert reads[0] == 0 and reads[77] > 0, reads
+    """)
