@@ -187,7 +187,7 @@ struct hc_layer {
     uint16_t* q_keep = nullptr;    // [n_reps][G][D] the pivots' queries of the last attention call
     uint32_t* mon_counts = nullptr;// [n_reps][4] tests, triggers, steps decided by the dense fallback, rows kept at the last step
     uint32_t* score_hist = nullptr;// [n_reps][HC_HIST_WORDS] histograms of scores made with the combine pass; clear between steps
-    bool hist_dirty = false;       // not known to be clear (a step that failed midway)
+    bool hist_dirty = false;       // not known to be clear (a step that failed midway): cleared at the next step, used again at the one after
     float* score_buf = nullptr;    // [n_reps][max_ctx] these scores, until the side work has run (nullptr: the ranges are too long for them)
     const void* last_arena = nullptr;   // the arena of the last attention call with pivot logits (the fallback reads K from it)
     bool filter_armed = false;     // a monitor call has set the filter: the selection passes are launched for few rows
@@ -300,6 +300,7 @@ struct hc_rep_logits_call {
 };
 hc_status hc_launch_rep_logits(hc_ctx* ctx, int n, const hc_rep_logits_call* calls, hipStream_t st);
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st);
+hc_status hc_launch_clear_hist(hc_ctx* ctx, const hc_layer* L, hipStream_t st);
 // may_overlap: another stream of the caller's may run the attention pass meanwhile (in hc_decode_step it is known)
 hc_status hc_launch_gather(hc_ctx* ctx, int n, const hc_gather_call* calls, bool may_overlap, hipStream_t st);
 hc_status hc_gather_set_lds_limit();     // once per process, at context creation

@@ -1167,11 +1167,11 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const Ws w = it.ws.rep(rep);
     const RepDev rd = it.reps[rep];
     const int need_of = MAP ? it.need[rep] : 0;
-    // (1 to 4: the pivot was handed on before it had a histogram; 5: by this launch's deciding workgroup)
     if (SRC == DIRECT_HIST && ks >= lists) {
         copy_scores<NT>(it, rep, rd.lo, min(rd.hi, rd.lo + most), ks - lists, (int)gridDim.y - lists);
         return;
     }
+    // (1 to 4: the pivot was handed on before it had a histogram; 5: by this launch's deciding workgroup)
     if (ks >= rd.nk || (need_of != 0 && need_of != 5)) return;
     const bool deciding = ks == 0;
     const int max_ctx = it.ws.max_ctx;
@@ -2465,6 +2465,16 @@ bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* ca
     }
     *plan = hc_score_plan{direct_most(form, DIRECT_HIST, candidates), nchunk, direct};
     return true;
+}
+
+// The histograms of scores made with the combine pass, after a step that failed between that pass and the selection.
+hc_status hc_launch_clear_hist(hc_ctx* ctx, const hc_layer* L, hipStream_t st)
+{
+    Ws ws{};                                             // (max_ctx 0: no bitmaps with these)
+    ws.hist = L->score_hist;
+    mon_prep<<<dim3(16, L->n_reps), dim3(256), 0, st>>>(ws);
+    HC_HIP(ctx, hipGetLastError());
+    return HC_OK;
 }
 
 hc_status hc_launch_monitor(hc_ctx* ctx, int n, const hc_monitor_call* calls, int scores_given, hipStream_t st)

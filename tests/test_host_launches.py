@@ -261,6 +261,30 @@ def test_a_step_that_failed_does_not_count_scores_twice(fake):
     """)
 
 
+def test_a_step_that_failed_costs_one_step_its_scores_with_the_combine_pass(fake):
+    """One of two groups' selection fails: at the next step its layers' histograms are cleared, ahead of everything that could use them, from the
+    one after that on both groups score with the combine pass again."""
+    run(fake, """
+        ctx = context(20000, 300)
+        layers = [layer(ctx, 20000, 300) for _ in range(4)]
+        def step(fail=0):
+            fake.fake_reset(fail)
+            st = L.hc_decode_step(ctx, io_of(layers), 4, 2, None, C.c_void_p(77))
+            return st, [l[0] for l in log()], [int(l[-1]) for l in log()]
+        st, good, _ = step()
+        assert st == 0 and sum("attn_combine_score" in n for n in good) == 2
+        at = [i for i, n in enumerate(good) if "mon_direct" in n][0]
+        assert step(at + 1 - sum("mon_prep" in n for n in good[:at]))[0] == hc.HC_EHIP
+        st, names, streams = step()
+        assert st == 0, names
+        clears = [i for i, n in enumerate(names) if "mon_prep" in n and streams[i] == 0]       # (on the side stream: the workspaces')
+        assert clears and clears[0] < min(i for i, n in enumerate(names) if "attn_combine" in n), names
+        for _ in range(2):
+            st, names, _ = step()
+            assert st == 0 and sum("attn_combine_score" in n for n in names) == 2 and not any("mon_score_hist" in n or "mon_prep" in n for n in names), names
+    """)
+
+
 def first_argument_sizes():
     """Bytes of every kernel's first argument, from the library's own metadata."""
     import msgpack
