@@ -1312,8 +1312,8 @@ hc_status launch_combine(hc_ctx* ctx, const CombineBatch& batch, int n, int n_he
         const int span = ctx->monitor_span > 0 ? ctx->monitor_span : std::max(1, std::min(8, reps * n * plan->max_nchunk / (2 * ctx->n_cu)));
         const int wgs = (plan->max_nchunk + span - 1) / span, n_score = reps * wgs;
         const dim3 grid(n_score + n_heads * G * (32 / CQ), 1, n);
-        if (!plan->direct) attn_combine_score_kernel<G, HIST_KEYS><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
-        else if (ctx->cfg.agg == HC_AGG_LOGIT) attn_combine_score_kernel<G, HIST_LINEAR><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
+        if (plan->hist == HIST_KEYS) attn_combine_score_kernel<G, HIST_KEYS><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
+        else if (plan->hist == HIST_LINEAR) attn_combine_score_kernel<G, HIST_LINEAR><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
         else attn_combine_score_kernel<G, HIST_FINE><<<grid, dim3(SCORE_BLK), 0, st>>>(both, n_score, wgs, span, ctx->cfg.agg, plan->most, ctx->cfg.max_ctx);
     } else if (n == 1) attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ), dim3(COMBINE_BLK), 0, st>>>(CombineOne{batch.it[0]});
     else attn_combine_kernel<G><<<dim3(n_heads * G, 32 / CQ, n), dim3(COMBINE_BLK), 0, st>>>(batch);

@@ -1398,7 +1398,7 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
         ctx->side_pad_now = ss != nullptr && w.all_filtered && ctx->G < 8;
         if (st == HC_OK) st = hc_launch_monitor(ctx, w.n_mon, w.mon, 0, run);
         for (int i = 0; i < w.n_mon && st == HC_OK; ++i)
-            if (w.mon[i].scored) const_cast<hc_layer*>(w.mon[i].L)->hist_dirty = false;
+            if (w.mon[i].scored.hist >= 0) const_cast<hc_layer*>(w.mon[i].L)->hist_dirty = false;
         if (st == HC_OK && w.n_gat > 0) st = hc_launch_gather(ctx, w.n_gat, w.gat, false, run);
         ctx->side_pad_now = ctx->beside_now = false;
         if (ss) {
@@ -1484,7 +1484,7 @@ extern "C" hc_status hc_decode_step(hc_ctx* ctx, const hc_layer_io* io, int32_t 
                 if (i == w.n_mon || io[l].layer != w.mon[i].L) continue;
                 hc_monitor_call& m = w.mon[i++];
                 if (hc_layer_filtered(ctx, m.L)) continue;
-                m.scored = true;
+                m.scored = plan;
                 if (n_layers > layers_per_group) {
                     m.copy_to = m.scores;
                     m.scores = m.L->score_buf;

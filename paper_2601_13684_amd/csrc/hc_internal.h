@@ -245,6 +245,12 @@ hc_status hc_hip_fail(hc_ctx* ctx, hipError_t e, const char* what);
 
 // kernel launchers (one translation unit each).  Monitor and gather take a batch of 1..HC_MAX_GROUP
 // layers and handle it with the launches of one layer.
+// What the combine pass needs to make scores, and what the selection behind it is told: the histogram's digits, candidates that are gone
+// through, and chunks of the longest range.
+struct hc_score_plan {
+    int hist = -1;                 // HIST_KEYS, ... (hc_score.h); -1: the combine pass makes none
+    int most = 0, max_nchunk = 0;
+};
 struct hc_monitor_call {
     const hc_layer* L;
     const float* rep_logits;
@@ -260,13 +266,8 @@ struct hc_monitor_call {
     int n_reps = 0, max_nchunk = 0, max_cand = 0, max_nk = 0;
     const void* arena = nullptr;   // the layer's K/V arena, for a layer that filters its pivot logits (nullptr: the one
                                    // its last attention call was given)
-    bool scored = false;           // the combine pass has made the scores, and their histogram in L->score_hist
+    hc_score_plan scored{};        // hist >= 0: the combine pass has made the scores, and their histogram in L->score_hist, by this plan
     float* copy_to = nullptr;      // ... and the selection copies them here
-};
-// What the combine pass needs to make scores: candidates that are gone through, and chunks of the longest range.
-struct hc_score_plan {
-    int most, max_nchunk;
-    bool direct;                   // for mon_direct (else the histogram is over the keys, and all candidates are gone through)
 };
 bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* calls, hc_score_plan* plan);
 struct hc_gather_call {

@@ -2269,6 +2269,34 @@ constexpr int SELECT_DIRECT = 8192;
 // launches; at 32K, lists of 3,776, 129 and 141).
 constexpr int SELECT_SURVIVORS = 13000, SELECT_SURVIVORS_PREFILL = 8000;
 
+// How a chain selects from its candidates: one place for it, because the combine pass makes a histogram for a selection that follows a
+// group later.
+struct Choice {
+    DirectForm form;
+    bool direct;                 // mon_direct, from a histogram by its own digits
+    bool long_lists;             // the six launches
+    int survivors, most;         // of the sample: expected, and with room for its spread
+    int hist;                    // what the histogram is over
+};
+// lists: workgroups that select; few: kept rows that fit in mon_select's LDS.
+//
+// mon_direct where it has room and the lists are not too long for it.  (candidates: of a filtering layer, what its launches are
+// sized for.)  Beside the attention pass, where a read takes many times as long, not for the kept rows of short lists: few waves
+// then have a tile, and the rows' positions are one read more behind the selection.  Steps of four layers, contexts of 66,000 to 123,000, a
+// drift at every step, us by mon_select / mon_direct: longest list 1,728, three and six sequences 277 278 / 424 425; 3,776 297 314 /
+// 459 480; 5,824 343 345 / 536 536; 7,872 478 467 / 596 594 (the kernel itself, 3,776, six sequences: 59 and 97).
+static Choice choose(const hc_ctx* ctx, int mode, bool armed, bool few, bool prefill, int candidates, int lists, int nchunk, int max_k, int max_nk)
+{
+    Choice c;
+    c.form = direct_form(ctx, mode, candidates, lists);
+    c.direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(c.form, candidates, nchunk * (HC_SEL_CHUNK / 32)) &&
+               !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk)) && !(ctx->beside_now && few && max_k <= 4096);
+    expected_survivors(max_k, candidates, &c.survivors, &c.most);
+    c.long_lists = !c.direct && (c.survivors > (prefill ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || c.most > ctx->sv_cap);
+    c.hist = !c.direct ? HIST_KEYS : ctx->cfg.agg == HC_AGG_LOGIT ? HIST_LINEAR : HIST_FINE;
+    return c;
+}
+
 // The launches of one chain over a batch of layers.  mode 0: the plain chain (every pivot, all candidate positions).
 // mode 1: the chain over the rows a filtering split pass kept.  mode 2: the chain that stands by behind
 // mode 1, for the pivots whose check failed (their logits and scores are there already: see
@@ -2336,7 +2364,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
             HC_HIP(ctx, hipGetLastError());
         }
         m.dirty = true;
-        if (x.scored) {
+        if (x.scored.hist >= 0) {
             it.ws.hist = x.L->score_hist;                // (not what is cleared above)
             it.copy_to = x.copy_to;
             if (x.copy_to) copiers = (max_real_chunk + 31) / 32;       // (a workgroup of its own to 32 K scores)
@@ -2347,19 +2375,20 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
     const dim3 gsel(max_reps, max_nk + copiers, n);
     const int bm_words = max_real_chunk * (HC_SEL_CHUNK / 32);
     const int pivots = max_reps * n;
-    const bool scored = mode == 0 && calls[0]->scored;       // (by all of the batch, or none)
+    const bool scored = mode == 0 && calls[0]->scored.hist >= 0;       // (by all of the batch, or none)
     // One launch for what one workgroup per pivot handles by itself: short ranges, and the rows that a set filter keeps (at a
     // margin of 1.25 about 1.6 times the longest list) as far as their keys fit in LDS.
     const int kept = (ctx->filter_margin <= 1.5f ? 7 : 14) * ((max_k + 3) / 4);
     const bool few = mode == 1 && armed && (select_small(ctx, kept) || (!(ctx->beside_now && ctx->G < 8) && kept <= SEL_KEYS(select_room<1024>(ctx) / 4)));
-    // mon_direct where it has room and the lists are not too long for it.  (candidates: of a filtering layer, what its launches are
-    // sized for.)  Beside the attention pass, where a read takes many times as long, not for the kept rows of short lists: few waves
-    // then have a tile, and the rows' positions are one read more behind the selection.  Steps of four layers, contexts of 66,000 to 123,000, a
-    // drift at every step, us by mon_select / mon_direct: longest list 1,728, three and six sequences 277 278 / 424 425; 3,776 297 314 /
-    // 459 480; 5,824 343 345 / 536 536; 7,872 478 467 / 596 594 (the kernel itself, 3,776, six sequences: 59 and 97).
-    const DirectForm form = direct_form(ctx, mode, candidates, pivots * max_nk);
-    const bool direct = (mode == 0 ? candidates > SELECT_DIRECT : mode == 1 && armed) && direct_fits(form, candidates, bm_words) &&
-                        !(mode == 0 && direct_outlasted(ctx, candidates, max_k, max_nk)) && !(ctx->beside_now && few && max_k <= 4096);
+    const Choice how = choose(ctx, mode, armed, few, calls[0]->store_slot == -2, candidates, pivots * max_nk, max_real_chunk, max_k, max_nk);
+    const DirectForm& form = how.form;
+    const bool direct = how.direct, long_lists = how.long_lists;
+    const int survivors = how.survivors, most = how.most;
+    for (int i = 0; i < n; ++i) {                        // a histogram is read as what it was made as
+        const hc_score_plan& made = calls[i]->scored;
+        if (scored ? made.hist != how.hist || long_lists || (direct && made.most != direct_most(form, DIRECT_HIST, candidates)) : made.hist >= 0)
+            return hc_fail(ctx, HC_ESTATE, "internal: scores and histogram for another selection");
+    }
     if (mode == 1) {
         if (direct)                                      // (more rows than it goes through, in a captured call: the dense chain's)
             for (int i = 0; i < n; ++i) B.it[i].cap_rows = std::min(B.it[i].cap_rows, direct_most(form, DIRECT_MAP, candidates));
@@ -2384,10 +2413,6 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         const bool small = few ? select_small(ctx, kept) : select_small(ctx, candidates);
         return launch_select<SRC_SCORES>(ctx, B, dc, gsel, max_nk, candidates, bm_words, small, st);
     }
-    int survivors, most;
-    expected_survivors(max_k, candidates, &survivors, &most);
-    const bool long_lists = !direct && (survivors > (calls[0]->store_slot == -2 ? SELECT_SURVIVORS_PREFILL : SELECT_SURVIVORS) || most > ctx->sv_cap);
-    if (scored && long_lists) return hc_fail(ctx, HC_ESTATE, "internal: scores and histogram for a selection that reads neither");
     if (!scored && (mode != 2 || long_lists)) {
         // Chunks per workgroup, at most 8: about 2048 workgroups per launch (a call over eight sequences of 9K to 131K takes
         // 36 us with one chunk each, 37, 41, 50 with two, four, eight; one of 32K 28, 29, 32, 39), beside the attention pass
@@ -2396,7 +2421,7 @@ static hc_status run_chain(hc_ctx* ctx, int n, const hc_monitor_call* const* cal
         const dim3 g1((max_nchunk + span - 1) / span, max_reps, n);
 #define HC_SCORE(GG, HIST)                                                                                                   \
     mon_score_hist<GG, HIST><<<g1, dim3(BLK), hc_side_lds(ctx, (const void*)mon_score_hist<GG, HIST>, 0), st>>>(B, scores_given, c.agg, span, long_lists, c.max_k, direct_most(form, DIRECT_HIST, candidates))
-        switch (ctx->G * 4 + (!direct ? HIST_KEYS : c.agg == HC_AGG_LOGIT ? HIST_LINEAR : HIST_FINE)) {
+        switch (ctx->G * 4 + how.hist) {
         case 4: HC_SCORE(1, HIST_KEYS); break;
         case 5: HC_SCORE(1, HIST_FINE); break;
         case 6: HC_SCORE(1, HIST_LINEAR); break;
@@ -2455,15 +2480,10 @@ bool hc_monitor_reads_scores(const hc_ctx* ctx, int n, const hc_monitor_call* ca
         candidates = std::max(candidates, L->max_cand);
         if (!L->score_buf) return false;             // (made when its ranges were longer)
     }
-    const DirectForm form = direct_form(ctx, 0, candidates, reps * m * nk);
     if (candidates <= SELECT_DIRECT || candidates > HC_SCORED_MOST) return false;
-    const bool direct = direct_fits(form, candidates, nchunk * (HC_SEL_CHUNK / 32)) && !direct_outlasted(ctx, candidates, k, nk);
-    if (!direct) {
-        int survivors, most;
-        expected_survivors(k, candidates, &survivors, &most);
-        if (survivors > SELECT_SURVIVORS || most > ctx->sv_cap || rows > 1600 * (int64_t)ctx->n_cu) return false;
-    }
-    *plan = hc_score_plan{direct_most(form, DIRECT_HIST, candidates), nchunk, direct};
+    const Choice how = choose(ctx, 0, false, false, false, candidates, reps * m * nk, nchunk, k, nk);
+    if (how.long_lists || (!how.direct && rows > 1600 * (int64_t)ctx->n_cu)) return false;
+    *plan = hc_score_plan{how.hist, how.direct ? direct_most(how.form, DIRECT_HIST, candidates) : HC_SCORED_MOST, nchunk};
     return true;
 }
 

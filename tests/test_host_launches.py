@@ -323,3 +323,44 @@ def test_the_scores_buffer_is_the_side_streams(fake, N, L, group, kernel):
             reads[int(l[-1])] += sum(x.scores == w for w in words[:n // 8] for x in io)
         assert reads[0] == 0 and reads[77] > 0, reads
     """)
+
+
+@pytest.mark.parametrize("agg", [0, 1])
+@pytest.mark.parametrize("side", [None, 77])
+def test_a_histogram_is_made_of_the_digits_that_are_read(fake, agg, side):
+    """Over drawn stacks of middle lengths: the digits of the combine pass's histogram are those of what selects from it, mon_direct's (1, 2 for mean
+    logits) or the keys' (0)."""
+    run(fake, f"""
+        import random, re
+        rng = random.Random(5)
+        seen = set()
+        for _ in range(120):
+            N, n, G, B = rng.randint(8000, 70000), rng.choice([2, 4, 8]), rng.choice([1, 2, 4, 8]), rng.choice([1, 1, 2, 4])
+            r = rng.choice([64, 700, 4000, 8000])
+            cfg = hc.hc_config(B=B, Hq=G * n, Hkv=n, D=128, max_ctx=(N + 63) // 64 * 64, max_k=r, window=1, metric=0, tau_num=1, tau_den=2, agg={agg}, window_mode=0)
+            ctx = C.c_void_p()
+            assert L.hc_create(C.byref(cfg), C.byref(ctx)) == 0
+            layers = []
+            for _ in range(rng.choice([2, 4])):
+                descs = (hc.hc_head_desc * (B * n))()
+                for i in range(B * n):
+                    h, c = i % n, N if i < n else min(N, 9000)
+                    descs[i] = hc.hc_head_desc(k_off=i * (1 << 26), v_off=i * (1 << 26) + (1 << 25), tier_off=i * (1 << 27), ctx=c, len=c if h == 0 else 12 + max(1, r - 7 * (h - 1)),
+                                               role=int(h > 0), rep=-1 if h == 0 else 0, sink=5 * (h > 0), recent=7 * (h > 0), k_mon=0, cap=0)
+                out = C.c_void_p()
+                assert L.hc_layer_create(ctx, descs, C.byref(out)) == 0, L.hc_last_error(ctx)
+                layers.append(out.value)
+            fake.fake_reset(0)
+            assert L.hc_decode_step(ctx, io_of(layers), len(layers), rng.choice([1, 2]), None, C.c_void_p({side})) == 0, L.hc_last_error(ctx)
+            names = [l[0] for l in log()]
+            made = [int(re.search("attn_combine_score_kernelILi.ELi(.)E", x)[1]) for x in names if "attn_combine_score" in x]
+            if made:
+                direct, select = sum(bool(re.search("mon_directILi[0-9]+ELi0E", x)) for x in names), sum(bool(re.search("mon_selectILi[0-9]+ELi2E", x)) for x in names)
+                assert sum(x == 0 for x in made) == select and sum(x == {1 + agg} for x in made) == direct and select + direct == len(made), (N, G, B, names)
+                assert not any("mon_score_hist" in x for x in names)
+                seen |= set(made)
+            for x in layers:
+                assert L.hc_layer_destroy(C.c_void_p(x)) == 0
+            assert L.hc_destroy(ctx) == 0
+        assert seen == ({{0, {1 + agg}}} if {side} else {{{1 + agg}}}), seen
+    """)
