@@ -179,3 +179,83 @@ def test_a_reader_on_the_side_stream(ctxs, lists, layers, group):
     for x in apart + cut + again:
         x.close()
     ctx.close()
+
+
+def run_on(made, qs, tokens, how, side=None, group=1, room=64):
+    """As `run`, every step appending its token (tokens: [steps, layers, 2, B, Hkv, D], or None) and with a re-scored window where the layers have one."""
+    spec = made[0][0]
+    grow = 0 if tokens is None else room
+    ctx = R.Context(R.make_config(spec, max_ctx=(max(spec.ctx) + grow + 63) // 64 * 64), DEV)
+    layers = [R.LayerRuntime(ctx, *m, own_scratch=True, growth=grow) for m in made]
+    seen, counts = [], []
+    for t, q in enumerate(qs):
+        if how == "step":
+            io = R.make_step_io(layers, q)
+            for l in range(len(layers) if grow else 0):
+                io[l].k_new, io[l].v_new = (x.data_ptr() for x in tokens[t, l])
+            hc.hc_decode_step(ctx.handle, io, len(layers), None, side, group)
+        else:
+            for l, (x, one) in enumerate(zip(layers, q)):
+                if grow:
+                    x.append(tokens[t, l, 0], tokens[t, l, 1])
+                x.attn(one)
+                if x.q_window is not None:
+                    x.rescore(one)
+                x.monitor()
+                x.gather()
+        torch.cuda.synchronize()
+        for x in layers:
+            seen += [y.clone() for y in (x.out, x.lse, x.topk_idx, x.base_idx, x.ring, x.inter, x.flag, x.slot_pos, x.arena)]
+            for b in range(x.spec.B):
+                for p in x.spec.reps(b):
+                    lo, hi = x.spec.cand_range(b, p)
+                    seen.append(x.scores[x.rep_slot(b, p), lo:hi + (t + 1 if grow else 0)].clone())
+                    counts.append(x.monitor_counts(b, p)["tests"])
+    for x in layers:
+        x.close()
+    ctx.close()
+    return seen, counts
+
+
+def drawn_tokens(spec, steps, layers, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return torch.randn((steps, layers, 2, spec.B, spec.Hkv, D), generator=g, device=DEV).to(torch.bfloat16)
+
+
+# windows of four steps, twice over and one step more; with a fixed context and a growing one; two pivots, and a batch with a sequence that is short
+@pytest.mark.parametrize("G,ctxs,n_full,lists", [(4, (20001,), 2, (300, 64)), (2, (12000, 9000, 700), 1, (300,)), (8, (33000,), 1, (2000,))])
+@pytest.mark.parametrize("grow", [False, True])
+def test_a_step_with_a_rescored_window_like_the_calls(G, ctxs, n_full, lists, grow):
+    """The combine pass keeps the step's queries and scores, and the re-scoring passes come between it and the selection that reads its histogram."""
+    print("scores with the combine pass, re-scored window", G, ctxs, lists, grow, flush=True)
+    made, _ = make(G, ctxs, n_full, lists, I.AGG_PROB, window=4, window_mode=2, layers=4)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11 + G)
+    spec = made[0][0]
+    qs = [torch.randn((4, spec.B, spec.Hq, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(9)]
+    tokens = drawn_tokens(spec, len(qs), 4, 12 + G) if grow else None
+    want, counts = run_on(made, qs, tokens, "calls")
+    assert max(counts) == 2                          # windows tested
+    for side, group in ((torch.cuda.Stream(), 2), (None, 2), (torch.cuda.Stream(), 1), (None, 4)):
+        have, n = run_on(made, qs, tokens, "step", side, group)
+        same(have, want)
+        assert n == counts
+
+
+# 9 positions are no candidates: 8,190 to 8,196 of them, the line being at 8,192, and 65,530 to 65,536, the line at 65,533; two layers, one of which
+# crosses it two steps later
+@pytest.mark.parametrize("first,lists", [(8198, (300, 64)), (65538, (700, 300))])
+def test_layers_that_grow_into_and_out_of_the_range(first, lists):
+    print("scores with the combine pass, growing from", first, flush=True)
+    long, _ = make(4, (first,), 1, lists, I.AGG_PROB, layers=1)
+    short, _ = make(4, (first - 2,), 1, lists, I.AGG_PROB, layers=1, seed=5)
+    made = [long[0], short[0]]
+    g = torch.Generator(device=DEV)
+    g.manual_seed(first)
+    spec = made[0][0]
+    qs = [torch.randn((2, 1, spec.Hq, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(9)]
+    tokens = drawn_tokens(spec, len(qs), 2, first + 1)
+    want, _ = run_on(made, qs, tokens, "calls")
+    for side, group in ((torch.cuda.Stream(), 1), (None, 1), (None, 2)):
+        same(run_on(made, qs, tokens, "step", side, group)[0], want)
