@@ -176,9 +176,7 @@ __device__ __forceinline__ uint64_t exponents(const WaveState<G>& st, const floa
     return __builtin_amdgcn_ballot_w64(mx > LAZY_SLACK);
 }
 
-// Rare: raise the reference to the largest logit of this row step, rounded up to an integer, and recompute the exponents.  (What brings sums from one
-// reference to another, here, where the waves' sums meet and in the combine pass, is a power of two then and exact.  Mean error of the outputs against 64
-// bits, with the largest logit itself / this way: groups of four, 4K 1.55e-7 / 1.51e-7, 70K 1.87e-7 / 1.82e-7.)
+// Rare: raise the reference to the largest logit of this row step and recompute the exponents.
 // Returns, per head, the factor 2^(old reference - new reference) by which everything accumulated so
 // far has to be multiplied.
 template <int G>
@@ -191,7 +189,7 @@ __device__ __forceinline__ void move_reference(WaveState<G>& st, const float (&s
         hi = fmaxf(hi, dpp<DPP_ROR8>(hi));
         hi = fmaxf(hi, __shfl_xor(hi, 16));
         hi = fmaxf(hi, __shfl_xor(hi, 32));
-        const float mn = ceilf(fmaxf(st.m[g], hi));
+        const float mn = fmaxf(st.m[g], hi);
         alpha[g] = __builtin_amdgcn_exp2f(st.m[g] - mn);
         st.m[g] = mn;
         x[g] = t - mn;
@@ -599,9 +597,7 @@ __device__ __forceinline__ void split_rows(const uint16_t* __restrict__ arena, c
 //   p.V      O^T[dim][head] += V^T P^T.  V goes through a padded LDS tile of the wave's own and comes back transposed
 //            (ds_read_b64_tr_b16).  The weights are not rounded to bf16: a weight is the sum of three bf16 numbers
 //            (8 + 8 + 8 bits of its 24), the products with V are exact and the sums are fp32.  Columns n < 8 take the
-//            high parts and columns n >= 8 the middle ones in one instruction, the low parts follow in a second one, into the
-//            middle ones' columns: rounded there, at 2^-8 of the high parts' size, their sum costs nothing (in the high
-//            parts' columns it cost 1 % of the error).
+//            high parts and columns n >= 8 the middle ones in one instruction, the low parts follow in a second one.
 // Relative error of the outputs against 64 bits: 1.8e-7 at 20K-90K (1.85e-7 with vector FMAs), 1.8e-7 at 229K (1.9e-7).
 // About 200 vector instructions per 32 rows, 16 query + 32 accumulator registers, two workgroups per compute unit:
 // 250 MB (four sequences of 20K to 90K) in 42 us where the vector form took 83.
@@ -770,13 +766,13 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
                 }
 #pragma unroll
                 for (int j = 0; j < 8; ++j) mx = fmaxf(mx, x[j]);
-                if (__builtin_amdgcn_ballot_w64(mx > LAZY_SLACK)) {   // rare: raise the reference to the tile's largest logit (rounded up: see move_reference)
+                if (__builtin_amdgcn_ballot_w64(mx > LAZY_SLACK)) {   // rare: raise the reference to the tile's largest logit
                     float hi = -INFINITY;
 #pragma unroll
                     for (int j = 0; j < 8; ++j) hi = fmaxf(hi, s[j] * (LOG2E * INV_SQRT_D));
                     hi = fmaxf(hi, __shfl_xor(hi, 16));
                     hi = fmaxf(hi, __shfl_xor(hi, 32));
-                    const float mn = ceilf(fmaxf(m, hi));
+                    const float mn = fmaxf(m, hi);
                     const float alpha = __builtin_amdgcn_exp2f(m - mn);
                     m = mn;
                     Z *= alpha;
@@ -794,7 +790,7 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
                     const float r1 = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
                     const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
                     b1[j] = first_half ? __float_as_uint(p) : __float_as_uint(r1);
-                    b2[j] = first_half ? 0u : __float_as_uint(r2);
+                    b2[j] = first_half ? __float_as_uint(r2) : 0u;
                 }
                 u32x4 p1, p2;
 #pragma unroll
@@ -1065,8 +1061,7 @@ __device__ __forceinline__ void combine_head(const CombineItem& item, int head, 
         }
         const float zz = sum4(zs);
         out[(size_t)head * HC_D + 4 * CQ * quarter + tid] = sum4(as) / zz;
-        // (M is an integer; rounded once, at the size of the result)
-        if (tid == 0 && quarter == 0) lse[head] = fmaf(M, LN2, __builtin_amdgcn_logf(zz) * LN2);
+        if (tid == 0 && quarter == 0) lse[head] = (M + __builtin_amdgcn_logf(zz)) * LN2;
     }
 }
 
@@ -1154,7 +1149,7 @@ __global__ __launch_bounds__(SCORE_BLK) void attn_combine_score_kernel(CombineSc
 #pragma unroll
                 for (int i = 0; i < 8; ++i) q[u] += sm_zz[tid][8 * u + i];
             }
-            sm_zz[tid][0] = fmaf(sm_M[tid], LN2, __builtin_amdgcn_logf(sum4(q)) * LN2);
+            sm_zz[tid][0] = (sm_M[tid] + __builtin_amdgcn_logf(sum4(q))) * LN2;
         }
     }
     __syncthreads();
