@@ -597,8 +597,11 @@ __device__ __forceinline__ void split_rows(const uint16_t* __restrict__ arena, c
 //   p.V      O^T[dim][head] += V^T P^T.  V goes through a padded LDS tile of the wave's own and comes back transposed
 //            (ds_read_b64_tr_b16).  The weights are not rounded to bf16: a weight is the sum of three bf16 numbers
 //            (8 + 8 + 8 bits of its 24), the products with V are exact and the sums are fp32.  Columns n < 8 take the
-//            high parts and columns n >= 8 the middle ones in one instruction, the low parts follow in a second one.
-// Relative error of the outputs against 64 bits: 1.8e-7 at 20K-90K (1.85e-7 with vector FMAs), 1.8e-7 at 229K (1.9e-7).
+//            high parts and columns n >= 8 the middle ones in one instruction, the low parts follow in a second one, into the
+//            middle ones' columns: rounded there, at 2^-8 of the high parts' size, their sum costs nothing (in the high
+//            parts' columns 1 % of the error).
+// Relative error of the outputs against 64 bits, means over 96 draws: 24K 1.68e-7, 70K 1.77e-7 (before these two 1.72 and 1.80; with the rows dealt
+// in equal shares across the heads, two workgroups to a compute unit, 1.67 and 1.79).
 // About 200 vector instructions per 32 rows, 16 query + 32 accumulator registers, two workgroups per compute unit:
 // 250 MB (four sequences of 20K to 90K) in 42 us where the vector form took 83.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -671,7 +674,8 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
     __shared__ __attribute__((aligned(16))) char sm_v[4][V8_WAVE];      // a wave's V tile; at the end of a segment its sums [G8][128]
     __shared__ int sm_kept[4];
     __shared__ FilterCtx<G8> fc;                     // (in registers all through the loop it leaves too few for a kernel beside this one)
-    static_assert(V8_WAVE >= G8 * HC_D * 4, "a wave's sums fit in its V tile");
+    constexpr int RED_ROW = HC_D + 4;                // of a wave's sums: padded, 16 columns written at once find all banks
+    static_assert(V8_WAVE >= 2 * G8 * RED_ROW * 4, "a wave's sums fit in its V tile");
     constexpr int CAP = REP_STASH_FLOATS / G8;       // positions per chunk of staged logits
     constexpr int CHUNK_TILES = CAP / T8_ROWS;
     static_assert(CHUNK_TILES % 4 == 0, "a chunk holds as many tiles of every wave");
@@ -790,7 +794,7 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
                     const float r1 = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
                     const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
                     b1[j] = first_half ? __float_as_uint(p) : __float_as_uint(r1);
-                    b2[j] = first_half ? __float_as_uint(r2) : 0u;
+                    b2[j] = first_half ? 0u : __float_as_uint(r2);
                 }
                 u32x4 p1, p2;
 #pragma unroll
@@ -831,17 +835,18 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
         if (stamps && tid == 0 && next_extra >= blk.extra_end && Z >= 0.f)
             stamps[2 * blockIdx.x + 1] = __builtin_amdgcn_s_memrealtime();
 
-        // ---- merge: high + middle columns, then the four waves in LDS, each relative to its own reference ----
+        // ---- merge in LDS: the four waves' middle columns, then the high ones, each relative to its wave's reference.  (High and middle columns
+        // added in every wave first cost 1 % of the error.) ----
         float* red = reinterpret_cast<float*>(vt);
         bool bad = false;
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                acc[b][r] += dpp<DPP_ROR8>(acc[b][r]);
-                bad |= acc[b][r] != acc[b][r];
+                const float whole = acc[b][r] + dpp<DPP_ROR8>(acc[b][r]);
+                bad |= whole != whole;
             }
-            if (first_half) *reinterpret_cast<f32x4*>(red + n * HC_D + 16 * b + 4 * g) = acc[b];
+            *reinterpret_cast<f32x4*>(red + n * RED_ROW + 16 * b + 4 * g) = acc[b];
         }
         if (__builtin_amdgcn_ballot_w64(bad)) {
             // Something was not finite.  If that is V, a zero part of a weight has made a NaN of an infinity that the
@@ -873,7 +878,10 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
                 }
             }
 #pragma unroll
-            for (int h = 0; h < G8; ++h) *reinterpret_cast<float2*>(red + h * HC_D + 2 * lane) = make_float2(a0[h], a1[h]);
+            for (int h = 0; h < G8; ++h) {
+                *reinterpret_cast<float2*>(red + h * RED_ROW + 2 * lane) = make_float2(a0[h], a1[h]);
+                *reinterpret_cast<float2*>(red + (G8 + h) * RED_ROW + 2 * lane) = make_float2(0.f, 0.f);
+            }
         }
         if (first_half) {
             sm_Z[w * 4 + g][n] = Z;
@@ -883,9 +891,14 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
         for (int o = tid; o < G8 * HC_D; o += 256) {
             const int h = o / HC_D;
             const float M = fmaxf(fmaxf(sm_m[0][h], sm_m[1][h]), fmaxf(sm_m[2][h], sm_m[3][h]));
-            float a = 0.f;
+            float f[4], a = 0.f;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) a += reinterpret_cast<const float*>(sm_v[p])[o] * __builtin_amdgcn_exp2f(sm_m[p][h] - M);
+            for (int p = 0; p < 4; ++p) {
+                f[p] = __builtin_amdgcn_exp2f(sm_m[p][h] - M);
+                a = fmaf(reinterpret_cast<const float*>(sm_v[p])[(G8 + h) * RED_ROW + o % HC_D], f[p], a);
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) a = fmaf(reinterpret_cast<const float*>(sm_v[p])[h * RED_ROW + o % HC_D], f[p], a);
             part_acc[(size_t)seg.slot * G8 * HC_D + o] = a;
         }
         if (tid < G8) {
