@@ -589,7 +589,7 @@ __device__ __forceinline__ void decide(const MonItem& it, int rep, int bh, int r
 // used, and set sizes go to workgroups of their own because the passes behind the histogram cost the same for each
 // of them (one workgroup for all: 97 us for 16,700 rows and three set sizes with 256 threads; one each: 43; with 512
 // threads of half the registers, two waves per SIMD: 28).
-// (Behind the `lists` rows of the grid that are set sizes there may be workgroups that copy scores: see copy_scores.)
+// (COPY: behind the `lists` rows of the grid that are set sizes there are workgroups that copy scores, see copy_scores.)
 enum { SRC_SCORES = 1, SRC_SURVIVORS = 2, SRC_RANGE = 3 };
 constexpr int SEL_LIST = 128;        // members of a threshold bin that are ranked by counting
 
@@ -628,7 +628,7 @@ __device__ __forceinline__ void dma_run(const void* words, uint32_t* lds, int n,
     }
 }
 
-template <int NT, int SRC>
+template <int NT, int SRC, bool COPY>
 __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n_group, int lds_words, int lists)
 {
     constexpr int NW = NT / 64, GROUP = NT == 512 ? 4 : 8;      // (four keep the small form within 40 registers)
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(NT) void mon_select(MonBatch B, DriftCfg cfg, int n
     const int max_ctx = it.ws.max_ctx;
     const RepDev rd = it.reps[rep];
     if (ks >= rd.nk) {
-        if (SRC == SRC_SURVIVORS && ks >= lists) copy_scores<NT>(it, rep, rd.lo, rd.hi, ks - lists, (int)gridDim.y - lists);
+        if (COPY && ks >= lists) copy_scores<NT>(it, rep, rd.lo, rd.hi, ks - lists, (int)gridDim.y - lists);
         return;
     }
     const bool deciding = ks == 0;
@@ -1149,7 +1149,7 @@ constexpr int DIRECT_TILES = 4;          // of a wave: two words to a lane
 static_assert(HC_SCORED_MOST + 3 == 1024 / 64 * DIRECT_TILES * HC_SEL_CHUNK, "what the large form goes through");
 
 enum { DIRECT_HIST = 0, DIRECT_MAP = 1, DIRECT_SCORES = 2, DIRECT_LOGITS = 3 };
-template <int NT, int SRC, int G>
+template <int NT, int SRC, int G, bool COPY>
 __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n_group, int bufs, int most, int bm_words, int lists)
 {
     constexpr int NW = NT / 64, TILE = HC_SEL_CHUNK;
@@ -1167,7 +1167,7 @@ __global__ __launch_bounds__(NT) void mon_direct(MonBatch B, DriftCfg cfg, int n
     const Ws w = it.ws.rep(rep);
     const RepDev rd = it.reps[rep];
     const int need_of = MAP ? it.need[rep] : 0;
-    if (SRC == DIRECT_HIST && ks >= lists) {
+    if (COPY && ks >= lists) {                       // (as in mon_select)
         copy_scores<NT>(it, rep, rd.lo, min(rd.hi, rd.lo + most), ks - lists, (int)gridDim.y - lists);
         return;
     }
@@ -2188,9 +2188,17 @@ static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch&
     bm_words = SRC == DIRECT_MAP ? bm_words + 1 : std::max(bm_words, (most + 3 + 31) / 32);      // (positions are counted from a multiple of four; a candidate's number is its bit)
     const int bufs = SRC < DIRECT_SCORES && items + 3 > f.threads / 64 * HC_SEL_CHUNK && direct_bytes(f, most, bm_words, 2) <= f.room ? 2 : 1;
     const unsigned lds = (unsigned)direct_bytes(f, most, bm_words, bufs);
-#define HC_DIRECT(NT, GG)                                                                                                    \
-    mon_direct<NT, SRC, GG><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words, lists)
+#define HC_DIRECT_AS(NT, GG, COPY)                                                                                           \
+    mon_direct<NT, SRC, GG, COPY><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_direct<NT, SRC, GG, COPY>, lds), st>>>(B, dc, ctx->G, bufs, most, bm_words, lists)
+#define HC_DIRECT(NT, GG) HC_DIRECT_AS(NT, GG, false)
     const bool small = f.threads == 512;
+    if constexpr (SRC == DIRECT_HIST)
+        if ((int)grid.y > lists) {
+            if (small) HC_DIRECT_AS(512, 1, true);
+            else HC_DIRECT_AS(1024, 1, true);
+            HC_HIP(ctx, hipGetLastError());
+            return HC_OK;
+        }
     if constexpr (SRC != DIRECT_LOGITS) {
         if (small) HC_DIRECT(512, 1);                                // (the group size only matters where logits are read)
         else HC_DIRECT(1024, 1);
@@ -2207,16 +2215,17 @@ static hc_status launch_direct(hc_ctx* ctx, const DirectForm& f, const MonBatch&
         }
     }
 #undef HC_DIRECT
+#undef HC_DIRECT_AS
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
 
 // Launches mon_select over the batch, with LDS for want_keys items and a baseline bitmap of bm_words as far as it goes.
-template <int NT, int SRC>
+template <int NT, int SRC, bool COPY>
 static hc_status launch_select_nt(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int lists, int want_keys, int bm_words, hipStream_t st)
 {
     const unsigned lds = (unsigned)std::min((long long)select_room<NT>(ctx), ((long long)want_keys + 255) / 256 * 264 * 4 + bm_words * 4);
-    mon_select<NT, SRC><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4), lists);
+    mon_select<NT, SRC, COPY><<<grid, dim3(NT), hc_side_lds(ctx, (const void*)mon_select<NT, SRC, COPY>, lds), st>>>(B, dc, ctx->G, (int)(lds / 4), lists);
     HC_HIP(ctx, hipGetLastError());
     return HC_OK;
 }
@@ -2225,8 +2234,12 @@ template <int SRC>
 static hc_status launch_select(hc_ctx* ctx, const MonBatch& B, const DriftCfg& dc, const dim3& grid, int lists, int want_keys, int bm_words, bool small,
                                hipStream_t st)
 {
-    return small ? launch_select_nt<512, SRC>(ctx, B, dc, grid, lists, want_keys, bm_words, st)
-                 : launch_select_nt<1024, SRC>(ctx, B, dc, grid, lists, want_keys, bm_words, st);
+    if constexpr (SRC == SRC_SURVIVORS)
+        if ((int)grid.y > lists)
+            return small ? launch_select_nt<512, SRC, true>(ctx, B, dc, grid, lists, want_keys, bm_words, st)
+                         : launch_select_nt<1024, SRC, true>(ctx, B, dc, grid, lists, want_keys, bm_words, st);
+    return small ? launch_select_nt<512, SRC, false>(ctx, B, dc, grid, lists, want_keys, bm_words, st)
+                 : launch_select_nt<1024, SRC, false>(ctx, B, dc, grid, lists, want_keys, bm_words, st);
 }
 
 // Items that the sample lets through for a longest list of k out of n candidates: expected, and with room for its spread.
@@ -2545,18 +2558,19 @@ hc_status hc_monitor_set_lds_limit()
 {
     // mon_select takes most of a compute unit's LDS, and beside the attention pass every kernel here reserves more
     // than half of it (hc_side_lds)
-    const void* fns[] = {(const void*)mon_direct<512, DIRECT_HIST, 1>, (const void*)mon_direct<512, DIRECT_MAP, 1>, (const void*)mon_direct<512, DIRECT_SCORES, 1>,
-                         (const void*)mon_direct<512, DIRECT_LOGITS, 1>, (const void*)mon_direct<512, DIRECT_LOGITS, 2>, (const void*)mon_direct<512, DIRECT_LOGITS, 4>,
-                         (const void*)mon_direct<512, DIRECT_LOGITS, 8>, (const void*)mon_direct<1024, DIRECT_HIST, 1>, (const void*)mon_direct<1024, DIRECT_MAP, 1>,
-                         (const void*)mon_direct<1024, DIRECT_SCORES, 1>, (const void*)mon_direct<1024, DIRECT_LOGITS, 1>, (const void*)mon_direct<1024, DIRECT_LOGITS, 2>,
-                         (const void*)mon_direct<1024, DIRECT_LOGITS, 4>, (const void*)mon_direct<1024, DIRECT_LOGITS, 8>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
+    const void* fns[] = {(const void*)mon_direct<512, DIRECT_HIST, 1, false>, (const void*)mon_direct<512, DIRECT_MAP, 1, false>, (const void*)mon_direct<512, DIRECT_SCORES, 1, false>,
+                         (const void*)mon_direct<512, DIRECT_LOGITS, 1, false>, (const void*)mon_direct<512, DIRECT_LOGITS, 2, false>, (const void*)mon_direct<512, DIRECT_LOGITS, 4, false>,
+                         (const void*)mon_direct<512, DIRECT_LOGITS, 8, false>, (const void*)mon_direct<1024, DIRECT_HIST, 1, false>, (const void*)mon_direct<1024, DIRECT_MAP, 1, false>,
+                         (const void*)mon_direct<1024, DIRECT_SCORES, 1, false>, (const void*)mon_direct<1024, DIRECT_LOGITS, 1, false>, (const void*)mon_direct<1024, DIRECT_LOGITS, 2, false>,
+                         (const void*)mon_direct<1024, DIRECT_LOGITS, 4, false>, (const void*)mon_direct<1024, DIRECT_LOGITS, 8, false>, (const void*)mon_direct<512, DIRECT_HIST, 1, true>, (const void*)mon_direct<1024, DIRECT_HIST, 1, true>,
+                         (const void*)mon_select<512, SRC_SURVIVORS, true>, (const void*)mon_select<1024, SRC_SURVIVORS, true>, (const void*)mon_hist<2>, (const void*)mon_hist<3>, (const void*)mon_count, (const void*)mon_write, (const void*)mon_decide,
                          (const void*)mon_compact, (const void*)mon_sparse_score<1>,
                          (const void*)mon_sparse_score<2>, (const void*)mon_sparse_score<4>, (const void*)mon_sparse_score<8>,
                          (const void*)mon_score_hist<1, HIST_KEYS>, (const void*)mon_score_hist<2, HIST_KEYS>, (const void*)mon_score_hist<4, HIST_KEYS>, (const void*)mon_score_hist<8, HIST_KEYS>,
                          (const void*)mon_score_hist<1, HIST_FINE>, (const void*)mon_score_hist<2, HIST_FINE>, (const void*)mon_score_hist<4, HIST_FINE>, (const void*)mon_score_hist<8, HIST_FINE>,
                          (const void*)mon_score_hist<1, HIST_LINEAR>, (const void*)mon_score_hist<2, HIST_LINEAR>, (const void*)mon_score_hist<4, HIST_LINEAR>, (const void*)mon_score_hist<8, HIST_LINEAR>,
-                         (const void*)mon_select<512, SRC_SCORES>, (const void*)mon_select<512, SRC_SURVIVORS>, (const void*)mon_select<512, SRC_RANGE>,
-                         (const void*)mon_select<1024, SRC_SCORES>, (const void*)mon_select<1024, SRC_SURVIVORS>, (const void*)mon_select<1024, SRC_RANGE>};
+                         (const void*)mon_select<512, SRC_SCORES, false>, (const void*)mon_select<512, SRC_SURVIVORS, false>, (const void*)mon_select<512, SRC_RANGE, false>,
+                         (const void*)mon_select<1024, SRC_SCORES, false>, (const void*)mon_select<1024, SRC_SURVIVORS, false>, (const void*)mon_select<1024, SRC_RANGE, false>};
     for (const void* fn : fns)
         if (hc_allow_lds(fn) != hipSuccess) return HC_EHIP;
     return HC_OK;
