@@ -543,6 +543,7 @@ def main():
                      "kernel": "attn_split_kernel", "kernel_us_mean": kern_us,
                      "kernel_us_median": float(np.median(kern_ms) * 1e3), "kernel_us_p95": float(np.percentile(kern_ms, 95) * 1e3),
                      "launches_timed": n_pairs,
+                     "launches": "one for each layer, as event pairs need; in the timed steps the layers of a group may share one",
                      "kernel_us_mean_without_overlap": iso_us,
                      "frac_without_overlap": (kv_bytes / (iso_us * 1e-6) / 1e9 / HBM_PEAK_GBPS) if iso_us else None,
                      "measured_stream_read_GBps": probes.get("stream_read_GBps"),

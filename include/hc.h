@@ -124,6 +124,8 @@ hc_status hc_destroy(hc_ctx* ctx);
 const char* hc_strerror(hc_status st);
 const char* hc_last_error(const hc_ctx* ctx);       /* text of the last failure on this ctx   */
 
+/* Device memory that a layer takes: its plan (a few KB), and for every pivot 8 KB and, where no pivot of the layer has more than 65,533
+ * candidates, 4 max_ctx bytes (scores on their way from the combine pass to the caller's buffer); with the pivot-logit filter 8 max_ctx more. */
 /* Validates the head table (all satellites of one pivot must share sink and recent; every k
  * must fit the candidate range [sink, ctx-recent) and max_k; at most HC_MAX_K_PER_REP distinct
  * set sizes per pivot), builds the split-K work partition and uploads the plans. */

@@ -991,7 +991,7 @@ struct CombineBatch {
     CombineItem it[HC_MAX_GROUP];
     __device__ __forceinline__ const CombineItem& item() const { return it[blockIdx.z]; }
 };
-// The 32 partial lanes' sums are added in fours of eight, these as a tree: an addend is rounded 10 times at most instead of 31.  Mean error against
+// The 32 partial lanes' sums are added in fours of eight, these as a tree: an addend is rounded 9 times at most instead of 31.  Mean error against
 // 64 bits over 12 inputs, in a row / this way: a layer of 4K 1.64e-7 / 1.55e-7 (1.60e-7 in a row with a quarter of the workgroups), 32K 1.77e-7 / 1.74e-7.
 __device__ __forceinline__ float sum4(const float (&x)[4]) { return (x[0] + x[1]) + (x[2] + x[3]); }
 
@@ -1394,11 +1394,12 @@ static bool split_filtered(const hc_ctx* ctx, const hc_attn_call& x) { return x.
 
 // Whether a layer may share its launch of the split pass with its neighbours of the group: if it has two granules of rows and more to
 // a compute unit.
-// (Shorter passes would gain as well, but keep a launch of their own: one that fails leaves the layers before it combined, layer by
-// layer.  Of a shared launch that fails, none of its layers is.  A caller that times the passes has a launch for each layer.)
+// (Shorter passes keep a launch each, of which one that fails leaves the layers before it combined; of a shared launch that fails, none of its
+// layers is.  A caller that times the passes has a launch for each layer.)
 // Layers that leave all of their pivots' logits, for the side stream to read beside the next group's attention, share one up to 1400 rows to a
 // compute unit only, and two of them by themselves up to 64 K candidates.  Beyond, the side chains, which find room as a launch ends, are what such
-// steps wait for.  us per step, a launch each / shared: two layers to a group 32K 95 / 86, 64K 131 / 123, 95K 181 / 178, 100K 217 / 225, 125K 207 / 206; four and
+// steps wait for.  (For two layers the figures scatter: from 64K to 160K either form may be ahead, by up to 4 %, from 180K a launch each is, by 5 to
+// 10 %.  Steps on one stream, where nothing runs beside, follow the same lines.)  us per step, a launch each / shared: two layers to a group 32K 95 / 86, 64K 131 / 123, 95K 181 / 178, 100K 217 / 225, 125K 207 / 206; four and
 // more 90K 445 / 393, 100K 248 / 249, 131K 340 / 315, 160K 384 / 367, 200K 405 / 453, 224K 450 / 505; six sequences of 12,000 to 81,000 320 / 329.  With the filter little is left to the side
 // stream (four of 224K 214 / 208), but in groups of eight heads, whose attention leaves no room beside it: 131K 171 / 187, 224K 561 / 590, eight 781 / 803.
 static bool split_together(const hc_ctx* ctx, const hc_attn_call& x, int n)

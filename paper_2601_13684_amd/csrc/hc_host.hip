@@ -359,9 +359,10 @@ struct ErrBuf {
 // second one on its compute unit costs it 1.7 us.  So: shares of the fewest granules with which every workgroup has a compute unit
 // to itself, or, where sharing one makes them more than 2 granules shorter, with which two share it (then as many workgroups as there is room
 // for, the spare ones to the heads with the longest shares).  Groups of eight heads, whose workgroups keep the vector units and
-// the matrix cores busier, have a compute unit to themselves up to SHORT_SHARE.  us per call, before (equal shares across head boundaries, at
-// least 4 granules) / now: two KV heads, one of them full, 4K 9.1 / 7.6, 8K 9.5 / 8.1, 12K 10.4 / 8.8; eight KV heads, two full, 8K 12.2 / 9.6, 16K
-// 13.8 / 10.8, 32K 15.7 / 14.4, 64K 21.8 / 20.6; groups of eight heads, 24K 13.8 / 13.0, 48K 19.9 / 17.4, 96K 27.7 / 26.6.
+// the matrix cores busier, have a compute unit to themselves up to SHORT_SHARE.  us per call in a graph, before (equal shares across head boundaries, at
+// least 4 granules, and a combine launch with the arguments of eight layers) / now: two KV heads, one of them full, 4K 8.5 / 7.3, 8K 8.7 / 7.8,
+// 12K 8.8 / 8.5; eight KV heads, two full, 8K 10.9 / 8.6, 16K 13.4 / 10.9, 32K 15.1 / 13.3, 64K 19.4 / 18.7; groups of eight heads, 24K 16.0 / 12.0,
+// 48K 19.0 / 15.7, 96K 26.6 / 25.5.
 constexpr int64_t SHORT_SHARE = 16;
 static std::vector<int64_t> short_shares(const hc_head_desc* hd, int nh, int64_t n_cu, int64_t limit, int group)
 {
@@ -950,7 +951,8 @@ extern "C" int32_t hc_layer_context(const hc_layer* layer, int32_t b)
 }
 
 // Rebuilds the split-K plan from the head table as it is now and copies it over the old one on `st`.
-// The workgroup count and the pivots do not change with the lengths; only shares, segments and slots do.
+// The pivots do not change with the lengths; shares, segments and slots do, and so may the workgroup count (up to what the layer has room
+// for): a pass gets more workgroups as it grows, and one that grows beyond short_shares' line is dealt in equal shares from then on.
 // Enqueue-only: the new tables are written into one of the layer's two pinned staging buffers and copied
 // from there in stream order (behind the append kernel whose lengths they include, ahead of the attention
 // that uses them).  The host waits only if the buffer's previous copy, two rebalancings ago, has not run yet.
