@@ -838,17 +838,14 @@ __device__ __forceinline__ void split_rows8(const uint16_t* __restrict__ arena, 
         // ---- merge in LDS: the four waves' middle columns, then the high ones, each relative to its wave's reference.  (High and middle columns
         // added in every wave first cost 1 % of the error.) ----
         float* red = reinterpret_cast<float*>(vt);
-        bool bad = false;
+        f32x4 nought = {0.f, 0.f, 0.f, 0.f};     // stays 0 unless a sum is not finite
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float whole = acc[b][r] + dpp<DPP_ROR8>(acc[b][r]);
-                bad |= whole != whole;
-            }
+            for (int r = 0; r < 4; ++r) nought[r] = fmaf(acc[b][r], 0.f, nought[r]);
             *reinterpret_cast<f32x4*>(red + n * RED_ROW + 16 * b + 4 * g) = acc[b];
         }
-        if (__builtin_amdgcn_ballot_w64(bad)) {
+        if (__builtin_amdgcn_ballot_w64((nought[0] + nought[1]) + (nought[2] + nought[3]) != 0.f)) {
             // Something was not finite.  If that is V, a zero part of a weight has made a NaN of an infinity that the
             // weight itself would have kept: these rows again with whole weights, one at a time, two dimensions to a lane.
             float a0[G8], a1[G8];
